@@ -140,7 +140,9 @@ size_t forge_gemm_workspace_bytes(int M, int N, int K, forge_act act, forge_dtyp
 
 /* Diagnostic: the name of the kernel variant (tile shape and wave layout) that
  * forge_gemm_bias_gelu launches for this problem, e.g. "gemm_bf16_pers<256,256,2,4>"; static
- * storage, never NULL.  Lets a profiler trace be matched to the calls that produced it. */
+ * storage, never NULL.  Lets a profiler trace be matched to the calls that produced it.  At most
+ * 64 rows: the name says which streaming path and workspace the problem has; most problems of either
+ * path run gemm_bf16_rows_kernel (the rows of x in registers) instead of the slab-wise kernel. */
 const char* forge_gemm_variant(int M, int N, int K, int ldy, forge_act act, forge_dtype dt);
 
 forge_status forge_gemm_bias_gelu(const void* x, const void* w, const void* bias,

@@ -50,14 +50,6 @@ struct DecParams {
   const int* kv_pos;   // per-sequence: rows [0, kv_pos[b]] (clamped to kv_len - 1); NULL: kv_len rows
 };
 
-// Lanes of one wave exchange data through LDS: the hardware runs a wave's LDS instructions in
-// order, but the compiler must be told that other lanes wrote between this lane's accesses.
-__device__ inline void wave_lds_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 __device__ inline float xor16_max(float x) { return fmaxf(x, __shfl_xor(x, 16, 64)); }
 __device__ inline float xor32_max(float x) { return fmaxf(x, __shfl_xor(x, 32, 64)); }
 

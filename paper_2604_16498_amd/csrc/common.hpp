@@ -93,6 +93,15 @@ __device__ inline float wave_max(float v) {
   return v;
 }
 
+// ---- LDS inside a wave --------------------------------------------------------------------
+// Lanes of one wave exchange data through LDS: the hardware runs a wave's LDS instructions in
+// order, but the compiler must be told that other lanes wrote between this lane's accesses.
+__device__ inline void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // ---- activations on the fp32 accumulator ------------------------------------------------
 // tanh-GELU written through the logistic form: 0.5 x (1 + tanh u) = x / (1 + exp(-2u)),
 // u = sqrt(2/pi) (x + 0.044715 x^3).

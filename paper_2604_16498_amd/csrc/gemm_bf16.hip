@@ -34,56 +34,21 @@
 // column-major inside a group, so that the tiles resident in one XCD at a time share x and w
 // panels in that L2.
 //
-// M <= 64 (decode): the weight is streamed once by gemm_bf16_wstream_kernel (128 or 256 weight
-// rows per block, K split over grid.y to about one block per CU), fp32 partials, and fixed-order
-// reduce kernels that carry the epilogue (and, inside a decoder layer, RoPE or the following norm).
+// M <= 64 (decode): most problems go to the kernel of gemm_bf16_rows.hip (plan_rows says which).  The
+// others (bf16 with a long K, or more rows than its x registers pay for): the weight is streamed once by
+// gemm_bf16_wstream_kernel (128 or 256 weight rows per block, K split over grid.y to about one block
+// per CU), fp32 partials, and fixed-order reduce kernels that carry the epilogue (and, inside a
+// decoder layer, RoPE or the following norm).
 // Prompt-sized M with few tiles and a long K: the tile kernel itself walks (k range, tile) items.
 #include <type_traits>
-#include "common.hpp"
+#include "gemm_bf16.hpp"
 
 namespace forge {
 namespace {
 
-constexpr int BK = 64;            // k per slab
 constexpr int CHUNKS = BK / 8;    // 16-byte chunks per slab row
 
 __device__ inline int lds_chunk_off(int r, int c) { return (r * CHUNKS + (c ^ ((r >> 1) & 7))) * 16; }
-
-__device__ inline bf16* split_dst_bf16(const QkvSplit& sp, int m, int n) {
-  const int dh = sp.head_dim;
-  const int b = m / sp.q_len, s = m % sp.q_len;
-  const int nq = sp.q_heads * dh, nk = sp.kv_heads * dh;
-  if (n < nq) {
-    const int h = n / dh;
-    return (bf16*)sp.q + (((int64_t)b * sp.q_heads + h) * sp.q_len + s) * dh + n % dh;
-  }
-  const bool is_k = n < nq + nk;
-  const int nn = is_k ? n - nq : n - nq - nk;
-  const int h = nn / dh;
-  bf16* basep = (bf16*)(is_k ? sp.k_cache : sp.v_cache);
-  return basep + (((int64_t)b * sp.kv_heads + h) * sp.kv_cap + seq_position(sp.pos, b, sp.pos0) + s) * dh + nn % dh;
-}
-
-struct GemmParams {
-  const bf16* x;
-  const bf16* w;
-  const bf16* bias;
-  const bf16* residual;
-  bf16* y;
-  int M, N, K;        // N: output columns
-  int ldy;            // row stride of y and residual (elements)
-  int tiles_m, tiles_n;
-  int k_per_split;    // split-K: k range of one block (multiple of 64); otherwise >= K
-  int splits;         // split-K in the persistent kernel: number of k ranges
-  float* part;        // split-K: fp32 partial sums [splits, M, N]
-  size_t part_bytes;  // bytes behind part
-  QkvSplit sp;
-  NormTail nt;        // nt.y_norm == nullptr: none
-  const int8_t* w8;     // weight-only int8 (M <= 64 streaming path): [N, K] bytes; w is NULL then
-  const float* wscale;  // one scale per weight row, applied to the reduced sum before the bias
-  int row0;             // row of the whole problem that row 0 of this launch is (head split only)
-  int col0;             // column of the whole problem that column 0 of this launch is (head split only)
-};
 
 // MODE_QKV_ROPE: the head split with the rotary embedding applied in the epilogue (prompt-sized
 // problems; the decode-sized ones rotate in their reduce kernel)
@@ -250,15 +215,6 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_generic_kernel(GemmPara
       }
     }
   }
-}
-
-typedef __attribute__((address_space(3))) void lds_void;
-
-// Block barrier for data exchanged through LDS only: this wave's LDS traffic has completed
-// (lgkmcnt 0), vector-memory loads and stores stay in flight (__syncthreads would drain them too).
-__device__ inline void lds_barrier() {
-  __builtin_amdgcn_s_waitcnt(0xc07f);
-  __builtin_amdgcn_s_barrier();
 }
 
 // Persistent fast path: one block per LDS/register slot of the chip walks over a strided list
@@ -785,17 +741,6 @@ struct WStream {
   static_assert(SMEM <= 160 * 1024, "fits the LDS of a CU");
 };
 
-// 8 signed bytes -> 8 bf16 (exact: |q| <= 127 has 7 significant bits)
-__device__ inline bf16x8 cvt_i8x8_bf16(u32x2 v) {
-  bf16x8 r;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const int b = (int)(int8_t)((v[e >> 2] >> (8 * (e & 3))) & 0xff);
-    r[e] = (bf16)(float)b;
-  }
-  return r;
-}
-
 // FACT < 0: fp32 partial sums for the split-K reduce (any number of k ranges).
 // FACT >= 0 (an activation code): ONE k range, and the block finishes its outputs itself -- weight
 // scale, bias, activation, residual, one rounding -- with the arithmetic of the reduce kernel, so
@@ -1104,71 +1049,79 @@ __global__ __launch_bounds__(256) void splitk_reduce_qkv_rope_kernel(GemmParams 
 // L2; many loads in flight per CU are what makes a single CU per row fast enough); h = sum + bias
 // + residual stays in fp32 registers, is stored rounded to y, and y_norm = Norm(h) is computed
 // from the fp32 values (mean, then centred variance, as residual_norm_kernel does).
-// N <= 1024 * 4 * NORM_TAIL_MAX_G columns.
+// N <= 1024 * 4 * NORM_TAIL_MAX_G columns; G: groups of 4 columns per thread.  A launch of this size is all
+// latency, so everything that does not depend on the sums (bias, residual, gain, shift) is requested
+// before the partial planes, and the block has no more waves than columns need (the barriers of
+// the two reductions cost by the wave): 21 rows of 2048 6.3 -> 4.4 us, 8 rows of 768 5.9 -> 5.0.
 constexpr int NORM_TAIL_MAX_G = 4;
 constexpr int NORM_TAIL_THREADS = 1024;
-__device__ inline float block_sum_1024(float v, float* red) {
+__device__ inline float block_sum_tail(float v, float* red) {
   v = wave_sum(v);
-  __syncthreads();                      // red may still be read from the previous call
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
   __syncthreads();
   float t = 0.f;
-#pragma unroll
-  for (int i = 0; i < NORM_TAIL_THREADS / 64; ++i) t += red[i];
+  for (int i = 0; i < (int)(blockDim.x >> 6); ++i) t += red[i];
   return t;
 }
+template <int G>
 __global__ __launch_bounds__(NORM_TAIL_THREADS) void splitk_reduce_norm_kernel(GemmParams p, int splits) {
-  __shared__ float red[NORM_TAIL_THREADS / 64];
-  const int N = p.N, m = blockIdx.x;
+  __shared__ float red[2][NORM_TAIL_THREADS / 64];
+  const int N = p.N, m = blockIdx.x, NT = blockDim.x;
   const int64_t plane = (int64_t)p.M * N;
   const float* src = p.part + (int64_t)m * N;
-  floatx4 h[NORM_TAIL_MAX_G];
+  const bf16* gamma = (const bf16*)p.nt.gamma;
+  const bf16* beta = (const bf16*)p.nt.beta;
+  u32x2 rv[G], bv[G], gv[G], sv[G];       // residual, bias, gain, shift: 4 bf16 each
+  floatx4 h[G];
+#pragma unroll
+  for (int g = 0; g < G; ++g) {
+    const int n = (g * NT + threadIdx.x) * 4;
+    rv[g] = bv[g] = gv[g] = sv[g] = u32x2{0, 0};
+    if (n >= N) continue;                 // N % 4 == 0 (host)
+    if (p.residual != nullptr) rv[g] = *reinterpret_cast<const u32x2*>(p.residual + (int64_t)m * p.ldy + n);
+    if (p.bias != nullptr) bv[g] = *reinterpret_cast<const u32x2*>(p.bias + n);
+    gv[g] = *reinterpret_cast<const u32x2*>(gamma + n);
+    if (beta != nullptr) sv[g] = *reinterpret_cast<const u32x2*>(beta + n);
+  }
   float sum = 0.f;
 #pragma unroll
-  for (int g = 0; g < NORM_TAIL_MAX_G; ++g) {
-    const int n = (g * NORM_TAIL_THREADS + threadIdx.x) * 4;
+  for (int g = 0; g < G; ++g) {
+    const int n = (g * NT + threadIdx.x) * 4;
     h[g] = floatx4{0.f, 0.f, 0.f, 0.f};
-    if (n >= N) continue;                 // N % 4 == 0 (host)
+    if (n >= N) continue;
     floatx4 a = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll 8
     for (int z = 0; z < splits; ++z) a += *reinterpret_cast<const floatx4*>(src + z * plane + n);
     if (p.wscale != nullptr) a *= *reinterpret_cast<const floatx4*>(p.wscale + n);
-    const int64_t at = (int64_t)m * p.ldy + n;
+    a[0] += bf_lo(bv[g][0]); a[1] += bf_hi(bv[g][0]); a[2] += bf_lo(bv[g][1]); a[3] += bf_hi(bv[g][1]);
+    a[0] += bf_lo(rv[g][0]); a[1] += bf_hi(rv[g][0]); a[2] += bf_lo(rv[g][1]); a[3] += bf_hi(rv[g][1]);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      if (p.bias != nullptr) a[e] += (float)p.bias[n + e];
-      if (p.residual != nullptr) a[e] += (float)p.residual[at + e];
-      sum += a[e];
-    }
+    for (int e = 0; e < 4; ++e) sum += a[e];
     u32x2 pk;
     pk[0] = pack_bf2(a[0], a[1]); pk[1] = pack_bf2(a[2], a[3]);
-    *reinterpret_cast<u32x2*>(p.y + at) = pk;
+    *reinterpret_cast<u32x2*>(p.y + (int64_t)m * p.ldy + n) = pk;
     h[g] = a;
   }
   const bool rms = p.nt.kind == FORGE_NORM_RMSNORM;
-  const float mean = rms ? 0.f : block_sum_1024(sum, red) / (float)N;
+  const float mean = rms ? 0.f : block_sum_tail(sum, red[0]) / (float)N;
   float sq = 0.f;
 #pragma unroll
-  for (int g = 0; g < NORM_TAIL_MAX_G; ++g) {
-    const int n = (g * NORM_TAIL_THREADS + threadIdx.x) * 4;
-    if (n >= N) continue;
+  for (int g = 0; g < G; ++g) {
+    if ((g * NT + (int)threadIdx.x) * 4 >= N) continue;
 #pragma unroll
     for (int e = 0; e < 4; ++e) { const float d = h[g][e] - mean; sq += d * d; }
   }
-  const float rstd = rsqrtf(block_sum_1024(sq, red) / (float)N + p.nt.eps);
-  const bf16* gamma = (const bf16*)p.nt.gamma;
-  const bf16* beta = (const bf16*)p.nt.beta;
+  const float rstd = rsqrtf(block_sum_tail(sq, red[1]) / (float)N + p.nt.eps);
   bf16* yn = (bf16*)p.nt.y_norm + (int64_t)m * N;
 #pragma unroll
-  for (int g = 0; g < NORM_TAIL_MAX_G; ++g) {
-    const int n = (g * NORM_TAIL_THREADS + threadIdx.x) * 4;
+  for (int g = 0; g < G; ++g) {
+    const int n = (g * NT + threadIdx.x) * 4;
     if (n >= N) continue;
+    const float ga[4] = {bf_lo(gv[g][0]), bf_hi(gv[g][0]), bf_lo(gv[g][1]), bf_hi(gv[g][1])};
+    const float sh[4] = {bf_lo(sv[g][0]), bf_hi(sv[g][0]), bf_lo(sv[g][1]), bf_hi(sv[g][1])};
     float o[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      o[e] = (h[g][e] - mean) * rstd * (float)gamma[n + e];
-      if (beta != nullptr) o[e] += (float)beta[n + e];
-    }
+    for (int e = 0; e < 4; ++e) o[e] = (h[g][e] - mean) * rstd * ga[e] + sh[e];
     u32x2 pk;
     pk[0] = pack_bf2(o[0], o[1]); pk[1] = pack_bf2(o[2], o[3]);
     *reinterpret_cast<u32x2*>(yn + n) = pk;
@@ -1369,9 +1322,21 @@ forge_status launch_act(const GemmParams& p, hipStream_t s) {
   q.N = sk.ncols;
   q.k_per_split = sk.k_per_split;
   forge_status st;
-  if (v == V_SKINNY_FAST && sk.fused && q.w8 == nullptr && MODE == MODE_PLAIN && p.nt.y_norm == nullptr)
+  const bool plain_out = MODE == MODE_PLAIN && p.nt.y_norm == nullptr;
+  int splits = sk.splits;
+  const bool w8 = p.w8 != nullptr, rows_ok = v == V_SKINNY_FAST;
+  // few rows of x: the kernel that keeps them in registers, where its plan takes the problem
+  if (rows_ok && p.nt.y_norm == nullptr) {
+    const RowsPlan rp = plan_rows(p.M, sk.ncols, p.K, w8, 0);
+    if (rp.ranges > 0) return launch_rows(p, rp, ACT, MODE == MODE_QKV, false, s);
+  }
+  if (rows_ok && sk.fused && !w8 && plain_out)
     return launch_wstream<128, false, ACT>(q, 1, s);     // finishes its outputs itself
-  if (v == V_SKINNY_FAST) {
+  const RowsPlan rp = rows_ok ? plan_rows(p.M, sk.ncols, p.K, w8, sk.splits) : RowsPlan{0, 0, 0};
+  if (rp.ranges > 0) {
+    splits = rp.ranges;                                  // (the workspace holds sk.splits planes)
+    st = launch_rows(q, rp, FORGE_ACT_NONE, false, true, s);
+  } else if (v == V_SKINNY_FAST) {
     if (q.w8 != nullptr) st = sk.bn == 256 ? launch_wstream<256, true>(q, sk.splits, s) : launch_wstream<128, true>(q, sk.splits, s);
     else st = sk.bn == 256 ? launch_wstream<256, false>(q, sk.splits, s) : launch_wstream<128, false>(q, sk.splits, s);
   } else {
@@ -1380,15 +1345,19 @@ forge_status launch_act(const GemmParams& p, hipStream_t s) {
   if (st != FORGE_OK) return st;
   if (MODE == MODE_QKV && p.sp.rope) {
     const int64_t threads = (int64_t)p.M * (p.sp.q_heads + 2 * p.sp.kv_heads) * (p.sp.head_dim / 8);
-    splitk_reduce_qkv_rope_kernel<<<(unsigned)ceil_div64(threads, 256), 256, 0, s>>>(p, sk.splits);
+    splitk_reduce_qkv_rope_kernel<<<(unsigned)ceil_div64(threads, 256), 256, 0, s>>>(p, splits);
     return launch_status();
   }
   if (MODE == MODE_PLAIN && ACT == FORGE_ACT_NONE && p.nt.y_norm != nullptr) {
-    splitk_reduce_norm_kernel<<<p.M, NORM_TAIL_THREADS, 0, s>>>(p, sk.splits);
+    const int nt = min(NORM_TAIL_THREADS, ceil_div(p.N, 256) * 64);     // one group of 4 columns per thread while that fits
+    const int groups = ceil_div(p.N, nt * 4);
+    if (groups == 1) splitk_reduce_norm_kernel<1><<<p.M, nt, 0, s>>>(p, splits);
+    else if (groups == 2) splitk_reduce_norm_kernel<2><<<p.M, nt, 0, s>>>(p, splits);
+    else splitk_reduce_norm_kernel<NORM_TAIL_MAX_G><<<p.M, nt, 0, s>>>(p, splits);
     return launch_status();
   }
   const int64_t threads = (int64_t)p.M * ceil_div(p.N, 4);
-  splitk_reduce_kernel<ACT, MODE == MODE_QKV><<<(unsigned)ceil_div64(threads, 256), 256, 0, s>>>(p, sk.splits, sk.ncols);
+  splitk_reduce_kernel<ACT, MODE == MODE_QKV><<<(unsigned)ceil_div64(threads, 256), 256, 0, s>>>(p, splits, sk.ncols);
   return launch_status();
   }
 }

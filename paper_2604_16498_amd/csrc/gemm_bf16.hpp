@@ -1,0 +1,78 @@
+// What the bf16 linear kernels share: the launch parameters, the head split's addressing, the int8
+// conversion and the LDS-only block barrier.  Internal to the library.
+#pragma once
+#include "common.hpp"
+
+namespace forge {
+
+constexpr int BK = 64;            // k per slab of the tile and streaming kernels
+
+__device__ inline bf16* split_dst_bf16(const QkvSplit& sp, int m, int n) {
+  const int dh = sp.head_dim;
+  const int b = m / sp.q_len, s = m % sp.q_len;
+  const int nq = sp.q_heads * dh, nk = sp.kv_heads * dh;
+  if (n < nq) {
+    const int h = n / dh;
+    return (bf16*)sp.q + (((int64_t)b * sp.q_heads + h) * sp.q_len + s) * dh + n % dh;
+  }
+  const bool is_k = n < nq + nk;
+  const int nn = is_k ? n - nq : n - nq - nk;
+  const int h = nn / dh;
+  bf16* basep = (bf16*)(is_k ? sp.k_cache : sp.v_cache);
+  return basep + (((int64_t)b * sp.kv_heads + h) * sp.kv_cap + seq_position(sp.pos, b, sp.pos0) + s) * dh + nn % dh;
+}
+
+struct GemmParams {
+  const bf16* x;
+  const bf16* w;
+  const bf16* bias;
+  const bf16* residual;
+  bf16* y;
+  int M, N, K;        // N: output columns
+  int ldy;            // row stride of y and residual (elements)
+  int tiles_m, tiles_n;
+  int k_per_split;    // split-K: k range of one block (multiple of 64); otherwise >= K
+  int splits;         // split-K in the persistent kernel: number of k ranges
+  float* part;        // split-K: fp32 partial sums [splits, M, N]
+  size_t part_bytes;  // bytes behind part
+  QkvSplit sp;
+  NormTail nt;        // nt.y_norm == nullptr: none
+  const int8_t* w8;     // weight-only int8 (M <= 64 streaming path): [N, K] bytes; w is NULL then
+  const float* wscale;  // one scale per weight row, applied to the reduced sum before the bias
+  int row0;             // row of the whole problem that row 0 of this launch is (head split only)
+  int col0;             // column of the whole problem that column 0 of this launch is (head split only)
+};
+
+typedef __attribute__((address_space(3))) void lds_void;
+
+// Block barrier for data exchanged through LDS only: this wave's LDS traffic has completed
+// (lgkmcnt 0), vector-memory loads and stores stay in flight (__syncthreads would drain them too).
+__device__ inline void lds_barrier() {
+  __builtin_amdgcn_s_waitcnt(0xc07f);
+  __builtin_amdgcn_s_barrier();
+}
+
+// 8 signed bytes -> 8 bf16 (exact: |q| <= 127 has 7 significant bits)
+__device__ inline bf16x8 cvt_i8x8_bf16(u32x2 v) {
+  bf16x8 r;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const int b = (int)(int8_t)((v[e >> 2] >> (8 * (e & 3))) & 0xff);
+    r[e] = (bf16)(float)b;
+  }
+  return r;
+}
+
+// ---- decode-sized problems with x in registers (gemm_bf16_rows.hip) ------------------------------
+struct RowsPlan {
+  int ranges;    // k ranges; 0: the problem does not take this path
+  int steps;     // 64-byte steps of a weight row that a wave loads
+  int spw;       // ... of which it multiplies at most this many
+};
+// rows: weight rows.  max_ranges 0: the plan of a launch that finishes its outputs itself (plain, head
+// split, rotated head split), one range; otherwise of one that writes at most that many fp32 planes
+// [ranges, M, rows] for the reduce kernels (raw).
+RowsPlan plan_rows(int M, int rows, int K, bool w8, int max_ranges);
+forge_status launch_rows(const GemmParams& p, const RowsPlan& pl, int act, bool qkv, bool raw, hipStream_t s);
+
+}  // namespace forge
