@@ -102,6 +102,15 @@ __device__ inline void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// Block barrier for data exchanged through LDS only: this wave's LDS traffic has completed
+// (lgkmcnt 0), vector-memory loads and stores stay in flight (__syncthreads would drain them too).
+__device__ inline void lds_barrier() {
+  asm volatile("" ::: "memory");        // the compiler moves no memory access across either
+  __builtin_amdgcn_s_waitcnt(0xc07f);
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
 // ---- activations on the fp32 accumulator ------------------------------------------------
 // tanh-GELU written through the logistic form: 0.5 x (1 + tanh u) = x / (1 + exp(-2u)),
 // u = sqrt(2/pi) (x + 0.044715 x^3).

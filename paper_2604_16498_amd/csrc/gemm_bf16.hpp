@@ -45,13 +45,6 @@ struct GemmParams {
 
 typedef __attribute__((address_space(3))) void lds_void;
 
-// Block barrier for data exchanged through LDS only: this wave's LDS traffic has completed
-// (lgkmcnt 0), vector-memory loads and stores stay in flight (__syncthreads would drain them too).
-__device__ inline void lds_barrier() {
-  __builtin_amdgcn_s_waitcnt(0xc07f);
-  __builtin_amdgcn_s_barrier();
-}
-
 // 8 signed bytes -> 8 bf16 (exact: |q| <= 127 has 7 significant bits)
 __device__ inline bf16x8 cvt_i8x8_bf16(u32x2 v) {
   bf16x8 r;
