@@ -1293,6 +1293,10 @@ forge_status launch_act(const GemmParams& p, hipStream_t s) {
     case V_FAST_256: return launch_pers<256, 256, 2, 4, ACT, MODE>(p, s);
     case V_FAST_128: {
       const int ncols = ACT == FORGE_ACT_SWIGLU ? 2 * p.N : p.N;
+      // (that kernel knows neither a column offset nor the scales of a dequantised weight)
+      const bool rows_ok = p.col0 == 0 && p.wscale == nullptr;
+      const RowsPlan one = rows_ok ? plan_rows_prompt(p.M, ncols, p.K, 0) : RowsPlan{0, 0, 0};
+      if (one.ranges > 0) return launch_rows(p, one, ACT, MODE == MODE_QKV, false, s);
       const PersSplit ps = plan_pers_split(p.M, ncols, p.K);
       if (ps.splits > 1 && p.part != nullptr &&
           p.part_bytes >= (size_t)ps.splits * p.M * ncols * sizeof(float)) {
@@ -1300,10 +1304,13 @@ forge_status launch_act(const GemmParams& p, hipStream_t s) {
         q.N = ncols;
         q.splits = ps.splits;
         q.k_per_split = ps.k_per_split;
-        const forge_status st = launch_pers<128, 128, 2, 4, FORGE_ACT_NONE, MODE_SPLITK>(q, s);
+        const RowsPlan rp = rows_ok ? plan_rows_prompt(p.M, ncols, p.K, ps.splits) : RowsPlan{0, 0, 0};
+        const forge_status st = rp.ranges > 0 ? launch_rows(q, rp, FORGE_ACT_NONE, false, true, s)
+                                              : launch_pers<128, 128, 2, 4, FORGE_ACT_NONE, MODE_SPLITK>(q, s);
         if (st != FORGE_OK) return st;
         const int64_t threads = (int64_t)p.M * ceil_div(p.N, 4);
-        splitk_reduce_kernel<ACT, MODE == MODE_QKV><<<(unsigned)ceil_div64(threads, 256), 256, 0, s>>>(p, ps.splits, ncols);
+        splitk_reduce_kernel<ACT, MODE == MODE_QKV><<<(unsigned)ceil_div64(threads, 256), 256, 0, s>>>(
+            p, rp.ranges > 0 ? rp.ranges : ps.splits, ncols);
         return launch_status();
       }
       // 8 waves of 64 x 32 (16 waves per CU) hide the L2 latency of the small tile better than 4

@@ -1,4 +1,4 @@
-"""GPU parity of the decode-sized linear that keeps the rows of x in registers, at the sizes where its
+"""GPU parity of the linear that keeps the rows of x in registers (decode steps, small prompts), at the sizes where its
 tiles (16 weight rows, 8 waves that share K, groups of 16 rows of x, up to 8 collected tiles) have
 remainders, against the fp64 oracle."""
 import math
@@ -33,6 +33,12 @@ CASES = [  # M, N, K, act, residual, padded row stride
     (7, 2048, 8192, "gelu_tanh", True, 0),     # several k ranges and the reduce launch
     (40, 768, 3072, "none", True, 0),
     (9, 520, 4160, "swiglu", False, 0),        # one step past a single range
+    # prompts in chunks of 128 and of 64 rows (int8: the bf16 copy on the tile kernels)
+    (65, 2304, 768, "none", False, 0),
+    (129, 1003, 704, "gelu_tanh", True, 1008), # one row in the second chunk
+    (300, 768, 768, "swiglu", False, 0),
+    (130, 2056, 2048, "relu", True, 0),        # chunks of 64, two rows in the third
+    (200, 768, 3072, "none", True, 0),         # planes of 128-row chunks
 ]
 
 
