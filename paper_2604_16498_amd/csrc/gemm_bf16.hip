@@ -40,6 +40,7 @@
 // per CU), fp32 partials, and fixed-order reduce kernels that carry the epilogue (and, inside a
 // decoder layer, RoPE or the following norm).
 // Prompt-sized M with few tiles and a long K: the tile kernel itself walks (k range, tile) items.
+#include <math.h>
 #include <type_traits>
 #include "gemm_bf16.hpp"
 
@@ -998,7 +999,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(GemmParams p, int sp
 // heads before the single rounding to bf16.  One thread owns 4 consecutive pair indices of one
 // head of one row: columns d..d+3 and d+dh/2..d+dh/2+3.  Angles as in rope_kernel: fp64
 // position * theta, theta_i = base^(-2i/dh).
-__global__ __launch_bounds__(256) void splitk_reduce_qkv_rope_kernel(GemmParams p, int splits) {
+__global__ __launch_bounds__(256) void splitk_reduce_qkv_rope_kernel(GemmParams p, int splits, double l2b) {
   const int dh = p.sp.head_dim, half = dh / 2, groups = half / 4;
   const int heads = p.sp.q_heads + 2 * p.sp.kv_heads;
   const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -1026,13 +1027,10 @@ __global__ __launch_bounds__(256) void splitk_reduce_qkv_rope_kernel(GemmParams 
   }
   if (hg < p.sp.q_heads + p.sp.kv_heads) {   // q and k heads rotate, v heads do not
     const double pos = (double)(seq_position(p.sp.pos, (p.row0 + m) / p.sp.q_len, p.sp.pos0) + (p.row0 + m) % p.sp.q_len);
-    const double l2b = log2((double)p.sp.rope_base);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const double theta = exp2(-2.0 * (double)(4 * j + e) / (double)dh * l2b);
-      double sv, cv;
-      sincos(pos * theta, &sv, &cv);
-      const float c = (float)cv, sn = (float)sv, a = lo[e], d = hi[e];
+      const floatx2 t = cos_sin(pos * exp2(-2.0 * (double)(4 * j + e) / (double)dh * l2b));
+      const float c = t[0], sn = t[1], a = lo[e], d = hi[e];
       lo[e] = a * c - d * sn;
       hi[e] = d * c + a * sn;
     }
@@ -1352,7 +1350,7 @@ forge_status launch_act(const GemmParams& p, hipStream_t s) {
   if (st != FORGE_OK) return st;
   if (MODE == MODE_QKV && p.sp.rope) {
     const int64_t threads = (int64_t)p.M * (p.sp.q_heads + 2 * p.sp.kv_heads) * (p.sp.head_dim / 8);
-    splitk_reduce_qkv_rope_kernel<<<(unsigned)ceil_div64(threads, 256), 256, 0, s>>>(p, splits);
+    splitk_reduce_qkv_rope_kernel<<<(unsigned)ceil_div64(threads, 256), 256, 0, s>>>(p, splits, log2((double)p.sp.rope_base));
     return launch_status();
   }
   if (MODE == MODE_PLAIN && ACT == FORGE_ACT_NONE && p.nt.y_norm != nullptr) {
@@ -1384,16 +1382,12 @@ __global__ __launch_bounds__(256) void dequant_int8_kernel(const int8_t* __restr
 // tab[s][i] = (cos, sin)(p * theta_i), theta_i = base^(-2i/dh), evaluated in fp64 as rope_kernel
 // does (p * theta reaches thousands of radians) and stored as fp32.
 __global__ __launch_bounds__(256) void rope_table_kernel(float* __restrict__ tab, int q_len, int head_dim,
-                                                         int pos0, float base) {
+                                                         int pos0, double l2b) {
   const int half = head_dim / 2;
   const int gid = blockIdx.x * blockDim.x + threadIdx.x;
   if (gid >= q_len * half) return;
   const int i = gid % half, s = gid / half;
-  const double theta = exp2(-2.0 * (double)i / (double)head_dim * log2((double)base));
-  double sv, cv;
-  sincos((double)(pos0 + s) * theta, &sv, &cv);
-  floatx2 o = {(float)cv, (float)sv};
-  *reinterpret_cast<floatx2*>(tab + 2 * (int64_t)gid) = o;
+  *reinterpret_cast<floatx2*>(tab + 2 * (int64_t)gid) = cos_sin((double)(pos0 + s) * exp2(-2.0 * (double)i / (double)head_dim * l2b));
 }
 
 }  // namespace
@@ -1495,7 +1489,7 @@ forge_status launch_gemm_bf16(const GemmArgs& a, hipStream_t s) {
       if (a.workspace == nullptr || a.workspace_bytes < tab_at + tab_bytes) return FORGE_ERR_WORKSPACE;
       float* tab = (float*)((char*)a.workspace + tab_at);
       const int n_tab = p.sp.q_len * (p.sp.head_dim / 2);
-      rope_table_kernel<<<ceil_div(n_tab, 256), 256, 0, s>>>(tab, p.sp.q_len, p.sp.head_dim, p.sp.pos0, p.sp.rope_base);
+      rope_table_kernel<<<ceil_div(n_tab, 256), 256, 0, s>>>(tab, p.sp.q_len, p.sp.head_dim, p.sp.pos0, log2((double)p.sp.rope_base));
       if (hipGetLastError() != hipSuccess) return FORGE_ERR_HIP;
       p.sp.rope_tab = tab;
       p.part = nullptr;
