@@ -88,7 +88,9 @@ int forge_version(void);
  * strides multiples of 8 elements; scale positive and finite (else FORGE_ERR_INVALID_ARG: the
  * paper's scale is 1/sqrt(d_k)).  q_len == 1 takes the split-KV (decode) path, which needs
  * workspace; the size reported for (.., q_len 1, kv_len L, ..) also serves every shorter
- * length, so a generation loop asks once, for the capacity of its cache.
+ * length, so a generation loop asks once, for the capacity of its cache.  bf16 prompts with few
+ * query blocks and many keys (a conversation's next turn) use their workspace to spread the keys
+ * over idle compute units; without it, or with less, they run slower, not refused.
  * ------------------------------------------------------------------------------------ */
 size_t forge_attn_fused_workspace_bytes(int batch, int q_heads, int kv_heads, int q_len,
                                         int kv_len, int head_dim, forge_dtype dt);

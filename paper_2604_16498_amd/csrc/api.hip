@@ -252,7 +252,8 @@ forge_status forge_attn_fused(const void* q, const void* k, const void* v, void*
     return FORGE_ERR_INVALID_ARG;
   if (kv_head_stride % 8 != 0 || kv_batch_stride % 8 != 0) return FORGE_ERR_INVALID_ARG;
   if (out == q || out == k || out == v) return FORGE_ERR_INVALID_ARG;
-  const size_t need = attn_ws(batch, q_heads, kv_heads, q_len, kv_len, head_dim, dt);
+  // (a prompt runs without its workspace too)
+  const size_t need = q_len == 1 ? attn_ws(batch, q_heads, kv_heads, q_len, kv_len, head_dim, dt) : 0;
   if (need > 0 && (workspace == nullptr || workspace_bytes < need)) return FORGE_ERR_WORKSPACE;
   AttnArgs a = {q, k, v, out, batch, q_heads, kv_heads, q_len, kv_len, head_dim,
                 kv_batch_stride, kv_head_stride, scale, causal, workspace, workspace_bytes, nullptr, 0, 0};

@@ -53,6 +53,8 @@ inline size_t attn_ws(int batch, int q_heads, int kv_heads, int q_len, int kv_le
                forge_dtype dt) {
   if (dt == FORGE_BF16 && q_len == 1)
     return attn_decode_workspace_bytes(batch, q_heads, kv_heads, kv_len, head_dim);
+  if (dt == FORGE_BF16 && (head_dim == 64 || head_dim == 128))      // optional, see there
+    return attn_prefill_workspace_bytes(batch, q_heads, q_len, kv_len, head_dim);
   return 0;
 }
 

@@ -61,6 +61,8 @@ struct AttnParams {
   int n_qblocks;
   const float* mask;        // additive, fp32 [*, *, q_len, kv_len]; only read by the MASKED kernel
   int64_t mask_bs, mask_hs;
+  float* part;              // SPLIT: fp32 partial rows [splits][batch * q_heads * q_len][dh], then (max, sum) pairs
+  int splits;
   int mask_vec;             // every group of 4 consecutive keys of a mask row is one aligned 16-byte load
 };
 
@@ -78,7 +80,10 @@ __device__ inline float xchg32_sum(float x) {
 // the scaled scores before the softmax.  A lane's 32 mask values of a tile (its query row, the keys
 // its score registers hold: 8 groups of 4 consecutive keys) are requested at the end of the
 // preceding matrix phase, 16 bytes per load, and arrive behind the half-tile barrier.
-template <int DH, bool MASKED>
+// SPLIT: block z of a query block walks only its share of the key tiles and writes unnormalised fp32
+// rows with their (maximum, sum); attn_prefill_merge adds the shares.  For calls with fewer query blocks
+// than CUs (a turn of 777 tokens has 4 per head).
+template <int DH, bool MASKED, bool SPLIT>
 __global__ __launch_bounds__(512) void attn_prefill_kernel(AttnParams p) {
   constexpr int BQ = 256, BKV = 64;
   constexpr int CPR = DH / 8;                 // 16-byte chunks per row
@@ -125,7 +130,10 @@ __global__ __launch_bounds__(512) void attn_prefill_kernel(AttnParams p) {
 
   // keys a query may see: [0, limit]
   const int last_q_blk = min(q0 + BQ, p.q_len) - 1;
-  const int n_tiles = ceil_div((p.causal ? last_q_blk + off : p.kv_len - 1) + 1, BKV);
+  const int all_tiles = ceil_div((p.causal ? last_q_blk + off : p.kv_len - 1) + 1, BKV);
+  const int share = SPLIT ? ceil_div(all_tiles, p.splits) : all_tiles;
+  const int t_first = SPLIT ? (int)blockIdx.z * share : 0;            // this block's tiles: [t_first, n_tiles)
+  const int n_tiles = min(all_tiles, t_first + share);                // (none: neutral rows, maximum -1e30, sum 0)
   const int my_limit = p.causal ? my_q + off : p.kv_len - 1;
   const int wave_max_limit = p.causal ? min(q0w + 31, p.q_len - 1) + off : p.kv_len - 1;
   const int wave_min_limit = p.causal ? q0w + off : p.kv_len - 1;
@@ -299,16 +307,16 @@ __global__ __launch_bounds__(512) void attn_prefill_kernel(AttnParams p) {
   auto wave_needs = [&](int t) { return t < n_tiles && t * BKV <= wave_max_limit; };   // wave-uniform
 
   // ---- prologue: K(0), V(0), K(1) in LDS, S(0) in registers ---------------------------------------
-  load_rows(kbase, 0, rk);
-  load_rows(vbase, 0, rv);
-  store_k(0);
-  store_v(0);
-  load_rows(kbase, 1, rk);             // (tiles past the end re-read the last key: a branch around the
-  load_rows(vbase, 1, rv);             // loads would make the waits of the loop drain them all)
+  load_rows(kbase, t_first, rk);
+  load_rows(vbase, t_first, rv);
+  store_k(t_first & 1);
+  store_v(t_first & 1);
+  load_rows(kbase, t_first + 1, rk);   // (tiles past the end re-read the last key: a branch around the
+  load_rows(vbase, t_first + 1, rv);   // loads would make the waits of the loop drain them all)
   lds_barrier();
-  if (wave_needs(0)) {
-    scores(0);
-    mask_prefetch(0);
+  if (wave_needs(t_first)) {
+    scores(t_first);
+    mask_prefetch(t_first);
   }
   lds_barrier();
 
@@ -327,7 +335,7 @@ __global__ __launch_bounds__(512) void attn_prefill_kernel(AttnParams p) {
     }
   };
   if (!late) {
-    for (int t = 0; t < n_tiles; ++t) {
+    for (int t = t_first; t < n_tiles; ++t) {
       if (t + 1 < n_tiles) store_k((t + 1) & 1);
       load_rows(kbase, t + 2, rk);
       if (wave_needs(t)) softmax(t);
@@ -340,7 +348,7 @@ __global__ __launch_bounds__(512) void attn_prefill_kernel(AttnParams p) {
     lds_barrier();                     // the late waves' last step
   } else {
     lds_barrier();                     // the early waves' first step
-    for (int t = 0; t < n_tiles; ++t) {
+    for (int t = t_first; t < n_tiles; ++t) {
       if (wave_needs(t)) softmax(t);
       lds_barrier();
       matrix_phase(t);
@@ -350,6 +358,22 @@ __global__ __launch_bounds__(512) void attn_prefill_kernel(AttnParams p) {
 
   // ---- normalise and store: lane owns query my_q; registers 4g..4g+3 are 4 consecutive d -----
   const float l_tot = xchg32_sum(l_run);
+  if constexpr (SPLIT) {
+    if (my_q >= p.q_len) return;
+    const int64_t rows = (int64_t)(gridDim.x) * p.q_len, row = (int64_t)blockIdx.x * p.q_len + my_q;   // blockIdx.x = batch * q_heads + head
+    float* prow = p.part + ((int64_t)blockIdx.z * rows + row) * DH;
+#pragma unroll
+    for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+      for (int gg = 0; gg < 4; ++gg)
+        *reinterpret_cast<floatx4*>(prow + dt * 32 + 8 * gg + 4 * fh) =
+            floatx4{o_acc[dt][4 * gg], o_acc[dt][4 * gg + 1], o_acc[dt][4 * gg + 2], o_acc[dt][4 * gg + 3]};
+    if (fh == 0) {
+      floatx2* ml = reinterpret_cast<floatx2*>(p.part + (int64_t)p.splits * rows * DH);
+      ml[(int64_t)blockIdx.z * rows + row] = floatx2{m_run * c, l_tot};
+    }
+    return;
+  }
   if (my_q < p.q_len) {
     const float inv = 1.0f / l_tot;
     bf16* orow = p.out + ((int64_t)b * p.q_len + my_q) * ((int64_t)p.q_heads * DH) + (int64_t)h * DH;
@@ -365,8 +389,37 @@ __global__ __launch_bounds__(512) void attn_prefill_kernel(AttnParams p) {
   }
 }
 
-template <int DH, bool MASKED>
-forge_status launch_dh(const AttnArgs& a, hipStream_t s) {
+// Merge of the key shares: DH / 8 lanes per row, 8 columns each; shares in order.
+template <int DH>
+__global__ __launch_bounds__(256) void attn_prefill_merge(const float* __restrict__ part, bf16* __restrict__ out,
+                                                          int q_heads, int q_len, int64_t rows, int splits) {
+  constexpr int LPR = DH / 8;
+  const int64_t row = (int64_t)blockIdx.x * (256 / LPR) + threadIdx.x / LPR;
+  const int c = threadIdx.x % LPR;
+  if (row >= rows) return;
+  const floatx2* ml = reinterpret_cast<const floatx2*>(part + (int64_t)splits * rows * DH);
+  float mx = -INFINITY;
+  for (int z = 0; z < splits; ++z) mx = fmaxf(mx, ml[z * rows + row][0]);
+  float o[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, l = 0.f;
+#pragma unroll 2
+  for (int z = 0; z < splits; ++z) {
+    const floatx2 t = ml[z * rows + row];
+    const float w = __builtin_amdgcn_exp2f(t[0] - mx);
+    l += t[1] * w;
+    float v[8];
+    Vec8<float>::load(part + (z * rows + row) * DH + c * 8, v);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) o[e] += v[e] * w;
+  }
+  const float inv = 1.0f / l;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) o[e] *= inv;
+  const int64_t bh = row / q_len, q = row % q_len, b = bh / q_heads, h = bh % q_heads;
+  Vec8<bf16>::store(out + ((b * q_len + q) * q_heads + h) * DH + c * 8, o);
+}
+
+template <int DH, bool MASKED, bool SPLIT>
+forge_status launch_split(const AttnArgs& a, int splits, hipStream_t s) {
   AttnParams p;
   p.q = (const bf16*)a.q;
   p.k = (const bf16*)a.k;
@@ -381,18 +434,55 @@ forge_status launch_dh(const AttnArgs& a, hipStream_t s) {
   p.scale_log2e = a.scale * 1.4426950408889634f;
   p.causal = a.causal;
   p.n_qblocks = ceil_div(a.q_len, 256);
+  p.part = (float*)a.workspace;
+  p.splits = splits;
   p.mask = a.mask;
   p.mask_bs = a.mask_batch_stride;
   p.mask_hs = a.mask_head_stride;
   p.mask_vec = a.mask != nullptr && a.kv_len % 4 == 0 && (reinterpret_cast<uintptr_t>(a.mask) & 15u) == 0 &&
                a.mask_batch_stride % 4 == 0 && a.mask_head_stride % 4 == 0;
   constexpr int smem = 2 * 64 * ((DH * 2 + 16) + (DH * 2 + 64));
-  auto kern = attn_prefill_kernel<DH, MASKED>;
+  auto kern = attn_prefill_kernel<DH, MASKED, SPLIT>;
   static std::atomic<uint64_t> lds_raised{0};   // per kernel instantiation
   if (raise_lds_limit(reinterpret_cast<const void*>(kern), smem, lds_raised) != FORGE_OK) return FORGE_ERR_HIP;
-  dim3 grid(a.q_heads * a.batch, p.n_qblocks), block(512);
+  dim3 grid(a.q_heads * a.batch, p.n_qblocks, splits), block(512);
   kern<<<grid, block, smem, s>>>(p);
+  if (!SPLIT) return launch_status();
+  if (hipGetLastError() != hipSuccess) return FORGE_ERR_HIP;
+  const int64_t rows = (int64_t)a.batch * a.q_heads * a.q_len;
+  attn_prefill_merge<DH><<<(unsigned)ceil_div64(rows, 256 / (DH / 8)), 256, 0, s>>>(p.part, p.out, a.q_heads, a.q_len, rows, splits);
   return launch_status();
+}
+
+// Key shares of a call: only where its query blocks leave CUs idle, at most as many as those CUs take and
+// none shorter than 256 keys.  A block walks a 64-key tile in 1.5 us, the merge launch costs 4.5 us and
+// a share's partial rows go out and back at about 5 TB/s; the count with the most left over is
+// non-decreasing in kv_len.  us: 777 queries behind 2500 keys (32 heads of 128) 96.8 -> 66.3, 80 behind 4000
+// 113 -> 27, 300 behind 1000 42.6 -> 27.4, 1 x 12 heads of 64 x 1000 25.9 -> 20.5; two shares of 520 x 32
+// heads would take 24.9 against 22.2 unsplit.
+inline int plan_shares(int batch, int q_heads, int q_len, int kv_len, int head_dim) {
+  const int64_t pairs = (int64_t)batch * q_heads, blocks = pairs * ceil_div(q_len, 256);
+  const int most = (int)min(min((int64_t)compute_units() / blocks, (int64_t)kv_len / 256), (int64_t)8);
+  const double tiles = kv_len / 64.0, share_us = (double)(pairs * q_len) * head_dim * 8 / 5e6;
+  int best = 1;
+  double left = 0.0;
+  for (int n = 2; n <= most; ++n) {
+    const double l = 1.5 * (tiles - tiles / n) - 4.5 - share_us * n;
+    if (l > left) { left = l; best = n; }
+  }
+  return best;
+}
+
+template <int DH, bool MASKED>
+forge_status launch_dh(const AttnArgs& a, hipStream_t s) {
+  if constexpr (!MASKED) {
+    // (the workspace is optional: without it, or with less, the call runs unsplit)
+    const int shares = plan_shares(a.batch, a.q_heads, a.q_len, a.kv_len, DH);
+    if (shares > 1 && a.workspace != nullptr &&
+        a.workspace_bytes >= (size_t)shares * a.batch * a.q_heads * a.q_len * (DH + 2) * sizeof(float))
+      return launch_split<DH, false, true>(a, shares, s);
+  }
+  return launch_split<DH, MASKED, false>(a, 1, s);
 }
 
 }  // namespace
@@ -401,6 +491,13 @@ forge_status launch_attn_prefill_bf16(const AttnArgs& a, hipStream_t s) {
   if (a.head_dim == 64) return a.mask ? launch_dh<64, true>(a, s) : launch_dh<64, false>(a, s);
   if (a.head_dim == 128) return a.mask ? launch_dh<128, true>(a, s) : launch_dh<128, false>(a, s);
   return FORGE_ERR_UNSUPPORTED;
+}
+
+// Non-decreasing in kv_len (the share count is), so that a buffer sized for a cache's capacity serves
+// every shorter length.
+size_t attn_prefill_workspace_bytes(int batch, int q_heads, int q_len, int kv_len, int head_dim) {
+  const int shares = plan_shares(batch, q_heads, q_len, kv_len, head_dim);
+  return shares > 1 ? (size_t)shares * batch * q_heads * q_len * (head_dim + 2) * sizeof(float) : 0;
 }
 
 }  // namespace forge

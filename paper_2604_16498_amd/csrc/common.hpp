@@ -290,6 +290,8 @@ forge_status launch_attn_f32_mfma(const AttnArgs& a, hipStream_t s);   // prompt
 forge_status launch_attn_simple_bf16(const AttnArgs& a, hipStream_t s);
 forge_status launch_attn_prefill_bf16(const AttnArgs& a, hipStream_t s);
 forge_status launch_attn_decode_bf16(const AttnArgs& a, hipStream_t s);
+// optional: without it the call runs on one block per query block, slower where those are few
+size_t attn_prefill_workspace_bytes(int batch, int q_heads, int q_len, int kv_len, int head_dim);
 size_t attn_decode_workspace_bytes(int batch, int q_heads, int kv_heads, int kv_len, int head_dim);
 // The library's own fixed scratch array for the decode attention (one per GPU): its size, and its
 // address on the current device.  Every call on a GPU shares it.
