@@ -1043,7 +1043,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_qkv_rope_kernel(GemmParams 
 }
 
 // Split-K second stage of a projection with residual, followed by the normalisation of the
-// finished rows: one 1024-thread block per row (the partials of a row are 10^5 bytes that sit in
+// finished rows: one block of up to 1024 threads per row (the partials of a row are 10^5 bytes that sit in
 // L2; many loads in flight per CU are what makes a single CU per row fast enough); h = sum + bias
 // + residual stays in fp32 registers, is stored rounded to y, and y_norm = Norm(h) is computed
 // from the fp32 values (mean, then centred variance, as residual_norm_kernel does).
