@@ -248,6 +248,9 @@ typedef struct {
   const float *s_qkv, *s_o, *s_up, *s_down;
 } forge_block_desc;
 
+/* For a prompt the size does not depend on kv_cap (the attention's key shares lie in bytes that the
+ * projections need anyway).  It is not monotone in q_len everywhere: the projections' k ranges become fewer as
+ * the rows become more, so a program with several prompt lengths takes the largest of their sizes. */
 size_t forge_decoder_block_workspace_bytes(const forge_block_desc* desc, int batch, int q_len,
                                            int kv_cap);
 

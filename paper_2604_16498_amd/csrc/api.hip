@@ -39,21 +39,14 @@ BlockPlan plan_block(const forge_block_desc* d, int batch, int q_len, int kv_cap
   const size_t es = esize(d->dt);
   const size_t T = (size_t)batch * q_len;
   const int hd = d->q_heads * d->head_dim;
-  const int nqkv = (d->q_heads + 2 * d->kv_heads) * d->head_dim;
   BlockPlan p;
   p.y = align_up(T * d->d_model * es, 256);
   p.q = align_up(T * hd * es, 256);
   p.o = align_up(T * hd * es, 256);
-  p.u = align_up(T * d->d_ff * es, 256);
-  p.attn = align_up(attn_ws(batch, d->q_heads, d->kv_heads, q_len, kv_cap, d->head_dim, d->dt), 256);
-  const bool w8 = block_w8(d);
-  size_t g = 0;
-  for (size_t v : {gemm_qkv_workspace_bytes((int)T, nqkv, d->d_model, d->dt, w8, d->use_rope != 0, q_len, d->head_dim),
-                   gemm_ws((int)T, d->d_model, hd, FORGE_ACT_NONE, d->dt, w8),
-                   gemm_ws((int)T, d->d_ff, d->d_model, d->mlp_act, d->dt, w8, true),
-                   gemm_ws((int)T, d->d_model, d->d_ff, FORGE_ACT_NONE, d->dt, w8)})
-    g = v > g ? v : g;
-  p.gemm = align_up(g, 256);
+  p.u = block_mlp_bytes(d, T);
+  // (a decode step's partial rows; a prompt's lie in u and what follows it: block_share_bytes)
+  p.attn = q_len == 1 ? align_up(attn_ws(batch, d->q_heads, d->kv_heads, q_len, kv_cap, d->head_dim, d->dt), 256) : 0;
+  p.gemm = block_gemm_bytes(d, (int)T, q_len);
   p.total = p.y + p.q + p.o + p.u + p.attn + p.gemm;
   return p;
 }
@@ -114,8 +107,10 @@ forge_status run_block(const forge_block_desc* d, const void* x_in, void* x_out,
     trace_mark(s, FORGE_OP_ROPE_K);
   }
   // 4. fused causal attention over cache rows [0, pos0 + q_len)
+  //    (u, aws and gws are contiguous)
   AttnArgs at = {q, k_cache, v_cache, o, batch, d->q_heads, d->kv_heads, q_len, pos0 + q_len, dh,
-                 kv_bs, kv_hs, 1.0f / sqrtf((float)dh), 1, aws, pl.attn, nullptr, 0, 0, seq_pos};
+                 kv_bs, kv_hs, 1.0f / sqrtf((float)dh), 1, q_len == 1 ? aws : u,
+                 q_len == 1 ? pl.attn : block_share_bytes(d, batch, q_len, pos0 + q_len), nullptr, 0, 0, seq_pos};
   st = attn_dispatch(at, d->dt, s);
   if (st != FORGE_OK) return st;
   trace_mark(s, FORGE_OP_ATTN);

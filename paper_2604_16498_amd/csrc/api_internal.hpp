@@ -67,6 +67,34 @@ inline size_t gemm_ws(int M, int N, int K, forge_act act, forge_dtype dt, bool w
 // int8 weights: all four scale vectors given (checked by check_block_desc: all or none)
 inline bool block_w8(const forge_block_desc* d) { return d->s_qkv != nullptr; }
 
+// bytes of the MLP rows of a layer, and of the scratch that its four projections share
+inline size_t block_mlp_bytes(const forge_block_desc* d, size_t rows) { return align_up(rows * d->d_ff * esize(d->dt), 256); }
+inline size_t block_gemm_bytes(const forge_block_desc* d, int rows, int q_len) {
+  const int hd = d->q_heads * d->head_dim, nqkv = (d->q_heads + 2 * d->kv_heads) * d->head_dim;
+  const bool w8 = block_w8(d);
+  size_t g = 0;
+  for (size_t v : {gemm_qkv_workspace_bytes(rows, nqkv, d->d_model, d->dt, w8, d->use_rope != 0, q_len, d->head_dim),
+                   gemm_ws(rows, d->d_model, hd, FORGE_ACT_NONE, d->dt, w8),
+                   gemm_ws(rows, d->d_ff, d->d_model, d->mlp_act, d->dt, w8, true),
+                   gemm_ws(rows, d->d_model, d->d_ff, FORGE_ACT_NONE, d->dt, w8)})
+    g = v > g ? v : g;
+  return align_up(g, 256);
+}
+
+// Inside a layer a prompt's key shares get no bytes of their own (a buffer for a long prompt serves the
+// shorter ones, which are cut into more shares): they lie in the MLP rows and the projections' scratch,
+// which nothing reads or writes while the attention runs.  0: they do not fit, the call runs
+// unsplit.  A function of the shapes alone, so that the plain and the compiled launch list, which place
+// them differently, cut alike: the compiled one keeps registers of one size together, so MLP rows as wide as
+// the residual stream or the heads lie among live ones there and are not counted.
+inline size_t block_share_bytes(const forge_block_desc* d, int batch, int q_len, int kv_len) {
+  if (q_len == 1) return 0;
+  const size_t need = attn_ws(batch, d->q_heads, d->kv_heads, q_len, kv_len, d->head_dim, d->dt);
+  const int rows = batch * q_len;
+  const bool apart = d->d_ff != d->d_model && d->d_ff != d->q_heads * d->head_dim;
+  return need <= (apart ? block_mlp_bytes(d, rows) : 0) + block_gemm_bytes(d, rows, q_len) ? need : 0;
+}
+
 inline forge_status gemm_dispatch(const GemmArgs& a, forge_dtype dt, hipStream_t s) {
   return dt == FORGE_BF16 ? launch_gemm_bf16(a, s) : launch_gemm_f32(a, s);
 }

@@ -10,6 +10,7 @@
 
 #include <algorithm>
 #include <new>
+#include <utility>
 #include <vector>
 
 #include "api_internal.hpp"
@@ -33,6 +34,7 @@ struct Instr {
                // layer's second norm; MLP down: the next layer's first norm or the final norm,
                // REG_EXT when that is the caller's output)
   int ws;      // scratch register
+  size_t share_bytes = 0, share_offset = 0;   // attention of a prompt: its key shares, in the space of registers not live then
 };
 
 }  // namespace
@@ -76,6 +78,32 @@ struct Lowering {
   }
 };
 
+// Key shares of a prompt's attention: the first gap of the planned workspace that no register live at
+// that instruction touches (the MLP rows and the projections' scratch lie side by side, and dead).  Behind the
+// planned bytes only where no gap holds them, which takes layers of different widths.
+void place_shares(forge_compiled* c) {
+  const size_t planned = c->ws_bytes;
+  std::vector<std::pair<size_t, size_t>> live;
+  for (int j = 0; j < (int)c->prog.size(); ++j) {
+    Instr& in = c->prog[j];
+    if (in.share_bytes == 0) continue;
+    live.clear();
+    for (size_t r = 0; r < c->reg_bytes.size(); ++r)
+      if (c->reg_bytes[r] > 0 && c->start[r] >= 0 && c->start[r] <= j && j <= c->end[r])
+        live.emplace_back(c->reg_offset[r], c->reg_offset[r] + c->reg_bytes[r]);
+    std::sort(live.begin(), live.end());
+    size_t at = 0;
+    bool fits = false;
+    for (const auto& l : live) {
+      if (l.first >= at + in.share_bytes) { fits = true; break; }
+      at = std::max(at, align_up(l.second, 256));
+    }
+    if (!fits && at + in.share_bytes > planned) at = align_up(planned, 256);
+    in.share_offset = at;
+    c->ws_bytes = std::max(c->ws_bytes, at + in.share_bytes);
+  }
+}
+
 void lower(forge_compiled* c) {
   const forge_model_desc& m = c->model;
   const forge_block_desc& d0 = c->layers[0];
@@ -117,8 +145,9 @@ void lower(forge_compiled* c) {
       lo.emit({FORGE_OP_ROPE_K, l, 0, REG_NONE, REG_NONE, REG_NONE, REG_NONE, REG_NONE}, {});
     }
     const int o = lo.new_reg(T * hd * es);
-    ws = lo.new_reg(attn_ws(c->batch, d.q_heads, d.kv_heads, c->q_len, c->pos0 + c->q_len, d.head_dim, dt));
-    lo.emit({FORGE_OP_ATTN, l, 0, o, q, REG_NONE, REG_NONE, ws}, {q, ws});
+    ws = lo.new_reg(c->q_len == 1 ? attn_ws(c->batch, d.q_heads, d.kv_heads, 1, c->pos0 + 1, d.head_dim, dt) : 0);
+    lo.emit({FORGE_OP_ATTN, l, 0, o, q, REG_NONE, REG_NONE, ws,
+             block_share_bytes(&d, c->batch, c->q_len, c->pos0 + c->q_len)}, {q, ws});
     const int h_mid = lo.new_reg(h_bytes);
     int y2;
     if (norm_in_gemm) {
@@ -170,6 +199,7 @@ void lower(forge_compiled* c) {
                 c->start.data(), c->end.data());
   c->ws_bytes = plan_workspace(n_regs, c->start.data(), c->end.data(), c->reg_bytes.data(),
                                c->reg_offset.data(), &c->n_bufs);
+  place_shares(c);
 }
 
 // the launches of the instruction list, in order, on stream s
@@ -224,7 +254,8 @@ forge_status run_program(const forge_compiled* c, hipStream_t s) {
       case FORGE_OP_ATTN: {
         AttnArgs at = {in(I.x), kc, vc, out(I.out), c->batch, d->q_heads, d->kv_heads, c->q_len,
                        c->pos0 + c->q_len, dh, kv_bs, kv_hs, 1.0f / sqrtf((float)dh), 1,
-                       out(I.ws), bytes(I.ws), nullptr, 0, 0, c->seq_pos};
+                       I.share_bytes > 0 ? c->workspace + I.share_offset : out(I.ws),
+                       I.share_bytes > 0 ? I.share_bytes : bytes(I.ws), nullptr, 0, 0, c->seq_pos};
         st = attn_dispatch(at, dt, s);
         break;
       }
