@@ -270,7 +270,9 @@ __global__ __launch_bounds__(512) void attn_prefill_kernel(AttnParams p) {
         for (int e = 0; e < 16; ++e) o_acc[i][e] *= alpha;
       m_run = m_new;
     }
-    const float mc = m_run * c;
+    // (a row of a share may have no visible key in a tile that other rows need; its maximum is then the initial
+    // -1e30, which a scale above 2.3e8 takes to -infinity, and hidden scores less it would be NaN)
+    const float mc = SPLIT ? fmaxf(m_run * c, -3.4e38f) : m_run * c;
     float psum = 0.f;
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb) {

@@ -46,3 +46,21 @@ def test_shares_match_the_definition(F, B, Hq, Hkv, Sq, Skv, dh, causal):
     check(outs[0], ref, True, "shared keys")
     check(outs[2], ref, True, "unsplit")
     assert torch.equal(outs[0], outs[1]) and torch.equal(outs[2], outs[3])
+
+
+@pytest.mark.parametrize("scale", [1e9, 1e-20])
+def test_shares_at_extreme_scales(F, scale):
+    """A share in which some rows of a wave see no key and others do, at scales that take the initial
+    maximum (-1e30) past the range of fp32, and close to zero.  Scores have a spread of about 3 either way."""
+    B, H, Sq, Skv, dh = 1, 4, 300, 1300, 64
+    std = math.sqrt(3.0 / (scale * math.sqrt(dh)))
+    q = I.normal(74, 0, "q", (B, H, Sq, dh), std, bf16=True)
+    k = I.normal(74, 0, "k", (B, H, Skv, dh), std, bf16=True)
+    v = I.normal(74, 0, "v", (B, H, Skv, dh), 1.0, bf16=True)
+    need = F.forge_attn_fused_workspace_bytes(B, H, H, Sq, Skv, dh, torch.bfloat16)
+    assert need > 0
+    for ws in (F.workspace(need), None):
+        out = torch.empty(B, Sq, H * dh, dtype=torch.bfloat16, device="cuda")
+        F.forge_attn_fused(dev(q, True), dev(k, True), dev(v, True), out, scale=scale, causal=True, workspace=ws)
+        torch.cuda.synchronize()
+        check(out, O.attention(q, k, v, scale, True), True, "scale %g, shares %s" % (scale, ws is not None))
