@@ -157,6 +157,23 @@ __global__ __launch_bounds__(NW * 64) void gemm_bf16_rows_kernel(RowsParams r) {
     fetch_affine(wr0, n);
   }
 
+  // angles of the block's tiles (at most SLOTS: launch_fin), spread over its lanes while x is on its way; q and k
+  // heads rotate, v heads do not.  Here and once, because the fp64 arithmetic wants a hundred registers:
+  // beside x's operands and the weights in flight it spilled up to 36 (a layer of 32 + 2 x 8 heads of 128,
+  // d_model 4096, MLP 128, at 24 rows: bf16 61.7 -> 53.6 us, int8 53.5 -> 46.3; behind the last product
+  // instead 59.5 and 48.0)
+  if constexpr (ROPE) {
+    const int n = ceil_div(r.tiles - (int)blockIdx.x, (int)gridDim.x) * MT * 128;
+#pragma unroll 1
+    for (int at = tid; at < n; at += NW * 64) {
+      const int t = blockIdx.x + at / (MT * 128) * gridDim.x, m = (at / 8) % (MT * 16);
+      const int pos = __shfl(my_pos, min(m, M - 1), 64);
+      if (t / octs >= p.sp.q_heads + p.sp.kv_heads) continue;
+      const double theta = exp2(-2.0 * (double)((t % octs) * 8 + at % 8) / (double)p.sp.head_dim * r.l2_base);
+      cs[at] = cos_sin((double)pos * theta);
+    }
+  }
+
   int tile = blockIdx.x, slot = 0;
   const char* src = src_of(tile);
   u32x4 wr[C::WIN];
@@ -183,20 +200,6 @@ __global__ __launch_bounds__(NW * 64) void gemm_bf16_rows_kernel(RowsParams r) {
     }
   }
   lds_barrier();                                          // the sums below are collected where the patches lie
-
-  // angles of the tiles collected next (`first`, `first` + gridDim.x, ...), spread over the block while
-  // the loads issued so far are on their way; q and k heads rotate, v heads do not
-  auto angles = [&](int first) {
-    const int n = min(C::SLOTS, (r.tiles - first + (int)gridDim.x - 1) / (int)gridDim.x) * MT * 128;
-#pragma unroll 1
-    for (int at = tid; at < n; at += NW * 64) {
-      const int t = first + at / (MT * 128) * (int)gridDim.x, m = (at / 8) % (MT * 16);
-      const int pos = __shfl(my_pos, min(m, M - 1), 64);
-      if (t / octs >= p.sp.q_heads + p.sp.kv_heads) continue;
-      const double theta = exp2(-2.0 * (double)((t % octs) * 8 + at % 8) / (double)p.sp.head_dim * r.l2_base);
-      cs[at] = cos_sin((double)pos * theta);
-    }
-  };
 
   auto one_tile = [&](auto more_c) {
     constexpr bool MORE = decltype(more_c)::value;
@@ -307,7 +310,6 @@ __global__ __launch_bounds__(NW * 64) void gemm_bf16_rows_kernel(RowsParams r) {
     }
   };
   int first = tile;
-  if constexpr (ROPE) angles(first);
   for (;;) {
     const bool more = tile + (int)gridDim.x < r.tiles;
     if (more) one_tile(std::true_type{});
@@ -320,7 +322,6 @@ __global__ __launch_bounds__(NW * 64) void gemm_bf16_rows_kernel(RowsParams r) {
       lds_barrier();                                      // ... and have been read
       slot = 0;
       first = tile + gridDim.x;
-      if constexpr (ROPE) angles(first);
     }
     tile += gridDim.x;
   }
@@ -331,7 +332,8 @@ forge_status launch_fin(const RowsParams& r, int ranges, hipStream_t s) {
   // one block per CU, also where the registers would hold two: two blocks read x twice (6144 x 2048 at
   // 8 rows 10.7 us, at 9 rows and one block 9.5 us)
   const int chunks = ceil_div(r.g.M, 16 * MT);
-  const int per = ceil_div(r.tiles, max(1, compute_units() / (ranges * chunks)));      // tiles per block
+  int per = ceil_div(r.tiles, max(1, compute_units() / (ranges * chunks)));      // tiles per block
+  if (FIN == FIN_ROPE) per = min(per, Rows<MT, STEPS, W8, FIN>::SLOTS);                // (their angles are computed once)
   auto kern = gemm_bf16_rows_kernel<MT, STEPS, W8, FIN>;
   // (more than half the LDS of a CU, whatever is needed: with two blocks resident some CUs get two and
   // others none, 2048 x 2048 at 16 rows 7.8 instead of 5.6 us)
