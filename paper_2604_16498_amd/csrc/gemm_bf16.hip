@@ -41,6 +41,7 @@
 // decoder layer, RoPE or the following norm).
 // Prompt-sized M with few tiles and a long K: the tile kernel itself walks (k range, tile) items.
 #include <math.h>
+#include <stdint.h>
 #include <type_traits>
 #include "gemm_bf16.hpp"
 
@@ -1240,6 +1241,42 @@ inline SkinnyPlan plan_skinny(int N, int K, forge_act act, int bk = BK) {
   return sp;
 }
 
+// The whole dispatch of a problem that does not rotate in its epilogue: the launcher follows it and the variant
+// query names it.
+struct Route {
+  Variant v;
+  SkinnyPlan sk;      // at most 64 rows
+  PersSplit ps;       // V_FAST_128: k ranges (1: unsplit)
+  RowsPlan rows;      // ranges > 0: the kernel with x in registers takes it
+  bool planes;        // fp32 planes and a reduce launch
+};
+// w8: the weight is streamed as int8.  offset_or_scaled: a prompt's launch with a column offset or the scales of
+// a dequantised weight, neither of which the kernel with x in registers knows.
+Route plan_route(int M, int N, int K, int ldy, forge_act act, bool qkv, bool norm_tail, bool w8,
+                 bool offset_or_scaled, size_t part_bytes) {
+  Route r = {choose_variant(M, N, K, ldy, act, qkv), {}, {1, K}, {0, 0, 0}, false};
+  const int ncols = act == FORGE_ACT_SWIGLU ? 2 * N : N;
+  if (r.v == V_FAST_128) {
+    if (!offset_or_scaled) r.rows = plan_rows_prompt(M, ncols, K, 0);
+    if (r.rows.ranges > 0) return r;
+    const PersSplit ps = plan_pers_split(M, ncols, K);
+    if (ps.splits < 2 || part_bytes < (size_t)ps.splits * M * ncols * sizeof(float)) return r;
+    r.ps = ps;
+    r.planes = true;
+    if (!offset_or_scaled) r.rows = plan_rows_prompt(M, ncols, K, ps.splits);
+  } else if (M <= 64) {
+    r.sk = plan_skinny(N, K, act, w8 ? 2 * BK : BK);
+    // (few rows of x: the kernel that keeps them in registers, where its plan takes the problem)
+    if (r.v == V_SKINNY_FAST && !norm_tail) {
+      r.rows = plan_rows(M, ncols, K, w8, 0);
+      if (r.rows.ranges > 0 || (r.sk.fused && !w8 && !qkv)) return r;      // outputs finished in the one launch
+    }
+    r.planes = true;
+    if (r.v == V_SKINNY_FAST) r.rows = plan_rows(M, ncols, K, w8, r.sk.splits);   // (the workspace holds sk.splits planes)
+  }
+  return r;
+}
+
 template <int BN, bool W8, int FACT = -1>
 forge_status launch_wstream(const GemmParams& q, int splits, hipStream_t s) {
   using C = WStream<BN, W8>;
@@ -1287,28 +1324,24 @@ forge_status launch_act(const GemmParams& p, hipStream_t s) {
     if (v == V_FAST_128) return launch_pers<128, 128, 2, 2, ACT, MODE>(p, s);
     return FORGE_ERR_UNSUPPORTED;
   } else {
+  const Route r = plan_route(p.M, p.N, p.K, p.ldy, (forge_act)ACT, MODE == MODE_QKV, p.nt.y_norm != nullptr, p.w8 != nullptr,
+                             p.col0 != 0 || (p.w8 == nullptr && p.wscale != nullptr), p.part != nullptr ? p.part_bytes : 0);
+  if (r.rows.ranges > 0 && !r.planes) return launch_rows(p, r.rows, ACT, MODE == MODE_QKV, false, s);
   switch (v) {
     case V_FAST_256: return launch_pers<256, 256, 2, 4, ACT, MODE>(p, s);
     case V_FAST_128: {
-      const int ncols = ACT == FORGE_ACT_SWIGLU ? 2 * p.N : p.N;
-      // (that kernel knows neither a column offset nor the scales of a dequantised weight)
-      const bool rows_ok = p.col0 == 0 && p.wscale == nullptr;
-      const RowsPlan one = rows_ok ? plan_rows_prompt(p.M, ncols, p.K, 0) : RowsPlan{0, 0, 0};
-      if (one.ranges > 0) return launch_rows(p, one, ACT, MODE == MODE_QKV, false, s);
-      const PersSplit ps = plan_pers_split(p.M, ncols, p.K);
-      if (ps.splits > 1 && p.part != nullptr &&
-          p.part_bytes >= (size_t)ps.splits * p.M * ncols * sizeof(float)) {
+      if (r.planes) {
+        const int ncols = ACT == FORGE_ACT_SWIGLU ? 2 * p.N : p.N;
         GemmParams q = p;       // the gated weight is a plain [2N, K] matrix here: gate columns, then up
         q.N = ncols;
-        q.splits = ps.splits;
-        q.k_per_split = ps.k_per_split;
-        const RowsPlan rp = rows_ok ? plan_rows_prompt(p.M, ncols, p.K, ps.splits) : RowsPlan{0, 0, 0};
-        const forge_status st = rp.ranges > 0 ? launch_rows(q, rp, FORGE_ACT_NONE, false, true, s)
-                                              : launch_pers<128, 128, 2, 4, FORGE_ACT_NONE, MODE_SPLITK>(q, s);
+        q.splits = r.ps.splits;
+        q.k_per_split = r.ps.k_per_split;
+        const forge_status st = r.rows.ranges > 0 ? launch_rows(q, r.rows, FORGE_ACT_NONE, false, true, s)
+                                                  : launch_pers<128, 128, 2, 4, FORGE_ACT_NONE, MODE_SPLITK>(q, s);
         if (st != FORGE_OK) return st;
         const int64_t threads = (int64_t)p.M * ceil_div(p.N, 4);
         splitk_reduce_kernel<ACT, MODE == MODE_QKV><<<(unsigned)ceil_div64(threads, 256), 256, 0, s>>>(
-            p, rp.ranges > 0 ? rp.ranges : ps.splits, ncols);
+            p, r.rows.ranges > 0 ? r.rows.ranges : r.ps.splits, ncols);
         return launch_status();
       }
       // 8 waves of 64 x 32 (16 waves per CU) hide the L2 latency of the small tile better than 4
@@ -1322,25 +1355,18 @@ forge_status launch_act(const GemmParams& p, hipStream_t s) {
     default: break;
   }
   // skinny: raw split-K GEMM over all weight rows into fp32 partials, then reduce + epilogue
-  const SkinnyPlan sk = plan_skinny(p.N, p.K, (forge_act)ACT, p.w8 != nullptr ? 2 * BK : BK);
+  const SkinnyPlan& sk = r.sk;
   GemmParams q = p;
   q.N = sk.ncols;
   q.k_per_split = sk.k_per_split;
-  forge_status st;
-  const bool plain_out = MODE == MODE_PLAIN && p.nt.y_norm == nullptr;
-  int splits = sk.splits;
-  const bool w8 = p.w8 != nullptr, rows_ok = v == V_SKINNY_FAST;
-  // few rows of x: the kernel that keeps them in registers, where its plan takes the problem
-  if (rows_ok && p.nt.y_norm == nullptr) {
-    const RowsPlan rp = plan_rows(p.M, sk.ncols, p.K, w8, 0);
-    if (rp.ranges > 0) return launch_rows(p, rp, ACT, MODE == MODE_QKV, false, s);
+  if constexpr (MODE == MODE_PLAIN) {
+    if (!r.planes) return launch_wstream<128, false, ACT>(q, 1, s);     // finishes its outputs itself
   }
-  if (rows_ok && sk.fused && !w8 && plain_out)
-    return launch_wstream<128, false, ACT>(q, 1, s);     // finishes its outputs itself
-  const RowsPlan rp = rows_ok ? plan_rows(p.M, sk.ncols, p.K, w8, sk.splits) : RowsPlan{0, 0, 0};
-  if (rp.ranges > 0) {
-    splits = rp.ranges;                                  // (the workspace holds sk.splits planes)
-    st = launch_rows(q, rp, FORGE_ACT_NONE, false, true, s);
+  forge_status st;
+  int splits = sk.splits;
+  if (r.rows.ranges > 0) {
+    splits = r.rows.ranges;
+    st = launch_rows(q, r.rows, FORGE_ACT_NONE, false, true, s);
   } else if (v == V_SKINNY_FAST) {
     if (q.w8 != nullptr) st = sk.bn == 256 ? launch_wstream<256, true>(q, sk.splits, s) : launch_wstream<128, true>(q, sk.splits, s);
     else st = sk.bn == 256 ? launch_wstream<256, false>(q, sk.splits, s) : launch_wstream<128, false>(q, sk.splits, s);
@@ -1440,12 +1466,17 @@ bool gemm_fuses_tail(int M, int N, forge_dtype dt) {
 }
 
 const char* gemm_bf16_variant(int M, int N, int K, int ldy, forge_act act) {
-  switch (choose_variant(M, N, K, ldy, act, false)) {   // the call launch_act makes for a plain output
+  // the call launch_act makes for a plain output, with the workspace asked for
+  const Route r = plan_route(M, N, K, ldy, act, false, false, false, false, SIZE_MAX);
+  if (r.rows.ranges > 0) return r.planes ? "gemm_bf16_rows+splitk" : "gemm_bf16_rows";
+  switch (r.v) {
     case V_FAST_256: return "gemm_bf16_pers<256,256,2,4>";
-    case V_FAST_128: return act == FORGE_ACT_SWIGLU ? "gemm_bf16_pers<128,128,2,2>" : "gemm_bf16_pers<128,128,2,4>";
+    case V_FAST_128:
+      if (r.planes) return "gemm_bf16_pers<128,128,2,4>+splitk";
+      return act == FORGE_ACT_SWIGLU ? "gemm_bf16_pers<128,128,2,2>" : "gemm_bf16_pers<128,128,2,4>";
     case V_GEN_256: return "gemm_bf16_generic<256,256,2,4>";
     case V_GEN_128: return "gemm_bf16_generic<128,128,2,2>";
-    case V_SKINNY_FAST: return plan_skinny(N, K, act).fused ? "gemm_bf16_wstream_fused<128>" : "gemm_bf16_wstream+splitk";
+    case V_SKINNY_FAST: return r.planes ? "gemm_bf16_wstream+splitk" : "gemm_bf16_wstream_fused<128>";
     default: return "gemm_bf16_generic<64,64,2,2>+splitk";
   }
 }

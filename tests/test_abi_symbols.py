@@ -131,13 +131,22 @@ def test_decode_attention_scratch_is_monotone_in_the_cache_length():
 
 def test_gemm_variant_names_the_kernel_that_runs():
     """The diagnostic applies the launcher's own rule: unaligned output rows (an odd dense N) and
-    a reduction that is not a whole number of 64-element slabs go to the generic kernel, a
-    decode-sized problem to the weight-streaming one, everything else to the persistent one."""
+    a reduction that is not a whole number of 64-element slabs go to the generic kernel, decode-sized
+    problems and prompts against few weight rows to the linear that keeps x in registers, other
+    decode-sized ones to the weight-streaming kernel, everything else to the persistent one."""
     import torch
     from paper_2604_16498_amd import binding as F
     v = lambda M, N, K, act="none", ldy=0: F.forge_gemm_variant(M, N, K, act, torch.bfloat16, ldy=ldy)
     assert v(300, 1001, 128) == "gemm_bf16_generic<128,128,2,2>"            # rows of 2002 bytes
-    assert v(300, 1001, 128, ldy=1008) == "gemm_bf16_pers<128,128,2,4>"
+    assert v(300, 3001, 128, ldy=3008) == "gemm_bf16_pers<128,128,2,4>"
+    assert v(300, 1001, 128, ldy=1008) == "gemm_bf16_rows"                  # 63 row tiles: one per block
+    assert v(128, 2304, 768) == v(256, 2048, 2048) == "gemm_bf16_rows"
+    assert v(200, 768, 3072) == "gemm_bf16_rows+splitk"                     # K = 3072 in four ranges
+    assert v(200, 6144, 4096) == "gemm_bf16_pers<128,128,2,4>+splitk"       # 384 row tiles: too many per block
+    assert v(8, 3072, 768, "gelu_tanh") == v(64, 1001, 512) == v(5, 14336, 4096, "swiglu") == "gemm_bf16_rows"
+    assert v(21, 2048, 8192) == "gemm_bf16_rows+splitk"
+    assert v(64, 24576, 256) == "gemm_bf16_wstream_fused<128>"              # more rows than many tiles pay for
+    assert v(8, 4096, 14336) == "gemm_bf16_wstream+splitk"                  # a long bf16 reduction
     assert v(300, 1000, 72) == "gemm_bf16_generic<128,128,2,2>"             # K % 64 != 0
     assert v(8192, 3072, 768, "gelu_tanh") == "gemm_bf16_pers<128,128,2,4>"
     assert v(8192, 50257, 768, ldy=50264) == "gemm_bf16_pers<256,256,2,4>"

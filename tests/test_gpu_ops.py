@@ -99,18 +99,22 @@ def test_gated_weight_with_alternating_rows(F, bf16, M, N, K):
 
 
 @pytest.mark.parametrize("epi", ["bias+residual", "bias", "residual", "none"])
-@pytest.mark.parametrize("M,N,K,ld", [(300, 1001, 128, 1008), (257, 515, 64, 520), (130, 50257, 64, 50264)])
-def test_gemm_padded_row_stride(F, M, N, K, ld, epi):
-    """Odd N with a padded, 16-byte aligned row stride takes the persistent kernel with or
-    without a bias / residual (the ragged last 8-column chunk of a row takes its bias element by
-    element and its residual from inside the padded stride); the padding stays untouched."""
+@pytest.mark.parametrize("M,N,K,ld,kernel", [
+    (300, 1001, 128, 1008, "rows"), (257, 515, 64, 520, "rows"), (130, 50257, 64, 50264, "pers"),
+    (300, 3001, 128, 3008, "pers"), (2500, 515, 64, 520, "pers"),
+])
+def test_gemm_padded_row_stride(F, M, N, K, ld, kernel, epi):
+    """Odd N with a padded, 16-byte aligned row stride takes the persistent kernel (few weight rows: the
+    one with x in registers) with or without a bias / residual (the ragged last 8-column chunk of a row
+    takes its bias element by element and its residual from inside the padded stride); the padding
+    stays untouched."""
     x = I.normal(67, 0, "x", (M, K), 1.0, bf16=True)
     w = I.normal(67, 0, "w_up", (N, K), 0.1, bf16=True)
     b = I.normal(67, 0, "b_up", (N,), 0.5, bf16=True) if "bias" in epi else None
     r = I.normal(67, 0, "residual", (M, ld), 1.0, bf16=True) if "residual" in epi else None
     ref = O.gemm_bias_act(x, w, b, None if r is None else r[:, :N], "gelu_tanh")
     ty = torch.full((M, ld), 7.0, dtype=torch.bfloat16, device="cuda")
-    assert "pers" in F.forge_gemm_variant(M, N, K, "gelu_tanh", torch.bfloat16, ldy=ld)
+    assert kernel in F.forge_gemm_variant(M, N, K, "gelu_tanh", torch.bfloat16, ldy=ld)
     F.forge_gemm_bias_gelu(dev(x, True), dev(w, True), dev(b, True), dev(r, True), ty, "gelu_tanh", n=N)
     torch.cuda.synchronize()
     check(ty[:, :N], ref, True, "padded-stride gemm, %s" % epi)
@@ -152,26 +156,27 @@ def test_gemm_many_tiles_per_block(F, M, N, K, act, use_b, use_r, ld):
     assert torch.equal(again, ty)
 
 
-@pytest.mark.parametrize("M,N,K,act,use_b,use_r,ld", [
-    (64, 24576, 256, "none", True, True, 0),           # 192 blocks of 128 weight rows: the smallest fused case
-    (64, 24576, 192, "gelu_tanh", True, False, 0),
-    (33, 24578, 128, "silu", False, True, 24584),      # ragged last chunk, padded row stride, fewer than 64 rows
-    (1, 30000, 64, "relu", True, False, 0),            # a single row, a single slab
-    (64, 12288, 256, "swiglu", True, False, 0),        # gated: 64 gate rows + their 64 up rows per block
-    (40, 12296, 128, "swiglu", False, False, 0),       # gated, outputs not a multiple of 64
-    (17, 50257, 128, "none", False, False, 50264),     # an LM head at decode size
-    (64, 24576, 128, "gelu_erf", True, True, 0),
+@pytest.mark.parametrize("M,N,K,act,use_b,use_r,ld,kernel", [
+    (64, 24576, 256, "none", True, True, 0, "wstream_fused<128>"),       # 192 blocks of 128 weight rows: the smallest fused case
+    (64, 24576, 192, "gelu_tanh", True, False, 0, "wstream_fused<128>"),
+    (33, 24578, 128, "silu", False, True, 24584, "wstream_fused<128>"),  # ragged last chunk, padded row stride, fewer than 64 rows
+    (1, 30000, 64, "relu", True, False, 0, "rows"),                      # a single row, a single slab
+    (17, 30000, 64, "relu", True, False, 0, "wstream_fused<128>"),       # a single slab
+    (64, 12288, 256, "swiglu", True, False, 0, "wstream_fused<128>"),    # gated: 64 gate rows + their 64 up rows per block
+    (40, 12296, 128, "swiglu", False, False, 0, "wstream_fused<128>"),   # gated, outputs not a multiple of 64
+    (17, 50257, 128, "none", False, False, 50264, "wstream_fused<128>"),   # an LM head at decode size
+    (64, 24576, 128, "gelu_erf", True, True, 0, "wstream_fused<128>"),
     # a short reduction (K < 1024) is one k range whatever the number of weight rows
-    (8, 3072, 768, "gelu_tanh", True, False, 0),       # the GPT-2-small MLP up projection of a decode step
-    (64, 1001, 512, "none", True, True, 1008),
-    (1, 8, 64, "silu", False, False, 0),
-    (5, 704, 960, "swiglu", True, False, 0),
+    (8, 3072, 768, "gelu_tanh", True, False, 0, "rows"),                 # the GPT-2-small MLP up projection of a decode step
+    (64, 1001, 512, "none", True, True, 1008, "rows"),
+    (1, 8, 64, "silu", False, False, 0, "rows"),
+    (5, 704, 960, "swiglu", True, False, 0, "rows"),
 ])
-def test_gemm_decode_sized_finishes_in_the_gemm(F, M, N, K, act, use_b, use_r, ld):
+def test_gemm_decode_sized_finishes_in_the_gemm(F, M, N, K, act, use_b, use_r, ld, kernel):
     """At most 64 rows against enough weight rows for one k range of 128-row blocks to cover the
-    chip, or a reduction short enough to be one k range anyway: the weight-streaming kernel applies
-    bias, activation and residual itself (no partial planes, no reduce launch) and needs no
-    workspace."""
+    chip, or a reduction short enough to be one k range anyway: the kernel that streams the weight
+    (slab-wise, or past the rows of x in registers) applies bias, activation and residual itself (no
+    partial planes, no reduce launch) and needs no workspace."""
     wn = 2 * N if act == "swiglu" else N
     ldy = ld or N
     x = I.normal(69, 0, "x", (M, K), 1.0, bf16=True)
@@ -179,7 +184,7 @@ def test_gemm_decode_sized_finishes_in_the_gemm(F, M, N, K, act, use_b, use_r, l
     b = I.normal(69, 0, "b_up", (wn,), 0.5, bf16=True) if use_b else None
     r = I.normal(69, 0, "residual", (M, ldy), 1.0, bf16=True) if use_r else None
     ref = O.gemm_bias_act(x, w, b, None if r is None else r[:, :N], act)
-    assert F.forge_gemm_variant(M, N, K, act, torch.bfloat16, ldy=ldy) == "gemm_bf16_wstream_fused<128>"
+    assert F.forge_gemm_variant(M, N, K, act, torch.bfloat16, ldy=ldy) == "gemm_bf16_" + kernel
     assert F.forge_gemm_workspace_bytes(M, N, K, act, torch.bfloat16) == 0
     ty = torch.full((M, ldy), 7.0, dtype=torch.bfloat16, device="cuda")
     args = (dev(x, True), dev(w, True), None if b is None else dev(b, True), None if r is None else dev(r, True))
@@ -193,13 +198,17 @@ def test_gemm_decode_sized_finishes_in_the_gemm(F, M, N, K, act, use_b, use_r, l
     assert torch.equal(again, ty)
 
 
-@pytest.mark.parametrize("M,N,K,act", [
-    (128, 512, 2048, "none"), (130, 520, 4096, "gelu_tanh"), (257, 256, 14336, "none"),
-    (100, 384, 2048, "swiglu"), (512, 128, 8192, "silu"),
+@pytest.mark.parametrize("M,N,K,act,kernel", [
+    (128, 512, 2048, "none", "rows"), (130, 520, 4096, "gelu_tanh", "rows+splitk"),
+    (257, 256, 14336, "none", "pers<128,128,2,4>+splitk"), (100, 384, 2048, "swiglu", "rows"),
+    (512, 128, 8192, "silu", "rows+splitk"), (130, 1032, 8192, "swiglu", "pers<128,128,2,4>+splitk"),
+    (100, 4104, 4096, "gelu_tanh", "pers<128,128,2,4>+splitk"),
 ])
-def test_gemm_few_tiles_long_k(F, M, N, K, act):
+def test_gemm_few_tiles_long_k(F, M, N, K, act, kernel):
     """A prompt-sized M against a long reduction: few output tiles, so the k loop is split over
-    the chip when the caller provides the workspace; without it the same problem runs unsplit."""
+    the chip when the caller provides the workspace (or a block's waves share all of K); without it the
+    same problem runs unsplit."""
+    assert F.forge_gemm_variant(M, N, K, act, torch.bfloat16) == "gemm_bf16_" + kernel
     wn = 2 * N if act == "swiglu" else N
     x = I.normal(69, 0, "x", (M, K), 1.0, bf16=True)
     w = I.normal(69, 0, "w_up", (wn, K), 1.0 / math.sqrt(K), bf16=True)

@@ -29,7 +29,8 @@ CASES = [  # M, N, K, act, residual, padded row stride
     (33, 2056, 2048, "silu", True, 0),         # past two groups
     (64, 776, 1920, "swiglu", False, 0),
     (5, 8200, 4096, "none", False, 0),         # the longest single range; more tiles than blocks
-    (24, 33000, 128, "gelu_tanh", False, 0),   # more than 8 tiles per block: the sums are collected twice
+    (16, 33000, 128, "gelu_tanh", False, 0),   # more than 8 tiles per block: the sums are collected twice
+    (24, 33000, 1024, "gelu_tanh", False, 0),  # ... with two groups of x rows
     (7, 2048, 8192, "gelu_tanh", True, 0),     # several k ranges and the reduce launch
     (40, 768, 3072, "none", True, 0),
     (9, 520, 4160, "swiglu", False, 0),        # one step past a single range
@@ -58,6 +59,8 @@ def test_rows_linear(F, M, N, K, act, use_r, ld, w8):
     tx, tb, tr = dev(x, True), dev(b, True), None if r is None else dev(r, True)
     tw = torch.from_numpy(q).cuda() if w8 else dev(w, True)
     ts = torch.from_numpy(s).cuda() if w8 else None
+    if not w8:
+        assert "gemm_bf16_rows" in F.forge_gemm_variant(M, N, K, act, torch.bfloat16, ldy=ldy)
     need = F.forge_gemm_w8_workspace_bytes(M, N, K, act) if w8 else F.forge_gemm_workspace_bytes(M, N, K, act, torch.bfloat16)
     outs = []
     for _ in range(2):
