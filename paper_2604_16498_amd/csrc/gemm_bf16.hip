@@ -1268,11 +1268,11 @@ Route plan_route(int M, int N, int K, int ldy, forge_act act, bool qkv, bool nor
     r.sk = plan_skinny(N, K, act, w8 ? 2 * BK : BK);
     // (few rows of x: the kernel that keeps them in registers, where its plan takes the problem)
     if (r.v == V_SKINNY_FAST && !norm_tail) {
-      r.rows = plan_rows(M, ncols, K, w8, 0);
+      r.rows = plan_rows(M, ncols, K, w8, 0, qkv);
       if (r.rows.ranges > 0 || (r.sk.fused && !w8 && !qkv)) return r;      // outputs finished in the one launch
     }
     r.planes = true;
-    if (r.v == V_SKINNY_FAST) r.rows = plan_rows(M, ncols, K, w8, r.sk.splits);   // (the workspace holds sk.splits planes)
+    if (r.v == V_SKINNY_FAST) r.rows = plan_rows(M, ncols, K, w8, r.sk.splits, qkv);   // (the workspace holds sk.splits planes)
   }
   return r;
 }

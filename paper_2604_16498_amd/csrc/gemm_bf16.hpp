@@ -65,7 +65,7 @@ struct RowsPlan {
 // rows: weight rows.  max_ranges 0: the plan of a launch that finishes its outputs itself (plain, head
 // split, rotated head split), one range; otherwise of one that writes at most that many fp32 planes
 // [ranges, M, rows] for the reduce kernels (raw).
-RowsPlan plan_rows(int M, int rows, int K, bool w8, int max_ranges);
+RowsPlan plan_rows(int M, int rows, int K, bool w8, int max_ranges, bool qkv);
 RowsPlan plan_rows_prompt(int M, int rows, int K, int max_ranges);   // more than 64 rows, bf16 weights
 forge_status launch_rows(const GemmParams& p, const RowsPlan& pl, int act, bool qkv, bool raw, hipStream_t s);
 

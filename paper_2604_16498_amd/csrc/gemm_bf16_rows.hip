@@ -54,7 +54,7 @@ struct Rows {
   static constexpr int XF = W8 ? 2 : 1;                   // 32-k MFMA steps per 64 bytes
   static constexpr int KE = 32 * XF;                      // k per step
   static constexpr int XREGS = MT * STEPS * XF * 4;
-  static constexpr int WIN = STEPS > 8 ? STEPS / 2 : STEPS;   // loads in flight per wave
+  static constexpr int WIN = STEPS > 10 ? STEPS / 2 : STEPS;   // loads in flight per wave
   static_assert(STEPS % WIN == 0, "a tile is whole windows");
   static_assert(XREGS + WIN * 4 <= 160, "x and the tile in flight stay in registers");
   // tiles whose partial sums are collected in LDS before they are finished: one per wave where the
@@ -364,9 +364,12 @@ forge_status launch_mt(const RowsParams& r, int fin, const RowsPlan& pl, hipStre
     FORGE_ROWS_CASE(2);
     FORGE_ROWS_CASE(3);
     FORGE_ROWS_CASE(4);
+    FORGE_ROWS_CASE(5);
     FORGE_ROWS_CASE(6);
     FORGE_ROWS_CASE(7);
     FORGE_ROWS_CASE(8);
+    FORGE_ROWS_CASE(9);
+    FORGE_ROWS_CASE(10);
     FORGE_ROWS_CASE(12);
     FORGE_ROWS_CASE(14);
     FORGE_ROWS_CASE(16);
@@ -381,43 +384,69 @@ forge_status launch_mt(const RowsParams& r, int fin, const RowsPlan& pl, hipStre
 namespace {
 RowsPlan with_steps(int total, int ranges) {
   const int spw = ceil_div(total, ranges * NW);
-  static constexpr int kSteps[] = {1, 2, 3, 4, 6, 7, 8, 12, 14, 16};
+  static constexpr int kSteps[] = {1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 12, 14, 16};
   for (int s : kSteps)
     if (s >= spw) return RowsPlan{ceil_div(total, spw * NW), s, spw};     // total > 8 (spw - 1), so a row has at least s steps
   return RowsPlan{0, 0, 0};
 }
-}  // namespace
 
 // Where this kernel is the faster one, against the slab-wise streaming kernel (microseconds of one
-// launch list, cold weights, this kernel | that one, a following reduce launch included).  Both read x
+// launch list, cold weights, that one | this kernel, a following reduce launch included).  Both read x
 // once per block; here a block reads all of its k range of x (M * K * 2 bytes) however few weight
 // rows it has, there 64 rows of it per 128 or 256 weight rows.
-RowsPlan plan_rows(int M, int rows, int K, bool w8, int max_ranges) {
+
+// bf16, at most 4096 elements of K.  While every CU has one tile, this kernel; beyond that its 64-byte pieces of
+// 16 rows stream at 4.3 TB/s and the slabs at 4.7 to 5.4, unless rows are a multiple of 4 KB apart, which
+// puts the slabs of all blocks on the same HBM channels (16384 x 4096 at 4 rows 41.2 | 26.0, x 3840 27.2 | 29.7).
+bool streams_faster(int M, int rows, int K, bool qkv) {
+  const int tiles = ceil_div(rows, TR), cus = compute_units();
+  if (tiles <= cus) return true;
+  const bool aligned = K % 2048 == 0;
+  // enough weight rows for the slab-wise kernel to finish its outputs itself: with a short K and few rows the
+  // per-block start still counts (50264 x 768 at 8 rows 21.5 | 20.1, 24576 x 1536 at 4 19.2 | 16.5), otherwise only where its
+  // streams collide (32768 x 4096 at 17 rows 70.6 | 50.9; x 3840 46.8 | 58.5; x 1920 at 4 25.6 | 27.9; 50304 x 832 19.8 | 22.2)
+  if (ceil_div(rows, 128) * 4 >= cus * 3)
+    return M <= 32 && K % (32 * NW) == 0 && (aligned || (M <= 16 && K <= 2048));
+  // many tiles per CU with more rows than pay for the time between two windows of a tile
+  if (tiles >= 4 * cus && M > (K < 1024 ? 16 : 32)) return false;
+  // between one and two tiles per CU the last round is half empty (5120 x 3840 at 17 rows 13.7 | 17.5, 6144 x 4096
+  // 15.5 | 16.1, 8192 x 4096 18.8 | 16.9); a head split saves its reduce launch there (a layer of
+  // 32 + 2 x 8 heads of 128 with a small MLP: 58 | 52)
+  if (qkv && tiles < 2 * cus) return true;
+  if (aligned) return K <= 2048 || M <= 16 || tiles * 4 >= 7 * cus;
+  return K <= (M > 16 ? 2304 : 2560);   // (10240 x 2304 at 4 rows 15.0 | 13.2, x 2560 16.0 | 15.5, at 17 rows 16.4 | 17.1, x 2816 at 4 16.1 | 16.9)
+}
+}  // namespace
+
+RowsPlan plan_rows(int M, int rows, int K, bool w8, int max_ranges, bool qkv) {
   const RowsPlan none = {0, 0, 0};
   if (M > MAX_ROWS || K % (w8 ? 2 * BK : BK) != 0) return none;
   const int total = K / (w8 ? 64 : 32);                        // steps of a row
   const int cap = NW * (w8 ? 8 : 16) / (M > 32 ? 2 : 1);       // ... that one range holds: x stays in registers
   const int least = ceil_div(total, cap);
   const int tiles = ceil_div(rows, TR), cus = compute_units();
-  const int64_t x = (int64_t)M * K;
   int ranges = 1;
   if (max_ranges == 0) {
     // One range, outputs finished here.  int8: wherever one range holds K (6144 x 4096 at 32 rows
-    // 11.8 | 17.2, 6144 x 2048 at 64 rows 9.9 | 16.1).  bf16 likewise (6144 x 4096 at 5 rows 14.3 | 15.1, at 24
-    // 16.5 | 15.8 where nothing follows the other's reduce launch, but a rotation there costs it 2 more;
-    // 8192 x 2048 at 64 rows 13.5 | 15.9), except many tiles per CU with more rows than pay for the
-    // time between two windows of a tile (28672 x 4096 at 32 rows 46 | 50; 50272 x 2048 at 32 rows
-    // 46.7 | 49.9, at 48 rows 51.6 | 50.6; 50257 x 768 at 16 rows 20.1 | 21.1, at 24 rows 23.7 | 21.6).
-    if (least > 1) return none;
-    if (!w8 && tiles >= 4 * cus && M > (K < 1024 ? 16 : 32)) return none;
+    // 17.2 | 11.8, 6144 x 2048 at 64 rows 16.1 | 9.9).
+    if (least > 1 || (!w8 && !streams_faster(M, rows, K, qkv))) return none;
   } else {
     // fp32 planes for a reduce kernel: enough ranges for a block per CU and for x to stay below half the
-    // weight bytes of a block (2048 x 8192 at 21 rows: 2 ranges 15.0, 8 ranges 13.4 | 15.3).  Not for long
-    // bf16 reductions (4096 x 14336 at 5 rows 28.0 | 25.8: rows 28 KB apart in 64-byte pieces stream at
-    // 5.1 TB/s against 5.5), nor for bf16 past 32 rows where the tiles alone cover the chip (4096 x 4096 at
-    // 48 rows 15.7 | 14.8) or K is past 4096, nor for int8 past 32 rows and 8192 (4096 x 14336 at 64 rows
-    // 29.9 | 26.5).
-    if (w8 ? M > 32 && K > 8192 : K > (M > 32 ? 4096 : 8192) || ((x > 131072 || M > 32) && tiles >= cus)) return none;
+    // weight bytes of a block (2048 x 8192 at 21 rows: 2 ranges 15.0, 8 ranges 13.4 against 15.3).
+    if (w8) {
+      // not past 32 rows with a long K (4096 x 14336 at 64 rows 26.5 | 29.9), nor with so many tiles that the planes
+      // weigh against the weight (32768 x 2560 at 33 rows 30.6 | 36.9, 16384 x 2560 20.4 | 21.8, x 3072 22.2 | 21.8)
+      if (M > 32 && (K > 8192 || 640 * (int64_t)tiles >= (int64_t)K * cus)) return none;
+    } else if (K <= 4096) {
+      // (4096 x 4096 at 48 rows 14.8 | 15.7)
+      if (tiles >= cus && (M > 32 || !streams_faster(M, rows, K, false))) return none;
+    } else {
+      // not for long reductions (4096 x 14336 at 5 rows 25.8 | 28.0), nor past 32 rows or one tile per CU (15360 x 5120 at
+      // 4 rows 33.4 | 45.3, 5120 x 5120 16.2 | 18.0), except few rows where the slabs collide (8192 x 8192 at 4 rows
+      // 38.9 | 33.4, 16384 x 8192 73.7 | 61.9)
+      const bool collide = K % 4096 == 0 && M <= 16 && tiles * 4 >= 7 * cus && ceil_div(rows, 128) * 4 < cus * 3;
+      if (K > 8192 || M > 32 || (tiles >= cus && !collide)) return none;
+    }
     ranges = max(ceil_div(cus, tiles), ceil_div(M * cus, 8 * tiles));
     const int most = min(max_ranges, total / (2 * NW));
     ranges = max(least, min(ranges, most));

@@ -145,6 +145,13 @@ def test_gemm_variant_names_the_kernel_that_runs():
     assert v(200, 6144, 4096) == "gemm_bf16_pers<128,128,2,4>+splitk"       # 384 row tiles: too many per block
     assert v(8, 3072, 768, "gelu_tanh") == v(64, 1001, 512) == v(5, 14336, 4096, "swiglu") == "gemm_bf16_rows"
     assert v(21, 2048, 8192) == "gemm_bf16_rows+splitk"
+    # decode-sized problems that stream faster slab-wise, and their neighbours that do not
+    assert v(4, 15360, 5120) == v(17, 5120, 5120) == v(4, 4096, 6144) == "gemm_bf16_wstream+splitk"
+    assert v(4, 16384, 3840) == v(17, 6144, 4096) == v(17, 10240, 2560) == "gemm_bf16_wstream+splitk"
+    assert v(17, 32768, 3840) == v(4, 32768, 1920) == v(4, 50304, 832) == "gemm_bf16_wstream_fused<128>"
+    assert v(4, 16384, 4096) == v(17, 8192, 4096) == v(4, 10240, 2560) == v(17, 32768, 4096) == "gemm_bf16_rows"
+    assert v(8, 50264, 768) == v(17, 3072, 3840) == "gemm_bf16_rows"
+    assert v(4, 2560, 5120) == v(4, 16384, 8192) == "gemm_bf16_rows+splitk"
     assert v(64, 24576, 256) == "gemm_bf16_wstream_fused<128>"              # more rows than many tiles pay for
     assert v(8, 4096, 14336) == "gemm_bf16_wstream+splitk"                  # a long bf16 reduction
     assert v(300, 1000, 72) == "gemm_bf16_generic<128,128,2,2>"             # K % 64 != 0

@@ -160,8 +160,7 @@ def test_gemm_many_tiles_per_block(F, M, N, K, act, use_b, use_r, ld):
     (64, 24576, 256, "none", True, True, 0, "wstream_fused<128>"),       # 192 blocks of 128 weight rows: the smallest fused case
     (64, 24576, 192, "gelu_tanh", True, False, 0, "wstream_fused<128>"),
     (33, 24578, 128, "silu", False, True, 24584, "wstream_fused<128>"),  # ragged last chunk, padded row stride, fewer than 64 rows
-    (1, 30000, 64, "relu", True, False, 0, "rows"),                      # a single row, a single slab
-    (17, 30000, 64, "relu", True, False, 0, "wstream_fused<128>"),       # a single slab
+    (1, 30000, 64, "relu", True, False, 0, "wstream_fused<128>"),        # a single row, a single slab
     (64, 12288, 256, "swiglu", True, False, 0, "wstream_fused<128>"),    # gated: 64 gate rows + their 64 up rows per block
     (40, 12296, 128, "swiglu", False, False, 0, "wstream_fused<128>"),   # gated, outputs not a multiple of 64
     (17, 50257, 128, "none", False, False, 50264, "wstream_fused<128>"),   # an LM head at decode size

@@ -29,8 +29,12 @@ CASES = [  # M, N, K, act, residual, padded row stride
     (33, 2056, 2048, "silu", True, 0),         # past two groups
     (64, 776, 1920, "swiglu", False, 0),
     (5, 8200, 4096, "none", False, 0),         # the longest single range; more tiles than blocks
-    (16, 33000, 128, "gelu_tanh", False, 0),   # more than 8 tiles per block: the sums are collected twice
-    (24, 33000, 1024, "gelu_tanh", False, 0),  # ... with two groups of x rows
+    (16, 33000, 256, "gelu_tanh", False, 0),   # more than 8 tiles per block: the sums are collected twice
+    (24, 33000, 2048, "gelu_tanh", False, 0),  # ... with two groups of x rows
+    (17, 1003, 1280, "silu", True, 1008),      # 5, 9 and 10 steps per wave (int8: 3, 5 and 5)
+    (40, 776, 1280, "swiglu", False, 0),
+    (20, 1003, 2304, "relu", True, 1008),
+    (30, 776, 2560, "swiglu", False, 0),
     (7, 2048, 8192, "gelu_tanh", True, 0),     # several k ranges and the reduce launch
     (40, 768, 3072, "none", True, 0),
     (9, 520, 4160, "swiglu", False, 0),        # one step past a single range
