@@ -2,7 +2,7 @@
 // every cached K and V row is read exactly once, with 128-bit loads, and nothing else of
 // comparable size moves.
 //
-// Split-KV: block (kv head, batch, split) streams one contiguous range of cache rows of ONE kv
+// Split-KV: a block (kv head, sequence, range) streams one contiguous range of cache rows of ONE kv
 // head for all G = Hq/Hkv query heads that share it (grouped-query attention reads the cache
 // once per group, not once per query head).  The 4 waves of a block take the 16-row tiles of the
 // range in turn (wave w: tiles w, w + 4, ...) and each keeps two tiles of K and V loads in flight
@@ -42,7 +42,8 @@ struct DecParams {
   const bf16* v;
   float* part;     // [B, Hkv, splits, G, dh + 2]
   bf16* out;       // [B, Hq * dh]: written directly when splits == 1
-  int q_heads, kv_heads, kv_len, splits;   // kv_heads counts blockIdx.x: cache heads x passes
+  int q_heads, kv_heads, kv_len, splits;   // kv_heads counts blocks: cache heads x passes
+  int heads_first;      // grid (kv_heads, batch, splits); otherwise (splits, kv_heads, batch)
   int passes;           // blocks (of G query heads each) that share one cache head
   int rows_per_split;   // multiple of GRAIN
   int64_t kv_bs, kv_hs;
@@ -67,7 +68,8 @@ __global__ __launch_bounds__(NWAVES * 64, G > 4 ? 2 : 3) void attn_decode_kernel
   __shared__ float sm[NWAVES][G][DH + 2];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int g = blockIdx.x, b = blockIdx.y, split = blockIdx.z;
+  const int g = p.heads_first ? blockIdx.x : blockIdx.y, b = p.heads_first ? blockIdx.y : blockIdx.z;
+  const int split = p.heads_first ? blockIdx.z : blockIdx.x;
   const int krow = lane & 15, kg = lane >> 4;          // MFMA layout: row in tile / lane group
   const int head = lane & 15;                          // ... and the accumulator's column
   const int slot = lane / LPR, c = lane % LPR;         // V layout: row in step / 16-byte chunk
@@ -310,7 +312,7 @@ inline int heads_per_block(int group) {
     if (group % d == 0) return group / d <= MAX_PASSES ? d : 0;
   return 0;
 }
-// blocks along x: cache heads x passes (the split plan counts these)
+// blocks per sequence and range: cache heads x passes (the split plan counts these)
 inline int block_heads(int q_heads, int kv_heads) {
   const int gb = heads_per_block(q_heads / kv_heads);
   return gb > 0 ? q_heads / gb : kv_heads;
@@ -336,10 +338,17 @@ forge_status launch_dg(const AttnArgs& a, hipStream_t s) {
   p.kv_hs = a.kv_head_stride;
   p.scale_log2e = a.scale * 1.4426950408889634f;
   p.kv_pos = a.kv_pos;
-  // heads fastest, ranges slowest: blocks go round-robin over the 8 XCDs, and with two ranges fastest
-  // every other XCD got only second ranges, which are short or empty where the lengths differ (21
-  // sequences up to 1400 rows, 16 heads: 41.2 -> 39.0 us, 24 up to 1500, 8 heads: 30.2 -> 27.1, merge included)
-  attn_decode_kernel<DH, G><<<dim3(yheads, a.batch, p.splits), NWAVES * 64, 0, s>>>(p);
+  // Ranges are the fastest block index, except two or four of them in a grid that is not whole rounds over the CUs:
+  // blocks go round-robin over the 8 XCDs, so with an even count every XCD gets the same ranges of all heads,
+  // and the last ones are short or empty where the lengths differ (us, ranges | heads fastest, merge included: 21
+  // sequences up to 1400 rows of 16 heads 39.5 | 33.7, 5 up to 1400 of 16 16.0 | 12.2, 24 up to 700 of 8 14.0 | 12.8).
+  // Elsewhere heads first keeps the same rows of all heads in flight at once and loses as often as it
+  // wins (1 sequence of 4096, 32 heads, 16 ranges 18.0 | 22.1; 3 up to 4508 in a cache of 8192, 8 heads, 12 ranges
+  // 13.8 | 17.1; 16 up to 6556, 16 heads, 512 blocks 107.6 | 117.5; 21 up to 4096, 12 heads, 3 ranges 38.1 | 40.9).
+  const int64_t blocks = (int64_t)p.splits * yheads * a.batch;
+  p.heads_first = (p.splits == 2 || p.splits == 4) && blocks % compute_units() != 0;
+  const dim3 grid = p.heads_first ? dim3(yheads, a.batch, p.splits) : dim3(p.splits, yheads, a.batch);
+  attn_decode_kernel<DH, G><<<grid, NWAVES * 64, 0, s>>>(p);
   if (p.splits == 1) return launch_status();
   if (hipGetLastError() != hipSuccess) return FORGE_ERR_HIP;
   attn_decode_combine<DH><<<dim3(a.q_heads, a.batch), DH, 0, s>>>(p.part, (bf16*)a.out, a.q_heads,
