@@ -241,8 +241,8 @@ def test_model_decode_step_hidden_state_stack(F, sh_name):
 
 def test_block_wide_model_short_prompt(F):
     """A 100-token prompt through a wide layer (d_model 1024, MLP 4096): every projection has few
-    output tiles and a long reduction, i.e. the k-split path of the tile kernel, including the
-    head split of the QKV projection."""
+    output tiles and a long reduction, so they run on the linear that keeps x in registers, chunk by
+    chunk of the rows, including the head split of the QKV projection."""
     sh = I.BlockShape(1024, 4, 2, 64, 4096, norm="rmsnorm", mlp_act="swiglu", use_rope=True,
                       rope_base=500000.0, has_bias=False)
     B, S = 1, 100
@@ -253,6 +253,37 @@ def test_block_wide_model_short_prompt(F):
     out, tk, tv = run_block(F, sh, w, x, True, S)
     check(tk, kc, True, "k cache"); check(tv, vc, True, "v cache")
     check(out, ref, True, "wide block, short prompt", chain=True)
+
+
+@pytest.mark.parametrize("rope", [False, True], ids=["plain", "rope"])
+def test_block_prompt_head_split_by_k_ranges(F, rope):
+    """A 100-token prompt against a 4096 x 4096 QKV weight: 32 tiles in eight k ranges, whose reduce kernel splits
+    the heads (and leaves the rotation to its own launches)."""
+    sh = I.BlockShape(4096, 16, 8, 128, 128, norm="rmsnorm", mlp_act="swiglu", use_rope=rope, rope_base=500000.0, has_bias=False)
+    B, S = 1, 100
+    w = I.block_weights(sh, 82, 0, bf16=True, random_affine=True)
+    x = I.normal(82, 0, "x", (B, S, sh.d_model), 1.0, bf16=True)
+    kc = np.zeros((B, sh.kv_heads, S, sh.head_dim)); vc = np.zeros_like(kc)
+    assert F.forge_gemm_variant(S, sh.qkv_out, sh.d_model, "none", torch.bfloat16) == "gemm_bf16_pers<128,128,2,4>+splitk"
+    ref = O.decoder_block(sh, w, x, kc, vc, pos0=0)
+    out, tk, tv = run_block(F, sh, w, x, True, S)
+    check(tk, kc, True, "k cache", chain=rope); check(tv, vc, True, "v cache")
+    check(out, ref, True, "head split by k ranges", chain=True)
+
+
+@pytest.mark.parametrize("d,norm", [(4168, "layernorm"), (4168, "rmsnorm"), (8200, "layernorm"), (8200, "rmsnorm"), (12288, "layernorm")])
+def test_block_decode_wide_norms(F, d, norm):
+    """A decode step of wide layers, whose second norm rides on the output projection's reduce launch with two and with
+    more groups of four columns per thread, the last one partly filled."""
+    sh = I.BlockShape(d, 4, 2, 64, 128, norm=norm, mlp_act="gelu_tanh", has_bias=norm == "layernorm")
+    B, pos0 = 3, 40
+    w = I.block_weights(sh, 83, 0, bf16=True, bias_std=0.05, random_affine=True)
+    x = I.normal(83, 0, "x", (B, 1, d), 1.0, bf16=True)
+    kc, vc = (I.normal(83, 0, n, (B, sh.kv_heads, pos0 + 1, sh.head_dim), 1.0, bf16=True) for n in ("k_cache", "v_cache"))
+    tk, tv = dev(kc, True), dev(vc, True)
+    ref = O.decoder_block(sh, w, x, kc.astype(np.float64), vc.astype(np.float64), pos0=pos0)
+    out, _, _ = run_block(F, sh, w, x, True, pos0 + 1, pos0=pos0, kc=tk, vc=tv)
+    check(out, ref, True, "wide decode layer", chain=True)
 
 
 def _random_block_cases():

@@ -197,6 +197,35 @@ def test_gemm_decode_sized_finishes_in_the_gemm(F, M, N, K, act, use_b, use_r, l
     assert torch.equal(again, ty)
 
 
+@pytest.mark.parametrize("M,N,K,act,ld", [
+    (5, 1001, 8256, "gelu_tanh", 1008),        # a long reduction: planes of the slab-wise kernel, ragged N and K
+    (40, 1032, 8256, "swiglu", 0),
+    (17, 4104, 10240, "none", 0),
+    (64, 520, 9216, "relu", 0),
+    (33, 4100, 4160, "silu", 0),               # past 32 rows and 4096 elements
+])
+def test_gemm_decode_sized_long_k(F, M, N, K, act, ld):
+    """At most 64 rows against a reduction that x does not stay in registers for: the slab-wise streaming kernel writes
+    fp32 planes of several k ranges, the reduce kernel finishes the outputs."""
+    wn = 2 * N if act == "swiglu" else N
+    ldy = ld or N
+    x = I.normal(70, 0, "x", (M, K), 1.0, bf16=True)
+    w = I.normal(70, 0, "w_up", (wn, K), 1.0 / math.sqrt(K), bf16=True)
+    b = I.normal(70, 0, "b_up", (wn,), 0.5, bf16=True)
+    r = I.normal(70, 0, "residual", (M, ldy), 1.0, bf16=True)
+    ref = O.gemm_bias_act(x, w, b, r[:, :N], act)
+    assert F.forge_gemm_variant(M, N, K, act, torch.bfloat16, ldy=ldy) == "gemm_bf16_wstream+splitk"
+    need = F.forge_gemm_workspace_bytes(M, N, K, act, torch.bfloat16)
+    assert need > 0
+    args, outs = (dev(x, True), dev(w, True), dev(b, True), dev(r, True)), []
+    for _ in range(2):
+        outs.append(torch.full((M, ldy), 7.0, dtype=torch.bfloat16, device="cuda"))
+        F.forge_gemm_bias_gelu(*args, outs[-1], act, F.workspace(need), n=N)
+    torch.cuda.synchronize()
+    check(outs[0][:, :N], ref, True, "slab-wise planes %s" % act)
+    assert torch.all(outs[0][:, N:] == 7.0) and torch.equal(outs[0], outs[1])
+
+
 @pytest.mark.parametrize("M,N,K,act,kernel", [
     (128, 512, 2048, "none", "rows"), (130, 520, 4096, "gelu_tanh", "rows+splitk"),
     (257, 256, 14336, "none", "pers<128,128,2,4>+splitk"), (100, 384, 2048, "swiglu", "rows"),
@@ -261,6 +290,25 @@ def test_gemm_random_shapes(F, M, N, K, act, use_b, use_r, pad):
     torch.cuda.synchronize()
     check(ty[:, :N], ref, True, "gemm %s %dx%dx%d via %s" % (act, M, N, K, F.forge_gemm_variant(M, N, K, act, torch.bfloat16, ldy=ldy)))
     assert torch.all(ty[:, N:] == 7.0)
+
+
+@pytest.mark.parametrize("Skv", [2, 3, 5, 62, 63, 66, 67, 127, 130, 131, 257, 1023])
+@pytest.mark.parametrize("dh,mb,mh,at", [(64, 2, 3, 0), (128, 1, 1, 1), (64, 2, 1, 3)])
+def test_masked_attention_row_ends(F, Skv, dh, mb, mh, at):
+    """Mask rows of every remainder of 4 (and of 64) keys, starting 4, 8 and 12 bytes past a 16-byte boundary: the
+    last keys of a row are read one by one."""
+    B, H, Sq = 2, 3, 37
+    q = I.normal(76, 0, "q", (B, H, Sq, dh), 1.0, bf16=True)
+    k, v = (I.normal(76, 0, n, (B, H, Skv, dh), 1.0, bf16=True) for n in ("k", "v"))
+    mask = I.normal(76, 0, "misc", (mb, mh, Sq, Skv), 2.0)
+    mask[..., 1:][I.normal(76, 0, "delta", (mb, mh, Sq, Skv - 1), 1.0) > 0.8] = -np.inf
+    room = torch.full((mask.size + 64,), float("nan"), device="cuda")     # whatever lies around the mask is not read into a result
+    tm = room[at:at + mask.size].view(mask.shape)
+    tm.copy_(torch.from_numpy(mask))
+    out = torch.empty(B, Sq, H * dh, dtype=torch.bfloat16, device="cuda")
+    F.forge_attn_fused_masked(dev(q, True), dev(k, True), dev(v, True), tm, out, causal=False)
+    torch.cuda.synchronize()
+    check(out, O.attention(q, k, v, 1.0 / math.sqrt(dh), False, mask), True, "mask rows of %d keys" % Skv)
 
 
 def test_gemm_residual_in_place(F):

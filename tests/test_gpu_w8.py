@@ -77,6 +77,25 @@ def test_gemm_w8(F, act, M, N, K):
     assert torch.equal(again, ty)
 
 
+@pytest.mark.parametrize("M,N,K,act", [
+    (40, 24584, 2560, "none"),        # 256 weight rows per block, more tiles than planes pay for x in registers
+    (33, 12296, 2176, "swiglu"),
+    (64, 520, 8320, "gelu_tanh"),     # past 32 rows and 8192 elements
+])
+def test_gemm_w8_slab_wise(F, M, N, K, act):
+    """Int8 weights of decode steps that x does not stay in registers for: the slab-wise streaming kernel."""
+    wn = 2 * N if act == "swiglu" else N
+    x = I.normal(94, 0, "x", (M, K), 1.0, bf16=True)
+    w = I.normal(94, 0, "w_up", (wn, K), 1.0 / math.sqrt(K), bf16=True)
+    q, s = O.quantize_int8(w)
+    ref = O.gemm_bias_act(x, O.dequantize_int8(q, s), None, None, act)
+    tq, ts = q_dev(q, s)
+    ty = torch.empty(M, N, dtype=torch.bfloat16, device="cuda")
+    F.forge_gemm_w8(dev(x, True), tq, ts, None, None, ty, act, F.workspace(F.forge_gemm_w8_workspace_bytes(M, N, K, act)))
+    torch.cuda.synchronize()
+    check(ty, ref, True, "w8 slab-wise %s" % act)
+
+
 def test_gemm_w8_extreme_rows(F):
     """Rows whose scale differs by orders of magnitude and a row of zeros: the scale is applied
     per output column after the reduction."""
