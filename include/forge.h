@@ -227,9 +227,9 @@ forge_status forge_embed(const int32_t* ids, const void* wte, const void* wpe, v
  * mlp_act: FORGE_ACT_GELU_TANH / GELU_ERF / RELU / SILU (w_up [d_ff,d]) or FORGE_ACT_SWIGLU
  * (w_up [2*d_ff,d]).
  * Biases and norm shifts may be NULL.  All pointers in the descriptor are device pointers.
- * With at most 64 rows (a decode step) the projections take a split-K path whose reduce step
- * also carries RoPE (QKV projection) and Norm2 (output projection): same results up to rounding
- * order, fewer launches.
+ * With at most 64 rows (a decode step) the QKV projection also rotates (as it finishes its outputs, or in
+ * its reduce step) and the reduce step of the output projection carries Norm2: same results up to
+ * rounding order, fewer launches.
  * ------------------------------------------------------------------------------------ */
 typedef struct {
   int d_model, q_heads, kv_heads, head_dim, d_ff;

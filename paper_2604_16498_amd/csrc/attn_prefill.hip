@@ -317,7 +317,7 @@ __global__ __launch_bounds__(512) void attn_prefill_kernel(AttnParams p) {
   };
   auto wave_needs = [&](int t) { return t < n_tiles && t * BKV <= wave_max_limit; };   // wave-uniform
 
-  // ---- prologue: K(0), V(0), K(1) in LDS, S(0) in registers ---------------------------------------
+  // ---- prologue: the first tile's K and V in LDS, the second's on their way, the first's S in registers ----
   load_rows(kbase, t_first, rk);
   load_rows(vbase, t_first, rv);
   store_k(t_first & 1);
@@ -466,9 +466,10 @@ forge_status launch_split(const AttnArgs& a, int splits, hipStream_t s) {
 // Key shares of a call: only where its query blocks leave CUs idle, at most as many as those CUs take and
 // none shorter than 256 keys.  A block walks a 64-key tile in 1.5 us, the merge launch costs 4.5 us and
 // a share's partial rows go out and back at about 5 TB/s; the count with the most left over is
-// non-decreasing in kv_len.  us: 777 queries behind 2500 keys (32 heads of 128) 96.8 -> 66.3, 80 behind 4000
-// 113 -> 27, 300 behind 1000 42.6 -> 27.4, 1 x 12 heads of 64 x 1000 25.9 -> 20.5; two shares of 520 x 32
-// heads would take 24.9 against 22.2 unsplit.
+// non-decreasing in kv_len.  us, merge included, calls back to back: 777 queries behind 2500 keys (32 heads of 128)
+// 74.3 -> 53.4, 80 behind 4000 107 -> 27.5, 300 behind 1000 33.2 -> 27.1, 1 x 12 heads of 64 x 1000 24.5 -> 20.5; two
+// shares of 520 x 32 heads would take 24.9 against 22.1 unsplit.  (Between the products of a model's step, on a warmer
+// card with the cache cold, the first takes 64.8 and its merge 6.9.)
 inline int plan_shares(int batch, int q_heads, int q_len, int kv_len, int head_dim) {
   const int64_t pairs = (int64_t)batch * q_heads, blocks = pairs * ceil_div(q_len, 256);
   const int most = (int)min(min((int64_t)compute_units() / blocks, (int64_t)kv_len / 256), (int64_t)8);

@@ -35,7 +35,7 @@
 // panels in that L2.
 //
 // M <= 64 (decode): most problems go to the kernel of gemm_bf16_rows.hip (plan_rows says which).  The
-// others (bf16 with a long K, or more rows than its x registers pay for): the weight is streamed once by
+// others (bf16 with a long K, many weight rows per CU, or more rows of x than its registers pay for): the weight is streamed once by
 // gemm_bf16_wstream_kernel (128 or 256 weight rows per block, K split over grid.y to about one block
 // per CU), fp32 partials, and fixed-order reduce kernels that carry the epilogue (and, inside a
 // decoder layer, RoPE or the following norm).

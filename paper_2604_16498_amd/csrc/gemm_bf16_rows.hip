@@ -8,8 +8,9 @@
 // over tiles of 16 weight rows without a barrier between them.  Per tile a wave loads its part of the
 // 16 rows straight from HBM in the A operand's layout (lane = row l%16, 16-byte chunk l/16: 64
 // contiguous bytes of each row per load, no LDS) and refills each register from further on as soon as
-// it has been multiplied: 8 KB per wave, 64 KB per CU are always in flight, and no vector-memory
-// request is spent on re-reading activations, which is what holds back the slab-wise streaming kernel.
+// it has been multiplied: a tile's steps per wave, up to 10 KB (half of them above that: 8 KB at 4096 elements),
+// are always in flight, 1 KB per step, and no vector-memory request is spent on re-reading activations,
+// which is what holds back the slab-wise streaming kernel.
 // The 8 partial sums of up to 8 tiles are collected in LDS; then every wave adds those of one tile in
 // wave order and finishes its outputs (weight scale, bias, activation, residual, head split, rotation).
 // Up to 4096 elements of K that is the whole reduction: no partial planes and no second launch.
