@@ -397,8 +397,9 @@ RowsPlan with_steps(int total, int ranges) {
 // rows it has, there 64 rows of it per 128 or 256 weight rows.
 
 // bf16, at most 4096 elements of K.  While every CU has one tile, this kernel; beyond that its 64-byte pieces of
-// 16 rows stream at 4.3 TB/s and the slabs at 4.7 to 5.4, unless rows are a multiple of 4 KB apart, which
-// puts the slabs of all blocks on the same HBM channels (16384 x 4096 at 4 rows 41.2 | 26.0, x 3840 27.2 | 29.7).
+// 16 rows stream at 4.3 to 5.0 TB/s and the slabs at 4.5 to 5.4, unless rows are a multiple of 4 KB apart, which
+// puts the slabs of all blocks on the same HBM channels (3.3 to 3.8, the pieces 5.2 to 5.6: 16384 x 4096 at 4 rows
+// 41.2 | 26.0, x 3840 27.2 | 29.7).
 bool streams_faster(int M, int rows, int K, bool qkv) {
   const int tiles = ceil_div(rows, TR), cus = compute_units();
   if (tiles <= cus) return true;
