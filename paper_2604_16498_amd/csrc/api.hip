@@ -110,7 +110,7 @@ forge_status run_block(const forge_block_desc* d, const void* x_in, void* x_out,
   //    (u, aws and gws are contiguous)
   AttnArgs at = {q, k_cache, v_cache, o, batch, d->q_heads, d->kv_heads, q_len, pos0 + q_len, dh,
                  kv_bs, kv_hs, 1.0f / sqrtf((float)dh), 1, q_len == 1 ? aws : u,
-                 q_len == 1 ? pl.attn : block_share_bytes(d, batch, q_len, pos0 + q_len), nullptr, 0, 0, seq_pos};
+                 q_len == 1 ? pl.attn : block_share_bytes(d, batch, q_len, pos0 + q_len), nullptr, 0, 0, seq_pos, true};
   st = attn_dispatch(at, d->dt, s);
   if (st != FORGE_OK) return st;
   trace_mark(s, FORGE_OP_ATTN);

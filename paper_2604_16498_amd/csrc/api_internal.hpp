@@ -83,16 +83,20 @@ inline size_t block_gemm_bytes(const forge_block_desc* d, int rows, int q_len) {
 
 // Inside a layer a prompt's key shares get no bytes of their own (a buffer for a long prompt serves the
 // shorter ones, which are cut into more shares): they lie in the MLP rows and the projections' scratch,
-// which nothing reads or writes while the attention runs.  0: they do not fit, the call runs
-// unsplit.  A function of the shapes alone, so that the plain and the compiled launch list, which place
-// them differently, cut alike: the compiled one keeps registers of one size together, so MLP rows as wide as
-// the residual stream or the heads lie among live ones there and are not counted.
+// which nothing reads or writes while the attention runs, as many of them as fit (12 heads of 64, 2 to 30 rows behind
+// 2500 keys: 7 of 8).  0: the call runs unsplit.  A function of the shapes alone, so that the plain and the
+// compiled launch list, which place them differently, cut alike: the compiled one keeps registers of one size
+// together, so MLP rows as wide as the residual stream or the heads lie among live ones there and are not counted.
 inline size_t block_share_bytes(const forge_block_desc* d, int batch, int q_len, int kv_len) {
   if (q_len == 1) return 0;
   const size_t need = attn_ws(batch, d->q_heads, d->kv_heads, q_len, kv_len, d->head_dim, d->dt);
+  if (need == 0) return 0;
   const int rows = batch * q_len;
   const bool apart = d->d_ff != d->d_model && d->d_ff != d->q_heads * d->head_dim;
-  return need <= (apart ? block_mlp_bytes(d, rows) : 0) + block_gemm_bytes(d, rows, q_len) ? need : 0;
+  const size_t room = (apart ? block_mlp_bytes(d, rows) : 0) + block_gemm_bytes(d, rows, q_len);
+  const size_t one = attn_prefill_share_bytes(batch, d->q_heads, q_len, d->head_dim);
+  const size_t fit = (need < room ? need : room) / one;
+  return fit > 1 ? fit * one : 0;
 }
 
 inline forge_status gemm_dispatch(const GemmArgs& a, forge_dtype dt, hipStream_t s) {

@@ -487,10 +487,10 @@ template <int DH, bool MASKED>
 forge_status launch_dh(const AttnArgs& a, hipStream_t s) {
   if constexpr (!MASKED) {
     // (the workspace is optional: without it, or with less, the call runs unsplit)
-    const int shares = plan_shares(a.batch, a.q_heads, a.q_len, a.kv_len, DH);
-    if (shares > 1 && a.workspace != nullptr &&
-        a.workspace_bytes >= (size_t)shares * a.batch * a.q_heads * a.q_len * (DH + 2) * sizeof(float))
-      return launch_split<DH, false, true>(a, shares, s);
+    int shares = plan_shares(a.batch, a.q_heads, a.q_len, a.kv_len, DH);
+    const size_t room = a.workspace != nullptr ? a.workspace_bytes / attn_prefill_share_bytes(a.batch, a.q_heads, a.q_len, DH) : 0;
+    if (a.fewer_shares && room < (size_t)shares) shares = (int)room;
+    if (shares > 1 && room >= (size_t)shares) return launch_split<DH, false, true>(a, shares, s);
   }
   return launch_split<DH, MASKED, false>(a, 1, s);
 }
@@ -507,7 +507,7 @@ forge_status launch_attn_prefill_bf16(const AttnArgs& a, hipStream_t s) {
 // every shorter length.
 size_t attn_prefill_workspace_bytes(int batch, int q_heads, int q_len, int kv_len, int head_dim) {
   const int shares = plan_shares(batch, q_heads, q_len, kv_len, head_dim);
-  return shares > 1 ? (size_t)shares * batch * q_heads * q_len * (head_dim + 2) * sizeof(float) : 0;
+  return shares > 1 ? shares * attn_prefill_share_bytes(batch, q_heads, q_len, head_dim) : 0;
 }
 
 }  // namespace forge

@@ -260,6 +260,7 @@ struct AttnArgs {
   // Per-sequence lengths (q_len == 1, no mask): device array [B]; sequence b attends to rows
   // [0, kv_pos[b]] (clamped to kv_len - 1); kv_len is then the upper bound that sizes the launch.
   const int* kv_pos;
+  bool fewer_shares;      // prompts: as many of the planned key shares as the workspace holds (otherwise all or none)
 };
 
 forge_status launch_attn_f32(const AttnArgs& a, hipStream_t s);
@@ -269,6 +270,9 @@ forge_status launch_attn_prefill_bf16(const AttnArgs& a, hipStream_t s);
 forge_status launch_attn_decode_bf16(const AttnArgs& a, hipStream_t s);
 // optional: without it the call runs on one block per query block, slower where those are few
 size_t attn_prefill_workspace_bytes(int batch, int q_heads, int q_len, int kv_len, int head_dim);
+inline size_t attn_prefill_share_bytes(int batch, int q_heads, int q_len, int head_dim) {   // partial rows, maxima and sums
+  return (size_t)batch * q_heads * q_len * (head_dim + 2) * sizeof(float);
+}
 size_t attn_decode_workspace_bytes(int batch, int q_heads, int kv_heads, int kv_len, int head_dim);
 // The library's own fixed scratch array for the decode attention (one per GPU): its size, and its
 // address on the current device.  Every call on a GPU shares it.

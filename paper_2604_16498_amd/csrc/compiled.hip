@@ -255,7 +255,7 @@ forge_status run_program(const forge_compiled* c, hipStream_t s) {
         AttnArgs at = {in(I.x), kc, vc, out(I.out), c->batch, d->q_heads, d->kv_heads, c->q_len,
                        c->pos0 + c->q_len, dh, kv_bs, kv_hs, 1.0f / sqrtf((float)dh), 1,
                        I.share_bytes > 0 ? c->workspace + I.share_offset : out(I.ws),
-                       I.share_bytes > 0 ? I.share_bytes : bytes(I.ws), nullptr, 0, 0, c->seq_pos};
+                       I.share_bytes > 0 ? I.share_bytes : bytes(I.ws), nullptr, 0, 0, c->seq_pos, true};
         st = attn_dispatch(at, dt, s);
         break;
       }

@@ -32,6 +32,7 @@ def test_a_buffer_for_the_longer_prompt_serves_the_shorter(shape, shorter, longe
 @pytest.mark.parametrize("d,hq,hkv,dh,ff,llama,S,pos", [
     (512, 4, 2, 128, 1408, True, 80, 1500),      # shares in the MLP rows and the GEMM planes
     (256, 4, 4, 64, 1024, False, 300, 1900),
+    (768, 12, 12, 64, 3072, False, 20, 2500),    # room for seven of eight shares
     (256, 4, 4, 64, 256, False, 70, 1500),       # MLP rows as wide as the residual stream: planes only, if they hold them
     (512, 2, 2, 128, 2048, False, 257, 0),       # nothing to share
 ])
