@@ -11,10 +11,10 @@
 // lane reads four consecutive floats per 128-bit LDS read.  The slabs are prefetched three
 // ahead in registers.
 //
-// Small problems (fewer tiles than CUs -- the 128-token fp32 layer has 24 to 96 of them, and a
-// block walks K slab by slab with a barrier each) are split along K over grid.z: raw fp32
-// partial sums go to the workspace and a second kernel adds them in split order (fixed order, no
-// atomics: bitwise reproducible) and carries the epilogue.
+// Most problems of up to some thousand tiles take gemm_f32_waves_kernel below instead (plan_waves says which).
+// Long reductions with few tiles are split along K over grid.z: raw fp32 partial sums go to the workspace
+// and a second kernel adds them in split order (fixed order, no atomics: bitwise reproducible) and
+// carries the epilogue.
 #include "common.hpp"
 
 namespace forge {
@@ -195,6 +195,142 @@ __global__ __launch_bounds__(256) void gemm_f32_reduce_kernel(
   }
 }
 
+// ---- k slabs shared by the waves of a block ---------------------------------------------------------
+// A layer of a few hundred fp32 rows has fewer 64 x 64 tiles than the chip has CUs, and each of them is a
+// serial chain of slabs with two block barriers per slab, a partial plane and a second launch.  Here a
+// block of 8 waves owns 32 rows x 16 CB weight rows and the waves take the 32-element k slabs in turn (wave w:
+// slabs w, w + 8, ...): every wave loads, stages (in an LDS patch of its own) and multiplies its slabs
+// without a block barrier, DEPTH slabs in flight in registers, and the 8 partial tiles are added through LDS in
+// wave order at the end, where the outputs are finished.  v_mfma_f32_16x16x4_f32: lane l supplies row
+// l%16 and the k of its quarter, 8 (l/16) ... + 7 of the slab.  The gated activation takes 16 gate rows and
+// their 16 up rows as the two column blocks.
+// Bound by the LDS (16 KB written and read per 32 x 32 x 32 products: 64 of 128 B/clk at the full matrix rate) and by the
+// start of a block (5 us for 768 k, 1.3 of them matrix work): tiles of 64 x 32 and 64 x 64 halve the LDS traffic and are
+// slower (2304 x 768 at 128 rows 11.9 and 22 us against 10.6), two blocks per CU need the 128 registers.
+// The four products of a 128-row layer of 768 (MLP 3072): 60.4 us with their reduce launches before, 39.6 now; the layer 76.8 -> 57.6.
+constexpr int FW = 8;                                // waves per block
+constexpr int FM = 32, RB = FM / 16;                 // rows of x per block
+
+template <int CB, int ACT, bool SPLIT>
+__global__ __launch_bounds__(FW * 64, 4) void gemm_f32_waves_kernel(
+    const float* __restrict__ x, const float* __restrict__ w, const float* __restrict__ bias,
+    const float* residual, float* y, int M, int N, int K, int ldy, QkvSplit sp) {
+  constexpr bool SWIGLU = ACT == FORGE_ACT_SWIGLU;
+  static_assert(!SWIGLU || CB == 2, "gate and up rows are the two column blocks");
+  constexpr int WR = 16 * CB;                        // weight rows per block
+  constexpr int OUT = SWIGLU ? 16 : WR;              // output columns per block
+  constexpr int DEPTH = CB == 1 ? 3 : 2;             // slabs in flight per wave (128 registers: two blocks per CU)
+  constexpr int CHAINS = CB == 1 ? 4 : 2;            // sums per output of a wave: shorter chains, smaller rounding error
+  constexpr int PATCH = (FM + WR) * LDK;             // floats of one wave's patch; rows padded as above
+  constexpr int LDR = WR + 4;                        // row of a partial tile
+    static_assert(FM * LDR <= PATCH, "the partial tiles fit where the patches lie");
+  extern __shared__ __attribute__((aligned(16))) float lds[];   // [FW * PATCH]
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int m0 = blockIdx.y * FM, n0 = blockIdx.x * OUT;
+  float* const ax = lds + wave * PATCH;
+  float* const bx = ax + FM * LDK;
+
+  // loads: 8 lanes per row piece of 32 floats, unconditional from clamped addresses (rows past the end
+  // re-read the last one and are dropped at the store; k past the end is zeroed on the way into LDS)
+  const int lrow = lane >> 3, lcol = (lane & 7) * 4;
+  uint32_t xsrc[FM / 8], wsrc[WR / 8];               // byte offsets of the rows (below 4 GB: the host has checked)
+#pragma unroll
+  for (int i = 0; i < FM / 8; ++i) xsrc[i] = (uint32_t)min(m0 + lrow + 8 * i, M - 1) * (uint32_t)K * 4;
+#pragma unroll
+  for (int i = 0; i < WR / 8; ++i) {
+    const int r = lrow + 8 * i;
+    const int row = SWIGLU ? min(n0 + (r & 15), N - 1) + (r >= 16 ? N : 0) : min(n0 + r, N - 1);
+    wsrc[i] = (uint32_t)row * (uint32_t)K * 4;
+  }
+  floatx4 va[DEPTH][FM / 8], vb[DEPTH][WR / 8];
+  auto gload = [&](int k0, int slot) {
+    const uint32_t kk = 4 * min(k0 + lcol, K - 4);
+#pragma unroll
+    for (int i = 0; i < FM / 8; ++i) va[slot][i] = *reinterpret_cast<const floatx4*>((const char*)x + (xsrc[i] + kk));
+#pragma unroll
+    for (int i = 0; i < WR / 8; ++i) vb[slot][i] = *reinterpret_cast<const floatx4*>((const char*)w + (wsrc[i] + kk));
+  };
+  floatx4 acc[CHAINS][RB][CB];
+#pragma unroll
+  for (int h = 0; h < CHAINS; ++h)
+#pragma unroll
+    for (int i = 0; i < RB; ++i)
+#pragma unroll
+      for (int j = 0; j < CB; ++j) acc[h][i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+
+#pragma unroll
+  for (int d = 0; d < DEPTH; ++d) gload((wave + d * FW) * BK, d);
+  for (int kb = wave * BK; kb < K; kb += DEPTH * FW * BK) {
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d) {
+      const int k0 = kb + d * FW * BK;
+      if (k0 < K) {                                  // wave-uniform
+        const bool k_ok = k0 + lcol < K;
+        const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
+        wave_lds_sync();                             // the previous slab has been read
+#pragma unroll
+        for (int i = 0; i < FM / 8; ++i) *reinterpret_cast<floatx4*>(ax + (lrow + 8 * i) * LDK + lcol) = k_ok ? va[d][i] : zero;
+#pragma unroll
+        for (int i = 0; i < WR / 8; ++i) *reinterpret_cast<floatx4*>(bx + (lrow + 8 * i) * LDK + lcol) = k_ok ? vb[d][i] : zero;
+        wave_lds_sync();
+        const int r = lane & 15, kq = (lane >> 4) * 8;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          floatx4 a[RB], b[CB];
+#pragma unroll
+          for (int i = 0; i < RB; ++i) a[i] = *reinterpret_cast<const floatx4*>(ax + (16 * i + r) * LDK + kq + 4 * j);
+#pragma unroll
+          for (int c = 0; c < CB; ++c) b[c] = *reinterpret_cast<const floatx4*>(bx + (16 * c + r) * LDK + kq + 4 * j);
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int i = 0; i < RB; ++i)
+#pragma unroll
+              for (int c = 0; c < CB; ++c)
+                acc[(j + 2 * e) % CHAINS][i][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][e], b[c][e], acc[(j + 2 * e) % CHAINS][i][c], 0, 0, 0);
+        }
+      }
+      gload(k0 + DEPTH * FW * BK, d);                // into the registers just consumed
+    }
+  }
+
+  // ---- the 8 partial tiles, added in wave order; accumulator: column lane%16, rows 4 (lane/16) ... + 3 --------
+  wave_lds_sync();
+#pragma unroll
+  for (int i = 0; i < RB; ++i)
+#pragma unroll
+    for (int c = 0; c < CB; ++c) {
+#pragma unroll
+      for (int h = 1; h < CHAINS; ++h) acc[0][i][c] += acc[h][i][c];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) ax[(16 * i + 4 * (lane >> 4) + v) * LDR + 16 * c + (lane & 15)] = acc[0][i][c][v];
+    }
+  __syncthreads();
+#pragma unroll
+  for (int at = tid; at < FM * OUT; at += FW * 64) {
+    const int mr = at / OUT, nc = at % OUT, m = m0 + mr, n = n0 + nc;
+    float v = 0.f, u = 0.f;
+#pragma unroll
+    for (int z = 0; z < FW; ++z) {
+      v += lds[z * PATCH + mr * LDR + nc];
+      if (SWIGLU) u += lds[z * PATCH + mr * LDR + 16 + nc];
+    }
+    if (m >= M || n >= N) continue;
+    if (bias != nullptr) {
+      v += bias[n];
+      if (SWIGLU) u += bias[n + N];
+    }
+    v = SWIGLU ? silu_f(v) * u : apply_act<ACT>(v);
+    if (SPLIT) {
+      *reinterpret_cast<float*>(split_dst(sp, m, n, sizeof(float))) = v;
+    } else {
+      if (residual != nullptr) v += residual[(int64_t)m * ldy + n];
+      y[(int64_t)m * ldy + n] = v;
+    }
+  }
+}
+
 // k ranges for a problem: none while the tiles fill the chip; otherwise towards two blocks per
 // CU, each with at least four slabs.
 struct SplitPlan { int splits, k_per_split; };
@@ -209,7 +345,48 @@ SplitPlan plan_split(int M, int N, int K) {
 
 }  // namespace
 
+namespace {
+template <int CB, int ACT, bool SPLIT>
+forge_status launch_tile(const float* x, const float* w, const float* bias, const float* res, float* y, int M, int N,
+                         int K, int ldy, const QkvSplit& sp, hipStream_t s) {
+  constexpr int smem = FW * (FM + 16 * CB) * LDK * (int)sizeof(float);
+  auto kern = gemm_f32_waves_kernel<CB, ACT, SPLIT>;
+  static std::atomic<uint64_t> lds_raised{0};   // per kernel instantiation
+  if (raise_lds_limit(reinterpret_cast<const void*>(kern), smem, lds_raised) != FORGE_OK) return FORGE_ERR_HIP;
+  const int cols = ACT == FORGE_ACT_SWIGLU ? 8 * CB : 16 * CB;
+  kern<<<dim3(ceil_div(N, cols), ceil_div(M, FM)), FW * 64, smem, s>>>(x, w, bias, res, y, M, N, K, ldy, sp);
+  return launch_status();
+}
+template <int ACT, bool SPLIT>
+forge_status launch_waves(int cb, const float* x, const float* w, const float* bias, const float* res, float* y, int M, int N,
+                          int K, int ldy, const QkvSplit& sp, hipStream_t s) {
+  if constexpr (ACT != FORGE_ACT_SWIGLU) {
+    if (cb == 1) return launch_tile<1, ACT, SPLIT>(x, w, bias, res, y, M, N, K, ldy, sp, s);
+  }
+  return launch_tile<2, ACT, SPLIT>(x, w, bias, res, y, M, N, K, ldy, sp, s);
+}
+// Column blocks (1 or 2) of the wave-shared tiles, or 0 for the 64 x 64 tiles.  Times are rounds of tiles over the
+// CUs times slabs plus a start, in units of 0.1 us as measured (7 per round of 64 x 64 tiles and slab, 1.9 and 1.2 per round
+// of 32 x 32 and 32 x 16; us, 64 x 64 with its reduce | wave-shared: 128 rows against 2304 x 768 15.1 | 10.6, 768 x 768 9.8 | 5.2,
+// 3072 x 768 18.1 | 10.9, 768 x 3072 17.4 | 12.9; 512 rows against 3072 x 768 34.3 | 29.4, 2048 rows 99 | 108, 256 rows
+// against 6144 x 72 9.2 | 10.1).  A long reduction with few tiles stays cut over the grid (64 rows against 768 x 8192
+// 21.9 | 28.7, 256 x 4096 at one row 13.8 | 15.0; from 24 tiles on 32.7 | 30.5).
+int plan_waves(int M, int N, int K, bool gated) {
+  const int64_t rows = gated ? 2 * (int64_t)N : N;
+  if ((int64_t)M * K >= (1ll << 30) || rows * K >= (1ll << 30)) return 0;       // 32-bit byte offsets
+  const int64_t cus = compute_units(), slabs = ceil_div(K, BK), slabs8 = (slabs + 7) / 8 * 8;
+  const int64_t t64 = (int64_t)ceil_div(M, BM) * ceil_div(N, BN), mt = ceil_div(M, FM);
+  if ((K > 3072 && t64 <= 16) || mt > 65535) return 0;
+  const int64_t c64 = ceil_div64(t64, cus) * slabs * (gated ? 14 : 7) + 45;
+  const int64_t c2 = ceil_div64(mt * ceil_div64(rows, 32), cus) * slabs8 * 19 / 10 + 22;
+  const int64_t c1 = gated ? c2 : ceil_div64(mt * ceil_div64(N, 16), cus) * slabs8 * 12 / 10 + 21;
+  if (c64 < c2 && c64 < c1) return 0;
+  return c1 < c2 ? 1 : 2;
+}
+}  // namespace
+
 size_t gemm_f32_workspace_bytes(int M, int N, int K, forge_act act) {
+  if (plan_waves(M, N, K, act == FORGE_ACT_SWIGLU) > 0) return 0;
   const SplitPlan sp = plan_split(M, N, K);
   if (sp.splits == 1) return 0;
   return (size_t)sp.splits * M * (act == FORGE_ACT_SWIGLU ? 2 * N : N) * sizeof(float);
@@ -229,9 +406,11 @@ forge_status launch_gemm_f32(const GemmArgs& a, hipStream_t s) {
   float* y = (float*)a.y;
   QkvSplit sp = {};
   const int ldy = a.ldy > 0 ? a.ldy : a.N;
+  const int cb = plan_waves(a.M, a.N, a.K, a.act == FORGE_ACT_SWIGLU);
   if (a.split != nullptr) {
     if (a.act != FORGE_ACT_NONE || a.residual != nullptr) return FORGE_ERR_UNSUPPORTED;
     sp = *a.split;
+    if (cb > 0) return launch_waves<FORGE_ACT_NONE, true>(cb, x, w, bias, res, y, a.M, a.N, a.K, ldy, sp, s);
     gemm_f32_kernel<FORGE_ACT_NONE, true><<<grid, block, 0, s>>>(x, w, bias, res, y, a.M, a.N, a.K, ldy, sp,
                                                                  pl.k_per_split, part);
     if (part != nullptr)
@@ -241,6 +420,7 @@ forge_status launch_gemm_f32(const GemmArgs& a, hipStream_t s) {
   switch (a.act) {
 #define FORGE_CASE(ACT)                                                                                        \
   case ACT:                                                                                                    \
+    if (cb > 0) return launch_waves<ACT, false>(cb, x, w, bias, res, y, a.M, a.N, a.K, ldy, sp, s);             \
     gemm_f32_kernel<ACT, false><<<grid, block, 0, s>>>(x, w, bias, res, y, a.M, a.N, a.K, ldy, sp,             \
                                                        pl.k_per_split, part);                                  \
     if (part != nullptr)                                                                                       \
