@@ -290,7 +290,7 @@ def operator_work(wl, F, torch, logits_ld):
                             "attn_decode<%d,%d>" % (sh.head_dim, G))
     else:
         ops["attention"] = ("mfma", attn_fl / wl.layers,
-                            "attn_prefill<%d,false,false>" % sh.head_dim if wl.bf16 else "attn_f32<%d>" % sh.head_dim)
+                            "attn_prefill<%d>" % sh.head_dim if wl.bf16 else "attn_f32<%d>" % sh.head_dim)
     if wl.vocab:
         ops["lm_head"] = gemm(wl.vocab, d, "none", 0, ldy=logits_ld)
     return ops

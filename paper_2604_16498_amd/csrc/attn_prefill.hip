@@ -1,8 +1,10 @@
 // bf16 fused causal attention for prefill on the gfx950 matrix cores: scores, scale, mask,
 // softmax and the product with V in one kernel; S and P live only in registers.
 //
-// Work split: a 512-thread block (8 waves, one block per CU) owns 256 consecutive queries of one
-// (batch, head); each wave owns 32 of them and walks the keys in tiles of 64 up to its diagonal.
+// Work split: a block owns 32 consecutive queries per wave of one (batch, head), and each wave walks the
+// keys in tiles of 64 up to its diagonal.  Blocks of 8 waves (one per CU) run the two waves of a SIMD half a
+// tile apart (Pipeline, below); blocks of 4 or 2 waves run a tile's steps in order and leave the overlap to the other
+// blocks of their CU.  launch_dh says which takes a call.
 //
 // Both contractions are computed TRANSPOSED so that the two MFMAs chain without any data
 // movement:
@@ -23,7 +25,7 @@
 // on both operands, so the sum is unchanged): element e of lane-half h is key
 // 16 s + 8 (e / 4) + 4 h + e % 4, which is what the S^T accumulator registers 8 (s % 2) + e hold.
 //
-// Pipeline: per wave and tile of 64 keys the softmax is ~1000 cycles of vector ALU work and the two
+// Pipeline (8 waves): per wave and tile of 64 keys the softmax is ~1000 cycles of vector ALU work and the two
 // contractions ~1100 cycles of MFMA, and a wave issues in order.  The matrix pipe and the vector ALU
 // of a SIMD do overlap when they are fed by two DIFFERENT waves (measured: the MFMA stream keeps its
 // pace, the vector stream loses about a quarter), so the work of a tile is cut into a pure vector
@@ -41,6 +43,12 @@
 // against 145.8, 777 queries behind 2500 keys 96.4 against 92.2, and a dense mask (8 x 12 heads x 1000,
 // whose loads the old barrier drained) 92.2 against 75.6.  (The same loads issue two to four times slower from waves 4-7, and
 // direct-to-LDS loads were measured slower still: +15 %.)
+//
+// Blocks of 4 and 2 waves: all waves copy, one barrier per tile, and S, the softmax and P.V of a tile follow each other in a
+// wave.  At head_dim 64 the vector work is twice the matrix work, the 8-wave kernel left two waves per SIMD
+// with it (154 registers) and its blocks filled the chip in 1.5 rounds at 8 x 12 heads x 1024; three blocks of 4 waves fit a
+// CU (131 registers, 39 KB).  us, 8 waves | 4 waves: 8 x 12 heads of 64 x 1024 causal 31.8 | 27.7, x 600 20.4 | 16.0, the
+// same dense 54 | 41.5, masked 82.6 | 60; head_dim 128 (two blocks per CU): 32 heads x 300 15.1 | 11.2, x 1500 49.6 | 42.4.
 #include "common.hpp"
 
 namespace forge {
@@ -54,7 +62,7 @@ struct AttnParams {
   const bf16* k;
   const bf16* v;
   bf16* out;
-  int q_heads, kv_heads, q_len, kv_len;
+  int batch, q_heads, kv_heads, q_len, kv_len;
   int64_t kv_bs, kv_hs;
   float scale_log2e;
   int causal;
@@ -82,16 +90,17 @@ __device__ inline float xchg32_sum(float x) {
 // SPLIT: block z of a query block walks only its share of the key tiles and writes unnormalised fp32
 // rows with their (maximum, sum); attn_prefill_merge adds the shares.  For calls with fewer query blocks
 // than CUs (a turn of 777 tokens has 4 per head).
-template <int DH, bool MASKED, bool SPLIT>
-__global__ __launch_bounds__(512) void attn_prefill_kernel(AttnParams p) {
-  constexpr int BQ = 256, BKV = 64;
+template <int DH, bool MASKED, bool SPLIT, int WAVES>
+__global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : DH == 128 || MASKED ? 2 : 3) void attn_prefill_kernel(AttnParams p) {
+  constexpr int BQ = WAVES * 32, BKV = 64;
   constexpr int CPR = DH / 8;                 // 16-byte chunks per row
   constexpr int KS = DH * 2 + 16;             // K row stride in LDS (bytes)
-  constexpr int VS = DH * 2 + 64;             // V row stride in LDS (bytes)
+  constexpr int VS = DH * 2 + (DH == 64 ? 32 : 64);   // V row stride in LDS (bytes)
   constexpr int K_BYTES = BKV * KS, V_BYTES = BKV * VS;
   // chunks per thread, tensor and tile: the early waves move the tiles (measured: the same loads
   // issue two to four times slower from the second wave of a SIMD)
-  constexpr int LPT = BKV * CPR / 256;        // per thread of the early waves; the late waves copy nothing
+  constexpr int COPY = WAVES < 4 ? WAVES * 64 : 256;   // copying threads
+  constexpr int LPT = BKV * CPR / COPY;       // per thread of the early waves; the late waves copy nothing
   constexpr int NKS = DH / 16;                // MFMA k-steps over dh
   constexpr int NDT = DH / 32;                // 32-row tiles of O^T
   extern __shared__ __attribute__((aligned(16))) char smem[];   // [K0 | K1 | V0 | V1]
@@ -102,12 +111,22 @@ __global__ __launch_bounds__(512) void attn_prefill_kernel(AttnParams p) {
   const int fr = lane & 31, fh = lane >> 5;
   // late (long) query blocks first, over all heads: they carry the most key tiles under the
   // causal mask, and blocks are handed out in launch order
-  const int qb = p.n_qblocks - 1 - blockIdx.y;
-  const int h = blockIdx.x % p.q_heads, b = blockIdx.x / p.q_heads;
+  const int at = blockIdx.x, pairs = p.batch * p.q_heads;
+  int qb = p.n_qblocks - 1 - at / pairs;
+  int h = at % pairs % p.q_heads, b = at % pairs / p.q_heads;
+  if (MASKED && p.mask_hs == 0) {
+    // One mask for all heads: the heads of a query block run side by side on one XCD (blocks are dealt round-robin
+    // over the 8), whose L2 then fetches those mask rows once; dealt over all of them, every L2 fetched
+    // the whole mask (8 x 12 heads x 1000: 83 -> 70 us by this alone).
+    const int n = gridDim.x, xcd = at & 7, item = xcd * (n >> 3) + min(xcd, n & 7) + (at >> 3);
+    h = item % p.q_heads;
+    qb = p.n_qblocks - 1 - item / p.q_heads % p.n_qblocks;
+    b = item / p.q_heads / p.n_qblocks;
+  }
   const int g = h / (p.q_heads / p.kv_heads);
   const int q0 = qb * BQ, q0w = q0 + wave * 32;
   const int off = p.kv_len - p.q_len;
-  const bool late = wave >= 4;                // the second wave of each SIMD runs half a tile behind (see above)
+  const bool late = WAVES == 8 && wave >= 4;                // the second wave of each SIMD runs half a tile behind (see above)
 
   const bf16* kbase = p.k + (int64_t)b * p.kv_bs + (int64_t)g * p.kv_hs;
   const bf16* vbase = p.v + (int64_t)b * p.kv_bs + (int64_t)g * p.kv_hs;
@@ -141,7 +160,7 @@ __global__ __launch_bounds__(512) void attn_prefill_kernel(AttnParams p) {
   int ld_row[LPT], ld_c[LPT];
 #pragma unroll
   for (int i = 0; i < LPT; ++i) {
-    const int idx = (tid & 255) + i * 256;
+    const int idx = (tid & (COPY - 1)) + i * COPY;
     ld_row[i] = idx / CPR;
     ld_c[i] = idx % CPR;
   }
@@ -324,46 +343,67 @@ __global__ __launch_bounds__(512) void attn_prefill_kernel(AttnParams p) {
   store_v(t_first & 1);
   load_rows(kbase, t_first + 1, rk);   // (tiles past the end re-read the last key: a branch around the
   load_rows(vbase, t_first + 1, rv);   // loads would make the waits of the loop drain them all)
+  if (WAVES < 8 && wave_needs(t_first)) mask_prefetch(t_first);
   lds_barrier();
-  if (wave_needs(t_first)) {
-    scores(t_first);
-    mask_prefetch(t_first);
-  }
-  lds_barrier();
-
-  // Steps of half a tile, a block barrier after each; the late waves run one step behind:
-  //   step 2t   : early waves  softmax(t), copy of K(t+1)           late waves  P.V(t-1), S(t)
-  //   step 2t+1 : early waves  P.V(t), S(t+1), copy of V(t+1)      late waves  softmax(t)
-  // K(t+1) goes into K buffer (t+1)&1 in step 2t; its last reader was the late waves' S(t-1) in step
-  // 2t-2, and it is first read by the early waves' S(t+1) in step 2t+1.  V(t+1) goes into V buffer (t+1)&1
-  // in step 2t+1; last read by the late waves' P.V(t-1) in step 2t, first read by the early waves'
-  // P.V(t+1) in step 2t+3.  The register loads of tile t+2 follow each store.
-  auto matrix_phase = [&](int t) {
-    if (wave_needs(t)) pv_mm(t);
-    if (wave_needs(t + 1)) {
-      scores(t + 1);
-      mask_prefetch(t + 1);
-    }
-  };
-  if (!late) {
+  if constexpr (WAVES < 8) {
+    // Tile t + 1 goes into the other buffers, whose last readers finished tile t - 1 before the barrier; the
+    // register loads of tile t + 2 follow.  One barrier per tile.
     for (int t = t_first; t < n_tiles; ++t) {
-      if (t + 1 < n_tiles) store_k((t + 1) & 1);
+      if (t + 1 < n_tiles) {
+        store_k((t + 1) & 1);
+        store_v((t + 1) & 1);
+      }
       load_rows(kbase, t + 2, rk);
-      if (wave_needs(t)) softmax(t);
-      lds_barrier();
-      if (t + 1 < n_tiles) store_v((t + 1) & 1);
       load_rows(vbase, t + 2, rv);
-      matrix_phase(t);
+      if (wave_needs(t)) {
+        scores(t);
+        softmax(t);
+        if (wave_needs(t + 1)) mask_prefetch(t + 1);
+        pv_mm(t);
+      }
       lds_barrier();
     }
-    lds_barrier();                     // the late waves' last step
   } else {
-    lds_barrier();                     // the early waves' first step
-    for (int t = t_first; t < n_tiles; ++t) {
-      if (wave_needs(t)) softmax(t);
-      lds_barrier();
-      matrix_phase(t);
-      lds_barrier();
+    if (wave_needs(t_first)) {
+      scores(t_first);
+      mask_prefetch(t_first);
+    }
+    lds_barrier();
+
+    // Steps of half a tile, a block barrier after each; the late waves run one step behind:
+    //   step 2t   : early waves  softmax(t), copy of K(t+1)           late waves  P.V(t-1), S(t)
+    //   step 2t+1 : early waves  P.V(t), S(t+1), copy of V(t+1)      late waves  softmax(t)
+    // K(t+1) goes into K buffer (t+1)&1 in step 2t; its last reader was the late waves' S(t-1) in step
+    // 2t-2, and it is first read by the early waves' S(t+1) in step 2t+1.  V(t+1) goes into V buffer (t+1)&1
+    // in step 2t+1; last read by the late waves' P.V(t-1) in step 2t, first read by the early waves'
+    // P.V(t+1) in step 2t+3.  The register loads of tile t+2 follow each store.
+    auto matrix_phase = [&](int t) {
+      if (wave_needs(t)) pv_mm(t);
+      if (wave_needs(t + 1)) {
+        scores(t + 1);
+        mask_prefetch(t + 1);
+      }
+    };
+    if (!late) {
+      for (int t = t_first; t < n_tiles; ++t) {
+        if (t + 1 < n_tiles) store_k((t + 1) & 1);
+        load_rows(kbase, t + 2, rk);
+        if (wave_needs(t)) softmax(t);
+        lds_barrier();
+        if (t + 1 < n_tiles) store_v((t + 1) & 1);
+        load_rows(vbase, t + 2, rv);
+        matrix_phase(t);
+        lds_barrier();
+      }
+      lds_barrier();                     // the late waves' last step
+    } else {
+      lds_barrier();                     // the early waves' first step
+      for (int t = t_first; t < n_tiles; ++t) {
+        if (wave_needs(t)) softmax(t);
+        lds_barrier();
+        matrix_phase(t);
+        lds_barrier();
+      }
     }
   }
 
@@ -371,7 +411,7 @@ __global__ __launch_bounds__(512) void attn_prefill_kernel(AttnParams p) {
   const float l_tot = xchg32_sum(l_run);
   if constexpr (SPLIT) {
     if (my_q >= p.q_len) return;
-    const int64_t rows = (int64_t)(gridDim.x) * p.q_len, row = (int64_t)blockIdx.x * p.q_len + my_q;   // blockIdx.x = batch * q_heads + head
+    const int64_t rows = (int64_t)pairs * p.q_len, row = (int64_t)(b * p.q_heads + h) * p.q_len + my_q;
     float* prow = p.part + ((int64_t)blockIdx.z * rows + row) * DH;
 #pragma unroll
     for (int dt = 0; dt < NDT; ++dt)
@@ -429,13 +469,14 @@ __global__ __launch_bounds__(256) void attn_prefill_merge(const float* __restric
   Vec8<bf16>::store(out + ((b * q_len + q) * q_heads + h) * DH + c * 8, o);
 }
 
-template <int DH, bool MASKED, bool SPLIT>
+template <int DH, bool MASKED, bool SPLIT, int WAVES>
 forge_status launch_split(const AttnArgs& a, int splits, hipStream_t s) {
   AttnParams p;
   p.q = (const bf16*)a.q;
   p.k = (const bf16*)a.k;
   p.v = (const bf16*)a.v;
   p.out = (bf16*)a.out;
+  p.batch = a.batch;
   p.q_heads = a.q_heads;
   p.kv_heads = a.kv_heads;
   p.q_len = a.q_len;
@@ -444,17 +485,17 @@ forge_status launch_split(const AttnArgs& a, int splits, hipStream_t s) {
   p.kv_hs = a.kv_head_stride;
   p.scale_log2e = a.scale * 1.4426950408889634f;
   p.causal = a.causal;
-  p.n_qblocks = ceil_div(a.q_len, 256);
+  p.n_qblocks = ceil_div(a.q_len, WAVES * 32);
   p.part = (float*)a.workspace;
   p.splits = splits;
   p.mask = a.mask;
   p.mask_bs = a.mask_batch_stride;
   p.mask_hs = a.mask_head_stride;
-  constexpr int smem = 2 * 64 * ((DH * 2 + 16) + (DH * 2 + 64));
-  auto kern = attn_prefill_kernel<DH, MASKED, SPLIT>;
+  constexpr int smem = 2 * 64 * ((DH * 2 + 16) + (DH * 2 + (DH == 64 ? 32 : 64)));
+  auto kern = attn_prefill_kernel<DH, MASKED, SPLIT, WAVES>;
   static std::atomic<uint64_t> lds_raised{0};   // per kernel instantiation
   if (raise_lds_limit(reinterpret_cast<const void*>(kern), smem, lds_raised) != FORGE_OK) return FORGE_ERR_HIP;
-  dim3 grid(a.q_heads * a.batch, p.n_qblocks, splits), block(512);
+  dim3 grid((unsigned)a.q_heads * a.batch * p.n_qblocks, 1, splits), block(WAVES * 64);
   kern<<<grid, block, smem, s>>>(p);
   if (!SPLIT) return launch_status();
   if (hipGetLastError() != hipSuccess) return FORGE_ERR_HIP;
@@ -463,36 +504,76 @@ forge_status launch_split(const AttnArgs& a, int splits, hipStream_t s) {
   return launch_status();
 }
 
-// Key shares of a call: only where its query blocks leave CUs idle, at most as many as those CUs take and
-// none shorter than 256 keys.  A block walks a 64-key tile in 1.5 us, the merge launch costs 4.5 us and
-// a share's partial rows go out and back at about 5 TB/s; the count with the most left over is
-// non-decreasing in kv_len.  us, merge included, calls back to back: 777 queries behind 2500 keys (32 heads of 128)
-// 74.3 -> 53.4, 80 behind 4000 107 -> 27.5, 300 behind 1000 33.2 -> 27.1, 1 x 12 heads of 64 x 1000 24.5 -> 20.5; two
-// shares of 520 x 32 heads would take 24.9 against 22.1 unsplit.  (Between the products of a model's step, on a warmer
-// card with the cache cold, the first takes 64.8 and its merge 6.9.)
-inline int plan_shares(int batch, int q_heads, int q_len, int kv_len, int head_dim) {
-  const int64_t pairs = (int64_t)batch * q_heads, blocks = pairs * ceil_div(q_len, 256);
-  const int most = (int)min(min((int64_t)compute_units() / blocks, (int64_t)kv_len / 256), (int64_t)8);
-  const double tiles = kv_len / 64.0, share_us = (double)(pairs * q_len) * head_dim * 8 / 5e6;
+// Blocks of w waves that a call has.
+inline int64_t query_blocks(int batch, int q_heads, int q_len, int w) { return (int64_t)batch * q_heads * ceil_div(q_len, 32 * w); }
+
+// Key shares of a call on blocks of w (4 or 8) waves: only where its query blocks leave CUs idle, at most 8 and none shorter than
+// 256 keys.  What a 64-key tile takes a block depends on how many of them a CU holds, the merge launch costs 4.5 us and
+// a share's partial rows go out and back at about 5 TB/s; the count with the least time is non-decreasing
+// in kv_len (fewer tiles per share against a fixed cost).  us, merge included, unsplit | shares: 80 queries behind 1000 keys
+// (12 heads of 64) 17.9 | 11.2 (4), 30 behind 2500 37.6 | 13.2 (8), 2 x 777 behind 2500 50 | 36 (3); heads of 128, 32 of them: 80 behind
+// 4000 87 | 24.6 (8), 300 behind 1000 32.5 | 26.9 (2), 500 behind 2500 69 | 45 (4), 777 behind 0 23.2 | 29.4 (2).
+inline int plan_shares(int batch, int q_heads, int q_len, int kv_len, int head_dim, int w) {
+  const int64_t cus = compute_units(), blocks = query_blocks(batch, q_heads, q_len, w);
+  const int per_cu = w == 8 ? 1 : head_dim == 128 ? 2 : 3;
+  const int most = (int)min(min(per_cu * cus / blocks, (int64_t)kv_len / 256), (int64_t)8);
+  const double tiles = kv_len / 64.0, share_us = (double)((int64_t)batch * q_heads * q_len) * head_dim * 8 / 5e6;
+  auto tile_us = [&](int n) {
+    const int64_t r = ceil_div64(blocks * n, cus);       // blocks on the fullest CU
+    if (w == 8) return 1.5;
+    if (head_dim == 128) return r <= 1 ? 1.4 : 1.9;
+    return r <= 1 ? 0.95 : r == 2 ? 1.35 : 1.9;
+  };
   int best = 1;
-  double left = 0.0;
+  double least = tile_us(1) * tiles;
   for (int n = 2; n <= most; ++n) {
-    const double l = 1.5 * (tiles - tiles / n) - 4.5 - share_us * n;
-    if (l > left) { left = l; best = n; }
+    const double us = tile_us(n) * tiles / n + 4.5 + share_us * n;
+    if (us < least) { least = us; best = n; }
   }
   return best;
 }
 
+// head_dim 128: blocks of 8 waves where they fill the chip.  With key shares: at least 2500 keys, query blocks not mostly
+// padding (us, 8 waves | 4: 777 queries behind 2500 keys 67.4 | 70, 1024 behind 3072 84 | 91, but 600 behind 2900 66 | 58,
+// 300 behind 3700 49 | 46).  Unsplit: whole query blocks, well past one round of them (32 heads x 4000 153 | 167, 3 x 16 x 2048
+// 71 | 75, but 32 x 2500, 1.25 rounds, 84 | 76, 3 x 32 x 1300, 15 % padding, 84 | 75, 32 x 2048, one round, 65 | 58).
+inline bool eight_waves_split(int batch, int q_heads, int q_len, int kv_len, int shares) {
+  return shares > 1 && kv_len >= 2500 && q_len * 10 >= ceil_div(q_len, 256) * 256 * 7 &&
+         query_blocks(batch, q_heads, q_len, 8) * shares * 10 >= (int64_t)compute_units() * 9;
+}
+inline bool eight_waves(int batch, int q_heads, int q_len) {
+  return (int64_t)q_len * 100 >= (int64_t)ceil_div(q_len, 256) * 256 * 93 &&
+         query_blocks(batch, q_heads, q_len, 8) * 10 >= (int64_t)compute_units() * 14;
+}
+
 template <int DH, bool MASKED>
 forge_status launch_dh(const AttnArgs& a, hipStream_t s) {
+  const int64_t cus = compute_units();
   if constexpr (!MASKED) {
     // (the workspace is optional: without it, or with less, the call runs unsplit)
-    int shares = plan_shares(a.batch, a.q_heads, a.q_len, a.kv_len, DH);
     const size_t room = a.workspace != nullptr ? a.workspace_bytes / attn_prefill_share_bytes(a.batch, a.q_heads, a.q_len, DH) : 0;
-    if (a.fewer_shares && room < (size_t)shares) shares = (int)room;
-    if (shares > 1 && room >= (size_t)shares) return launch_split<DH, false, true>(a, shares, s);
+    auto shares_on = [&](int w) {
+      const int n = plan_shares(a.batch, a.q_heads, a.q_len, a.kv_len, DH, w);
+      return room >= (size_t)n ? n : a.fewer_shares ? (int)room : 1;
+    };
+    if constexpr (DH == 128) {
+      const int n = shares_on(8);
+      if (eight_waves_split(a.batch, a.q_heads, a.q_len, a.kv_len, n)) return launch_split<DH, false, true, 8>(a, n, s);
+    }
+    const int n = shares_on(4);
+    if (n > 1) return launch_split<DH, false, true, 4>(a, n, s);
   }
-  return launch_split<DH, MASKED, false>(a, 1, s);
+  // half as many queries per block while that leaves one block per CU (us, 4 waves | 2: 12 heads of 64 x 500 11.2 | 10.5, x 128
+  // 5.9 | 5.1, masked x 1000 26 | 22; 2 x 12 x 700 masked, 264 blocks, 20 | 22.5; 32 heads of 128 x 80 7.5 | 6.2)
+  if constexpr (!(MASKED && DH == 128)) {
+    if (query_blocks(a.batch, a.q_heads, a.q_len, 2) <= cus) return launch_split<DH, MASKED, false, 2>(a, 1, s);
+  }
+  if constexpr (DH == 128) {
+    // (the mask's registers leave no room for a second block; 16 heads x 1000 46 | 36, 3 x 16 x 700, 288 blocks of 4 waves, 36 | 40)
+    if (MASKED ? query_blocks(a.batch, a.q_heads, a.q_len, 4) > cus : eight_waves(a.batch, a.q_heads, a.q_len))
+      return launch_split<DH, MASKED, false, 8>(a, 1, s);
+  }
+  return launch_split<DH, MASKED, false, 4>(a, 1, s);
 }
 
 }  // namespace
@@ -503,10 +584,11 @@ forge_status launch_attn_prefill_bf16(const AttnArgs& a, hipStream_t s) {
   return FORGE_ERR_UNSUPPORTED;
 }
 
-// Non-decreasing in kv_len (the share count is), so that a buffer sized for a cache's capacity serves
+// Non-decreasing in kv_len (both share counts are), so that a buffer sized for a cache's capacity serves
 // every shorter length.
 size_t attn_prefill_workspace_bytes(int batch, int q_heads, int q_len, int kv_len, int head_dim) {
-  const int shares = plan_shares(batch, q_heads, q_len, kv_len, head_dim);
+  int shares = plan_shares(batch, q_heads, q_len, kv_len, head_dim, 4);
+  if (head_dim == 128) shares = max(shares, plan_shares(batch, q_heads, q_len, kv_len, head_dim, 8));
   return shares > 1 ? shares * attn_prefill_share_bytes(batch, q_heads, q_len, head_dim) : 0;
 }
 
