@@ -34,8 +34,9 @@
 // column-major inside a group, so that the tiles resident in one XCD at a time share x and w
 // panels in that L2.
 //
-// M <= 64 (decode): most problems go to the kernel of gemm_bf16_rows.hip (plan_rows says which).  The
-// others (bf16 with a long K, many weight rows per CU, or more rows of x than its registers pay for): the weight is streamed once by
+// M <= 64 (decode) and prompts against few weight rows: most problems go to the kernels of gemm_bf16_rows.hip and
+// gemm_bf16_waves.hip (plan_route says which).  The
+// others of M <= 64 (bf16 with a long K, many weight rows per CU, or more rows of x than its registers pay for): the weight is streamed once by
 // gemm_bf16_wstream_kernel (128 or 256 weight rows per block, K split over grid.y to about one block
 // per CU), fp32 partials, and fixed-order reduce kernels that carry the epilogue (and, inside a
 // decoder layer, RoPE or the following norm).
@@ -1242,34 +1243,71 @@ inline SkinnyPlan plan_skinny(int N, int K, forge_act act, int bk = BK) {
 }
 
 // The whole dispatch of a problem that does not rotate in its epilogue: the launcher follows it and the variant
-// query names it.
+// query names its class.
 struct Route {
   Variant v;
   SkinnyPlan sk;      // at most 64 rows
   PersSplit ps;       // V_FAST_128: k ranges (1: unsplit)
   RowsPlan rows;      // ranges > 0: the kernel with x in registers takes it
   bool planes;        // fp32 planes and a reduce launch
+  bool few_rows;      // more than 64 rows: see few_weight_rows
+  int waves = -1;     // tile of the kernel whose waves share the k slabs, which then takes the problem
 };
+
+// More than 64 rows against a weight with few row tiles of 16: the 128 x 128 tiles leave most of the chip idle, each walking
+// all of K alone (10.5 us for K = 768 however few there are).  planes: the k ranges that the tile kernel would cut K into.
+bool few_weight_rows(int M, int rows, int K, int planes) {
+  const int total = K / 32, ranges = planes == 0 ? 1 : ceil_div(total, 24);
+  if (planes > 0 && (ranges < 2 || ranges > planes)) return false;
+  const int steps = ceil_div(total, ranges * 8);
+  if (steps > 8) return false;
+  const int chunks = ceil_div(M, steps <= 3 ? 128 : 64), slots = compute_units() / (ceil_div(total, steps * 8) * chunks);
+  return slots >= 1 && ceil_div(ceil_div(rows, 16), slots) <= (planes > 0 ? 3 : steps <= 3 ? 2 : 6);
+}
+
+// The 128 x 128 tiles with K cut into ranges, planes and reduce launch included (us; fitted to 153 drawn problems, within 7 %
+// for nine of ten): the weight from HBM, the slabs of a block, more than one block per CU, the planes' bytes.
+double pers_split_us(int M, int ncols, int K, const PersSplit& ps) {
+  const int per = ps.k_per_split / BK;
+  const int64_t blocks = (int64_t)ceil_div(M, 128) * ceil_div(ncols, 128) * ps.splits;
+  return 6.9 + (double)ncols * K * 2 * 0.27 / 6e6 + 0.78 * per + 0.18 * per * (ceil_div64(blocks, compute_units()) - 1) +
+         0.55e-6 * ps.splits * M * ncols * 4;
+}
+
 // w8: the weight is streamed as int8.  offset_or_scaled: a prompt's launch with a column offset or the scales of
-// a dequantised weight, neither of which the kernel with x in registers knows.
+// a dequantised weight, which only the tile kernels know.
 Route plan_route(int M, int N, int K, int ldy, forge_act act, bool qkv, bool norm_tail, bool w8,
                  bool offset_or_scaled, size_t part_bytes) {
-  Route r = {choose_variant(M, N, K, ldy, act, qkv), {}, {1, K}, {0, 0, 0}, false};
-  const int ncols = act == FORGE_ACT_SWIGLU ? 2 * N : N;
+  Route r = {choose_variant(M, N, K, ldy, act, qkv), {}, {1, K}, {0, 0, 0}, false, false};
+  const bool gated = act == FORGE_ACT_SWIGLU;
+  const int ncols = gated ? 2 * N : N;
   if (r.v == V_FAST_128) {
-    if (!offset_or_scaled) r.rows = plan_rows_prompt(M, ncols, K, 0);
-    if (r.rows.ranges > 0) return r;
+    // Waves that share the k slabs: everywhere against few weight rows (250 drawn problems 0.9 to 2.1 times as fast as
+    // x in registers, which took them before, 1.4 in the middle); instead of a split reduction where the estimates are
+    // clearly apart, they being less sure at long K (128 rows against 4096 x 4096 23.4 | 17.5, 200 against 6144 x 4096 stays).
+    const WavesPlan wp = offset_or_scaled ? WavesPlan{-1, 0.0} : plan_waves(M, N, K, gated);
+    if (wp.tile >= 0 && few_weight_rows(M, ncols, K, 0)) {
+      r.few_rows = true;
+      r.waves = wp.tile;
+      return r;
+    }
     const PersSplit ps = plan_pers_split(M, ncols, K);
-    if (ps.splits < 2 || part_bytes < (size_t)ps.splits * M * ncols * sizeof(float)) return r;
+    if (ps.splits < 2) return r;
+    r.few_rows = wp.tile >= 0 && few_weight_rows(M, ncols, K, ps.splits);
+    if (wp.tile >= 0 && (r.few_rows || wp.us < (K <= 4096 ? 0.85 : 0.65) * pers_split_us(M, ncols, K, ps))) r.waves = wp.tile;
+    else if (part_bytes < (size_t)ps.splits * M * ncols * sizeof(float)) return r;
     r.ps = ps;
     r.planes = true;
-    if (!offset_or_scaled) r.rows = plan_rows_prompt(M, ncols, K, ps.splits);
   } else if (M <= 64) {
     r.sk = plan_skinny(N, K, act, w8 ? 2 * BK : BK);
-    // (few rows of x: the kernel that keeps them in registers, where its plan takes the problem)
+    // outputs finished in the one launch: few rows of x in registers where that plan takes the problem; up to 4096 x 8192, the
+    // waves that share the k slabs (187 drawn problems 0.93 to 1.9 times as fast, 1.2 in the geometric mean; 24 rows
+    // against 14336 gated pairs x 4096 50.7 | 51.9, against 4096 x 14336 28.9 | 31), but not with short rows: a decode
+    // step of d_model 768 took 457 | 466 us at 8 sequences, 456 | 468 at 16, one of 2048 1406 | 1328 at 8, 2240 | 2083 at 48
     if (r.v == V_SKINNY_FAST && !norm_tail) {
+      if (!w8 && !gated && K >= 1024 && K <= 4096 && N <= 8192) r.waves = plan_waves(M, N, K, false).tile;
       r.rows = plan_rows(M, ncols, K, w8, 0, qkv);
-      if (r.rows.ranges > 0 || (r.sk.fused && !w8 && !qkv)) return r;      // outputs finished in the one launch
+      if (r.rows.ranges > 0 || (r.sk.fused && !w8 && !qkv)) return r;
     }
     r.planes = true;
     if (r.v == V_SKINNY_FAST) r.rows = plan_rows(M, ncols, K, w8, r.sk.splits, qkv);   // (the workspace holds sk.splits planes)
@@ -1326,6 +1364,7 @@ forge_status launch_act(const GemmParams& p, hipStream_t s) {
   } else {
   const Route r = plan_route(p.M, p.N, p.K, p.ldy, (forge_act)ACT, MODE == MODE_QKV, p.nt.y_norm != nullptr, p.w8 != nullptr,
                              p.col0 != 0 || (p.w8 == nullptr && p.wscale != nullptr), p.part != nullptr ? p.part_bytes : 0);
+  if (r.waves >= 0 && !p.sp.rope) return launch_waves(p, r.waves, ACT, MODE == MODE_QKV, s);
   if (r.rows.ranges > 0 && !r.planes) return launch_rows(p, r.rows, ACT, MODE == MODE_QKV, false, s);
   switch (v) {
     case V_FAST_256: return launch_pers<256, 256, 2, 4, ACT, MODE>(p, s);
@@ -1336,12 +1375,11 @@ forge_status launch_act(const GemmParams& p, hipStream_t s) {
         q.N = ncols;
         q.splits = r.ps.splits;
         q.k_per_split = r.ps.k_per_split;
-        const forge_status st = r.rows.ranges > 0 ? launch_rows(q, r.rows, FORGE_ACT_NONE, false, true, s)
-                                                  : launch_pers<128, 128, 2, 4, FORGE_ACT_NONE, MODE_SPLITK>(q, s);
+        const forge_status st = launch_pers<128, 128, 2, 4, FORGE_ACT_NONE, MODE_SPLITK>(q, s);
         if (st != FORGE_OK) return st;
         const int64_t threads = (int64_t)p.M * ceil_div(p.N, 4);
         splitk_reduce_kernel<ACT, MODE == MODE_QKV><<<(unsigned)ceil_div64(threads, 256), 256, 0, s>>>(
-            p, r.rows.ranges > 0 ? r.rows.ranges : r.ps.splits, ncols);
+            p, r.ps.splits, ncols);
         return launch_status();
       }
       // 8 waves of 64 x 32 (16 waves per CU) hide the L2 latency of the small tile better than 4
@@ -1468,7 +1506,7 @@ bool gemm_fuses_tail(int M, int N, forge_dtype dt) {
 const char* gemm_bf16_variant(int M, int N, int K, int ldy, forge_act act) {
   // the call launch_act makes for a plain output, with the workspace asked for
   const Route r = plan_route(M, N, K, ldy, act, false, false, false, false, SIZE_MAX);
-  if (r.rows.ranges > 0) return r.planes ? "gemm_bf16_rows+splitk" : "gemm_bf16_rows";
+  if (r.rows.ranges > 0 || r.few_rows) return r.planes ? "gemm_bf16_rows+splitk" : "gemm_bf16_rows";
   switch (r.v) {
     case V_FAST_256: return "gemm_bf16_pers<256,256,2,4>";
     case V_FAST_128:

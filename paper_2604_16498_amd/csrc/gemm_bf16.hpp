@@ -66,7 +66,14 @@ struct RowsPlan {
 // split, rotated head split), one range; otherwise of one that writes at most that many fp32 planes
 // [ranges, M, rows] for the reduce kernels (raw).
 RowsPlan plan_rows(int M, int rows, int K, bool w8, int max_ranges, bool qkv);
-RowsPlan plan_rows_prompt(int M, int rows, int K, int max_ranges);   // more than 64 rows, bf16 weights
 forge_status launch_rows(const GemmParams& p, const RowsPlan& pl, int act, bool qkv, bool raw, hipStream_t s);
+
+// ---- prompts of some hundred rows, small decode problems (gemm_bf16_waves.hip) ----------------------
+struct WavesPlan {
+  int tile;      // -1: the problem does not take this path
+  double us;     // estimated time
+};
+WavesPlan plan_waves(int M, int N, int K, bool gated);      // K % 64 == 0, bf16 weights, operands below 4 GB
+forge_status launch_waves(const GemmParams& p, int tile, int act, bool qkv, hipStream_t s);
 
 }  // namespace forge

@@ -1,5 +1,4 @@
-// bf16 / weight-only-int8 linear for at most 64 rows of x (a decode step), and for prompts of a few
-// hundred rows against small weights, in chunks of 64 or 128 rows.
+// bf16 / weight-only-int8 linear for at most 64 rows of x (a decode step).
 //
 // HBM-bound: the weight is streamed once and nothing else of its size moves.  What the kernel is
 // built around is that so few rows of x fit in REGISTERS: a block of 8 waves owns one k range of up
@@ -80,8 +79,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_bf16_rows_kernel(RowsParams r) {
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 15, lg = lane >> 4;
   const int N = p.N, K = p.K;
-  const int mz = blockIdx.z * (16 * MT);                 // this block's rows of x: [mz, mz + M)
-  const int M = min(16 * MT, p.M - mz);
+  const int M = p.M;                                     // at most 16 MT (launch_rows)
   const bool gated = FIN == FIN_OUT && r.act == FORGE_ACT_SWIGLU;
 
   // this wave's steps: [s0, s0 + ns) of the K / KE steps of a row (ns may be 0 in the last waves)
@@ -124,7 +122,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_bf16_rows_kernel(RowsParams r) {
     for (int i = 0; i < XL; ++i) {
       const int m = mt * 16 + (i * 64 + lane) / XCH, c = (i * 64 + lane) % XCH;
       // (rows past the end re-read the last one; skipped by a branch, they cost a wait per load)
-      xt[mt][i] = *reinterpret_cast<const u32x4*>(p.x + (int64_t)(mz + min(m, M - 1)) * K + sl * C::KE + c * 8);
+      xt[mt][i] = *reinterpret_cast<const u32x4*>(p.x + (int64_t)min(m, M - 1) * K + sl * C::KE + c * 8);
     }
 
   // weight row of the 4 consecutive rows that this lane finishes of a tile, and their output column n
@@ -243,7 +241,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_bf16_rows_kernel(RowsParams r) {
       if constexpr (RAW) {
         const int n = tile * TR + 4 * lg;
         if (m >= M || n >= r.rows) continue;
-        float* dst = p.part + ((int64_t)blockIdx.y * p.M + mz + m) * r.rows + n;
+        float* dst = p.part + ((int64_t)blockIdx.y * M + m) * r.rows + n;
         if ((r.rows & 3) == 0) *reinterpret_cast<floatx4*>(dst) = v;
         else
           for (int e = 0; e < 4 && n + e < r.rows; ++e) dst[e] = v[e];
@@ -291,10 +289,10 @@ __global__ __launch_bounds__(NW * 64) void gemm_bf16_rows_kernel(RowsParams r) {
         u32x2 pk;
         pk[0] = pack_bf2(v[0], v[1]);
         pk[1] = pack_bf2(v[2], v[3]);
-        *reinterpret_cast<u32x2*>(split_dst_bf16(p.sp, p.row0 + mz + m, n)) = pk;
+        *reinterpret_cast<u32x2*>(split_dst_bf16(p.sp, p.row0 + m, n)) = pk;
         continue;
       }
-      const int64_t out = (int64_t)(mz + m) * p.ldy + n;
+      const int64_t out = (int64_t)m * p.ldy + n;
       if (n + 4 <= N && (p.ldy & 3) == 0) {
         if (p.residual != nullptr) {
           const u32x2 rr = *reinterpret_cast<const u32x2*>(p.residual + out);
@@ -332,8 +330,7 @@ template <int MT, int STEPS, bool W8, int FIN>
 forge_status launch_fin(const RowsParams& r, int ranges, hipStream_t s) {
   // one block per CU, also where the registers would hold two: two blocks read x twice (6144 x 2048 at
   // 8 rows 10.7 us, at 9 rows and one block 9.5 us)
-  const int chunks = ceil_div(r.g.M, 16 * MT);
-  int per = ceil_div(r.tiles, max(1, compute_units() / (ranges * chunks)));      // tiles per block
+  int per = ceil_div(r.tiles, max(1, compute_units() / ranges));      // tiles per block
   if (FIN == FIN_ROPE) per = min(per, Rows<MT, STEPS, W8, FIN>::SLOTS);                // (their angles are computed once)
   auto kern = gemm_bf16_rows_kernel<MT, STEPS, W8, FIN>;
   // (more than half the LDS of a CU, whatever is needed: with two blocks resident some CUs get two and
@@ -341,16 +338,14 @@ forge_status launch_fin(const RowsParams& r, int ranges, hipStream_t s) {
   constexpr int smem = Rows<MT, STEPS, W8, FIN>::SMEM > 82 * 1024 ? Rows<MT, STEPS, W8, FIN>::SMEM : 82 * 1024;
   static std::atomic<uint64_t> lds_raised{0};   // per kernel instantiation
   if (raise_lds_limit(reinterpret_cast<const void*>(kern), smem, lds_raised) != FORGE_OK) return FORGE_ERR_HIP;
-  kern<<<dim3(ceil_div(r.tiles, per), ranges, chunks), NW * 64, smem, s>>>(r);
+  kern<<<dim3(ceil_div(r.tiles, per), ranges), NW * 64, smem, s>>>(r);
   return launch_status();
 }
 
 template <int MT, int STEPS, bool W8>
 forge_status launch_steps(const RowsParams& r, int fin, int ranges, hipStream_t s) {
   if (fin == FIN_RAW) return launch_fin<MT, STEPS, W8, FIN_RAW>(r, ranges, s);
-  if constexpr (MT <= 4) {
-    if (fin == FIN_ROPE) return launch_fin<MT, STEPS, W8, FIN_ROPE>(r, ranges, s);
-  }
+  if (fin == FIN_ROPE) return launch_fin<MT, STEPS, W8, FIN_ROPE>(r, ranges, s);
   return launch_fin<MT, STEPS, W8, FIN_OUT>(r, ranges, s);
 }
 
@@ -359,7 +354,7 @@ forge_status launch_mt(const RowsParams& r, int fin, const RowsPlan& pl, hipStre
   switch (pl.steps) {
 #define FORGE_ROWS_CASE(STEPS)                                                     \
     case STEPS:                                                                    \
-      if constexpr (STEPS * (W8 ? 2 : 1) <= (MT > 4 ? 3 : MT > 2 ? 8 : 16)) return launch_steps<MT, STEPS, W8>(r, fin, pl.ranges, s); \
+      if constexpr (STEPS * (W8 ? 2 : 1) <= (MT > 2 ? 8 : 16)) return launch_steps<MT, STEPS, W8>(r, fin, pl.ranges, s); \
       else break
     FORGE_ROWS_CASE(1);
     FORGE_ROWS_CASE(2);
@@ -460,25 +455,6 @@ RowsPlan plan_rows(int M, int rows, int K, bool w8, int max_ranges, bool qkv) {
   return with_steps(total, ranges);
 }
 
-// A prompt of a few hundred rows against a weight with few 128 x 128 tiles (each of which walks all of K
-// alone: 10.5 us for K = 768 however few there are) in chunks of 128 rows of x, 64 where x needs more
-// than 3 steps' registers.  The weight is read once per chunk (from cache after the first), so only as long
-// as a block has few tiles to walk: 2 of 128 rows (us, this kernel | the tile kernel: 128 rows against
-// 2304 x 768 6.9 | 10.9, 384 rows 9.2 | 10.8, 512 rows with 3 tiles 11.2 | 10.8), 3 where fp32 planes
-// follow (768 x 3072 at 128 rows 9.2 | 12.9, at 512 rows 15.4 | 18.2), 6 of 64 rows (6144 x 2048 at 128 rows
-// 14.5 | 21.7, at 256 rows 21.9 | 26.6, at 512 rows with 12 tiles 37.2 | 34.2; 2048 x 2048 at 256 rows 10.9 | 19.0).
-RowsPlan plan_rows_prompt(int M, int rows, int K, int max_ranges) {
-  const RowsPlan none = {0, 0, 0};
-  if (M <= 64 || K % BK != 0) return none;
-  const int total = K / 32, ranges = max_ranges == 0 ? 1 : ceil_div(total, 3 * NW);
-  if (max_ranges > 0 && (ranges < 2 || ranges > max_ranges)) return none;
-  const RowsPlan pl = with_steps(total, ranges);
-  if (pl.ranges == 0 || pl.steps > 8) return none;
-  const int chunks = ceil_div(M, pl.steps <= 3 ? 128 : 64), slots = compute_units() / (pl.ranges * chunks);
-  const int most = max_ranges > 0 ? 3 : pl.steps <= 3 ? 2 : 6;
-  return slots >= 1 && ceil_div(ceil_div(rows, TR), slots) <= most ? pl : none;
-}
-
 forge_status launch_rows(const GemmParams& p, const RowsPlan& pl, int act, bool qkv, bool raw, hipStream_t s) {
   RowsParams r;
   r.g = p;
@@ -491,7 +467,6 @@ forge_status launch_rows(const GemmParams& p, const RowsPlan& pl, int act, bool 
   r.spw = pl.spw;
   if (p.w8 != nullptr)
     return p.M > 32 ? launch_mt<4, true>(r, fin, pl, s) : p.M > 16 ? launch_mt<2, true>(r, fin, pl, s) : launch_mt<1, true>(r, fin, pl, s);
-  if (p.M > MAX_ROWS && pl.steps <= 3) return launch_mt<8, false>(r, fin, pl, s);
   return p.M > 32 ? launch_mt<4, false>(r, fin, pl, s) : p.M > 16 ? launch_mt<2, false>(r, fin, pl, s) : launch_mt<1, false>(r, fin, pl, s);
 }
 

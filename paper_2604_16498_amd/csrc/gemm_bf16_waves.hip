@@ -1,0 +1,218 @@
+// bf16 linear for prompts of some tens to some hundred rows, and for decode steps against small weights: the
+// waves of a block share the k slabs.
+//
+// Such a problem is all latency: launch, first loads, a few products, the store.  A block of 8 waves owns
+// 16 RB rows of x and 16 CB weight rows, small enough that the tiles cover the chip; the waves take the 64-element
+// k slabs in turn (wave w: slabs w, w + 8, ...), each loads its slabs in whole 128-byte row pieces, DEPTH of
+// them in flight in registers, turns them into the operand layout through an LDS patch of its own and
+// multiplies with v_mfma_f32_16x16x32_bf16, without a block barrier; the 8 partial tiles are added
+// through LDS in wave order and finished (bias, activation, residual, head split) in the one launch.
+// The weight is the A operand, so that a lane holds 4 consecutive output columns of one row.
+//
+// us, cold weights, the kernel that took the problem before (x in registers, 128 x 128 tiles, slab-wise, with a reduce launch
+// where it needed one) | this one: 128 rows against 768 x 768 7.0 | 3.9, 2304 x 768 7.4 | 6.2, 3072 x 768 8.0 | 6.4, 768 x 3072
+// 10.3 | 6.3, 256 x 2048 x 2048 11.6 | 9.5, 128 x 2048 x 8192 23.1 | 19.7, 24 x 2048 x 2048 6.6 | 4.9, 64 x 4096 x 4096
+// 17.4 | 13.6.  plan_waves says where.
+#include <math.h>
+#include "gemm_bf16.hpp"
+
+namespace forge {
+namespace {
+
+constexpr int NW = 8;                                // waves per block
+constexpr int LDB = BK * 2 + 16;                     // bytes of a patch row: 64 bf16 and padding (conflict-free 128-bit accesses)
+
+struct WavesParams {
+  GemmParams g;                                      // g.N: output columns
+  int act;
+  int qkv;                                           // head split
+};
+
+template <int RB, int CB, bool GATED>
+__global__ __launch_bounds__(NW * 64, RB * CB <= 4 ? 4 : 2) void gemm_bf16_waves_kernel(WavesParams r) {
+  const GemmParams& p = r.g;
+  constexpr int FM = 16 * RB, WR = 16 * CB;          // rows of x, weight rows
+  constexpr int OUT = GATED ? WR / 2 : WR;           // output columns
+  constexpr int DEPTH = 2;                           // slabs in flight per wave
+  constexpr int PATCH = (FM + WR) * LDB;             // bytes
+  constexpr int LDR = WR + 4;                        // floats of a row of a partial tile
+  static_assert(FM * LDR * 4 <= PATCH, "the partial tiles fit where the patches lie");
+  extern __shared__ __attribute__((aligned(16))) char smem[];   // [NW * PATCH]
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int M = p.M, N = p.N, K = p.K;
+  const int m0 = blockIdx.y * FM, n0 = blockIdx.x * OUT;
+  char* const ax = smem + wave * PATCH;
+  char* const bx = ax + FM * LDB;
+
+  // loads: 8 lanes per row piece, unconditional from clamped addresses (rows past the end re-read the last one,
+  // their outputs are dropped; a slab past the end is not multiplied)
+  const int lrow = lane >> 3, lcol = (lane & 7) * 16;
+  uint32_t xsrc[FM / 8], wsrc[WR / 8];               // byte offsets (operands below 4 GB: choose_variant)
+#pragma unroll
+  for (int i = 0; i < FM / 8; ++i) xsrc[i] = (uint32_t)min(m0 + lrow + 8 * i, M - 1) * (uint32_t)K * 2 + lcol;
+#pragma unroll
+  for (int i = 0; i < WR / 8; ++i) {
+    const int rr = lrow + 8 * i;
+    const int row = GATED ? min(n0 + rr % OUT, N - 1) + (rr >= OUT ? N : 0) : min(n0 + rr, N - 1);
+    wsrc[i] = (uint32_t)row * (uint32_t)K * 2 + lcol;
+  }
+  const int slabs = K / BK;
+  u32x4 va[DEPTH][FM / 8], vb[DEPTH][WR / 8];
+  auto load = [&](int slab, int slot) {
+    const uint32_t at = (uint32_t)min(slab, slabs - 1) * (BK * 2);
+#pragma unroll
+    for (int i = 0; i < WR / 8; ++i) vb[slot][i] = *reinterpret_cast<const u32x4*>((const char*)p.w + (wsrc[i] + at));
+#pragma unroll
+    for (int i = 0; i < FM / 8; ++i) va[slot][i] = *reinterpret_cast<const u32x4*>((const char*)p.x + (xsrc[i] + at));
+  };
+  // bias and residual of the outputs that this thread finishes, fetched long before they are needed
+  constexpr int ITEMS = (FM * OUT / 4 + NW * 64 - 1) / (NW * 64);
+  const bool vec = (N & 3) == 0 && (p.ldy & 3) == 0;
+  u32x2 bi[ITEMS], ub[ITEMS], rv[ITEMS];
+#pragma unroll
+  for (int it = 0; it < ITEMS; ++it) {
+    const int at = tid + it * NW * 64, m = m0 + at / (OUT / 4), n = n0 + at % (OUT / 4) * 4;
+    bi[it] = ub[it] = rv[it] = u32x2{0, 0};
+    if (!vec || at >= FM * OUT / 4 || m >= M || n >= N) continue;
+    if (p.bias != nullptr) {
+      bi[it] = *reinterpret_cast<const u32x2*>(p.bias + n);
+      if (GATED) ub[it] = *reinterpret_cast<const u32x2*>(p.bias + N + n);
+    }
+    if (p.residual != nullptr) rv[it] = *reinterpret_cast<const u32x2*>(p.residual + (int64_t)m * p.ldy + n);
+  }
+
+  floatx4 acc[RB][CB];
+#pragma unroll
+  for (int i = 0; i < RB; ++i)
+#pragma unroll
+    for (int c = 0; c < CB; ++c) acc[i][c] = floatx4{0.f, 0.f, 0.f, 0.f};
+
+  const int fr = lane & 15, fg = lane >> 4;
+#pragma unroll
+  for (int d = 0; d < DEPTH; ++d) load(wave + d * NW, d);
+  for (int s0 = wave; s0 < slabs; s0 += DEPTH * NW) {
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d) {
+      const int slab = s0 + d * NW;
+      if (slab < slabs) {                            // wave-uniform
+        wave_lds_sync();                             // the previous slab has been read
+#pragma unroll
+        for (int i = 0; i < FM / 8; ++i) *reinterpret_cast<u32x4*>(ax + (lrow + 8 * i) * LDB + lcol) = va[d][i];
+#pragma unroll
+        for (int i = 0; i < WR / 8; ++i) *reinterpret_cast<u32x4*>(bx + (lrow + 8 * i) * LDB + lcol) = vb[d][i];
+        wave_lds_sync();
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          bf16x8 xf[RB], wf[CB];
+#pragma unroll
+          for (int i = 0; i < RB; ++i) xf[i] = *reinterpret_cast<const bf16x8*>(ax + (16 * i + fr) * LDB + (4 * k + fg) * 16);
+#pragma unroll
+          for (int c = 0; c < CB; ++c) wf[c] = *reinterpret_cast<const bf16x8*>(bx + (16 * c + fr) * LDB + (4 * k + fg) * 16);
+#pragma unroll
+          for (int i = 0; i < RB; ++i)
+#pragma unroll
+            for (int c = 0; c < CB; ++c) acc[i][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[c], xf[i], acc[i][c], 0, 0, 0);
+        }
+      }
+      load(slab + DEPTH * NW, d);                    // into the registers just consumed
+    }
+  }
+
+  // ---- the 8 partial tiles, added in wave order; accumulator: row lane % 16, columns 4 (lane / 16) ... + 3 ------
+  wave_lds_sync();
+#pragma unroll
+  for (int i = 0; i < RB; ++i)
+#pragma unroll
+    for (int c = 0; c < CB; ++c) *reinterpret_cast<floatx4*>(ax + ((16 * i + fr) * LDR + 16 * c + 4 * fg) * 4) = acc[i][c];
+  __syncthreads();
+  auto unpack = [](u32x2 t) { return floatx4{bf_lo(t[0]), bf_hi(t[0]), bf_lo(t[1]), bf_hi(t[1])}; };
+#pragma unroll
+  for (int it = 0; it < ITEMS; ++it) {
+    const int at = tid + it * NW * 64;
+    const int mr = at / (OUT / 4), nc = at % (OUT / 4) * 4, m = m0 + mr, n = n0 + nc;
+    if (at >= FM * OUT / 4 || m >= M || n >= N) continue;
+    floatx4 v = {0.f, 0.f, 0.f, 0.f}, u = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int z = 0; z < NW; ++z) {
+      const char* src = smem + z * PATCH + (mr * LDR + nc) * 4;
+      v += *reinterpret_cast<const floatx4*>(src);
+      if (GATED) u += *reinterpret_cast<const floatx4*>(src + OUT * 4);
+    }
+    if (vec) {
+      v += unpack(bi[it]);
+      if (GATED) u += unpack(ub[it]);
+    } else if (p.bias != nullptr) {
+      for (int e = 0; e < 4 && n + e < N; ++e) {
+        v[e] += (float)p.bias[n + e];
+        if (GATED) u[e] += (float)p.bias[N + n + e];
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if (GATED) { v[e] = silu_f(v[e]) * u[e]; continue; }
+      switch (r.act) {
+        case FORGE_ACT_GELU_TANH: v[e] = gelu_tanh_f(v[e]); break;
+        case FORGE_ACT_RELU: v[e] = fmaxf(v[e], 0.0f); break;
+        case FORGE_ACT_SILU: v[e] = silu_f(v[e]); break;
+        case FORGE_ACT_GELU_ERF: v[e] = gelu_erf_f(v[e]); break;
+        default: break;
+      }
+    }
+    bf16* dst = r.qkv ? split_dst_bf16(p.sp, p.row0 + m, n) : p.y + (int64_t)m * p.ldy + n;   // 4 columns stay inside a head
+    if (vec) {
+      if (p.residual != nullptr) v += unpack(rv[it]);
+      *reinterpret_cast<u32x2*>(dst) = u32x2{pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3])};
+    } else {
+      const bf16* res = p.residual != nullptr ? p.residual + (int64_t)m * p.ldy + n : nullptr;
+      for (int e = 0; e < 4 && n + e < N; ++e) dst[e] = (bf16)(v[e] + (res != nullptr ? (float)res[e] : 0.f));
+    }
+  }
+}
+
+template <int RB, int CB, bool GATED>
+forge_status launch_tile(const WavesParams& r, hipStream_t s) {
+  constexpr int smem = NW * 16 * (RB + CB) * LDB;
+  auto kern = gemm_bf16_waves_kernel<RB, CB, GATED>;
+  static std::atomic<uint64_t> lds_raised{0};        // per kernel instantiation
+  if (raise_lds_limit(reinterpret_cast<const void*>(kern), smem, lds_raised) != FORGE_OK) return FORGE_ERR_HIP;
+  kern<<<dim3(ceil_div(r.g.N, GATED ? 8 * CB : 16 * CB), ceil_div(r.g.M, 16 * RB)), NW * 64, smem, s>>>(r);
+  return launch_status();
+}
+
+}  // namespace
+
+// Tiles (row blocks, column blocks) and their times in us: a start, a round of tiles over the CUs, and what 1024 elements of
+// K add to a round; fitted to 800 drawn problems (within 15 % for nine of ten).
+namespace {
+struct WavesTile { int rb, cb; double start, round, per_k; };
+constexpr WavesTile kTiles[] = {{1, 1, 2.7, 0.33, 0.73}, {1, 2, 2.4, 0.75, 1.04}, {2, 2, 2.4, 1.01, 1.42}, {4, 2, 0.9, 2.97, 2.37}, {4, 4, -0.2, 4.9, 3.24}};
+}  // namespace
+
+WavesPlan plan_waves(int M, int N, int K, bool gated) {
+  const int rows = gated ? 2 * N : N;
+  WavesPlan best = {-1, 0.0};
+  for (int i = gated ? 1 : 0; i < (int)(sizeof(kTiles) / sizeof(kTiles[0])); ++i) {
+    const WavesTile& t = kTiles[i];
+    const int64_t rounds = ceil_div64((int64_t)ceil_div(M, 16 * t.rb) * ceil_div(rows, 16 * t.cb), compute_units());
+    const double us = t.start + rounds * (t.round + t.per_k * K / 1024);
+    if (best.tile < 0 || us < best.us) best = WavesPlan{i, us};
+  }
+  best.us += (double)rows * K * 2 * 0.62 / 6e6;      // the weight from HBM
+  return best;
+}
+
+forge_status launch_waves(const GemmParams& p, int tile, int act, bool qkv, hipStream_t s) {
+  const WavesParams r = {p, act, qkv ? 1 : 0};
+  const bool gated = act == FORGE_ACT_SWIGLU;
+  switch (tile) {
+    case 0: return gated ? FORGE_ERR_UNSUPPORTED : launch_tile<1, 1, false>(r, s);
+    case 1: return gated ? launch_tile<1, 2, true>(r, s) : launch_tile<1, 2, false>(r, s);
+    case 2: return gated ? launch_tile<2, 2, true>(r, s) : launch_tile<2, 2, false>(r, s);
+    case 3: return gated ? launch_tile<4, 2, true>(r, s) : launch_tile<4, 2, false>(r, s);
+    case 4: return gated ? launch_tile<4, 4, true>(r, s) : launch_tile<4, 4, false>(r, s);
+    default: return FORGE_ERR_UNSUPPORTED;
+  }
+}
+
+}  // namespace forge
