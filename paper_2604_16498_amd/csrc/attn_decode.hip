@@ -26,14 +26,14 @@
 // Wave and block partials are merged in a fixed order; with more than one split the block writes
 // (m, l, o) per query head to the workspace and a second kernel merges the splits in split order
 // -- no atomics, so the result is bitwise reproducible.
+#include <math.h>
 #include "common.hpp"
 
 namespace forge {
 namespace {
 
-constexpr int NWAVES = 4;                 // waves per block
 constexpr int TILE = 16;                  // cache rows per MFMA tile
-constexpr int GRAIN = 2 * NWAVES * TILE;  // a split is a multiple of this many rows (two tiles per wave)
+constexpr int GRAIN = 128;                // a split is a multiple of this many rows (two tiles per wave of four)
 constexpr int MAX_SPLITS = 64;            // the combine holds one split per lane
 
 struct DecParams {
@@ -56,8 +56,8 @@ __device__ inline float xor32_max(float x) { return fmaxf(x, __shfl_xor(x, 32, 6
 
 // G: query heads per KV head, 1 ... 8 (the MFMA's 16 head columns hold them zero-padded; the
 // P . V accumulators grow with G, so the larger groups run at two blocks per SIMD instead of three)
-template <int DH, int G>
-__global__ __launch_bounds__(NWAVES * 64, G > 4 ? 2 : 3) void attn_decode_kernel(DecParams p) {
+template <int DH, int G, int NWAVES>
+__global__ __launch_bounds__(NWAVES * 64, G > 4 || NWAVES == 8 ? 2 : 3) void attn_decode_kernel(DecParams p) {
   constexpr int NJ = DH / 32;          // MFMAs (and K loads) per tile
   constexpr int LPR = DH / 8;          // lanes per V row
   constexpr int KPS = 64 / LPR;        // rows per wave-wide V load
@@ -277,28 +277,34 @@ __global__ __launch_bounds__(DH) void attn_decode_combine(const float* __restric
   out[((int64_t)b * q_heads + h) * DH + d] = (bf16)(o / ltot);
 }
 
-// Number of row ranges: about two blocks per compute unit, but no range shorter than
-// MIN_SPLIT_ROWS: a block streams that many rows in less time than the second launch (the merge of
-// the ranges) costs, so a cache shorter than twice that is walked by one block per (head, sequence)
-// however few of those there are.
-constexpr int MIN_SPLIT_ROWS = 2 * GRAIN;
+// Number of row ranges.  A block streams about 45 B/ns of cache however many waves it has, the chip 5900 (counted
+// against 0.7 of the longest cache: the lengths of a batch differ), and the merge of the ranges is a launch of
+// 4.2 us: the count with the least time, at most one block per CU (more only queue) and at least 128 rows each.
+// us, cold cache, merge included, about two blocks per CU and ranges of 256 rows at least as before | this rule: 24
+// sequences up to 1501 rows of 8 heads 30.2 (3) | 23.8 (1), 31 up to 2683 52.5 | 44.3 (1), 11 x 1612 rows of 16 heads 36.2 | 28.6 (1),
+// 5 up to 8192 rows of 8 heads 36.3 (13) | 27.1 (6), 1 x 1594 of 16 heads 10.1 (6) | 9.3 (13).
 struct SplitPlan { int splits, rows_per_split; };
 // the most ranges a batch is ever cut into, whatever the cache length
 inline int max_splits(int batch, int kv_heads) {
-  const int64_t pairs = (int64_t)batch * kv_heads;
-  const int64_t for_two_per_cu = ceil_div64(2 * (int64_t)compute_units(), pairs);
-  return for_two_per_cu < MAX_SPLITS ? (int)for_two_per_cu : MAX_SPLITS;
+  return (int)max((int64_t)1, min((int64_t)MAX_SPLITS, compute_units() / ((int64_t)batch * kv_heads)));
 }
-inline SplitPlan plan_splits(int batch, int kv_heads, int kv_len) {
-  const int want = max(1, min(max_splits(batch, kv_heads), kv_len / MIN_SPLIT_ROWS));
-  const int rows = ceil_div(ceil_div(kv_len, want), GRAIN) * GRAIN;
-  return SplitPlan{ceil_div(kv_len, rows), rows};   // rows >= kv_len / want, so splits <= want
+inline SplitPlan plan_splits(int batch, int kv_heads, int kv_len, int head_dim) {
+  const double row_bytes = head_dim * 4.0, all_us = (double)batch * kv_heads * kv_len * row_bytes * 0.7 / 5.9e6;
+  SplitPlan best = {1, ceil_div(kv_len, GRAIN) * GRAIN};
+  double least = fmax(kv_len * row_bytes / 45e3, all_us);
+  const int most = min(max_splits(batch, kv_heads), kv_len / GRAIN);
+  for (int want = 2; want <= most; ++want) {
+    const int rows = ceil_div(ceil_div(kv_len, want), GRAIN) * GRAIN;
+    const double us = fmax(rows * row_bytes / 45e3, all_us) + 4.2;
+    if (us < least) { least = us; best = SplitPlan{ceil_div(kv_len, rows), rows}; }   // rows >= kv_len / want, so splits <= want
+  }
+  return best;
 }
 // Upper bound of plan_splits(.., len).splits over every len <= kv_len: the number of ranges is
 // not monotone in the length (the range size is rounded up to GRAIN), the scratch size must be,
 // because a generation loop sizes its scratch once, for the capacity of its cache.
 inline int splits_bound(int batch, int kv_heads, int kv_len) {
-  return max(1, min(max_splits(batch, kv_heads), kv_len / MIN_SPLIT_ROWS));
+  return max(1, min(max_splits(batch, kv_heads), kv_len / GRAIN));
 }
 
 // Query heads per block for `group` heads sharing one cache head: the whole group up to 8, else
@@ -321,7 +327,7 @@ inline int block_heads(int q_heads, int kv_heads) {
 template <int DH, int G>
 forge_status launch_dg(const AttnArgs& a, hipStream_t s) {
   const int yheads = a.q_heads / G;
-  const SplitPlan pl = plan_splits(a.batch, yheads, a.kv_len);
+  const SplitPlan pl = plan_splits(a.batch, yheads, a.kv_len, DH);
   DecParams p;
   p.q = (const bf16*)a.q;
   p.k = (const bf16*)a.k;
@@ -348,7 +354,14 @@ forge_status launch_dg(const AttnArgs& a, hipStream_t s) {
   const int64_t blocks = (int64_t)p.splits * yheads * a.batch;
   p.heads_first = (p.splits == 2 || p.splits == 4) && blocks % compute_units() != 0;
   const dim3 grid = p.heads_first ? dim3(yheads, a.batch, p.splits) : dim3(p.splits, yheads, a.batch);
-  attn_decode_kernel<DH, G><<<grid, NWAVES * 64, 0, s>>>(p);
+  // 8 waves where 4 have not enough bytes in flight: short rows, one block per CU at most, a cache of some length (us, 4 | 8:
+  // 8 sequences up to 641 rows of 12 heads of 64 9.0 | 7.2, 4 x 348 6.5 | 5.8, but 25 x 743 15.0 | 16.9, 2 x 113 4.2 | 4.4)
+  bool eight = false;
+  if constexpr (DH == 64 && G == 1) {
+    eight = p.splits == 1 && blocks <= compute_units() && a.kv_len >= 256;
+    if (eight) attn_decode_kernel<DH, G, 8><<<grid, 8 * 64, 0, s>>>(p);
+  }
+  if (!eight) attn_decode_kernel<DH, G, 4><<<grid, 4 * 64, 0, s>>>(p);
   if (p.splits == 1) return launch_status();
   if (hipGetLastError() != hipSuccess) return FORGE_ERR_HIP;
   attn_decode_combine<DH><<<dim3(a.q_heads, a.batch), DH, 0, s>>>(p.part, (bf16*)a.out, a.q_heads,
@@ -407,7 +420,7 @@ forge_status attn_decode_static_scratch(void** ptr) {
 
 forge_status launch_attn_decode_bf16(const AttnArgs& a, hipStream_t s) {
   // what THIS launch writes (at most the bound the size query reports for any cache >= kv_len)
-  const int splits = plan_splits(a.batch, block_heads(a.q_heads, a.kv_heads), a.kv_len).splits;
+  const int splits = plan_splits(a.batch, block_heads(a.q_heads, a.kv_heads), a.kv_len, a.head_dim).splits;
   const size_t need = splits == 1 ? 0 : (size_t)a.batch * a.q_heads * splits * (a.head_dim + 2) * sizeof(float);
   if (need > 0 && (a.workspace == nullptr || a.workspace_bytes < need)) return FORGE_ERR_WORKSPACE;
   if (a.head_dim == 64) return launch_d<64>(a, s);
