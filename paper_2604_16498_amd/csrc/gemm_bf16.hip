@@ -1174,8 +1174,8 @@ inline Variant choose_variant(int M, int N, int K, int ldy, forge_act act, bool 
   if (M <= 64) return k_ok ? V_SKINNY_FAST : V_SKINNY_GEN;
   const bool rows_ok = qkv ? N % 8 == 0 : (ldy % 8 == 0 && (N % 8 == 0 || act != FORGE_ACT_SWIGLU));
   const bool fast = k_ok && rows_ok && small_ok;
-  // the 256-row tile multiplies faster (half the operand traffic per flop) but fills a CU on its
-  // own: take it when its tiles come to whole rounds over the CUs, or to many rounds
+  // the class of the large tile: its tiles come to whole rounds over the CUs, or to many rounds (the fast kernel's
+  // tile is then picked by plan_tile, which starts from this)
   const int64_t big = (int64_t)ceil_div(M, 256) * ceil_div(N, act == FORGE_ACT_SWIGLU ? 128 : 256);
   const int64_t cus = compute_units();
   const int64_t rounds = (big + cus - 1) / cus;
@@ -1242,6 +1242,36 @@ inline SkinnyPlan plan_skinny(int N, int K, forge_act act, int bk = BK) {
   return sp;
 }
 
+// Tiles of the persistent kernel.  A block multiplies faster the larger its tile is, but a tile count just over
+// whole rounds of the chip leaves the last round nearly empty, and prompts come in any length; so the tile is picked by an
+// estimate (us) of its rounds: each pays a start and its slabs, a slab more on a full chip (power limit).  Fitted to 224
+// problems drawn over the lengths of the 768-, 2048- and 4096-wide models' projections, within 6 % for half of them, 15 %
+// for nine of ten (128), 9 to 10 % (the others).  192 x 256 exists for the lengths where 256 rows overshoot.  us, the earlier
+// rule (256 for nearly whole rounds, 128 otherwise) | this one: 2600 rows against 4096 x 14336 416 | 289, 6000 against
+// 2048 x 8192 234 | 178, 1299 against 6144 x 2048 55 | 43, 346 against 14336 gated pairs x 4096 128 | 100, 169 against
+// 50264 x 768 31 | 26, 2100 against 4096 x 4096 106 | 77.
+enum Tile { T_128 = 0, T_192 = 1, T_256 = 2 };       // 128 x 128 (two blocks per CU), 192 x 256, 256 x 256
+struct TileCost { int bm, bn, per_cu; double round, slab, full; };
+constexpr TileCost kTileCosts[] = {{128, 128, 2, 3.9, 0.51, 0.55}, {192, 256, 1, 11.2, 0.81, 0.41}, {256, 256, 1, 14.2, 1.0, 0.51}};
+double tile_us(int tile, int M, int ncols, int K) {
+  const TileCost& t = kTileCosts[tile];
+  const int64_t tiles = (int64_t)ceil_div(M, t.bm) * ceil_div(ncols, t.bn), slots = (int64_t)compute_units() * t.per_cu;
+  const double slabs = (double)K / BK, rounds = (double)ceil_div64(tiles, slots);
+  return rounds * (t.round + slabs * t.slab) + slabs * t.full * tiles / slots;
+}
+// The other tiles have to be estimated 5 % faster than the class's own; from 256 down to 128 the estimate was up to 15 % too
+// good (its operand traffic near many full rounds): 1147 rows against 50264 x 768 128 | 139.
+Tile plan_tile(int M, int ncols, int K, Tile own) {
+  const double us = tile_us(own, M, ncols, K);
+  Tile best = own;
+  double least = 0.95 * us;
+  for (int i = T_128; i <= T_256; ++i) {
+    const double e = tile_us(i, M, ncols, K) * (own == T_256 && i == T_128 ? 1.15 : 1.0);
+    if (i != own && e < least) { best = (Tile)i; least = e; }
+  }
+  return best;
+}
+
 // The whole dispatch of a problem that does not rotate in its epilogue: the launcher follows it and the variant
 // query names its class.
 struct Route {
@@ -1251,6 +1281,7 @@ struct Route {
   RowsPlan rows;      // ranges > 0: the kernel with x in registers takes it
   bool planes;        // fp32 planes and a reduce launch
   bool few_rows;      // more than 64 rows: see few_weight_rows
+  Tile tile = T_128;  // the persistent kernel's, where it takes the problem unsplit
   int waves = -1;     // tile of the kernel whose waves share the k slabs, which then takes the problem
 };
 
@@ -1281,6 +1312,7 @@ Route plan_route(int M, int N, int K, int ldy, forge_act act, bool qkv, bool nor
   Route r = {choose_variant(M, N, K, ldy, act, qkv), {}, {1, K}, {0, 0, 0}, false, false};
   const bool gated = act == FORGE_ACT_SWIGLU;
   const int ncols = gated ? 2 * N : N;
+  if (r.v == V_FAST_128 || r.v == V_FAST_256) r.tile = plan_tile(M, ncols, K, r.v == V_FAST_256 ? T_256 : T_128);
   if (r.v == V_FAST_128) {
     // Waves that share the k slabs: everywhere against few weight rows (250 drawn problems 0.9 to 2.1 times as fast as
     // x in registers, which took them before, 1.4 in the middle); instead of a split reduction where the estimates are
@@ -1296,6 +1328,13 @@ Route plan_route(int M, int N, int K, int ldy, forge_act act, bool qkv, bool nor
     r.few_rows = wp.tile >= 0 && few_weight_rows(M, ncols, K, ps.splits);
     if (wp.tile >= 0 && (r.few_rows || wp.us < (K <= 4096 ? 0.85 : 0.65) * pers_split_us(M, ncols, K, ps))) r.waves = wp.tile;
     else if (part_bytes < (size_t)ps.splits * M * ncols * sizeof(float)) return r;
+    // whole reductions where the planes and the second launch cost more than they give (1195 rows against 2048 x 2048
+    // 36 | 26, 416 against 8192 x 2048 38 | 27, 4151 against 768 x 3072 43 | 37)
+    const double whole_us = tile_us(r.tile, M, ncols, K) + (double)ncols * K * 2 * 0.27 / 6e6;     // the weight from HBM
+    if (!r.few_rows && whole_us < (r.waves >= 0 ? 0.85 * wp.us : 0.95 * pers_split_us(M, ncols, K, ps))) {
+      r.waves = -1;
+      return r;
+    }
     r.ps = ps;
     r.planes = true;
   } else if (M <= 64) {
@@ -1340,7 +1379,8 @@ forge_status launch_act(const GemmParams& p, hipStream_t s) {
       while (r != 0) { const int t = g % r; g = r; r = t; }          // gcd(tm, cus)
       const int64_t cols_per_round = (int64_t)(cus / g) * 256;
       const int c = (int)(p.N / cols_per_round * cols_per_round);
-      if (c >= 256 && c < p.N && 2 * (int64_t)c >= p.N) {
+      const double cut_us = c > 0 ? tile_us(T_256, p.M, c, p.K) + tile_us(T_128, p.M, p.N - c, p.K) : 0.0;
+      if (c >= 256 && c < p.N && 2 * (int64_t)c >= p.N && cut_us < tile_us(plan_tile(p.M, p.N, p.K, T_128), p.M, p.N, p.K)) {
         GemmParams a = p, b = p;
         a.N = c;
         b.N = p.N - c;
@@ -1358,16 +1398,19 @@ forge_status launch_act(const GemmParams& p, hipStream_t s) {
   if constexpr (MODE == MODE_QKV_ROPE) {
     // only the persistent kernels rotate in their epilogue; gemm_qkv_fuses_rope() has vouched for
     // the fast path, and the 128-tile takes the wave layout with two accumulators per wave
-    if (v == V_FAST_256) return launch_pers<256, 256, 2, 4, ACT, MODE>(p, s);
-    if (v == V_FAST_128) return launch_pers<128, 128, 2, 2, ACT, MODE>(p, s);
-    return FORGE_ERR_UNSUPPORTED;
+    if (v != V_FAST_256 && v != V_FAST_128) return FORGE_ERR_UNSUPPORTED;
+    switch (plan_tile(p.M, p.N, p.K, v == V_FAST_256 ? T_256 : T_128)) {
+      case T_256: return launch_pers<256, 256, 2, 4, ACT, MODE>(p, s);
+      case T_192: return launch_pers<192, 256, 2, 4, ACT, MODE>(p, s);
+      default: return launch_pers<128, 128, 2, 2, ACT, MODE>(p, s);
+    }
   } else {
   const Route r = plan_route(p.M, p.N, p.K, p.ldy, (forge_act)ACT, MODE == MODE_QKV, p.nt.y_norm != nullptr, p.w8 != nullptr,
                              p.col0 != 0 || (p.w8 == nullptr && p.wscale != nullptr), p.part != nullptr ? p.part_bytes : 0);
   if (r.waves >= 0 && !p.sp.rope) return launch_waves(p, r.waves, ACT, MODE == MODE_QKV, s);
   if (r.rows.ranges > 0 && !r.planes) return launch_rows(p, r.rows, ACT, MODE == MODE_QKV, false, s);
   switch (v) {
-    case V_FAST_256: return launch_pers<256, 256, 2, 4, ACT, MODE>(p, s);
+    case V_FAST_256:
     case V_FAST_128: {
       if (r.planes) {
         const int ncols = ACT == FORGE_ACT_SWIGLU ? 2 * p.N : p.N;
@@ -1382,6 +1425,8 @@ forge_status launch_act(const GemmParams& p, hipStream_t s) {
             p, r.ps.splits, ncols);
         return launch_status();
       }
+      if (r.tile == T_256) return launch_pers<256, 256, 2, 4, ACT, MODE>(p, s);
+      if (r.tile == T_192) return launch_pers<192, 256, 2, 4, ACT, MODE>(p, s);
       // 8 waves of 64 x 32 (16 waves per CU) hide the L2 latency of the small tile better than 4
       // waves of 64 x 64 (measured 7-13 % on the d_model = 768 shapes); the gated epilogue pairs
       // two accumulator columns per wave and keeps the 2 x 2 layout
@@ -1508,9 +1553,11 @@ const char* gemm_bf16_variant(int M, int N, int K, int ldy, forge_act act) {
   const Route r = plan_route(M, N, K, ldy, act, false, false, false, false, SIZE_MAX);
   if (r.rows.ranges > 0 || r.few_rows) return r.planes ? "gemm_bf16_rows+splitk" : "gemm_bf16_rows";
   switch (r.v) {
-    case V_FAST_256: return "gemm_bf16_pers<256,256,2,4>";
+    case V_FAST_256:
     case V_FAST_128:
       if (r.planes) return "gemm_bf16_pers<128,128,2,4>+splitk";
+      if (r.tile == T_256) return "gemm_bf16_pers<256,256,2,4>";
+      if (r.tile == T_192) return "gemm_bf16_pers<192,256,2,4>";
       return act == FORGE_ACT_SWIGLU ? "gemm_bf16_pers<128,128,2,2>" : "gemm_bf16_pers<128,128,2,4>";
     case V_GEN_256: return "gemm_bf16_generic<256,256,2,4>";
     case V_GEN_128: return "gemm_bf16_generic<128,128,2,2>";
