@@ -946,14 +946,24 @@ template <int ACT, bool QKV>
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(GemmParams p, int splits, int ncols) {
   constexpr bool SWIGLU = ACT == FORGE_ACT_SWIGLU;
   const int N = p.N;                        // output columns
-  const int groups = ceil_div(N, 4);
-  const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (gid >= (int64_t)p.M * groups) return;
-  const int m = (int)(gid / groups), n0 = (int)(gid % groups) * 4;
+  const int m = blockIdx.y, n0 = (int)(blockIdx.x * blockDim.x + threadIdx.x) * 4;
+  if (n0 >= N) return;
   const int64_t plane = (int64_t)p.M * ncols;
   const float* src = p.part + (int64_t)m * ncols + n0;
   float a[4] = {0.f, 0.f, 0.f, 0.f}, u[4] = {0.f, 0.f, 0.f, 0.f};
   const bool vec = (ncols & 3) == 0 && n0 + 4 <= N && (!SWIGLU || (N & 3) == 0);
+  // whole rows in groups of 4 columns: bias and residual are 8-byte loads that go out before the planes' and the outputs one
+  // 8-byte store (two planes of 777 x 4096 with residual, element by element after the sums and rows by division | this:
+  // 10.5 | 8.5 us; the bytes take 6).
+  const bool wide = (N & 3) == 0 && (QKV || (p.ldy & 3) == 0);
+  u32x2 bi = {0, 0}, ub = {0, 0}, rv = {0, 0};
+  if (wide) {
+    if (p.bias != nullptr) {
+      bi = *reinterpret_cast<const u32x2*>(p.bias + n0);
+      if (SWIGLU) ub = *reinterpret_cast<const u32x2*>(p.bias + N + n0);
+    }
+    if (!QKV && p.residual != nullptr) rv = *reinterpret_cast<const u32x2*>(p.residual + (int64_t)m * p.ldy + n0);
+  }
   if (vec) {
     // independent 128-bit loads, summed in split order
 #pragma unroll 4
@@ -973,6 +983,29 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(GemmParams p, int sp
         a[e] += src[z * plane + e];
         if (SWIGLU) u[e] += src[z * plane + e + N];
       }
+  }
+  if (wide) {
+    const float b4[4] = {bf_lo(bi[0]), bf_hi(bi[0]), bf_lo(bi[1]), bf_hi(bi[1])};
+    const float ub4[4] = {bf_lo(ub[0]), bf_hi(ub[0]), bf_lo(ub[1]), bf_hi(ub[1])};
+    const float r4[4] = {bf_lo(rv[0]), bf_hi(rv[0]), bf_lo(rv[1]), bf_hi(rv[1])};
+    float o[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      float av = a[e], uv = u[e];
+      if (p.wscale != nullptr) {
+        av *= p.wscale[n0 + e];
+        if (SWIGLU) uv *= p.wscale[N + n0 + e];
+      }
+      if (p.bias != nullptr) {
+        av += b4[e];
+        if (SWIGLU) uv += ub4[e];
+      }
+      o[e] = SWIGLU ? silu_f(av) * uv : apply_act<ACT>(av);
+      if (!QKV && p.residual != nullptr) o[e] += r4[e];
+    }
+    bf16* dst = QKV ? split_dst_bf16(p.sp, p.row0 + m, n0) : p.y + (int64_t)m * p.ldy + n0;   // 4 columns stay inside a head
+    *reinterpret_cast<u32x2*>(dst) = u32x2{pack_bf2(o[0], o[1]), pack_bf2(o[2], o[3])};
+    return;
   }
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
@@ -1365,6 +1398,14 @@ forge_status launch_wstream(const GemmParams& q, int splits, hipStream_t s) {
   return launch_status();
 }
 
+// one row of outputs per grid.y (problems cut along K have at most 128 x 256 rows), 4 columns per thread
+template <int ACT, bool QKV>
+forge_status launch_reduce(const GemmParams& p, int splits, int ncols, hipStream_t s) {
+  const int groups = ceil_div(p.N, 4), nt = min(256, ceil_div(groups, 64) * 64);
+  splitk_reduce_kernel<ACT, QKV><<<dim3(ceil_div(groups, nt), p.M), nt, 0, s>>>(p, splits, ncols);
+  return launch_status();
+}
+
 template <int ACT, int MODE>
 forge_status launch_act(const GemmParams& p, hipStream_t s) {
   const Variant v = choose_variant(p.M, p.N, p.K, p.ldy, (forge_act)ACT, MODE == MODE_QKV || MODE == MODE_QKV_ROPE);
@@ -1420,10 +1461,7 @@ forge_status launch_act(const GemmParams& p, hipStream_t s) {
         q.k_per_split = r.ps.k_per_split;
         const forge_status st = launch_pers<128, 128, 2, 4, FORGE_ACT_NONE, MODE_SPLITK>(q, s);
         if (st != FORGE_OK) return st;
-        const int64_t threads = (int64_t)p.M * ceil_div(p.N, 4);
-        splitk_reduce_kernel<ACT, MODE == MODE_QKV><<<(unsigned)ceil_div64(threads, 256), 256, 0, s>>>(
-            p, r.ps.splits, ncols);
-        return launch_status();
+        return launch_reduce<ACT, MODE == MODE_QKV>(p, r.ps.splits, ncols, s);
       }
       if (r.tile == T_256) return launch_pers<256, 256, 2, 4, ACT, MODE>(p, s);
       if (r.tile == T_192) return launch_pers<192, 256, 2, 4, ACT, MODE>(p, s);
@@ -1470,9 +1508,7 @@ forge_status launch_act(const GemmParams& p, hipStream_t s) {
     else splitk_reduce_norm_kernel<NORM_TAIL_MAX_G><<<p.M, nt, 0, s>>>(p, splits);
     return launch_status();
   }
-  const int64_t threads = (int64_t)p.M * ceil_div(p.N, 4);
-  splitk_reduce_kernel<ACT, MODE == MODE_QKV><<<(unsigned)ceil_div64(threads, 256), 256, 0, s>>>(p, splits, sk.ncols);
-  return launch_status();
+  return launch_reduce<ACT, MODE == MODE_QKV>(p, splits, sk.ncols, s);
   }
 }
 
