@@ -84,7 +84,10 @@ def recorded_traffic(workload, inst):
     digest = kernel_source_digest()
     if rec.get("source_sha256") != digest:
         return None, "kernel sources changed since the counters were taken"
-    ent = rec.get("workloads", {}).get(workload, {}).get("kernels", {}).get(inst)
+    kernels = rec.get("workloads", {}).get(workload, {}).get("kernels", {})
+    # attention names leave out the instantiation's last parameters (mask, shares, waves): one record fits
+    names = [k for k in kernels if k == inst or k.startswith(inst[:-1] + ",")] if inst.startswith("attn_") else [inst]
+    ent = kernels.get(names[0]) if len(names) == 1 else None
     if ent is None:
         return None, "no counter record for this kernel"
     return (round(ent["fetch_bytes_per_launch"] + ent["write_bytes_per_launch"]),
