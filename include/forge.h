@@ -88,7 +88,8 @@ int forge_version(void);
  * strides multiples of 8 elements; scale positive and finite (else FORGE_ERR_INVALID_ARG: the
  * paper's scale is 1/sqrt(d_k)).  q_len == 1 takes the split-KV (decode) path, which needs
  * workspace; the size reported for (.., q_len 1, kv_len L, ..) also serves every shorter
- * length, so a generation loop asks once, for the capacity of its cache.  bf16 prompts with few
+ * length and every smaller batch, so a generation loop asks once, for the capacity of its cache
+ * (a cache of less than 512 rows needs none).  bf16 prompts with few
  * query blocks and many keys (a conversation's next turn) use their workspace to spread the keys
  * over idle compute units; without it, or with less, they run slower, not refused.
  * ------------------------------------------------------------------------------------ */
@@ -319,10 +320,10 @@ forge_status forge_attn_decode_varlen(const void* q, const void* k, const void* 
  * fixed array inside the library's device image instead of a caller workspace.  Same kernels,
  * same order, bit-identical output.  The call allocates nothing and frees nothing; its first use
  * on a device looks the array's address up once.
- * Limit: forge_attn_fused_workspace_bytes(batch, q_heads, kv_heads, 1, kv_len, head_dim,
- * FORGE_BF16) must not exceed forge_attn_decode_static_max_bytes() (4 MiB; each GPU the library
- * runs on holds that much until the process ends), else FORGE_ERR_WORKSPACE and nothing is
- * enqueued.  Every call on one GPU shares the array: calls that may overlap on one GPU (different
+ * Limit: the partial results of this batch (at most forge_attn_fused_workspace_bytes(batch, q_heads,
+ * kv_heads, 1, kv_len, head_dim, FORGE_BF16)) must not exceed forge_attn_decode_static_max_bytes()
+ * (4 MiB; each GPU the library runs on holds that much until the process ends), else
+ * FORGE_ERR_WORKSPACE and nothing is enqueued.  Every call on one GPU shares the array: calls that may overlap on one GPU (different
  * streams, different threads) race and must be ordered by the caller.  Nothing in it needs
  * clearing between calls: every partial a call reads it has written first.
  * Other arguments, layouts and errors as forge_attn_fused. */

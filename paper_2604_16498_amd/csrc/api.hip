@@ -247,8 +247,7 @@ forge_status forge_attn_fused(const void* q, const void* k, const void* v, void*
     return FORGE_ERR_INVALID_ARG;
   if (kv_head_stride % 8 != 0 || kv_batch_stride % 8 != 0) return FORGE_ERR_INVALID_ARG;
   if (out == q || out == k || out == v) return FORGE_ERR_INVALID_ARG;
-  // (a prompt runs without its workspace too)
-  const size_t need = q_len == 1 ? attn_ws(batch, q_heads, kv_heads, q_len, kv_len, head_dim, dt) : 0;
+  const size_t need = attn_needed(batch, q_heads, kv_heads, q_len, kv_len, head_dim, dt);
   if (need > 0 && (workspace == nullptr || workspace_bytes < need)) return FORGE_ERR_WORKSPACE;
   AttnArgs a = {q, k, v, out, batch, q_heads, kv_heads, q_len, kv_len, head_dim,
                 kv_batch_stride, kv_head_stride, scale, causal, workspace, workspace_bytes, nullptr, 0, 0};
@@ -504,7 +503,7 @@ forge_status forge_attn_decode_varlen(const void* q, const void* k, const void* 
     return FORGE_ERR_INVALID_ARG;
   if (kv_head_stride % 8 != 0 || kv_batch_stride % 8 != 0) return FORGE_ERR_INVALID_ARG;
   if (out == q || out == k || out == v) return FORGE_ERR_INVALID_ARG;
-  const size_t need = attn_ws(batch, q_heads, kv_heads, 1, kv_len, head_dim, dt);
+  const size_t need = attn_needed(batch, q_heads, kv_heads, 1, kv_len, head_dim, dt);
   if (need > 0 && (workspace == nullptr || workspace_bytes < need)) return FORGE_ERR_WORKSPACE;
   AttnArgs a = {q, k, v, out, batch, q_heads, kv_heads, 1, kv_len, head_dim,
                 kv_batch_stride, kv_head_stride, scale, 1, workspace, workspace_bytes, nullptr, 0, 0, seq_pos};
@@ -525,7 +524,7 @@ forge_status forge_attn_decode_static(const void* q, const void* k, const void* 
   if (kv_head_stride % 8 != 0 || kv_batch_stride % 8 != 0) return FORGE_ERR_INVALID_ARG;
   if (out == q || out == k || out == v) return FORGE_ERR_INVALID_ARG;
   // the partials of this call must fit the fixed array
-  if (attn_ws(batch, q_heads, kv_heads, 1, kv_len, head_dim, FORGE_BF16) > attn_decode_static_scratch_bytes())
+  if (attn_needed(batch, q_heads, kv_heads, 1, kv_len, head_dim, FORGE_BF16) > attn_decode_static_scratch_bytes())
     return FORGE_ERR_WORKSPACE;
   void* scratch_ptr = nullptr;
   const forge_status st = attn_decode_static_scratch(&scratch_ptr);

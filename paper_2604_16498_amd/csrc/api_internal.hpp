@@ -58,6 +58,11 @@ inline size_t attn_ws(int batch, int q_heads, int kv_heads, int q_len, int kv_le
   return 0;
 }
 
+// what attention calls that have to bring their workspace are refused without (at most attn_ws; a prompt's is optional)
+inline size_t attn_needed(int batch, int q_heads, int kv_heads, int q_len, int kv_len, int head_dim, forge_dtype dt) {
+  return dt == FORGE_BF16 && q_len == 1 ? attn_decode_needed_bytes(batch, q_heads, kv_heads, kv_len, head_dim) : 0;
+}
+
 // plain: see gemm_bf16_workspace_bytes
 inline size_t gemm_ws(int M, int N, int K, forge_act act, forge_dtype dt, bool w8, bool plain = false) {
   if (w8) return gemm_w8_workspace_bytes(M, N, K, act);

@@ -284,6 +284,7 @@ __global__ __launch_bounds__(DH) void attn_decode_combine(const float* __restric
 // sequences up to 1501 rows of 8 heads 30.2 (3) | 23.8 (1), 31 up to 2683 52.5 | 44.3 (1), 11 x 1612 rows of 16 heads 36.2 | 28.6 (1),
 // 5 up to 8192 rows of 8 heads 36.3 (13) | 27.1 (6), 1 x 1594 of 16 heads 10.1 (6) | 9.3 (13).
 struct SplitPlan { int splits, rows_per_split; };
+constexpr int MIN_CUT_ROWS = 512;         // a shorter cache is never cut, so its calls need no workspace
 // the most ranges a batch is ever cut into, whatever the cache length
 inline int max_splits(int batch, int kv_heads) {
   return (int)max((int64_t)1, min((int64_t)MAX_SPLITS, compute_units() / ((int64_t)batch * kv_heads)));
@@ -291,6 +292,7 @@ inline int max_splits(int batch, int kv_heads) {
 inline SplitPlan plan_splits(int batch, int kv_heads, int kv_len, int head_dim) {
   const double row_bytes = head_dim * 4.0, all_us = (double)batch * kv_heads * kv_len * row_bytes * 0.7 / 5.9e6;
   SplitPlan best = {1, ceil_div(kv_len, GRAIN) * GRAIN};
+  if (kv_len < MIN_CUT_ROWS) return best;
   double least = fmax(kv_len * row_bytes / 45e3, all_us);
   const int most = min(max_splits(batch, kv_heads), kv_len / GRAIN);
   for (int want = 2; want <= most; ++want) {
@@ -304,7 +306,7 @@ inline SplitPlan plan_splits(int batch, int kv_heads, int kv_len, int head_dim) 
 // not monotone in the length (the range size is rounded up to GRAIN), the scratch size must be,
 // because a generation loop sizes its scratch once, for the capacity of its cache.
 inline int splits_bound(int batch, int kv_heads, int kv_len) {
-  return max(1, min(max_splits(batch, kv_heads), kv_len / GRAIN));
+  return kv_len < MIN_CUT_ROWS ? 1 : min(max_splits(batch, kv_heads), kv_len / GRAIN);
 }
 
 // Query heads per block for `group` heads sharing one cache head: the whole group up to 8, else
@@ -380,16 +382,39 @@ forge_status launch_d(const AttnArgs& a, hipStream_t s) {
     case 6: return launch_dg<DH, 6>(a, s);
     case 7: return launch_dg<DH, 7>(a, s);
     case 8: return launch_dg<DH, 8>(a, s);
-    default: return launch_attn_simple_bf16(a, s);   // groups no pass count covers: vector-ALU path
+    default: return FORGE_ERR_UNSUPPORTED;
   }
 }
 
 }  // namespace
 
-size_t attn_decode_workspace_bytes(int batch, int q_heads, int kv_heads, int kv_len, int head_dim) {
+namespace {
+// partial rows of (query head, range) pairs, with their maximum and sum
+inline size_t partial_bytes(int64_t pairs, int head_dim) { return (size_t)pairs * (head_dim + 2) * sizeof(float); }
+
+// Groups that run on the vector-ALU kernel write no partials.  Their sizes stay those by which calls have been
+// accepted and refused, the fixed array's among them: ranges of 256 rows, two blocks per CU.
+inline size_t vector_group_bytes(int batch, int q_heads, int kv_heads, int kv_len, int head_dim) {
+  const int64_t two_per_cu = ceil_div64(2 * (int64_t)compute_units(), (int64_t)batch * kv_heads);
+  const int splits = (int)min(min(two_per_cu, (int64_t)MAX_SPLITS), (int64_t)(kv_len / 256));
+  return splits > 1 ? partial_bytes((int64_t)batch * q_heads * splits, head_dim) : 0;
+}
+}  // namespace
+
+// what a call of this batch has to bring: room for the ranges of any cache up to kv_len
+size_t attn_decode_needed_bytes(int batch, int q_heads, int kv_heads, int kv_len, int head_dim) {
+  if (heads_per_block(q_heads / kv_heads) == 0) return vector_group_bytes(batch, q_heads, kv_heads, kv_len, head_dim);
   const int splits = splits_bound(batch, block_heads(q_heads, kv_heads), kv_len);
-  if (splits == 1) return 0;       // one block per (kv head, sequence) writes the output itself
-  return (size_t)batch * q_heads * splits * (head_dim + 2) * sizeof(float);
+  return splits > 1 ? partial_bytes((int64_t)batch * q_heads * splits, head_dim) : 0;   // else the blocks write the output
+}
+
+// The size to ask for: also what any smaller batch needs, which is cut into more ranges (24 sequences of 8 heads run
+// uncut, 16 in two ranges): b * splits_bound(b) over all b <= batch is at most the CUs per head, and 64 ranges of each.
+size_t attn_decode_workspace_bytes(int batch, int q_heads, int kv_heads, int kv_len, int head_dim) {
+  if (heads_per_block(q_heads / kv_heads) == 0) return vector_group_bytes(batch, q_heads, kv_heads, kv_len, head_dim);
+  const int64_t per_head = compute_units() / block_heads(q_heads, kv_heads);
+  if (per_head < 2 || kv_len < MIN_CUT_ROWS) return 0;
+  return partial_bytes(min(per_head, (int64_t)batch * min(MAX_SPLITS, kv_len / GRAIN)) * q_heads, head_dim);
 }
 
 // ---- scratch that nobody allocates -----------------------------------------------------------
@@ -419,9 +444,10 @@ forge_status attn_decode_static_scratch(void** ptr) {
 }
 
 forge_status launch_attn_decode_bf16(const AttnArgs& a, hipStream_t s) {
-  // what THIS launch writes (at most the bound the size query reports for any cache >= kv_len)
+  if (heads_per_block(a.q_heads / a.kv_heads) == 0) return launch_attn_simple_bf16(a, s);   // no pass count covers the group
+  // what THIS launch writes (at most attn_decode_needed_bytes of any cache >= kv_len)
   const int splits = plan_splits(a.batch, block_heads(a.q_heads, a.kv_heads), a.kv_len, a.head_dim).splits;
-  const size_t need = splits == 1 ? 0 : (size_t)a.batch * a.q_heads * splits * (a.head_dim + 2) * sizeof(float);
+  const size_t need = splits == 1 ? 0 : partial_bytes((int64_t)a.batch * a.q_heads * splits, a.head_dim);
   if (need > 0 && (a.workspace == nullptr || a.workspace_bytes < need)) return FORGE_ERR_WORKSPACE;
   if (a.head_dim == 64) return launch_d<64>(a, s);
   if (a.head_dim == 128) return launch_d<128>(a, s);

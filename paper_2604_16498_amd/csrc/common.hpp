@@ -284,7 +284,8 @@ size_t attn_prefill_workspace_bytes(int batch, int q_heads, int q_len, int kv_le
 inline size_t attn_prefill_share_bytes(int batch, int q_heads, int q_len, int head_dim) {   // partial rows, maxima and sums
   return (size_t)batch * q_heads * q_len * (head_dim + 2) * sizeof(float);
 }
-size_t attn_decode_workspace_bytes(int batch, int q_heads, int kv_heads, int kv_len, int head_dim);
+size_t attn_decode_workspace_bytes(int batch, int q_heads, int kv_heads, int kv_len, int head_dim);   // serves smaller batches too
+size_t attn_decode_needed_bytes(int batch, int q_heads, int kv_heads, int kv_len, int head_dim);      // ... without which a call is refused
 // The library's own fixed scratch array for the decode attention (one per GPU): its size, and its
 // address on the current device.  Every call on a GPU shares it.
 size_t attn_decode_static_scratch_bytes();
