@@ -35,7 +35,8 @@ struct BlockPlan {
   size_t y, q, o, u, attn, gemm, total;
 };
 
-BlockPlan plan_block(const forge_block_desc* d, int batch, int q_len, int kv_cap) {
+// asked: the size to report, which serves smaller batches too; otherwise what this call needs and carves
+BlockPlan plan_block(const forge_block_desc* d, int batch, int q_len, int kv_cap, bool asked = false) {
   const size_t es = esize(d->dt);
   const size_t T = (size_t)batch * q_len;
   const int hd = d->q_heads * d->head_dim;
@@ -45,7 +46,7 @@ BlockPlan plan_block(const forge_block_desc* d, int batch, int q_len, int kv_cap
   p.o = align_up(T * hd * es, 256);
   p.u = block_mlp_bytes(d, T);
   // (a decode step's partial rows; a prompt's lie in u and what follows it: block_share_bytes)
-  p.attn = q_len == 1 ? align_up(attn_ws(batch, d->q_heads, d->kv_heads, q_len, kv_cap, d->head_dim, d->dt), 256) : 0;
+  p.attn = q_len == 1 ? align_up((asked ? attn_ws : attn_needed)(batch, d->q_heads, d->kv_heads, q_len, kv_cap, d->head_dim, d->dt), 256) : 0;
   p.gemm = block_gemm_bytes(d, (int)T, q_len);
   p.total = p.y + p.q + p.o + p.u + p.attn + p.gemm;
   return p;
@@ -146,7 +147,7 @@ struct ModelPlan {
   size_t h, yf, block, total;
 };
 
-ModelPlan plan_model(const forge_model_desc* m, int batch, int q_len, int kv_cap) {
+ModelPlan plan_model(const forge_model_desc* m, int batch, int q_len, int kv_cap, bool asked = false) {
   const forge_block_desc* d0 = &m->layers[0];
   const size_t es = esize(d0->dt);
   const size_t T = (size_t)batch * q_len;
@@ -155,7 +156,7 @@ ModelPlan plan_model(const forge_model_desc* m, int batch, int q_len, int kv_cap
   p.yf = m->wte != nullptr ? align_up(T * d0->d_model * es, 256) : 0;
   p.block = 0;
   for (int l = 0; l < m->n_layers; ++l) {
-    const size_t b = plan_block(&m->layers[l], batch, q_len, kv_cap).total;
+    const size_t b = plan_block(&m->layers[l], batch, q_len, kv_cap, asked).total;
     p.block = b > p.block ? b : p.block;
   }
   const size_t head = m->wte != nullptr ? align_up(gemm_ws((int)T, m->vocab, d0->d_model, FORGE_ACT_NONE, d0->dt, false, true), 256) : 0;
@@ -389,7 +390,7 @@ size_t forge_decoder_block_workspace_bytes(const forge_block_desc* desc, int bat
                                            int kv_cap) {
   if (check_block_desc(desc) != FORGE_OK || batch < 1 || q_len < 1 || kv_cap < q_len) return 0;
   if (!grid_ok(batch, desc->q_heads) || !rows_ok(batch, q_len)) return 0;
-  return plan_block(desc, batch, q_len, kv_cap).total;
+  return plan_block(desc, batch, q_len, kv_cap, true).total;
 }
 
 forge_status forge_decoder_block(const forge_block_desc* desc, const void* x_in, void* x_out,
@@ -409,7 +410,7 @@ forge_status forge_decoder_block(const forge_block_desc* desc, const void* x_in,
 size_t forge_model_workspace_bytes(const forge_model_desc* model, int batch, int q_len, int kv_cap) {
   if (check_model(model) != FORGE_OK || batch < 1 || q_len < 1 || kv_cap < q_len) return 0;
   if (!grid_ok(batch, 1) || !rows_ok(batch, q_len)) return 0;
-  return plan_model(model, batch, q_len, kv_cap).total;
+  return plan_model(model, batch, q_len, kv_cap, true).total;
 }
 
 static forge_status model_forward(const forge_model_desc* model, const void* input, void* output,

@@ -8,7 +8,7 @@ from oracle import forge_oracle as O
 from paper_2604_16498_amd import binding as F
 from paper_2604_16498_amd import inputs as I
 from test_plan_host import fake_model
-from util import check, dev
+from util import check, dev, dev_dict
 
 HEADS = [(12, 12, 64), (16, 16, 128), (32, 8, 128), (32, 32, 128), (32, 2, 128), (25, 25, 64), (300, 300, 64)]
 
@@ -56,3 +56,20 @@ def test_calls_that_need_no_more(B, Hq, Hkv, dh, kv, given):
         call(out)
         torch.cuda.synchronize()
         check(out, ref, True, "B=%d heads %d/%d kv %d, workspace: %s" % (B, Hq, Hkv, kv, given))
+
+
+@pytest.mark.gpu
+def test_layer_of_a_batch_that_is_never_cut():
+    """48 sequences of 12 heads fill the chip with one block each: a layer over 600 rows runs in the workspace of one over 500."""
+    sh, B, cap = I.GPT2_SMALL, 48, 600
+    desc = F.make_block_desc(sh, dev_dict(I.block_weights(sh, 92, 0, bf16=True, weight_std=0.05), True))
+    pos = torch.arange(cap - B, cap, dtype=torch.int32, device="cuda")
+    x = dev(I.normal(92, 0, "x", (B, 1, sh.d_model), 1.0, bf16=True), True)
+    outs = []
+    for rows in (cap, 500):
+        kv = [dev(I.normal(92, 0, n, (B, sh.kv_heads, cap, sh.head_dim), 1.0, bf16=True), True) for n in ("k_cache", "v_cache")]
+        outs.append(torch.empty_like(x))
+        ws = F.workspace(F.forge_decoder_block_workspace_bytes(desc, B, 1, rows))
+        F.forge_decoder_block_decode(desc, x, outs[-1], *kv, pos, cap - 1, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(*outs)
