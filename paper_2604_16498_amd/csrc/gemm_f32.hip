@@ -371,12 +371,13 @@ forge_status launch_waves(int cb, const float* x, const float* w, const float* b
 // 3072 x 768 18.1 | 10.9, 768 x 3072 17.4 | 12.9; 512 rows against 3072 x 768 34.3 | 29.4, 2048 rows 99 | 108, 256 rows
 // against 6144 x 72 9.2 | 10.1).  A long reduction with few tiles stays cut over the grid (64 rows against 768 x 8192
 // 21.9 | 28.7, 256 x 4096 at one row 13.8 | 15.0; from 24 tiles on 32.7 | 30.5).
+constexpr int LONG_K = 3072, FEW_TILES = 16;
 int plan_waves(int M, int N, int K, bool gated) {
   const int64_t rows = gated ? 2 * (int64_t)N : N;
   if ((int64_t)M * K >= (1ll << 30) || rows * K >= (1ll << 30)) return 0;       // 32-bit byte offsets
   const int64_t cus = compute_units(), slabs = ceil_div(K, BK), slabs8 = (slabs + 7) / 8 * 8;
   const int64_t t64 = (int64_t)ceil_div(M, BM) * ceil_div(N, BN), mt = ceil_div(M, FM);
-  if ((K > 3072 && t64 <= 16) || mt > 65535) return 0;
+  if ((K > LONG_K && t64 <= FEW_TILES) || mt > 65535) return 0;
   const int64_t c64 = ceil_div64(t64, cus) * slabs * (gated ? 14 : 7) + 45;
   const int64_t c2 = ceil_div64(mt * ceil_div64(rows, 32), cus) * slabs8 * 19 / 10 + 22;
   const int64_t c1 = gated ? c2 : ceil_div64(mt * ceil_div64(N, 16), cus) * slabs8 * 12 / 10 + 21;
@@ -385,16 +386,25 @@ int plan_waves(int M, int N, int K, bool gated) {
 }
 }  // namespace
 
-size_t gemm_f32_workspace_bytes(int M, int N, int K, forge_act act) {
+// fp32 planes of this very problem, 0 where it runs whole
+static size_t planes_bytes(int M, int N, int K, forge_act act) {
   if (plan_waves(M, N, K, act == FORGE_ACT_SWIGLU) > 0) return 0;
   const SplitPlan sp = plan_split(M, N, K);
   if (sp.splits == 1) return 0;
   return (size_t)sp.splits * M * (act == FORGE_ACT_SWIGLU ? 2 * N : N) * sizeof(float);
 }
 
+// The size to ask for: a long reduction that this many rows run whole is cut at fewer rows, and a buffer for the larger
+// problem serves the smaller ones.
+size_t gemm_f32_workspace_bytes(int M, int N, int K, forge_act act) {
+  const size_t own = planes_bytes(M, N, K, act);
+  const int cut_rows = K > LONG_K ? FEW_TILES / ceil_div(N, BN) * BM : 0;      // the most rows that are cut
+  return M > cut_rows && cut_rows > 0 ? max(own, planes_bytes(cut_rows, N, K, act)) : own;
+}
+
 forge_status launch_gemm_f32(const GemmArgs& a, hipStream_t s) {
   SplitPlan pl = plan_split(a.M, a.N, a.K);
-  const size_t need = gemm_f32_workspace_bytes(a.M, a.N, a.K, a.act);
+  const size_t need = planes_bytes(a.M, a.N, a.K, a.act);
   if (need > a.workspace_bytes || (need > 0 && a.workspace == nullptr)) pl = SplitPlan{1, a.K};   // unsplit
   float* part = pl.splits > 1 ? (float*)a.workspace : nullptr;
   dim3 grid(ceil_div(a.N, BN), ceil_div(a.M, BM), pl.splits), block(256);

@@ -28,6 +28,14 @@ def test_a_buffer_for_the_longer_prompt_serves_the_shorter(shape, shorter, longe
     assert compiled(shorter, 0) == compiled(shorter, 4000) <= compiled(longer, 4000)
 
 
+@pytest.mark.parametrize("N,K,act", [(768, 4100, "none"), (320, 8192, "swiglu"), (64, 16384, "none")])
+def test_an_fp32_size_serves_the_cut_reductions_of_fewer_rows(N, K, act):
+    size = lambda M: B.forge_gemm_workspace_bytes(M, N, K, act, torch.float32)
+    cut = 16 // -(-N // 64) * 64                  # up to here a reduction of more than 3072 is cut
+    assert 0 < size(cut)
+    assert all(size(M) >= size(cut) for M in range(cut + 1, 4 * cut, 37))
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("d,hq,hkv,dh,ff,llama,S,pos", [
     (512, 4, 2, 128, 1408, True, 80, 1500),      # shares in the MLP rows and the GEMM planes
