@@ -264,10 +264,16 @@ def operator_work(wl, F, torch, logits_ld):
     _, attn_fl = step_flops(wl)
     G = sh.q_heads // sh.kv_heads
 
-    def gemm(N, K, act, mode, ldy=0):
+    def gemm(N, K, act, mode, ldy=0, tail=False):
         nw = 2 * N if act == "swiglu" else N
         var = F.forge_gemm_variant(T, N, K, act, dt, ldy=ldy)
-        inst = "%s,%d,%d>" % (var[:-1], F.ACT[act], mode) if var.endswith(">") and wl.bf16 and "+" not in var else var
+        if "waves" in var:
+            inst = "%s,%s>" % (var[:-1], str(act == "swiglu").lower()) if wl.bf16 else var
+        else:
+            inst = "%s,%d,%d>" % (var[:-1], F.ACT[act], mode) if var.endswith(">") and wl.bf16 and "+" not in var else var
+        if decode and wl.bf16 and T <= 64 and inst.startswith("gemm_bf16_waves") and (tail or (mode == 1 and sh.use_rope)):
+            # a norm or a rotation behind the projection: the kernel that finishes plain outputs does not take it
+            inst = "gemm_bf16 + " + ("splitk_reduce_norm" if tail else "rotation")
         if decode:
             return ("hbm", float(nw) * K * es, inst)
         return ("mfma", 2.0 * T * nw * K, inst)
@@ -283,9 +289,9 @@ def operator_work(wl, F, torch, logits_ld):
         "gemm_qkv": qkv,
         "rope_q": ("hbm", 2.0 * T * hd * es, "rope"),
         "rope_k": ("hbm", 2.0 * T * sh.kv_heads * sh.head_dim * es, "rope"),
-        "out_proj": gemm(d, hd, "none", 0),
+        "out_proj": gemm(d, hd, "none", 0, tail=True),
         "mlp_up": gemm(F_, d, sh.mlp_act, 0),
-        "mlp_down": gemm(d, F_, "none", 0),
+        "mlp_down": gemm(d, F_, "none", 0, tail=True),
         "embed": ("hbm", 3.0 * T * d * es, "embed"),
     }
     if decode:

@@ -141,13 +141,12 @@ forge_status forge_attn_fused_masked(const void* q, const void* k, const void* v
  * ------------------------------------------------------------------------------------ */
 size_t forge_gemm_workspace_bytes(int M, int N, int K, forge_act act, forge_dtype dt);
 
-/* Diagnostic: the class of kernel (tile shape and wave layout) that this problem of
- * forge_gemm_bias_gelu belongs to when it has the workspace that
- * forge_gemm_workspace_bytes asks for, e.g. "gemm_bf16_pers<256,256,2,4>" or "gemm_bf16_rows" (the
- * linear that keeps the rows of x in registers); "+splitk": fp32 planes of several k ranges and a reduce
- * launch.  Small problems of these classes run instead on a kernel whose waves share the k slabs and that finishes its outputs
- * in one launch (gemm_bf16_waves_kernel, gemm_f32_waves_kernel in a trace); their names are those of the class.
- * Static storage, never NULL.  Lets a profiler trace be matched to the calls that produced it. */
+/* Diagnostic: the name of the kernel variant (tile shape and wave layout) that
+ * forge_gemm_bias_gelu launches for this problem when it has the workspace that
+ * forge_gemm_workspace_bytes asks for, e.g. "gemm_bf16_pers<256,256,2,4>", "gemm_bf16_rows" (the
+ * linear that keeps the rows of x in registers) or "gemm_bf16_waves<2,2>" (the one whose waves share
+ * the k slabs); "+splitk": fp32 planes of several k ranges and a reduce
+ * launch.  Static storage, never NULL.  Lets a profiler trace be matched to the calls that produced it. */
 const char* forge_gemm_variant(int M, int N, int K, int ldy, forge_act act, forge_dtype dt);
 
 forge_status forge_gemm_bias_gelu(const void* x, const void* w, const void* bias,

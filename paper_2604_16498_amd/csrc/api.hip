@@ -290,7 +290,7 @@ size_t forge_gemm_workspace_bytes(int M, int N, int K, forge_act act, forge_dtyp
 
 const char* forge_gemm_variant(int M, int N, int K, int ldy, forge_act act, forge_dtype dt) {
   if (M < 1 || N < 1 || K < 1) return "none";
-  return dt == FORGE_BF16 ? gemm_bf16_variant(M, N, K, ldy > 0 ? ldy : N, act) : "gemm_f32<64,64,2,2>";
+  return dt == FORGE_BF16 ? gemm_bf16_variant(M, N, K, ldy > 0 ? ldy : N, act) : gemm_f32_variant(M, N, K, act);
 }
 
 forge_status forge_gemm_bias_gelu(const void* x, const void* w, const void* bias,

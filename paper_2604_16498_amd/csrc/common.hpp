@@ -253,6 +253,7 @@ size_t gemm_w8_workspace_bytes(int M, int N, int K, forge_act act);   // require
 forge_status launch_quantize_int8(const void* w, int8_t* q, float* scale, int N, int K, forge_dtype dt,
                                   hipStream_t s);
 const char* gemm_bf16_variant(int M, int N, int K, int ldy, forge_act act);
+const char* gemm_f32_variant(int M, int N, int K, forge_act act);
 size_t gemm_f32_workspace_bytes(int M, int N, int K, forge_act act);
 
 struct AttnArgs {

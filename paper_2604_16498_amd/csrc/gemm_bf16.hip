@@ -1306,7 +1306,7 @@ Tile plan_tile(int M, int ncols, int K, Tile own) {
 }
 
 // The whole dispatch of a problem that does not rotate in its epilogue: the launcher follows it and the variant
-// query names its class.
+// query names its kernel.
 struct Route {
   Variant v;
   SkinnyPlan sk;      // at most 64 rows
@@ -1587,7 +1587,8 @@ bool gemm_fuses_tail(int M, int N, forge_dtype dt) {
 const char* gemm_bf16_variant(int M, int N, int K, int ldy, forge_act act) {
   // the call launch_act makes for a plain output, with the workspace asked for
   const Route r = plan_route(M, N, K, ldy, act, false, false, false, false, SIZE_MAX);
-  if (r.rows.ranges > 0 || r.few_rows) return r.planes ? "gemm_bf16_rows+splitk" : "gemm_bf16_rows";
+  if (r.waves >= 0) return waves_variant(r.waves);
+  if (r.rows.ranges > 0) return r.planes ? "gemm_bf16_rows+splitk" : "gemm_bf16_rows";
   switch (r.v) {
     case V_FAST_256:
     case V_FAST_128:

@@ -75,5 +75,6 @@ struct WavesPlan {
 };
 WavesPlan plan_waves(int M, int N, int K, bool gated);      // K % 64 == 0, bf16 weights, operands below 4 GB
 forge_status launch_waves(const GemmParams& p, int tile, int act, bool qkv, hipStream_t s);
+const char* waves_variant(int tile);
 
 }  // namespace forge

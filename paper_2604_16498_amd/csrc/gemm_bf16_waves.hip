@@ -215,4 +215,10 @@ forge_status launch_waves(const GemmParams& p, int tile, int act, bool qkv, hipS
   }
 }
 
+const char* waves_variant(int tile) {
+  constexpr const char* names[] = {"gemm_bf16_waves<1,1>", "gemm_bf16_waves<1,2>", "gemm_bf16_waves<2,2>", "gemm_bf16_waves<4,2>",
+                                   "gemm_bf16_waves<4,4>"};
+  return names[tile];
+}
+
 }  // namespace forge

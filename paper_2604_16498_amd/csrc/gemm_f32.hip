@@ -223,7 +223,7 @@ __global__ __launch_bounds__(FW * 64, 4) void gemm_f32_waves_kernel(
   constexpr int CHAINS = CB == 1 ? 4 : 2;            // sums per output of a wave: shorter chains, smaller rounding error
   constexpr int PATCH = (FM + WR) * LDK;             // floats of one wave's patch; rows padded as above
   constexpr int LDR = WR + 4;                        // row of a partial tile
-    static_assert(FM * LDR <= PATCH, "the partial tiles fit where the patches lie");
+  static_assert(FM * LDR <= PATCH, "the partial tiles fit where the patches lie");
   extern __shared__ __attribute__((aligned(16))) float lds[];   // [FW * PATCH]
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -400,6 +400,12 @@ size_t gemm_f32_workspace_bytes(int M, int N, int K, forge_act act) {
   const size_t own = planes_bytes(M, N, K, act);
   const int cut_rows = K > LONG_K ? FEW_TILES / ceil_div(N, BN) * BM : 0;      // the most rows that are cut
   return M > cut_rows && cut_rows > 0 ? max(own, planes_bytes(cut_rows, N, K, act)) : own;
+}
+
+const char* gemm_f32_variant(int M, int N, int K, forge_act act) {
+  const int cb = plan_waves(M, N, K, act == FORGE_ACT_SWIGLU);
+  if (cb > 0) return cb == 1 ? "gemm_f32_waves<1>" : "gemm_f32_waves<2>";
+  return plan_split(M, N, K).splits > 1 ? "gemm_f32<64,64,2,2>+splitk" : "gemm_f32<64,64,2,2>";
 }
 
 forge_status launch_gemm_f32(const GemmArgs& a, hipStream_t s) {

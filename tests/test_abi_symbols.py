@@ -132,25 +132,26 @@ def test_decode_attention_scratch_is_monotone_in_the_cache_length():
 def test_gemm_variant_names_the_kernel_that_runs():
     """The diagnostic applies the launcher's own rule: unaligned output rows (an odd dense N) and
     a reduction that is not a whole number of 64-element slabs go to the generic kernel, decode-sized
-    problems and prompts against few weight rows to the linear that keeps x in registers, other
-    decode-sized ones to the weight-streaming kernel, everything else to the persistent one."""
+    problems to the linear that keeps x in registers, the one whose waves share the k slabs (prompts against few
+    weight rows too) or the weight-streaming kernel, everything else to the persistent one."""
     import torch
     from paper_2604_16498_amd import binding as F
     v = lambda M, N, K, act="none", ldy=0: F.forge_gemm_variant(M, N, K, act, torch.bfloat16, ldy=ldy)
+    waves = lambda *a, **k: v(*a, **k).startswith("gemm_bf16_waves<")
     assert v(300, 1001, 128) == "gemm_bf16_generic<128,128,2,2>"            # rows of 2002 bytes
     assert v(300, 3001, 128, ldy=3008) == "gemm_bf16_pers<128,128,2,4>"
-    assert v(300, 1001, 128, ldy=1008) == "gemm_bf16_rows"                  # 63 row tiles: one per block
-    assert v(128, 2304, 768) == v(256, 2048, 2048) == "gemm_bf16_rows"
-    assert v(200, 768, 3072) == "gemm_bf16_rows+splitk"                     # K = 3072 in four ranges
-    assert v(200, 6144, 4096) == "gemm_bf16_pers<128,128,2,4>+splitk"       # 384 row tiles: too many per block
+    assert v(300, 1001, 128, ldy=1008) == "gemm_bf16_waves<4,2>"            # prompts against few weight rows
+    assert v(65, 24, 64) == "gemm_bf16_waves<1,1>"
+    assert waves(128, 2304, 768) and waves(256, 2048, 2048) and waves(200, 768, 3072) and waves(128, 768, 768, "swiglu")
+    assert waves(24, 2048, 2048) and waves(64, 4096, 4096) and waves(17, 6144, 4096)     # decode-sized, K of 1024 to 4096
+    assert v(200, 6144, 4096) == "gemm_bf16_pers<128,128,2,4>+splitk"       # too many weight rows
     assert v(8, 3072, 768, "gelu_tanh") == v(64, 1001, 512) == v(5, 14336, 4096, "swiglu") == "gemm_bf16_rows"
     assert v(21, 2048, 8192) == "gemm_bf16_rows+splitk"
     # decode-sized problems that stream faster slab-wise, and their neighbours that do not
     assert v(4, 15360, 5120) == v(17, 5120, 5120) == v(4, 4096, 6144) == "gemm_bf16_wstream+splitk"
-    assert v(4, 16384, 3840) == v(17, 6144, 4096) == v(17, 10240, 2560) == "gemm_bf16_wstream+splitk"
+    assert v(4, 16384, 3840) == v(17, 10240, 2560) == "gemm_bf16_wstream+splitk"
     assert v(17, 32768, 3840) == v(4, 32768, 1920) == v(4, 50304, 832) == "gemm_bf16_wstream_fused<128>"
-    assert v(4, 16384, 4096) == v(17, 8192, 4096) == v(4, 10240, 2560) == v(17, 32768, 4096) == "gemm_bf16_rows"
-    assert v(8, 50264, 768) == v(17, 3072, 3840) == "gemm_bf16_rows"
+    assert v(4, 16384, 4096) == v(4, 10240, 2560) == v(17, 32768, 4096) == v(8, 50264, 768) == "gemm_bf16_rows"
     assert v(4, 2560, 5120) == v(4, 16384, 8192) == "gemm_bf16_rows+splitk"
     assert v(64, 24576, 256) == "gemm_bf16_wstream_fused<128>"              # more rows than many tiles pay for
     assert v(8, 4096, 14336) == "gemm_bf16_wstream+splitk"                  # a long bf16 reduction
@@ -159,6 +160,8 @@ def test_gemm_variant_names_the_kernel_that_runs():
     assert v(8192, 50257, 768, ldy=50264) == "gemm_bf16_pers<256,256,2,4>"
     assert v(4096, 14336, 4096, "swiglu") == "gemm_bf16_pers<256,256,2,4>"
     assert v(4096, 1001, 4096, "swiglu", ldy=1008) == "gemm_bf16_generic<128,128,2,2>"   # gated pairs need N % 8 == 0
-    assert v(64, 4096, 4096) == "gemm_bf16_wstream+splitk"
+    assert v(64, 8200, 4096) == "gemm_bf16_wstream+splitk"
     assert v(64, 4096, 72) == "gemm_bf16_generic<64,64,2,2>+splitk"
-    assert F.forge_gemm_variant(128, 768, 768, "none", torch.float32) == "gemm_f32<64,64,2,2>"
+    f = lambda M, N, K, act="none": F.forge_gemm_variant(M, N, K, act, torch.float32)
+    assert f(128, 768, 768) == "gemm_f32_waves<1>" and f(128, 768, 768, "swiglu") == "gemm_f32_waves<2>"
+    assert f(64, 768, 8192) == "gemm_f32<64,64,2,2>+splitk" and f(2048, 3072, 768) == "gemm_f32<64,64,2,2>"

@@ -1,5 +1,6 @@
 """bf16 linears whose k slabs are shared by the waves of a block: edges of the tiles (16, 32 and 64 rows of x and of the
-weight), one slab, a slab for each of the 8 waves and one more, all epilogues, padded and odd row strides."""
+weight), one slab, a slab for each of the 8 waves and one more, all epilogues, padded and odd row strides.  Every case
+names the kernel that takes it, so that a rule which sends it elsewhere is seen."""
 import math
 
 import pytest
@@ -12,17 +13,22 @@ from util import check, dev
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("act,use_b,use_r", [("none", True, True), ("gelu_tanh", True, False), ("swiglu", True, True),
-                                             ("silu", False, True)])
-@pytest.mark.parametrize("M,N,K,ld", [
-    (1, 8, 64, 0), (15, 40, 64, 0), (17, 1001, 512, 1008), (33, 515, 576, 0),            # decode-sized, odd widths
-    (64, 4096, 1088, 0), (63, 2056, 2048, 0), (40, 8192, 128, 0),
-    (65, 24, 64, 0), (66, 776, 576, 0), (127, 2304, 768, 0), (129, 768, 3072, 0),        # prompts against few weight rows
-    (257, 515, 128, 520), (300, 1001, 1152, 1008), (255, 2048, 2048, 0), (385, 2312, 640, 0),
-    (513, 1536, 4096, 0),
-])
+def _epilogues(gated):
+    return [("none", True, True), ("gelu_tanh", True, False), ("silu", False, True)] + ([("swiglu", True, True)] if gated else [])
+
+
+@pytest.mark.parametrize("M,N,K,ld,act,use_b,use_r", [(*c, *e) for c, gated in [
+    # decode-sized: one row, odd widths and strides (element-wise outputs), two row blocks
+    ((1, 40, 1024, 0), False), ((15, 1001, 1088, 1003), False), ((33, 515, 2048, 0), False), ((64, 2056, 1088, 0), False),
+    ((63, 1030, 4096, 1036), False), ((17, 1602, 1152, 0), False),
+    # prompts against few weight rows, tiles of 16 x 16 to 64 x 64
+    ((65, 24, 64, 0), True), ((66, 776, 576, 0), True), ((127, 2304, 768, 0), True), ((129, 768, 3072, 0), True),
+    ((257, 515, 128, 520), False), ((300, 1001, 1152, 1008), False), ((255, 2048, 2048, 0), True), ((383, 2312, 640, 0), False),
+    ((513, 1536, 4096, 0), False),
+] for e in _epilogues(gated)])
 def test_linear_shared_slabs(M, N, K, ld, act, use_b, use_r):
     from paper_2604_16498_amd import binding as F
+    assert F.forge_gemm_variant(M, N, K, act, torch.bfloat16, ldy=ld or N).startswith("gemm_bf16_waves<")
     wn = 2 * N if act == "swiglu" else N
     ldy = ld or N
     x = I.normal(64, 0, "x", (M, K), 1.0, bf16=True)

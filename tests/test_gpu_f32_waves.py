@@ -21,6 +21,7 @@ pytestmark = pytest.mark.gpu
 ])
 def test_f32_linear_shared_slabs(M, N, K, act, use_b, use_r):
     from paper_2604_16498_amd import binding as F
+    assert "waves" in F.forge_gemm_variant(M, N, K, act, torch.float32)
     wn = 2 * N if act == "swiglu" else N
     x = I.normal(63, 0, "x", (M, K), 1.0, bf16=False)
     w = I.normal(63, 0, "w_up", (wn, K), 1.0 / math.sqrt(K), bf16=False)
