@@ -1313,20 +1313,22 @@ struct Route {
   PersSplit ps;       // V_FAST_128: k ranges (1: unsplit)
   RowsPlan rows;      // ranges > 0: the kernel with x in registers takes it
   bool planes;        // fp32 planes and a reduce launch
-  bool few_rows;      // more than 64 rows: see few_weight_rows
   Tile tile = T_128;  // the persistent kernel's, where it takes the problem unsplit
   int waves = -1;     // tile of the kernel whose waves share the k slabs, which then takes the problem
 };
 
-// More than 64 rows against a weight with few row tiles of 16: the 128 x 128 tiles leave most of the chip idle, each walking
-// all of K alone (10.5 us for K = 768 however few there are).  planes: the k ranges that the tile kernel would cut K into.
-bool few_weight_rows(int M, int rows, int K, int planes) {
-  const int total = K / 32, ranges = planes == 0 ? 1 : ceil_div(total, 24);
-  if (planes > 0 && (ranges < 2 || ranges > planes)) return false;
-  const int steps = ceil_div(total, ranges * 8);
-  if (steps > 8) return false;
-  const int chunks = ceil_div(M, steps <= 3 ? 128 : 64), slots = compute_units() / (ceil_div(total, steps * 8) * chunks);
-  return slots >= 1 && ceil_div(ceil_div(rows, 16), slots) <= (planes > 0 ? 3 : steps <= 3 ? 2 : 6);
+// More than 64 rows and so few outputs that 128 x 128 tiles leave most of the chip idle, each walking all of K alone
+// (10.5 us for K = 768 however few there are).  planes: the k ranges that the tile kernel would cut K into.  The
+// lines are where waves that share the slabs stopped being the faster ones among 3700 drawn problems (outputs per CU,
+// rows in whole tiles of 64, of 128 where a short K leaves the padding's stores to count).
+bool few_outputs(int M, int rows, int K, int planes) {
+  const int64_t cus = compute_units();
+  if (planes == 0) {
+    const int unit = K <= 768 ? 128 : 64;
+    return K <= 2048 && (int64_t)ceil_div(M, unit) * unit * rows <= cus * (K <= 768 ? 4096 : 6144);
+  }
+  const int ranges = ceil_div(K, 768);
+  return ranges >= 2 && ranges <= planes && (int64_t)ceil_div(M, 128) * 128 * rows * ranges <= cus * 6144;
 }
 
 // The 128 x 128 tiles with K cut into ranges, planes and reduce launch included (us; fitted to 153 drawn problems, within 7 %
@@ -1342,29 +1344,30 @@ double pers_split_us(int M, int ncols, int K, const PersSplit& ps) {
 // a dequantised weight, which only the tile kernels know.
 Route plan_route(int M, int N, int K, int ldy, forge_act act, bool qkv, bool norm_tail, bool w8,
                  bool offset_or_scaled, size_t part_bytes) {
-  Route r = {choose_variant(M, N, K, ldy, act, qkv), {}, {1, K}, {0, 0, 0}, false, false};
+  Route r = {choose_variant(M, N, K, ldy, act, qkv), {}, {1, K}, {0, 0, 0}, false};
   const bool gated = act == FORGE_ACT_SWIGLU;
   const int ncols = gated ? 2 * N : N;
   if (r.v == V_FAST_128 || r.v == V_FAST_256) r.tile = plan_tile(M, ncols, K, r.v == V_FAST_256 ? T_256 : T_128);
   if (r.v == V_FAST_128) {
-    // Waves that share the k slabs: everywhere against few weight rows (250 drawn problems 0.9 to 2.1 times as fast as
-    // x in registers, which took them before, 1.4 in the middle); instead of a split reduction where the estimates are
-    // clearly apart, they being less sure at long K (128 rows against 4096 x 4096 23.4 | 17.5, 200 against 6144 x 4096 stays).
+    // Waves that share the k slabs: everywhere with few outputs; instead of a split reduction or a whole one where the
+    // estimates are clearly apart, they being less sure at long K (128 rows against 4096 x 4096 23.4 | 17.5, 200 against
+    // 6144 x 4096 stays).
     const WavesPlan wp = offset_or_scaled ? WavesPlan{-1, 0.0} : plan_waves(M, N, K, gated);
-    if (wp.tile >= 0 && few_weight_rows(M, ncols, K, 0)) {
-      r.few_rows = true;
+    if (wp.tile >= 0 && few_outputs(M, ncols, K, 0)) {
       r.waves = wp.tile;
       return r;
     }
     const PersSplit ps = plan_pers_split(M, ncols, K);
     if (ps.splits < 2) return r;
-    r.few_rows = wp.tile >= 0 && few_weight_rows(M, ncols, K, ps.splits);
-    if (wp.tile >= 0 && (r.few_rows || wp.us < (K <= 4096 ? 0.85 : 0.65) * pers_split_us(M, ncols, K, ps))) r.waves = wp.tile;
+    const bool few = wp.tile >= 0 && few_outputs(M, ncols, K, ps.splits);
+    if (wp.tile >= 0 && (few || wp.us < (K <= 4096 ? 0.9 : 0.82) * pers_split_us(M, ncols, K, ps))) r.waves = wp.tile;
     else if (part_bytes < (size_t)ps.splits * M * ncols * sizeof(float)) return r;
     // whole reductions where the planes and the second launch cost more than they give (1195 rows against 2048 x 2048
-    // 36 | 26, 416 against 8192 x 2048 38 | 27, 4151 against 768 x 3072 43 | 37)
-    const double whole_us = tile_us(r.tile, M, ncols, K) + (double)ncols * K * 2 * 0.27 / 6e6;     // the weight from HBM
-    if (!r.few_rows && whole_us < (r.waves >= 0 ? 0.85 * wp.us : 0.95 * pers_split_us(M, ncols, K, ps))) {
+    // 36 | 26, 416 against 8192 x 2048 38 | 27, 4151 against 768 x 3072 43 | 37).  The tiles' estimate holds for weights in
+    // the last-level cache, from HBM they take up to 1.25 of it: without the 1.1 in between, 85 of 3700 drawn
+    // problems with cold weights were more than 5 % slower than split (697 rows against 1920 x 2304 35.8 | 30.1), with it 30.
+    const double whole_us = 1.1 * tile_us(r.tile, M, ncols, K) + (double)ncols * K * 2 * 0.27 / 6e6;
+    if (!few && whole_us < (r.waves >= 0 ? 0.9 * wp.us : 0.95 * pers_split_us(M, ncols, K, ps))) {
       r.waves = -1;
       return r;
     }
@@ -1372,13 +1375,17 @@ Route plan_route(int M, int N, int K, int ldy, forge_act act, bool qkv, bool nor
     r.planes = true;
   } else if (M <= 64) {
     r.sk = plan_skinny(N, K, act, w8 ? 2 * BK : BK);
-    // outputs finished in the one launch: few rows of x in registers where that plan takes the problem; up to 4096 x 8192, the
-    // waves that share the k slabs (187 drawn problems 0.93 to 1.9 times as fast, 1.2 in the geometric mean; 24 rows
-    // against 14336 gated pairs x 4096 50.7 | 51.9, against 4096 x 14336 28.9 | 31), but not with short rows: a decode
+    // outputs finished in the one launch: few rows of x in registers where that plan takes the problem; up to 4096 x 8192
+    // the waves that share the k slabs where they are estimated faster, or that plan would write planes (740 drawn
+    // problems, weights in HBM, against the paths before: 0.89 in the geometric mean, 2 % more than 3 % slower; without
+    // the comparison 11 %: 28 rows against 3000 x 1024 5.2 | 5.8, 9 against 8192 x 4096 16.4 | 18.9); not with short rows: a decode
     // step of d_model 768 took 457 | 466 us at 8 sequences, 456 | 468 at 16, one of 2048 1406 | 1328 at 8, 2240 | 2083 at 48
     if (r.v == V_SKINNY_FAST && !norm_tail) {
-      if (!w8 && !gated && K >= 1024 && K <= 4096 && N <= 8192) r.waves = plan_waves(M, N, K, false).tile;
       r.rows = plan_rows(M, ncols, K, w8, 0, qkv);
+      if (!w8 && !gated && K >= 1024 && K <= 4096 && N <= 8192) {
+        const WavesPlan wp = plan_waves(M, N, K, false);
+        if (r.rows.ranges == 0 || 1.03 * wp.us < rows_us(M, ncols, K)) r.waves = wp.tile;
+      }
       if (r.rows.ranges > 0 || (r.sk.fused && !w8 && !qkv)) return r;
     }
     r.planes = true;

@@ -66,6 +66,7 @@ struct RowsPlan {
 // split, rotated head split), one range; otherwise of one that writes at most that many fp32 planes
 // [ranges, M, rows] for the reduce kernels (raw).
 RowsPlan plan_rows(int M, int rows, int K, bool w8, int max_ranges, bool qkv);
+double rows_us(int M, int rows, int K);                     // estimated time of one range, bf16, K >= 1024
 forge_status launch_rows(const GemmParams& p, const RowsPlan& pl, int act, bool qkv, bool raw, hipStream_t s);
 
 // ---- prompts of some hundred rows, small decode problems (gemm_bf16_waves.hip) ----------------------

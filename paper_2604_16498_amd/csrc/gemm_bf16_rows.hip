@@ -455,6 +455,15 @@ RowsPlan plan_rows(int M, int rows, int K, bool w8, int max_ranges, bool qkv) {
   return with_steps(total, ranges);
 }
 
+// The rows of x, then the tiles that a block walks, then the weight from HBM; fitted to 630 drawn problems of up to 8192
+// weight rows (within 3 % for half of them, 7 % for nine of ten).
+double rows_us(int M, int rows, int K) {
+  static constexpr double kX[] = {0.68, 1.22, 1.33}, kTile[] = {0.89, 0.84, 1.54};     // per 1024 elements of K: up to 16, 32, 64 rows
+  const int m = M > 32 ? 2 : M > 16 ? 1 : 0, per = ceil_div(ceil_div(rows, TR), compute_units());
+  const double k = K / 1024.0;
+  return 2.7 + kX[m] * k + per * (0.58 + kTile[m] * k) + (double)rows * K * 2 * 0.24 / 6e6;
+}
+
 forge_status launch_rows(const GemmParams& p, const RowsPlan& pl, int act, bool qkv, bool raw, hipStream_t s) {
   RowsParams r;
   r.g = p;

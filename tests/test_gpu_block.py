@@ -241,8 +241,8 @@ def test_model_decode_step_hidden_state_stack(F, sh_name):
 
 def test_block_wide_model_short_prompt(F):
     """A 100-token prompt through a wide layer (d_model 1024, MLP 4096): every projection has few
-    output tiles and a long reduction, so they run on the linear that keeps x in registers, chunk by
-    chunk of the rows, including the head split of the QKV projection."""
+    output tiles, so they run on the linear whose waves share the k slabs, including the head split of
+    the QKV projection."""
     sh = I.BlockShape(1024, 4, 2, 64, 4096, norm="rmsnorm", mlp_act="swiglu", use_rope=True,
                       rope_base=500000.0, has_bias=False)
     B, S = 1, 100
@@ -257,9 +257,9 @@ def test_block_wide_model_short_prompt(F):
 
 @pytest.mark.parametrize("rope", [False, True], ids=["plain", "rope"])
 def test_block_prompt_head_split_by_k_ranges(F, rope):
-    """A 100-token prompt against a 4096 x 4096 QKV weight: 32 tiles in eight k ranges, whose reduce kernel splits
+    """A 100-token prompt against a 4608 x 4096 QKV weight: 36 tiles in eight k ranges, whose reduce kernel splits
     the heads (and leaves the rotation to its own launches)."""
-    sh = I.BlockShape(4096, 16, 8, 128, 128, norm="rmsnorm", mlp_act="swiglu", use_rope=rope, rope_base=500000.0, has_bias=False)
+    sh = I.BlockShape(4096, 18, 9, 128, 128, norm="rmsnorm", mlp_act="swiglu", use_rope=rope, rope_base=500000.0, has_bias=False)
     B, S = 1, 100
     w = I.block_weights(sh, 82, 0, bf16=True, random_affine=True)
     x = I.normal(82, 0, "x", (B, S, sh.d_model), 1.0, bf16=True)
