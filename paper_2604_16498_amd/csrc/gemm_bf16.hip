@@ -1353,6 +1353,12 @@ Route plan_route(int M, int N, int K, int ldy, forge_act act, bool qkv, bool nor
     // estimates are clearly apart, they being less sure at long K (128 rows against 4096 x 4096 23.4 | 17.5, 200 against
     // 6144 x 4096 stays).
     const WavesPlan wp = offset_or_scaled ? WavesPlan{-1, 0.0} : plan_waves(M, N, K, gated);
+    double rows_prompt_us = 0.0;
+    if (wp.tile >= 0) r.rows = plan_rows_prompt(M, ncols, K, &rows_prompt_us);
+    if (r.rows.ranges > 0) {
+      if (rows_prompt_us < 0.97 * wp.us) return r;
+      r.rows = RowsPlan{0, 0, 0};
+    }
     if (wp.tile >= 0 && few_outputs(M, ncols, K, 0)) {
       r.waves = wp.tile;
       return r;

@@ -66,6 +66,7 @@ struct RowsPlan {
 // split, rotated head split), one range; otherwise of one that writes at most that many fp32 planes
 // [ranges, M, rows] for the reduce kernels (raw).
 RowsPlan plan_rows(int M, int rows, int K, bool w8, int max_ranges, bool qkv);
+RowsPlan plan_rows_prompt(int M, int rows, int K, double* us);   // 65 to 128 rows, bf16 weights
 double rows_us(int M, int rows, int K);                     // estimated time of one range, bf16, K >= 1024
 forge_status launch_rows(const GemmParams& p, const RowsPlan& pl, int act, bool qkv, bool raw, hipStream_t s);
 

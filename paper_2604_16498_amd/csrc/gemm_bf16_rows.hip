@@ -1,4 +1,4 @@
-// bf16 / weight-only-int8 linear for at most 64 rows of x (a decode step).
+// bf16 / weight-only-int8 linear for at most 64 rows of x (a decode step), and for some prompts of up to 128 rows in two chunks.
 //
 // HBM-bound: the weight is streamed once and nothing else of its size moves.  What the kernel is
 // built around is that so few rows of x fit in REGISTERS: a block of 8 waves owns one k range of up
@@ -79,7 +79,8 @@ __global__ __launch_bounds__(NW * 64) void gemm_bf16_rows_kernel(RowsParams r) {
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 15, lg = lane >> 4;
   const int N = p.N, K = p.K;
-  const int M = p.M;                                     // at most 16 MT (launch_rows)
+  const int mz = blockIdx.z * (16 * MT);                 // this block's rows of x: [mz, mz + M)
+  const int M = min(16 * MT, p.M - mz);
   const bool gated = FIN == FIN_OUT && r.act == FORGE_ACT_SWIGLU;
 
   // this wave's steps: [s0, s0 + ns) of the K / KE steps of a row (ns may be 0 in the last waves)
@@ -122,7 +123,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_bf16_rows_kernel(RowsParams r) {
     for (int i = 0; i < XL; ++i) {
       const int m = mt * 16 + (i * 64 + lane) / XCH, c = (i * 64 + lane) % XCH;
       // (rows past the end re-read the last one; skipped by a branch, they cost a wait per load)
-      xt[mt][i] = *reinterpret_cast<const u32x4*>(p.x + (int64_t)min(m, M - 1) * K + sl * C::KE + c * 8);
+      xt[mt][i] = *reinterpret_cast<const u32x4*>(p.x + (int64_t)(mz + min(m, M - 1)) * K + sl * C::KE + c * 8);
     }
 
   // weight row of the 4 consecutive rows that this lane finishes of a tile, and their output column n
@@ -241,7 +242,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_bf16_rows_kernel(RowsParams r) {
       if constexpr (RAW) {
         const int n = tile * TR + 4 * lg;
         if (m >= M || n >= r.rows) continue;
-        float* dst = p.part + ((int64_t)blockIdx.y * M + m) * r.rows + n;
+        float* dst = p.part + ((int64_t)blockIdx.y * p.M + mz + m) * r.rows + n;
         if ((r.rows & 3) == 0) *reinterpret_cast<floatx4*>(dst) = v;
         else
           for (int e = 0; e < 4 && n + e < r.rows; ++e) dst[e] = v[e];
@@ -289,10 +290,10 @@ __global__ __launch_bounds__(NW * 64) void gemm_bf16_rows_kernel(RowsParams r) {
         u32x2 pk;
         pk[0] = pack_bf2(v[0], v[1]);
         pk[1] = pack_bf2(v[2], v[3]);
-        *reinterpret_cast<u32x2*>(split_dst_bf16(p.sp, p.row0 + m, n)) = pk;
+        *reinterpret_cast<u32x2*>(split_dst_bf16(p.sp, p.row0 + mz + m, n)) = pk;
         continue;
       }
-      const int64_t out = (int64_t)m * p.ldy + n;
+      const int64_t out = (int64_t)(mz + m) * p.ldy + n;
       if (n + 4 <= N && (p.ldy & 3) == 0) {
         if (p.residual != nullptr) {
           const u32x2 rr = *reinterpret_cast<const u32x2*>(p.residual + out);
@@ -330,7 +331,8 @@ template <int MT, int STEPS, bool W8, int FIN>
 forge_status launch_fin(const RowsParams& r, int ranges, hipStream_t s) {
   // one block per CU, also where the registers would hold two: two blocks read x twice (6144 x 2048 at
   // 8 rows 10.7 us, at 9 rows and one block 9.5 us)
-  int per = ceil_div(r.tiles, max(1, compute_units() / ranges));      // tiles per block
+  const int chunks = ceil_div(r.g.M, 16 * MT);
+  int per = ceil_div(r.tiles, max(1, compute_units() / (ranges * chunks)));      // tiles per block
   if (FIN == FIN_ROPE) per = min(per, Rows<MT, STEPS, W8, FIN>::SLOTS);                // (their angles are computed once)
   auto kern = gemm_bf16_rows_kernel<MT, STEPS, W8, FIN>;
   // (more than half the LDS of a CU, whatever is needed: with two blocks resident some CUs get two and
@@ -338,7 +340,7 @@ forge_status launch_fin(const RowsParams& r, int ranges, hipStream_t s) {
   constexpr int smem = Rows<MT, STEPS, W8, FIN>::SMEM > 82 * 1024 ? Rows<MT, STEPS, W8, FIN>::SMEM : 82 * 1024;
   static std::atomic<uint64_t> lds_raised{0};   // per kernel instantiation
   if (raise_lds_limit(reinterpret_cast<const void*>(kern), smem, lds_raised) != FORGE_OK) return FORGE_ERR_HIP;
-  kern<<<dim3(ceil_div(r.tiles, per), ranges), NW * 64, smem, s>>>(r);
+  kern<<<dim3(ceil_div(r.tiles, per), ranges, chunks), NW * 64, smem, s>>>(r);
   return launch_status();
 }
 
@@ -462,6 +464,20 @@ double rows_us(int M, int rows, int K) {
   const int m = M > 32 ? 2 : M > 16 ? 1 : 0, per = ceil_div(ceil_div(rows, TR), compute_units());
   const double k = K / 1024.0;
   return 2.7 + kX[m] * k + per * (0.58 + kTile[m] * k) + (double)rows * K * 2 * 0.24 / 6e6;
+}
+
+// Prompts of 65 to 128 rows in two chunks, K of 768 to 2048: the weight is read once per chunk (the second time from cache),
+// as long as a block has few tiles to walk.  us: fitted to 420 drawn problems (within 4 % for half of them, 10 % for
+// nine of ten); plan_route takes them where the waves that share the k slabs are estimated slower (this | that: 100 rows
+// against 12288 x 1024 15.2 | 19.2, 105 against 10240 x 2048 22.3 | 27.1).  Three chunks and more gain as often as they lose
+// (553 rows against 2304 x 1536 19.2 | 22.4, 173 against 6144 x 1920 26.4 | 21.7) and stay there.
+RowsPlan plan_rows_prompt(int M, int rows, int K, double* us) {
+  const RowsPlan none = {0, 0, 0};
+  const int steps = ceil_div(K / 32, NW), per = ceil_div(ceil_div(rows, TR), compute_units() / 2);
+  if (M <= 64 || M > 128 || K % BK != 0 || steps < 4 || steps > 8 || per > 6) return none;
+  const double k = steps / 4.0;
+  *us = 2.6 + 1.68 * k + per * (0.76 + 1.22 * k) + (double)rows * K * 2 * 0.285 / 6e6;
+  return with_steps(K / 32, 1);
 }
 
 forge_status launch_rows(const GemmParams& p, const RowsPlan& pl, int act, bool qkv, bool raw, hipStream_t s) {

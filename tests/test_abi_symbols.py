@@ -150,6 +150,7 @@ def test_gemm_variant_names_the_kernel_that_runs():
     # ... where they are estimated faster than x in registers, and than planes or whole reductions on tiles
     assert v(28, 3000, 1024) == v(9, 8192, 4096) == v(18, 2560, 2048) == "gemm_bf16_rows"
     assert v(697, 1920, 2304) == v(1433, 1024, 2560) == v(276, 3840, 2560, "swiglu") == "gemm_bf16_pers<128,128,2,4>+splitk"
+    assert v(100, 12288, 1024) == v(105, 10240, 2048) == "gemm_bf16_rows"   # two chunks of 64 rows
     # decode-sized problems that stream faster slab-wise, and their neighbours that do not
     assert v(4, 15360, 5120) == v(17, 5120, 5120) == v(4, 4096, 6144) == "gemm_bf16_wstream+splitk"
     assert v(4, 16384, 3840) == v(17, 10240, 2560) == "gemm_bf16_wstream+splitk"

@@ -1,6 +1,6 @@
-"""GPU parity of the linear that keeps the rows of x in registers (decode steps), at the sizes where its
+"""GPU parity of the linear that keeps the rows of x in registers (decode steps, some prompts), at the sizes where its
 tiles (16 weight rows, 8 waves that share K, groups of 16 rows of x, up to 8 collected tiles) have
-remainders, against the fp64 oracle.  Prompts of the same widths: what takes them, and the bf16 copy of an int8 weight."""
+remainders, against the fp64 oracle.  Prompts: its two chunks of 64 rows, what takes the others, and the bf16 copy of an int8 weight."""
 import math
 
 import numpy as np
@@ -38,13 +38,19 @@ CASES = [  # M, N, K, act, residual, padded row stride
     (7, 2048, 8192, "gelu_tanh", True, 0),     # several k ranges and the reduce launch
     (40, 768, 3072, "swiglu", True, 0),
     (9, 520, 4160, "swiglu", False, 0),        # one step past a single range
-    # prompts (int8: the bf16 copy on the tile kernels)
+    # prompts in two chunks of 64 rows: ragged second chunks, odd columns in a padded stride, a ragged last tile, gated
+    (105, 8203, 2048, "silu", True, 8208),
+    (99, 10248, 1280, "relu", False, 0),
+    (114, 6144, 1280, "swiglu", True, 0),
+    (127, 10248, 1024, "none", True, 0),
+    # other prompts (int8: the bf16 copy on the tile kernels)
     (65, 2304, 768, "none", False, 0),
     (129, 1003, 704, "gelu_tanh", True, 1008),
     (300, 768, 768, "swiglu", False, 0),
     (130, 2056, 2048, "relu", True, 0),
     (200, 768, 3072, "none", True, 0),
 ]
+OTHERS = [c[:3] for c in CASES[-5:]]
 
 
 @pytest.mark.parametrize("w8", [False, True], ids=["bf16", "int8"])
@@ -64,7 +70,7 @@ def test_rows_linear(F, M, N, K, act, use_r, ld, w8):
     tw = torch.from_numpy(q).cuda() if w8 else dev(w, True)
     ts = torch.from_numpy(s).cuda() if w8 else None
     if not w8:
-        kernel = "gemm_bf16_rows" if M <= 64 else "gemm_bf16_waves"
+        kernel = "gemm_bf16_waves" if (M, N, K) in OTHERS else "gemm_bf16_rows"
         assert kernel in F.forge_gemm_variant(M, N, K, act, torch.bfloat16, ldy=ldy)
     need = F.forge_gemm_w8_workspace_bytes(M, N, K, act) if w8 else F.forge_gemm_workspace_bytes(M, N, K, act, torch.bfloat16)
     outs = []
