@@ -4,12 +4,12 @@
 //
 // Split-KV: a block (kv head, sequence, range) streams one contiguous range of cache rows of ONE kv
 // head for all G = Hq/Hkv query heads that share it (grouped-query attention reads the cache
-// once per group, not once per query head).  The 4 waves of a block take the 16-row tiles of the
-// range in turn (wave w: tiles w, w + 4, ...) and each keeps two tiles of K and V loads in flight
-// ahead of the one it is working on.  The number of splits is chosen on the host so that about
-// two blocks per compute unit exist: a large batch needs no split at all (one block per
+// once per group, not once per query head).  The 4 waves of a block (8 for some short rows) take the 16-row tiles
+// of the range in turn and each keeps two tiles of K and V loads in flight
+// ahead of the one it is working on.  The number of ranges is chosen on the host by an estimate of their time, at
+// most two blocks per compute unit: a large batch needs no split at all (one block per
 // (kv head, sequence) walks the whole cache and writes the final output itself: no partials, no
-// second kernel), a small batch is cut into ranges that are multiples of 128 rows, 256 at least.
+// second kernel), a small batch is cut into ranges that are multiples of 128 rows.
 //
 // Per tile of 16 rows:
 //   scores   S[row, head] = K . q^T on the matrix cores (v_mfma_f32_16x16x32_bf16, heads padded
@@ -277,28 +277,40 @@ __global__ __launch_bounds__(DH) void attn_decode_combine(const float* __restric
   out[((int64_t)b * q_heads + h) * DH + d] = (bf16)(o / ltot);
 }
 
-// Number of row ranges.  A block streams about 45 B/ns of cache however many waves it has, the chip 5900 (counted
-// against 0.7 of the longest cache: the lengths of a batch differ), and the merge of the ranges is a launch of
-// 4.2 us: the count with the least time, at most one block per CU (more only queue) and at least 128 rows each.
-// us, cold cache, merge included, about two blocks per CU and ranges of 256 rows at least as before | this rule: 24
-// sequences up to 1501 rows of 8 heads 30.2 (3) | 23.8 (1), 31 up to 2683 52.5 | 44.3 (1), 11 x 1612 rows of 16 heads 36.2 | 28.6 (1),
-// 5 up to 8192 rows of 8 heads 36.3 (13) | 27.1 (6), 1 x 1594 of 16 heads 10.1 (6) | 9.3 (13).
+// Number of row ranges: the count with the least estimated time.  A block alone on its CU streams 43.5 KB of cache per us
+// (rows of 64: 29, with 8 waves 42), slower with others beside it, the chip 6.5 MB (of a ragged batch 0.7 of the longest
+// cache: a guess at its lengths, which the host does not know), and the merge of the ranges is a launch of 3.5 us.  Fitted
+// by choice, not by time, to 2000 drawn caches timed at every count: 0.4 % off the best in the geometric mean, where about
+// two blocks per CU and ranges of 256 rows at least (the rule before last) were 9 % off, one block per CU and a block
+// of 45 KB per us whatever its rows (the last rule) 2.8 %, with 7 % of the caches more than 5 % slower than before it.
+// us, merge included, those two | this: 33 sequences up to 5183 rows of 4 heads of 64 34.3, 60.1 | 31.4, 20 up to 6187 of
+// 8 of 128 63.2, 76.3 | 63.1, 24 up to 1501 of 8 of 128 30.2, 23.8 | 23.8, 7 up to 8352 of 12 of 64 29.3, 38.2 | 28.8.
 struct SplitPlan { int splits, rows_per_split; };
 constexpr int MIN_CUT_ROWS = 512;         // a shorter cache is never cut, so its calls need no workspace
 // the most ranges a batch is ever cut into, whatever the cache length
 inline int max_splits(int batch, int kv_heads) {
-  return (int)max((int64_t)1, min((int64_t)MAX_SPLITS, compute_units() / ((int64_t)batch * kv_heads)));
+  return (int)min((int64_t)MAX_SPLITS, ceil_div64(2 * (int64_t)compute_units(), (int64_t)batch * kv_heads));
 }
-inline SplitPlan plan_splits(int batch, int kv_heads, int kv_len, int head_dim) {
-  const double row_bytes = head_dim * 4.0, all_us = (double)batch * kv_heads * kv_len * row_bytes * 0.7 / 5.9e6;
+// 8 waves where 4 have not enough bytes in flight: short rows, one block per CU at most, a cache of some length (us, 4 | 8:
+// 8 sequences up to 641 rows of 12 heads of 64 9.0 | 7.2, 4 x 348 6.5 | 5.8, but 25 x 743 15.0 | 16.9, 2 x 113 4.2 | 4.4)
+inline bool eight_waves(int batch, int kv_heads, int kv_len, int head_dim, int group) {
+  return head_dim == 64 && group == 1 && (int64_t)batch * kv_heads <= compute_units() && kv_len >= 256;
+}
+inline SplitPlan plan_splits(int batch, int kv_heads, int kv_len, int head_dim, int group, bool ragged) {
   SplitPlan best = {1, ceil_div(kv_len, GRAIN) * GRAIN};
   if (kv_len < MIN_CUT_ROWS) return best;
-  double least = fmax(kv_len * row_bytes / 45e3, all_us);
-  const int most = min(max_splits(batch, kv_heads), kv_len / GRAIN);
-  for (int want = 2; want <= most; ++want) {
-    const int rows = ceil_div(ceil_div(kv_len, want), GRAIN) * GRAIN;
-    const double us = fmax(rows * row_bytes / 45e3, all_us) + 4.2;
-    if (us < least) { least = us; best = SplitPlan{ceil_div(kv_len, rows), rows}; }   // rows >= kv_len / want, so splits <= want
+  const int64_t pairs = (int64_t)batch * kv_heads, cus = compute_units();
+  const double row_kb = head_dim * 4e-3, all_us = (double)pairs * kv_len * row_kb * (ragged ? 0.71 : 1.0) / 6500.0;
+  const double beside = head_dim == 64 ? 0.3 : 1.37;
+  double least = 0.0;
+  for (int want = 1, most = max(1, min(max_splits(batch, kv_heads), kv_len / GRAIN)); want <= most; ++want) {
+    const int rows = ceil_div(ceil_div(kv_len, want), GRAIN) * GRAIN, splits = ceil_div(kv_len, rows);   // splits <= want
+    const double rate = head_dim != 64 ? 43.5 : splits == 1 && eight_waves(batch, kv_heads, kv_len, head_dim, group) ? 42.0 : 29.0;
+    const int64_t on_cu = ceil_div64(pairs * splits, cus);                   // on the fullest CU; of uneven lengths, on the average
+    const double share = ragged ? fmax(1.0, (double)(pairs * splits) / cus) : (double)on_cu;
+    const double us = fmax(min(rows, kv_len) * row_kb / rate * (1.0 + beside * sqrt(share - 1.0)) + 1.2 * (on_cu - 1), all_us) +
+                      (splits > 1 ? 3.5 : 0.0);
+    if (want == 1 || us < least) { least = us; best = SplitPlan{splits, rows}; }
   }
   return best;
 }
@@ -327,9 +339,8 @@ inline int block_heads(int q_heads, int kv_heads) {
 }
 
 template <int DH, int G>
-forge_status launch_dg(const AttnArgs& a, hipStream_t s) {
+forge_status launch_dg(const AttnArgs& a, const SplitPlan& pl, hipStream_t s) {
   const int yheads = a.q_heads / G;
-  const SplitPlan pl = plan_splits(a.batch, yheads, a.kv_len, DH);
   DecParams p;
   p.q = (const bf16*)a.q;
   p.k = (const bf16*)a.k;
@@ -356,11 +367,9 @@ forge_status launch_dg(const AttnArgs& a, hipStream_t s) {
   const int64_t blocks = (int64_t)p.splits * yheads * a.batch;
   p.heads_first = (p.splits == 2 || p.splits == 4) && blocks % compute_units() != 0;
   const dim3 grid = p.heads_first ? dim3(yheads, a.batch, p.splits) : dim3(p.splits, yheads, a.batch);
-  // 8 waves where 4 have not enough bytes in flight: short rows, one block per CU at most, a cache of some length (us, 4 | 8:
-  // 8 sequences up to 641 rows of 12 heads of 64 9.0 | 7.2, 4 x 348 6.5 | 5.8, but 25 x 743 15.0 | 16.9, 2 x 113 4.2 | 4.4)
   bool eight = false;
   if constexpr (DH == 64 && G == 1) {
-    eight = p.splits == 1 && blocks <= compute_units() && a.kv_len >= 256;
+    eight = p.splits == 1 && eight_waves(a.batch, yheads, a.kv_len, DH, G);
     if (eight) attn_decode_kernel<DH, G, 8><<<grid, 8 * 64, 0, s>>>(p);
   }
   if (!eight) attn_decode_kernel<DH, G, 4><<<grid, 4 * 64, 0, s>>>(p);
@@ -372,16 +381,16 @@ forge_status launch_dg(const AttnArgs& a, hipStream_t s) {
 }
 
 template <int DH>
-forge_status launch_d(const AttnArgs& a, hipStream_t s) {
+forge_status launch_d(const AttnArgs& a, const SplitPlan& pl, hipStream_t s) {
   switch (heads_per_block(a.q_heads / a.kv_heads)) {
-    case 1: return launch_dg<DH, 1>(a, s);
-    case 2: return launch_dg<DH, 2>(a, s);
-    case 3: return launch_dg<DH, 3>(a, s);
-    case 4: return launch_dg<DH, 4>(a, s);
-    case 5: return launch_dg<DH, 5>(a, s);
-    case 6: return launch_dg<DH, 6>(a, s);
-    case 7: return launch_dg<DH, 7>(a, s);
-    case 8: return launch_dg<DH, 8>(a, s);
+    case 1: return launch_dg<DH, 1>(a, pl, s);
+    case 2: return launch_dg<DH, 2>(a, pl, s);
+    case 3: return launch_dg<DH, 3>(a, pl, s);
+    case 4: return launch_dg<DH, 4>(a, pl, s);
+    case 5: return launch_dg<DH, 5>(a, pl, s);
+    case 6: return launch_dg<DH, 6>(a, pl, s);
+    case 7: return launch_dg<DH, 7>(a, pl, s);
+    case 8: return launch_dg<DH, 8>(a, pl, s);
     default: return FORGE_ERR_UNSUPPORTED;
   }
 }
@@ -409,12 +418,14 @@ size_t attn_decode_needed_bytes(int batch, int q_heads, int kv_heads, int kv_len
 }
 
 // The size to ask for: also what any smaller batch needs, which is cut into more ranges (24 sequences of 8 heads run
-// uncut, 16 in two ranges): b * splits_bound(b) over all b <= batch is at most the CUs per head, and 64 ranges of each.
+// uncut, 16 in two ranges): b * splits_bound(b) over all b <= batch is at most b + (2 CUs - 1) / heads, and 64 ranges of each;
+// a batch of two blocks per CU is not cut.
 size_t attn_decode_workspace_bytes(int batch, int q_heads, int kv_heads, int kv_len, int head_dim) {
   if (heads_per_block(q_heads / kv_heads) == 0) return vector_group_bytes(batch, q_heads, kv_heads, kv_len, head_dim);
-  const int64_t per_head = compute_units() / block_heads(q_heads, kv_heads);
-  if (per_head < 2 || kv_len < MIN_CUT_ROWS) return 0;
-  return partial_bytes(min(per_head, (int64_t)batch * min(MAX_SPLITS, kv_len / GRAIN)) * q_heads, head_dim);
+  const int per_head = (2 * compute_units() - 1) / block_heads(q_heads, kv_heads);
+  if (per_head < 1 || kv_len < MIN_CUT_ROWS) return 0;
+  const int64_t b = min(batch, per_head);
+  return partial_bytes(min(b + per_head, b * min(MAX_SPLITS, kv_len / GRAIN)) * q_heads, head_dim);
 }
 
 // ---- scratch that nobody allocates -----------------------------------------------------------
@@ -446,11 +457,12 @@ forge_status attn_decode_static_scratch(void** ptr) {
 forge_status launch_attn_decode_bf16(const AttnArgs& a, hipStream_t s) {
   if (heads_per_block(a.q_heads / a.kv_heads) == 0) return launch_attn_simple_bf16(a, s);   // no pass count covers the group
   // what THIS launch writes (at most attn_decode_needed_bytes of any cache >= kv_len)
-  const int splits = plan_splits(a.batch, block_heads(a.q_heads, a.kv_heads), a.kv_len, a.head_dim).splits;
-  const size_t need = splits == 1 ? 0 : partial_bytes((int64_t)a.batch * a.q_heads * splits, a.head_dim);
+  const SplitPlan pl = plan_splits(a.batch, block_heads(a.q_heads, a.kv_heads), a.kv_len, a.head_dim,
+                                   heads_per_block(a.q_heads / a.kv_heads), a.kv_pos != nullptr);
+  const size_t need = pl.splits == 1 ? 0 : partial_bytes((int64_t)a.batch * a.q_heads * pl.splits, a.head_dim);
   if (need > 0 && (a.workspace == nullptr || a.workspace_bytes < need)) return FORGE_ERR_WORKSPACE;
-  if (a.head_dim == 64) return launch_d<64>(a, s);
-  if (a.head_dim == 128) return launch_d<128>(a, s);
+  if (a.head_dim == 64) return launch_d<64>(a, pl, s);
+  if (a.head_dim == 128) return launch_d<128>(a, pl, s);
   return FORGE_ERR_UNSUPPORTED;
 }
 

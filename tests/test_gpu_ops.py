@@ -372,7 +372,7 @@ ATTN_SHAPES = [  # B, Hq, Hkv, Sq, Skv, cap, dh
     # decode with many (sequence, KV head) pairs: one block walks the whole cache, no combine
     (66, 8, 8, 1, 777, 800, 64),
     (130, 8, 4, 1, 45, 64, 128),
-    # ... and with about one pair per CU: two row ranges
+    # ... and with about one pair per CU
     (33, 32, 8, 1, 1000, 1000, 128),
     # decode with 3, 5, 6, 7, 8 and 16 query heads per KV head (16: two blocks of 8 per KV head)
     (2, 64, 8, 1, 513, 520, 128),

@@ -39,8 +39,8 @@ def _case(F, seed, B, Hq, Hkv, dh, kv_len, cap):
 
 
 def test_two_calls_in_a_row_share_the_scratch(F):
-    _case(F, 91, 4, 32, 8, 128, 2049, 2100)      # 32 pairs -> 16 ranges of partials
-    _case(F, 92, 2, 8, 2, 64, 700, 704)          # smaller: 4 pairs -> 2 ranges, over the stale partials
+    _case(F, 91, 4, 32, 8, 128, 2049, 2100)      # 32 pairs, 6 ranges of partials
+    _case(F, 92, 2, 8, 2, 64, 700, 704)          # smaller: 4 pairs, 3 ranges, over the stale partials
 
 
 def test_too_large_for_the_fixed_array_is_rejected(F):
