@@ -1382,15 +1382,17 @@ Route plan_route(int M, int N, int K, int ldy, forge_act act, bool qkv, bool nor
   } else if (M <= 64) {
     r.sk = plan_skinny(N, K, act, w8 ? 2 * BK : BK);
     // outputs finished in the one launch: few rows of x in registers where that plan takes the problem; up to 4096 x 8192
-    // the waves that share the k slabs where they are estimated faster, or that plan would write planes (740 drawn
-    // problems, weights in HBM, against the paths before: 0.89 in the geometric mean, 2 % more than 3 % slower; without
-    // the comparison 11 %: 28 rows against 3000 x 1024 5.2 | 5.8, 9 against 8192 x 4096 16.4 | 18.9); not with short rows: a decode
+    // the waves that share the k slabs where they are estimated faster, or that plan would write planes (750 drawn
+    // problems replayed back to back over 3 GB of weights, against the paths before: 0.85 in the geometric mean, 0.7 % of
+    // them more than 5 % slower; 28 rows against 3000 x 1024 5.2 | 5.8 stay; single bursts after an idle card time the waves up
+    // to 15 % slower, and a whole step says otherwise: 8 sequences through 24 layers of 2048 1294 | 1339 with the up
+    // projection there); not with short rows: a decode
     // step of d_model 768 took 457 | 466 us at 8 sequences, 456 | 468 at 16, one of 2048 1406 | 1328 at 8, 2240 | 2083 at 48
     if (r.v == V_SKINNY_FAST && !norm_tail) {
       r.rows = plan_rows(M, ncols, K, w8, 0, qkv);
       if (!w8 && !gated && K >= 1024 && K <= 4096 && N <= 8192) {
         const WavesPlan wp = plan_waves(M, N, K, false);
-        if (r.rows.ranges == 0 || 1.03 * wp.us < rows_us(M, ncols, K)) r.waves = wp.tile;
+        if (r.rows.ranges == 0 || wp.us < rows_us(M, ncols, K)) r.waves = wp.tile;
       }
       if (r.rows.ranges > 0 || (r.sk.fused && !w8 && !qkv)) return r;
     }

@@ -148,7 +148,7 @@ def test_gemm_variant_names_the_kernel_that_runs():
     assert v(8, 3072, 768, "gelu_tanh") == v(64, 1001, 512) == v(5, 14336, 4096, "swiglu") == "gemm_bf16_rows"
     assert v(21, 2048, 8192) == "gemm_bf16_rows+splitk"
     # ... where they are estimated faster than x in registers, and than planes or whole reductions on tiles
-    assert v(28, 3000, 1024) == v(9, 8192, 4096) == v(18, 2560, 2048) == "gemm_bf16_rows"
+    assert v(28, 3000, 1024) == v(26, 2560, 1280) == "gemm_bf16_rows" and waves(21, 8192, 2048)
     assert v(697, 1920, 2304) == v(1433, 1024, 2560) == v(276, 3840, 2560, "swiglu") == "gemm_bf16_pers<128,128,2,4>+splitk"
     assert v(100, 12288, 1024) == v(105, 10240, 2048) == "gemm_bf16_rows"   # two chunks of 64 rows
     # decode-sized problems that stream faster slab-wise, and their neighbours that do not
