@@ -370,15 +370,17 @@ forge_status launch_waves(int cb, const float* x, const float* w, const float* b
 // of 32 x 32 and 32 x 16; us, 64 x 64 with its reduce | wave-shared: 128 rows against 2304 x 768 15.1 | 10.6, 768 x 768 9.8 | 5.2,
 // 3072 x 768 18.1 | 10.9, 768 x 3072 17.4 | 12.9; 512 rows against 3072 x 768 34.3 | 29.4, 2048 rows 99 | 108, 256 rows
 // against 6144 x 72 9.2 | 10.1).  A long reduction with few tiles stays cut over the grid (64 rows against 768 x 8192
-// 21.9 | 28.7, 256 x 4096 at one row 13.8 | 15.0; from 24 tiles on 32.7 | 30.5).
-constexpr int LONG_K = 3072, FEW_TILES = 16;
+// 21.9 | 28.7, 256 x 4096 at one row 13.8 | 15.0; from 24 tiles on 32.7 | 30.5), a gated one sooner (24 rows against 256 pairs x
+// 2560 15.7 | 19.3).  Past four rounds the last one no longer counts as whole: blocks of 64 x 64 share CUs (1063 rows
+// against 6144 x 512 70 | 82).
+inline int few_tiles(int K, bool gated) { return K > 3072 ? 16 : gated && K > 2304 ? 8 : 0; }
 int plan_waves(int M, int N, int K, bool gated) {
   const int64_t rows = gated ? 2 * (int64_t)N : N;
   if ((int64_t)M * K >= (1ll << 30) || rows * K >= (1ll << 30)) return 0;       // 32-bit byte offsets
   const int64_t cus = compute_units(), slabs = ceil_div(K, BK), slabs8 = (slabs + 7) / 8 * 8;
   const int64_t t64 = (int64_t)ceil_div(M, BM) * ceil_div(N, BN), mt = ceil_div(M, FM);
-  if ((K > LONG_K && t64 <= FEW_TILES) || mt > 65535) return 0;
-  const int64_t c64 = ceil_div64(t64, cus) * slabs * (gated ? 14 : 7) + 45;
+  if (t64 <= few_tiles(K, gated) || mt > 65535) return 0;
+  const int64_t slab64 = slabs * (gated ? 14 : 7), c64 = (t64 > 4 * cus ? t64 * slab64 / cus : ceil_div64(t64, cus) * slab64) + 45;
   const int64_t c2 = ceil_div64(mt * ceil_div64(rows, 32), cus) * slabs8 * 19 / 10 + 22;
   const int64_t c1 = gated ? c2 : ceil_div64(mt * ceil_div64(N, 16), cus) * slabs8 * 12 / 10 + 21;
   if (c64 < c2 && c64 < c1) return 0;
@@ -398,7 +400,7 @@ static size_t planes_bytes(int M, int N, int K, forge_act act) {
 // problem serves the smaller ones.
 size_t gemm_f32_workspace_bytes(int M, int N, int K, forge_act act) {
   const size_t own = planes_bytes(M, N, K, act);
-  const int cut_rows = K > LONG_K ? FEW_TILES / ceil_div(N, BN) * BM : 0;      // the most rows that are cut
+  const int cut_rows = few_tiles(K, act == FORGE_ACT_SWIGLU) / ceil_div(N, BN) * BM;      // the most rows that are cut
   return M > cut_rows && cut_rows > 0 ? max(own, planes_bytes(cut_rows, N, K, act)) : own;
 }
 

@@ -168,4 +168,5 @@ def test_gemm_variant_names_the_kernel_that_runs():
     assert v(64, 4096, 72) == "gemm_bf16_generic<64,64,2,2>+splitk"
     f = lambda M, N, K, act="none": F.forge_gemm_variant(M, N, K, act, torch.float32)
     assert f(128, 768, 768) == "gemm_f32_waves<1>" and f(128, 768, 768, "swiglu") == "gemm_f32_waves<2>"
-    assert f(64, 768, 8192) == "gemm_f32<64,64,2,2>+splitk" and f(2048, 3072, 768) == "gemm_f32<64,64,2,2>"
+    assert f(64, 768, 8192) == f(24, 256, 2560, "swiglu") == "gemm_f32<64,64,2,2>+splitk"
+    assert f(1063, 6144, 512) == f(2048, 3072, 768) == "gemm_f32<64,64,2,2>"
