@@ -115,13 +115,16 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : DH == 128 || MASKED ? 
   int qb = p.n_qblocks - 1 - at / pairs;
   int h = at % pairs % p.q_heads, b = at % pairs / p.q_heads;
   if (MASKED && p.mask_hs == 0) {
-    // One mask for all heads: the heads of a query block run side by side on one XCD (blocks are dealt round-robin
-    // over the 8), whose L2 then fetches those mask rows once; dealt over all of them, every L2 fetched
-    // the whole mask (8 x 12 heads x 1000: 83 -> 70 us by this alone).
-    const int n = gridDim.x, xcd = at & 7, item = xcd * (n >> 3) + min(xcd, n & 7) + (at >> 3);
+    // One mask for all heads: within a row of query blocks, those of neighbouring heads run on one XCD (blocks are dealt
+    // round-robin over the 8), whose L2 then fetches their mask rows once; dealt over all of them, every L2 fetched
+    // the whole mask (8 x 12 heads x 1000: 83 -> 70 us by this alone).  Every XCD gets its share of each row, so that a last
+    // row that is mostly padding does not leave some of them idle (3 x 64 heads of 128 x 541 90 us with whole rows per XCD, 81).
+    // Blocks r of this row with (r + o) % 8 == x are XCD x's; the k-th of them is pair (those of the XCDs before) + k.
+    const int o = (at - at % pairs) & 7, x = at & 7, r = at % pairs;
+    int item = r >> 3;
+    for (int y = 0; y < x; ++y) item += (pairs - ((y - o) & 7) + 7) >> 3;
     h = item % p.q_heads;
-    qb = p.n_qblocks - 1 - item / p.q_heads % p.n_qblocks;
-    b = item / p.q_heads / p.n_qblocks;
+    b = item / p.q_heads;
   }
   const int g = h / (p.q_heads / p.kv_heads);
   const int q0 = qb * BQ, q0w = q0 + wave * 32;
