@@ -573,7 +573,12 @@ forge_status launch_dh(const AttnArgs& a, hipStream_t s) {
   }
   if constexpr (DH == 128) {
     // (the mask's registers leave no room for a second block; 16 heads x 1000 46 | 36, 3 x 16 x 700, 288 blocks of 4 waves, 36 | 40)
-    if (MASKED ? query_blocks(a.batch, a.q_heads, a.q_len, 4) > cus : eight_waves(a.batch, a.q_heads, a.q_len))
+    // blocks of one length (no causal cut, or few new queries) that are one round of 8 waves or less, and more than one per CU
+    // of 4: the half-filled CUs of the smaller blocks cost more than the larger ones' idle ones (us, 4 waves | 8, not causal:
+    // 16 heads x 2499 behind 2502 keys 158 | 139, 3 x 16 x 944 38.8 | 35.2, 5 x 32 x 134 behind 670 33.3 | 29.4)
+    const bool even = !a.causal || a.kv_len / 3 >= a.q_len;
+    const int64_t blocks4 = query_blocks(a.batch, a.q_heads, a.q_len, 4), blocks8 = query_blocks(a.batch, a.q_heads, a.q_len, 8);
+    if (MASKED ? blocks4 > cus : eight_waves(a.batch, a.q_heads, a.q_len) || (even && blocks4 > cus && blocks8 <= cus))
       return launch_split<DH, MASKED, false, 8>(a, 1, s);
   }
   return launch_split<DH, MASKED, false, 4>(a, 1, s);

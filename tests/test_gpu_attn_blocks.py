@@ -27,6 +27,8 @@ def _qkv(B, Hq, Hkv, Sq, Skv, dh):
     (1, 4, 4, 33, 1100, 64), (1, 6, 2, 130, 1500, 128),
     # 8 waves: shares behind 2500 keys and more, then whole query blocks well past one round
     (1, 64, 16, 480, 2600, 128), (4, 95, 19, 250, 250, 128),
+    # ... blocks of even length in less than one round of 8 waves, more than one per CU of 4
+    (5, 32, 8, 134, 804, 128),
 ])
 def test_query_blocks(B, Hq, Hkv, Sq, Skv, dh):
     from paper_2604_16498_amd import binding as F
