@@ -34,7 +34,7 @@
 // the same sequence HALF A TILE APART: while one is in its vector phase the other is in its matrix
 // phase.  A block barrier ends every half tile.  Only one set of score registers is alive per wave.
 //
-// LDS: K tile rows padded by 16 B and V tile rows by 64 B so that the row reads (K) and the
+// LDS: K tile rows padded by 16 B and V tile rows by 64 B (32 at head_dim 64) so that the row reads (K) and the
 // 4-rows-by-64-B transposing reads (V) of a half wave fall on disjoint banks; two buffers each.
 // Tiles go HBM -> registers -> LDS, moved by the early waves (0-3): K(t+1) is stored at the start of
 // the softmax step of tile t and the loads of K(t+2) go out right behind it, V likewise at the start
