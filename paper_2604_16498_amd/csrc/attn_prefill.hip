@@ -536,13 +536,18 @@ inline int plan_shares(int batch, int q_heads, int q_len, int kv_len, int head_d
   return best;
 }
 
-// head_dim 128: blocks of 8 waves where they fill the chip.  With key shares: at least 2500 keys, query blocks not mostly
-// padding (us, 8 waves | 4: 777 queries behind 2500 keys 67.4 | 70, 1024 behind 3072 84 | 91, but 600 behind 2900 66 | 58,
+// head_dim 128: blocks of 8 waves where they fill the chip.  With key shares: at least 1700 keys, query blocks not mostly
+// padding, nine tenths of the chip, or of up to three shares seven tenths without the padding (us, 8 waves | 4, 32 heads: 988
+// queries over 1564 keys 41.3 | 40.5, 777 over 1777 44.6 | 46.6, over 3277 67.4 | 70, 512 over 2012 34.4 | 35.7, 1024 over
+// 2424 53.5 | 59.1, over 4096 84 | 91; 12 heads x 1533 over 2481, 216 blocks, 40.0 | 43.5, 2 x 16 x 750 over 1953, 192 blocks,
+// 43.6 | 48.5; but 256 over 2056, 224 blocks in seven shares, 28.1 | 25.8, 600 over 3500, 192 with padding, 66 | 58,
 // 300 behind 3700 49 | 46).  Unsplit: whole query blocks, well past one round of them (32 heads x 4000 153 | 167, 3 x 16 x 2048
 // 71 | 75, but 32 x 2500, 1.25 rounds, 84 | 76, 3 x 32 x 1300, 15 % padding, 84 | 75, 32 x 2048, one round, 65 | 58).
 inline bool eight_waves_split(int batch, int q_heads, int q_len, int kv_len, int shares) {
-  return shares > 1 && kv_len >= 2500 && q_len * 10 >= ceil_div(q_len, 256) * 256 * 7 &&
-         query_blocks(batch, q_heads, q_len, 8) * shares * 10 >= (int64_t)compute_units() * 9;
+  if (shares < 2 || kv_len < 1700 || q_len * 10 < ceil_div(q_len, 256) * 256 * 7) return false;
+  const int64_t cus = compute_units();
+  return query_blocks(batch, q_heads, q_len, 8) * shares * 10 >= cus * 9 ||
+         (shares <= 3 && (int64_t)batch * q_heads * q_len * shares * 10 >= cus * 256 * 7);
 }
 inline bool eight_waves(int batch, int q_heads, int q_len) {
   return (int64_t)q_len * 100 >= (int64_t)ceil_div(q_len, 256) * 256 * 93 &&

@@ -25,8 +25,8 @@ def _qkv(B, Hq, Hkv, Sq, Skv, dh):
     (3, 48, 48, 127, 127, 64), (4, 40, 8, 129, 129, 64), (4, 34, 34, 128, 200, 128), (2, 50, 10, 193, 193, 128),
     # 4 waves with shares: the last share short, heads of both sizes
     (1, 4, 4, 33, 1100, 64), (1, 6, 2, 130, 1500, 128),
-    # 8 waves: shares behind 2500 keys and more, then whole query blocks well past one round
-    (1, 64, 16, 480, 2600, 128), (4, 95, 19, 250, 250, 128),
+    # 8 waves: shares, of nine tenths of the chip and of less (the edge in keys too), then whole query blocks well past one round
+    (1, 64, 16, 480, 2600, 128), (1, 32, 8, 512, 1700, 128), (2, 16, 4, 750, 1953, 128), (4, 95, 19, 250, 250, 128),
     # ... blocks of even length in less than one round of 8 waves, more than one per CU of 4
     (5, 32, 8, 134, 804, 128),
 ])
