@@ -204,9 +204,10 @@ __global__ __launch_bounds__(256) void gemm_f32_reduce_kernel(
 // wave order at the end, where the outputs are finished.  v_mfma_f32_16x16x4_f32: lane l supplies row
 // l%16 and the k of its quarter, 8 (l/16) ... + 7 of the slab.  The gated activation takes 16 gate rows and
 // their 16 up rows as the two column blocks.
-// Bound by the LDS (16 KB written and read per 32 x 32 x 32 products: 64 of 128 B/clk at the full matrix rate) and by the
-// start of a block (5 us for 768 k, 1.3 of them matrix work): tiles of 64 x 32 and 64 x 64 halve the LDS traffic and are
-// slower (2304 x 768 at 128 rows 11.9 and 22 us against 10.6), two blocks per CU need the 128 registers.
+// Bound by latency: the start of a block (5 us for 768 k, 1.3 of them matrix work) and the chain load, patch, product of
+// each slab.  Counted at 128 rows against 2304 x 768 and 3072 x 768: matrix units 14 and 18 % busy, LDS 2.5 and 3.4 us of
+// the 14.3 and 13.9 us under a profiler (a quarter of that bank conflicts).  Tiles of 64 x 32 and 64 x 64 halve the LDS
+// traffic and are slower (2304 x 768 at 128 rows 11.9 and 22 us against 10.6); two blocks per CU need the 128 registers.
 // The four products of a 128-row layer of 768 (MLP 3072): 60.4 us with their reduce launches before, 39.6 now; the layer 76.8 -> 57.6.
 constexpr int FW = 8;                                // waves per block
 constexpr int FM = 32, RB = FM / 16;                 // rows of x per block
