@@ -20,6 +20,7 @@ namespace forge {
 namespace {
 
 constexpr int NW = 8;                                // waves per block
+constexpr int DEPTH = 2;                             // slabs in flight per wave
 constexpr int LDB = BK * 2 + 16;                     // bytes of a patch row: 64 bf16 and padding (conflict-free 128-bit accesses)
 
 struct WavesParams {
@@ -28,25 +29,24 @@ struct WavesParams {
   int qkv;                                           // head split
 };
 
-template <int RB, int CB, bool GATED>
+// SHORT: no wave has more than DEPTH slabs; otherwise every wave has DEPTH at least
+template <int RB, int CB, bool GATED, bool SHORT>
 __global__ __launch_bounds__(NW * 64, RB * CB <= 4 ? 4 : 2) void gemm_bf16_waves_kernel(WavesParams r) {
   const GemmParams& p = r.g;
   constexpr int FM = 16 * RB, WR = 16 * CB;          // rows of x, weight rows
   constexpr int OUT = GATED ? WR / 2 : WR;           // output columns
-  constexpr int DEPTH = 2;                           // slabs in flight per wave
   constexpr int PATCH = (FM + WR) * LDB;             // bytes
   constexpr int LDR = WR + 4;                        // floats of a row of a partial tile
   static_assert(FM * LDR * 4 <= PATCH, "the partial tiles fit where the patches lie");
   extern __shared__ __attribute__((aligned(16))) char smem[];   // [NW * PATCH]
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int M = p.M, N = p.N, K = p.K;
   const int m0 = blockIdx.y * FM, n0 = blockIdx.x * OUT;
   char* const ax = smem + wave * PATCH;
   char* const bx = ax + FM * LDB;
 
-  // loads: 8 lanes per row piece, unconditional from clamped addresses (rows past the end re-read the last one,
-  // their outputs are dropped; a slab past the end is not multiplied)
+  // loads: 8 lanes per row piece, from clamped addresses (rows past the end re-read the last one, their outputs are dropped)
   const int lrow = lane >> 3, lcol = (lane & 7) * 16;
   uint32_t xsrc[FM / 8], wsrc[WR / 8];               // byte offsets (operands below 4 GB: choose_variant)
 #pragma unroll
@@ -57,30 +57,15 @@ __global__ __launch_bounds__(NW * 64, RB * CB <= 4 ? 4 : 2) void gemm_bf16_waves
     const int row = GATED ? min(n0 + rr % OUT, N - 1) + (rr >= OUT ? N : 0) : min(n0 + rr, N - 1);
     wsrc[i] = (uint32_t)row * (uint32_t)K * 2 + lcol;
   }
-  const int slabs = K / BK;
+  const int slabs = K / BK, n_slabs = slabs > wave ? (slabs - wave - 1) / NW + 1 : 0;   // of them this wave's
   u32x4 va[DEPTH][FM / 8], vb[DEPTH][WR / 8];
-  auto load = [&](int slab, int slot) {
-    const uint32_t at = (uint32_t)min(slab, slabs - 1) * (BK * 2);
+  auto load = [&](int i, int slot) {                 // this wave's slab i
+    const uint32_t at = (uint32_t)min(wave + i * NW, slabs - 1) * (BK * 2);
 #pragma unroll
     for (int i = 0; i < WR / 8; ++i) vb[slot][i] = *reinterpret_cast<const u32x4*>((const char*)p.w + (wsrc[i] + at));
 #pragma unroll
     for (int i = 0; i < FM / 8; ++i) va[slot][i] = *reinterpret_cast<const u32x4*>((const char*)p.x + (xsrc[i] + at));
   };
-  // bias and residual of the outputs that this thread finishes, fetched long before they are needed
-  constexpr int ITEMS = (FM * OUT / 4 + NW * 64 - 1) / (NW * 64);
-  const bool vec = (N & 3) == 0 && (p.ldy & 3) == 0;
-  u32x2 bi[ITEMS], ub[ITEMS], rv[ITEMS];
-#pragma unroll
-  for (int it = 0; it < ITEMS; ++it) {
-    const int at = tid + it * NW * 64, m = m0 + at / (OUT / 4), n = n0 + at % (OUT / 4) * 4;
-    bi[it] = ub[it] = rv[it] = u32x2{0, 0};
-    if (!vec || at >= FM * OUT / 4 || m >= M || n >= N) continue;
-    if (p.bias != nullptr) {
-      bi[it] = *reinterpret_cast<const u32x2*>(p.bias + n);
-      if (GATED) ub[it] = *reinterpret_cast<const u32x2*>(p.bias + N + n);
-    }
-    if (p.residual != nullptr) rv[it] = *reinterpret_cast<const u32x2*>(p.residual + (int64_t)m * p.ldy + n);
-  }
 
   floatx4 acc[RB][CB];
 #pragma unroll
@@ -89,34 +74,70 @@ __global__ __launch_bounds__(NW * 64, RB * CB <= 4 ? 4 : 2) void gemm_bf16_waves
     for (int c = 0; c < CB; ++c) acc[i][c] = floatx4{0.f, 0.f, 0.f, 0.f};
 
   const int fr = lane & 15, fg = lane >> 4;
+  auto multiply = [&](int d) {
+    __builtin_amdgcn_sched_barrier(0);               // (mixed with its neighbours' loads and stores a slab wants twice the registers)
+    wave_lds_sync();                                 // the previous slab has been read
 #pragma unroll
-  for (int d = 0; d < DEPTH; ++d) load(wave + d * NW, d);
-  for (int s0 = wave; s0 < slabs; s0 += DEPTH * NW) {
+    for (int i = 0; i < FM / 8; ++i) *reinterpret_cast<u32x4*>(ax + (lrow + 8 * i) * LDB + lcol) = va[d][i];
 #pragma unroll
-    for (int d = 0; d < DEPTH; ++d) {
-      const int slab = s0 + d * NW;
-      if (slab < slabs) {                            // wave-uniform
-        wave_lds_sync();                             // the previous slab has been read
+    for (int i = 0; i < WR / 8; ++i) *reinterpret_cast<u32x4*>(bx + (lrow + 8 * i) * LDB + lcol) = vb[d][i];
+    wave_lds_sync();
 #pragma unroll
-        for (int i = 0; i < FM / 8; ++i) *reinterpret_cast<u32x4*>(ax + (lrow + 8 * i) * LDB + lcol) = va[d][i];
+    for (int k = 0; k < 2; ++k) {
+      bf16x8 xf[RB], wf[CB];
 #pragma unroll
-        for (int i = 0; i < WR / 8; ++i) *reinterpret_cast<u32x4*>(bx + (lrow + 8 * i) * LDB + lcol) = vb[d][i];
-        wave_lds_sync();
+      for (int i = 0; i < RB; ++i) xf[i] = *reinterpret_cast<const bf16x8*>(ax + (16 * i + fr) * LDB + (4 * k + fg) * 16);
 #pragma unroll
-        for (int k = 0; k < 2; ++k) {
-          bf16x8 xf[RB], wf[CB];
+      for (int c = 0; c < CB; ++c) wf[c] = *reinterpret_cast<const bf16x8*>(bx + (16 * c + fr) * LDB + (4 * k + fg) * 16);
 #pragma unroll
-          for (int i = 0; i < RB; ++i) xf[i] = *reinterpret_cast<const bf16x8*>(ax + (16 * i + fr) * LDB + (4 * k + fg) * 16);
+      for (int i = 0; i < RB; ++i)
 #pragma unroll
-          for (int c = 0; c < CB; ++c) wf[c] = *reinterpret_cast<const bf16x8*>(bx + (16 * c + fr) * LDB + (4 * k + fg) * 16);
-#pragma unroll
-          for (int i = 0; i < RB; ++i)
-#pragma unroll
-            for (int c = 0; c < CB; ++c) acc[i][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[c], xf[i], acc[i][c], 0, 0, 0);
-        }
-      }
-      load(slab + DEPTH * NW, d);                    // into the registers just consumed
+        for (int c = 0; c < CB; ++c) acc[i][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[c], xf[i], acc[i][c], 0, 0, 0);
     }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // bias and residual of the outputs that this thread finishes: requested behind the first slabs, long before they are
+  // needed.  Unconditional (a load under a branch would make every wait behind it a full one): what is not there is read
+  // from the weight and dropped.
+  constexpr int ITEMS = (FM * OUT / 4 + NW * 64 - 1) / (NW * 64);
+  const bool vec = (N & 3) == 0 && (p.ldy & 3) == 0;
+  const bool has_bias = vec && p.bias != nullptr, has_res = vec && p.residual != nullptr;
+  u32x2 bi[ITEMS], ub[ITEMS], rv[ITEMS];
+  auto fetch_ends = [&] {
+    const bf16* const bsrc = has_bias ? p.bias : p.w;
+    const bf16* const rsrc = has_res ? p.residual : p.w;
+    const int ldb = has_bias ? -1 : 0, ldr = has_res ? -1 : 0;     // masks of the offsets
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it) {
+      const int at = min(tid + it * NW * 64, FM * OUT / 4 - 1);
+      const int m = min(m0 + at / (OUT / 4), M - 1), n = min(n0 + at % (OUT / 4) * 4, N - 4);
+      bi[it] = *reinterpret_cast<const u32x2*>(bsrc + (n & ldb));
+      if (GATED) ub[it] = *reinterpret_cast<const u32x2*>(bsrc + ((N + n) & ldb));
+      rv[it] = *reinterpret_cast<const u32x2*>(rsrc + (int64_t)(m & ldr) * p.ldy + (n & ldr));
+    }
+  };
+  // No slab past the end is loaded but one where the count is odd: at most DEPTH slabs per wave are straight code, and the loop
+  // runs at least once and is followed by the last slabs.  (As one loop that always refills, 768 of K were 32 slabs of requests
+  // instead of 16, and a loop that may be skipped makes the compiler copy the slabs in flight, a wait for each: 128 rows against
+  // 2304 x 768 6.8 -> 5.95 us, 3072 x 768 7.1 -> 6.4, 768 x 3072 8.0 -> 7.8, 256 x 2048 x 2048 10.6 -> 9.9.)
+  load(0, 0);
+  load(1, 1);
+  fetch_ends();
+  if constexpr (SHORT) {
+    if (0 < n_slabs) multiply(0);                    // (wave-uniform)
+    if (1 < n_slabs) multiply(1);
+  } else {                                           // (n_slabs >= DEPTH)
+    int i = DEPTH;
+#pragma unroll 1
+    do {
+      multiply(0);
+      load(i, 0);
+      multiply(1);
+      load(i + 1, 1);
+      i += DEPTH;
+    } while (i < n_slabs);
+    if (i - 2 < n_slabs) multiply(0);
+    if (i - 1 < n_slabs) multiply(1);
   }
 
   // ---- the 8 partial tiles, added in wave order; accumulator: row lane % 16, columns 4 (lane / 16) ... + 3 ------
@@ -139,7 +160,7 @@ __global__ __launch_bounds__(NW * 64, RB * CB <= 4 ? 4 : 2) void gemm_bf16_waves
       v += *reinterpret_cast<const floatx4*>(src);
       if (GATED) u += *reinterpret_cast<const floatx4*>(src + OUT * 4);
     }
-    if (vec) {
+    if (has_bias) {
       v += unpack(bi[it]);
       if (GATED) u += unpack(ub[it]);
     } else if (p.bias != nullptr) {
@@ -161,7 +182,7 @@ __global__ __launch_bounds__(NW * 64, RB * CB <= 4 ? 4 : 2) void gemm_bf16_waves
     }
     bf16* dst = r.qkv ? split_dst_bf16(p.sp, p.row0 + m, n) : p.y + (int64_t)m * p.ldy + n;   // 4 columns stay inside a head
     if (vec) {
-      if (p.residual != nullptr) v += unpack(rv[it]);
+      if (has_res) v += unpack(rv[it]);
       *reinterpret_cast<u32x2*>(dst) = u32x2{pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3])};
     } else {
       const bf16* res = p.residual != nullptr ? p.residual + (int64_t)m * p.ldy + n : nullptr;
@@ -170,14 +191,20 @@ __global__ __launch_bounds__(NW * 64, RB * CB <= 4 ? 4 : 2) void gemm_bf16_waves
   }
 }
 
-template <int RB, int CB, bool GATED>
-forge_status launch_tile(const WavesParams& r, hipStream_t s) {
+template <int RB, int CB, bool GATED, bool SHORT>
+forge_status launch_slabs(const WavesParams& r, hipStream_t s) {
   constexpr int smem = NW * 16 * (RB + CB) * LDB;
-  auto kern = gemm_bf16_waves_kernel<RB, CB, GATED>;
+  auto kern = gemm_bf16_waves_kernel<RB, CB, GATED, SHORT>;
   static std::atomic<uint64_t> lds_raised{0};        // per kernel instantiation
   if (raise_lds_limit(reinterpret_cast<const void*>(kern), smem, lds_raised) != FORGE_OK) return FORGE_ERR_HIP;
   kern<<<dim3(ceil_div(r.g.N, GATED ? 8 * CB : 16 * CB), ceil_div(r.g.M, 16 * RB)), NW * 64, smem, s>>>(r);
   return launch_status();
+}
+
+template <int RB, int CB, bool GATED>
+forge_status launch_tile(const WavesParams& r, hipStream_t s) {
+  if (r.g.K / BK <= DEPTH * NW) return launch_slabs<RB, CB, GATED, true>(r, s);
+  return launch_slabs<RB, CB, GATED, false>(r, s);
 }
 
 }  // namespace

@@ -22,19 +22,17 @@ namespace {
 
 constexpr int BM = 64, BN = 64, BK = 32, LDK = BK + 4;
 
+// (head_dim is 64 or 128: shifts instead of divisions)
 __device__ inline void* split_dst(const QkvSplit& sp, int m, int n, size_t esz) {
-  const int dh = sp.head_dim;
-  const int b = m / sp.q_len, s = m % sp.q_len;
-  const int nq = sp.q_heads * dh, nk = sp.kv_heads * dh;
-  if (n < nq) {
-    const int h = n / dh;
-    return (char*)sp.q + ((((int64_t)b * sp.q_heads + h) * sp.q_len + s) * dh + n % dh) * esz;
-  }
-  const bool is_k = n < nq + nk;
-  const int nn = is_k ? n - nq : n - nq - nk;
-  const int h = nn / dh;
-  char* basep = (char*)(is_k ? sp.k_cache : sp.v_cache);
-  return basep + ((((int64_t)b * sp.kv_heads + h) * sp.kv_cap + seq_position(sp.pos, b, sp.pos0) + s) * dh + nn % dh) * esz;
+  const int dh = sp.head_dim, shift = __builtin_ctz(dh), c = n & (dh - 1);
+  const int b = sp.q_len == 1 ? m : m / sp.q_len, s = sp.q_len == 1 ? 0 : m - b * sp.q_len;
+  int h = n >> shift;
+  if (h < sp.q_heads) return (char*)sp.q + (((((int64_t)b * sp.q_heads + h) * sp.q_len + s) << shift) + c) * esz;
+  h -= sp.q_heads;
+  const bool is_k = h < sp.kv_heads;
+  h -= is_k ? 0 : sp.kv_heads;
+  char* const base = (char*)(is_k ? sp.k_cache : sp.v_cache);
+  return base + (((((int64_t)b * sp.kv_heads + h) * sp.kv_cap + seq_position(sp.pos, b, sp.pos0) + s) << shift) + c) * esz;
 }
 
 template <int ACT, bool SPLIT>
@@ -212,7 +210,10 @@ __global__ __launch_bounds__(256) void gemm_f32_reduce_kernel(
 constexpr int FW = 8;                                // waves per block
 constexpr int FM = 32, RB = FM / 16;                 // rows of x per block
 
-template <int CB, int ACT, bool SPLIT>
+constexpr int slabs_in_flight(int cb) { return cb == 1 ? 3 : 2; }   // per wave (128 registers: two blocks per CU)
+
+// SHORT: no wave has more than DEPTH slabs; otherwise every wave has DEPTH at least
+template <int CB, int ACT, bool SPLIT, bool SHORT>
 __global__ __launch_bounds__(FW * 64, 4) void gemm_f32_waves_kernel(
     const float* __restrict__ x, const float* __restrict__ w, const float* __restrict__ bias,
     const float* residual, float* y, int M, int N, int K, int ldy, QkvSplit sp) {
@@ -220,14 +221,14 @@ __global__ __launch_bounds__(FW * 64, 4) void gemm_f32_waves_kernel(
   static_assert(!SWIGLU || CB == 2, "gate and up rows are the two column blocks");
   constexpr int WR = 16 * CB;                        // weight rows per block
   constexpr int OUT = SWIGLU ? 16 : WR;              // output columns per block
-  constexpr int DEPTH = CB == 1 ? 3 : 2;             // slabs in flight per wave (128 registers: two blocks per CU)
+  constexpr int DEPTH = slabs_in_flight(CB);
   constexpr int CHAINS = CB == 1 ? 4 : 2;            // sums per output of a wave: shorter chains, smaller rounding error
   constexpr int PATCH = (FM + WR) * LDK;             // floats of one wave's patch; rows padded as above
   constexpr int LDR = WR + 4;                        // row of a partial tile
   static_assert(FM * LDR <= PATCH, "the partial tiles fit where the patches lie");
   extern __shared__ __attribute__((aligned(16))) float lds[];   // [FW * PATCH]
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int m0 = blockIdx.y * FM, n0 = blockIdx.x * OUT;
   float* const ax = lds + wave * PATCH;
   float* const bx = ax + FM * LDK;
@@ -260,40 +261,75 @@ __global__ __launch_bounds__(FW * 64, 4) void gemm_f32_waves_kernel(
 #pragma unroll
       for (int j = 0; j < CB; ++j) acc[h][i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
 
+  auto multiply = [&](int i, int d) {                // slab i of this wave, from slot d
+    __builtin_amdgcn_sched_barrier(0);               // (mixed with its neighbours' loads and stores a slab wants more registers)
+    const bool k_ok = (wave + i * FW) * BK + lcol < K;
+    const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
+    wave_lds_sync();                                 // the previous slab has been read
+#pragma unroll
+    for (int i = 0; i < FM / 8; ++i) *reinterpret_cast<floatx4*>(ax + (lrow + 8 * i) * LDK + lcol) = k_ok ? va[d][i] : zero;
+#pragma unroll
+    for (int i = 0; i < WR / 8; ++i) *reinterpret_cast<floatx4*>(bx + (lrow + 8 * i) * LDK + lcol) = k_ok ? vb[d][i] : zero;
+    wave_lds_sync();
+    const int r = lane & 15, kq = (lane >> 4) * 8;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      floatx4 a[RB], b[CB];
+#pragma unroll
+      for (int i = 0; i < RB; ++i) a[i] = *reinterpret_cast<const floatx4*>(ax + (16 * i + r) * LDK + kq + 4 * j);
+#pragma unroll
+      for (int c = 0; c < CB; ++c) b[c] = *reinterpret_cast<const floatx4*>(bx + (16 * c + r) * LDK + kq + 4 * j);
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int i = 0; i < RB; ++i)
+#pragma unroll
+          for (int c = 0; c < CB; ++c)
+            acc[(j + 2 * e) % CHAINS][i][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][e], b[c][e], acc[(j + 2 * e) % CHAINS][i][c], 0, 0, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // bias and residual of the outputs that this thread finishes, behind the first slabs: unconditional (a load under a branch would
+  // make every wait behind it a full one), what is not there is read from the weight and dropped
+  constexpr int ITEMS = FM * OUT / (FW * 64);
+  const int has_bias = bias != nullptr ? -1 : 0, has_res = residual != nullptr ? -1 : 0;      // masks of the offsets
+  float bi[ITEMS], ub[ITEMS], rv[ITEMS];
+  auto fetch_ends = [&] {
+    const float* const bsrc = has_bias ? bias : w;
+    const float* const rsrc = has_res ? residual : w;
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it) {
+      const int at = tid + it * FW * 64, m = min(m0 + at / OUT, M - 1), n = min(n0 + at % OUT, N - 1);
+      bi[it] = bsrc[n & has_bias];
+      if (SWIGLU) ub[it] = bsrc[(N + n) & has_bias];
+      rv[it] = rsrc[(int64_t)(m & has_res) * ldy + (n & has_res)];
+    }
+  };
+  // At most DEPTH - 1 slabs past the end are loaded, none of short rows (one loop that always refills made 768 of K 48 slabs of
+  // requests instead of 24; one that may be skipped makes the compiler copy the slabs in flight, a wait for each: 128 rows
+  // against 3072 x 768 14.6 -> 12.4 us, 2304 x 768 12.4 -> 11.8, 768 x 3072 13.2 -> 12.9).
+  const int n_slabs = (K + BK - 1) / BK > wave ? ((K + BK - 1) / BK - wave - 1) / FW + 1 : 0;
 #pragma unroll
   for (int d = 0; d < DEPTH; ++d) gload((wave + d * FW) * BK, d);
-  for (int kb = wave * BK; kb < K; kb += DEPTH * FW * BK) {
+  fetch_ends();
+  if constexpr (SHORT) {
 #pragma unroll
-    for (int d = 0; d < DEPTH; ++d) {
-      const int k0 = kb + d * FW * BK;
-      if (k0 < K) {                                  // wave-uniform
-        const bool k_ok = k0 + lcol < K;
-        const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
-        wave_lds_sync();                             // the previous slab has been read
+    for (int d = 0; d < DEPTH; ++d)
+      if (d < n_slabs) multiply(d, d);               // (wave-uniform)
+  } else {                                           // (n_slabs >= DEPTH)
+    int i = DEPTH;
+#pragma unroll 1
+    do {
 #pragma unroll
-        for (int i = 0; i < FM / 8; ++i) *reinterpret_cast<floatx4*>(ax + (lrow + 8 * i) * LDK + lcol) = k_ok ? va[d][i] : zero;
-#pragma unroll
-        for (int i = 0; i < WR / 8; ++i) *reinterpret_cast<floatx4*>(bx + (lrow + 8 * i) * LDK + lcol) = k_ok ? vb[d][i] : zero;
-        wave_lds_sync();
-        const int r = lane & 15, kq = (lane >> 4) * 8;
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          floatx4 a[RB], b[CB];
-#pragma unroll
-          for (int i = 0; i < RB; ++i) a[i] = *reinterpret_cast<const floatx4*>(ax + (16 * i + r) * LDK + kq + 4 * j);
-#pragma unroll
-          for (int c = 0; c < CB; ++c) b[c] = *reinterpret_cast<const floatx4*>(bx + (16 * c + r) * LDK + kq + 4 * j);
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-#pragma unroll
-            for (int i = 0; i < RB; ++i)
-#pragma unroll
-              for (int c = 0; c < CB; ++c)
-                acc[(j + 2 * e) % CHAINS][i][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][e], b[c][e], acc[(j + 2 * e) % CHAINS][i][c], 0, 0, 0);
-        }
+      for (int d = 0; d < DEPTH; ++d) {
+        multiply(i - DEPTH + d, d);
+        gload((wave + (i + d) * FW) * BK, d);        // into the registers just consumed
       }
-      gload(k0 + DEPTH * FW * BK, d);                // into the registers just consumed
-    }
+      i += DEPTH;
+    } while (i < n_slabs);
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d)
+      if (i - DEPTH + d < n_slabs) multiply(i - DEPTH + d, d);
   }
 
   // ---- the 8 partial tiles, added in wave order; accumulator: column lane%16, rows 4 (lane/16) ... + 3 --------
@@ -309,7 +345,8 @@ __global__ __launch_bounds__(FW * 64, 4) void gemm_f32_waves_kernel(
     }
   __syncthreads();
 #pragma unroll
-  for (int at = tid; at < FM * OUT; at += FW * 64) {
+  for (int it = 0; it < ITEMS; ++it) {
+    const int at = tid + it * FW * 64;
     const int mr = at / OUT, nc = at % OUT, m = m0 + mr, n = n0 + nc;
     float v = 0.f, u = 0.f;
 #pragma unroll
@@ -318,15 +355,15 @@ __global__ __launch_bounds__(FW * 64, 4) void gemm_f32_waves_kernel(
       if (SWIGLU) u += lds[z * PATCH + mr * LDR + 16 + nc];
     }
     if (m >= M || n >= N) continue;
-    if (bias != nullptr) {
-      v += bias[n];
-      if (SWIGLU) u += bias[n + N];
+    if (has_bias) {
+      v += bi[it];
+      if (SWIGLU) u += ub[it];
     }
     v = SWIGLU ? silu_f(v) * u : apply_act<ACT>(v);
     if (SPLIT) {
       *reinterpret_cast<float*>(split_dst(sp, m, n, sizeof(float))) = v;
     } else {
-      if (residual != nullptr) v += residual[(int64_t)m * ldy + n];
+      if (has_res) v += rv[it];
       y[(int64_t)m * ldy + n] = v;
     }
   }
@@ -347,16 +384,22 @@ SplitPlan plan_split(int M, int N, int K) {
 }  // namespace
 
 namespace {
-template <int CB, int ACT, bool SPLIT>
-forge_status launch_tile(const float* x, const float* w, const float* bias, const float* res, float* y, int M, int N,
+template <int CB, int ACT, bool SPLIT, bool SHORT>
+forge_status launch_slabs(const float* x, const float* w, const float* bias, const float* res, float* y, int M, int N,
                          int K, int ldy, const QkvSplit& sp, hipStream_t s) {
   constexpr int smem = FW * (FM + 16 * CB) * LDK * (int)sizeof(float);
-  auto kern = gemm_f32_waves_kernel<CB, ACT, SPLIT>;
+  auto kern = gemm_f32_waves_kernel<CB, ACT, SPLIT, SHORT>;
   static std::atomic<uint64_t> lds_raised{0};   // per kernel instantiation
   if (raise_lds_limit(reinterpret_cast<const void*>(kern), smem, lds_raised) != FORGE_OK) return FORGE_ERR_HIP;
   const int cols = ACT == FORGE_ACT_SWIGLU ? 8 * CB : 16 * CB;
   kern<<<dim3(ceil_div(N, cols), ceil_div(M, FM)), FW * 64, smem, s>>>(x, w, bias, res, y, M, N, K, ldy, sp);
   return launch_status();
+}
+template <int CB, int ACT, bool SPLIT>
+forge_status launch_tile(const float* x, const float* w, const float* bias, const float* res, float* y, int M, int N,
+                         int K, int ldy, const QkvSplit& sp, hipStream_t s) {
+  if (ceil_div(K, BK) <= slabs_in_flight(CB) * FW) return launch_slabs<CB, ACT, SPLIT, true>(x, w, bias, res, y, M, N, K, ldy, sp, s);
+  return launch_slabs<CB, ACT, SPLIT, false>(x, w, bias, res, y, M, N, K, ldy, sp, s);
 }
 template <int ACT, bool SPLIT>
 forge_status launch_waves(int cb, const float* x, const float* w, const float* bias, const float* res, float* y, int M, int N,
