@@ -1086,19 +1086,13 @@ __global__ __launch_bounds__(256) void splitk_reduce_qkv_rope_kernel(GemmParams 
 // latency, so everything that does not depend on the sums (bias, residual, gain, shift) is requested
 // before the partial planes, and the block has no more waves than columns need (the barriers of
 // the two reductions cost by the wave): 21 rows of 2048 6.3 -> 4.4 us, 8 rows of 768 5.9 -> 5.0.
+// P planes are requested at once, from clamped addresses (a loop unrolled by 8 fetched 3, 4 or 6 planes one by one, 0.2 us each),
+// and each wave takes the mean and the squared deviations of its own columns first: one barrier instead of two.
 constexpr int NORM_TAIL_MAX_G = 4;
 constexpr int NORM_TAIL_THREADS = 1024;
-__device__ inline float block_sum_tail(float v, float* red) {
-  v = wave_sum(v);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-  __syncthreads();
-  float t = 0.f;
-  for (int i = 0; i < (int)(blockDim.x >> 6); ++i) t += red[i];
-  return t;
-}
-template <int G>
+template <int G, int P>
 __global__ __launch_bounds__(NORM_TAIL_THREADS) void splitk_reduce_norm_kernel(GemmParams p, int splits) {
-  __shared__ float red[2][NORM_TAIL_THREADS / 64];
+  __shared__ floatx2 red[NORM_TAIL_THREADS / 64];     // a wave's mean and squared deviations from it
   const int N = p.N, m = blockIdx.x, NT = blockDim.x;
   const int64_t plane = (int64_t)p.M * N;
   const float* src = p.part + (int64_t)m * N;
@@ -1123,8 +1117,14 @@ __global__ __launch_bounds__(NORM_TAIL_THREADS) void splitk_reduce_norm_kernel(G
     h[g] = floatx4{0.f, 0.f, 0.f, 0.f};
     if (n >= N) continue;
     floatx4 a = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 8
-    for (int z = 0; z < splits; ++z) a += *reinterpret_cast<const floatx4*>(src + z * plane + n);
+    for (int z0 = 0; z0 < splits; z0 += P) {
+      floatx4 t[P];
+#pragma unroll
+      for (int z = 0; z < P; ++z) t[z] = *reinterpret_cast<const floatx4*>(src + min(z0 + z, splits - 1) * plane + n);
+#pragma unroll
+      for (int z = 0; z < P; ++z)
+        if (z0 + z < splits) a += t[z];
+    }
     if (p.wscale != nullptr) a *= *reinterpret_cast<const floatx4*>(p.wscale + n);
     a[0] += bf_lo(bv[g][0]); a[1] += bf_hi(bv[g][0]); a[2] += bf_lo(bv[g][1]); a[3] += bf_hi(bv[g][1]);
     a[0] += bf_lo(rv[g][0]); a[1] += bf_hi(rv[g][0]); a[2] += bf_lo(rv[g][1]); a[3] += bf_hi(rv[g][1]);
@@ -1136,7 +1136,15 @@ __global__ __launch_bounds__(NORM_TAIL_THREADS) void splitk_reduce_norm_kernel(G
     h[g] = a;
   }
   const bool rms = p.nt.kind == FORGE_NORM_RMSNORM;
-  const float mean = rms ? 0.f : block_sum_tail(sum, red[0]) / (float)N;
+  // columns of a wave: G groups of 256, the last ones may be short
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  auto columns = [&](int w) {
+    int c = 0;
+#pragma unroll
+    for (int g = 0; g < G; ++g) c += min(max(N - (g * NT + w * 64) * 4, 0), 256);
+    return (float)c;
+  };
+  float mean = rms ? 0.f : wave_sum(sum) / fmaxf(columns(wave), 1.f);
   float sq = 0.f;
 #pragma unroll
   for (int g = 0; g < G; ++g) {
@@ -1144,7 +1152,21 @@ __global__ __launch_bounds__(NORM_TAIL_THREADS) void splitk_reduce_norm_kernel(G
 #pragma unroll
     for (int e = 0; e < 4; ++e) { const float d = h[g][e] - mean; sq += d * d; }
   }
-  const float rstd = rsqrtf(block_sum_tail(sq, red[1]) / (float)N + p.nt.eps);
+  sq = wave_sum(sq);
+  if (lane == 0) red[wave] = floatx2{mean, sq};
+  __syncthreads();
+  // the waves' parts, a lane each (a loop over them waited for every read): N var = their squared deviations and those of
+  // their means
+  const floatx2 part = lane < (NT >> 6) ? red[lane] : floatx2{0.f, 0.f};
+  sq = part[1];
+  if (!rms) {
+    const float c = lane < (NT >> 6) ? columns(lane) : 0.f;
+    mean = wave_sum(part[0] * c) / (float)N;
+    const float d = part[0] - mean;
+    sq += d * d * c;
+  }
+  sq = wave_sum(sq);
+  const float rstd = rsqrtf(sq / (float)N + p.nt.eps);
   bf16* yn = (bf16*)p.nt.y_norm + (int64_t)m * N;
 #pragma unroll
   for (int g = 0; g < G; ++g) {
@@ -1518,9 +1540,13 @@ forge_status launch_act(const GemmParams& p, hipStream_t s) {
   if (MODE == MODE_PLAIN && ACT == FORGE_ACT_NONE && p.nt.y_norm != nullptr) {
     const int nt = min(NORM_TAIL_THREADS, ceil_div(p.N, 256) * 64);     // one group of 4 columns per thread while that fits
     const int groups = ceil_div(p.N, nt * 4);
-    if (groups == 1) splitk_reduce_norm_kernel<1><<<p.M, nt, 0, s>>>(p, splits);
-    else if (groups == 2) splitk_reduce_norm_kernel<2><<<p.M, nt, 0, s>>>(p, splits);
-    else splitk_reduce_norm_kernel<NORM_TAIL_MAX_G><<<p.M, nt, 0, s>>>(p, splits);
+    if (groups == 1) {
+      if (splits == 1) splitk_reduce_norm_kernel<1, 1><<<p.M, nt, 0, s>>>(p, splits);
+      else if (splits <= 4) splitk_reduce_norm_kernel<1, 4><<<p.M, nt, 0, s>>>(p, splits);
+      else splitk_reduce_norm_kernel<1, 8><<<p.M, nt, 0, s>>>(p, splits);
+    }
+    else if (groups == 2) splitk_reduce_norm_kernel<2, 8><<<p.M, nt, 0, s>>>(p, splits);
+    else splitk_reduce_norm_kernel<NORM_TAIL_MAX_G, 8><<<p.M, nt, 0, s>>>(p, splits);
     return launch_status();
   }
   return launch_reduce<ACT, MODE == MODE_QKV>(p, splits, sk.ncols, s);
