@@ -7,19 +7,22 @@ namespace forge {
 
 constexpr int BK = 64;            // k per slab of the tile and streaming kernels
 
+// Where column n of row m (position `pos` of its sequence: seq_position) of a head split goes.  head_dim is a power of two
+// (64 or 128), and the rows of a decode step are sequences: no division then.
+__device__ inline bf16* split_dst_bf16(const QkvSplit& sp, int m, int n, int pos) {
+  const int dh = sp.head_dim, shift = __builtin_ctz(dh), c = n & (dh - 1);
+  const int b = sp.q_len == 1 ? m : m / sp.q_len, s = sp.q_len == 1 ? 0 : m - b * sp.q_len;
+  int h = n >> shift;
+  if (h < sp.q_heads) return (bf16*)sp.q + (((((int64_t)b * sp.q_heads + h) * sp.q_len + s) << shift) + c);
+  h -= sp.q_heads;
+  const bool is_k = h < sp.kv_heads;
+  h -= is_k ? 0 : sp.kv_heads;
+  bf16* const base = (bf16*)(is_k ? sp.k_cache : sp.v_cache);
+  return base + (((((int64_t)b * sp.kv_heads + h) * sp.kv_cap + pos + s) << shift) + c);
+}
+// ... the position read here
 __device__ inline bf16* split_dst_bf16(const QkvSplit& sp, int m, int n) {
-  const int dh = sp.head_dim;
-  const int b = m / sp.q_len, s = m % sp.q_len;
-  const int nq = sp.q_heads * dh, nk = sp.kv_heads * dh;
-  if (n < nq) {
-    const int h = n / dh;
-    return (bf16*)sp.q + (((int64_t)b * sp.q_heads + h) * sp.q_len + s) * dh + n % dh;
-  }
-  const bool is_k = n < nq + nk;
-  const int nn = is_k ? n - nq : n - nq - nk;
-  const int h = nn / dh;
-  bf16* basep = (bf16*)(is_k ? sp.k_cache : sp.v_cache);
-  return basep + (((int64_t)b * sp.kv_heads + h) * sp.kv_cap + seq_position(sp.pos, b, sp.pos0) + s) * dh + nn % dh;
+  return split_dst_bf16(sp, m, n, seq_position(sp.pos, sp.q_len == 1 ? m : m / sp.q_len, sp.pos0));
 }
 
 struct GemmParams {

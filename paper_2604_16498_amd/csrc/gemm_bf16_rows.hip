@@ -65,6 +65,7 @@ struct Rows {
   static constexpr int BASE = RED > NW * PATCH ? RED : NW * PATCH;
   static constexpr int SMEM = BASE + (FIN == FIN_ROPE ? SLOTS * MT * 1024 : 0);
   static_assert(SMEM <= 160 * 1024, "fits the LDS of a CU");
+  static constexpr int READS = XREGS + WIN * 4 <= 96 ? NW - 1 : 2;       // partial sums read at once (more cost registers that x needs)
 };
 
 template <int MT, int STEPS, bool W8, int FIN>
@@ -104,11 +105,14 @@ __global__ __launch_bounds__(NW * 64) void gemm_bf16_rows_kernel(RowsParams r) {
   auto src_of = [&](int tile) { return wb + w_row(tile, lr) * row_bytes + in_row; };
   auto load = [&](const char* src, int s) { return __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(src + s * 64)); };
 
-  // position of x row `lane` for the rotation (fetched here: behind the weight loads it would wait for them)
-  int my_pos = 0;
-  if constexpr (ROPE) {
-    const int m = p.row0 + min(lane, M - 1);
-    my_pos = seq_position(p.sp.pos, m / p.sp.q_len, p.sp.pos0) + m % p.sp.q_len;
+  // position of x row `lane` for the rotation and of its sequence for the cache rows (fetched here: behind the weight loads
+  // they would wait for them)
+  const bool split = ROPE || (FIN == FIN_OUT && r.qkv);
+  int my_pos = 0, my_seq_pos = 0;
+  if (split) {
+    const int m = p.row0 + mz + min(lane, M - 1), b = p.sp.q_len == 1 ? m : m / p.sp.q_len;
+    my_seq_pos = seq_position(p.sp.pos, b, p.sp.pos0);
+    my_pos = my_seq_pos + m - b * p.sp.q_len;
   }
 
   // ---- x: whole pieces of rows (64 consecutive lanes, consecutive 16-byte chunks), put into the operand
@@ -236,9 +240,10 @@ __global__ __launch_bounds__(NW * 64) void gemm_bf16_rows_kernel(RowsParams r) {
     for (int item = wave; item < n_tiles * MT; item += NW) {
       const int at = item / MT, mt = item % MT, tile = first + at * (int)gridDim.x;
       floatx4 v = red[((at * NW) * MT + mt) * 64 + lane];
-#pragma unroll 2                                            // (more reads in flight cost registers that x needs)
+#pragma unroll C::READS
       for (int w = 1; w < NW; ++w) v += red[((at * NW + w) * MT + mt) * 64 + lane];
       const int m = mt * 16 + lr;
+      const int seq_pos = split ? __shfl(my_seq_pos, min(m, M - 1), 64) : 0;
       if constexpr (RAW) {
         const int n = tile * TR + 4 * lg;
         if (m >= M || n >= r.rows) continue;
@@ -290,7 +295,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_bf16_rows_kernel(RowsParams r) {
         u32x2 pk;
         pk[0] = pack_bf2(v[0], v[1]);
         pk[1] = pack_bf2(v[2], v[3]);
-        *reinterpret_cast<u32x2*>(split_dst_bf16(p.sp, p.row0 + mz + m, n)) = pk;
+        *reinterpret_cast<u32x2*>(split_dst_bf16(p.sp, p.row0 + mz + m, n, seq_pos)) = pk;
         continue;
       }
       const int64_t out = (int64_t)(mz + m) * p.ldy + n;
