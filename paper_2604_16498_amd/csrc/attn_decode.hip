@@ -49,6 +49,8 @@ struct DecParams {
   int64_t kv_bs, kv_hs;
   float scale_log2e;
   const int* kv_pos;   // per-sequence: rows [0, kv_pos[b]] (clamped to kv_len - 1); NULL: kv_len rows
+  int batch;
+  int by_length;       // > 0: blocks take the sequences by length, in rounds of this many; at most 64 sequences then
 };
 
 // lanes l, l ^ 16, l ^ 32, l ^ 48 (on the vector ALU: the LDS permute that a shuffle is costs 50 ns a step)
@@ -85,8 +87,28 @@ __global__ __launch_bounds__(NWAVES * 64, G > 4 || NWAVES == 8 ? 2 : 3) void att
   __shared__ float sm[NWAVES][G][DH + 2];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int g = p.heads_first ? blockIdx.x : blockIdx.y, b = p.heads_first ? blockIdx.y : blockIdx.z;
-  const int split = p.heads_first ? blockIdx.z : blockIdx.x;
+  // Lengths are known here only.  All blocks of a round are resident, one per CU, and a CU's next block comes a round later: the
+  // sequences from the longest to the shortest, every other round backwards, give each CU about the same number of rows.
+  int bx = blockIdx.x, by = blockIdx.y, bz = blockIdx.z;
+  if (p.by_length > 0) {
+    const int mine = lane < p.batch ? min(max(p.kv_pos[lane], 0), p.kv_len - 1) : -1;    // a lane per sequence
+    if (!__all(mine == __builtin_amdgcn_readfirstlane(mine) || mine < 0)) {
+      const int l = bx + gridDim.x * (by + gridDim.y * bz), first = l - l % p.by_length;
+      const int all = gridDim.x * gridDim.y * gridDim.z;
+      const int at = (l / p.by_length) & 1 ? 2 * first + min(all - first, p.by_length) - 1 - l : l;
+      bx = at % gridDim.x;
+      by = at / gridDim.x % gridDim.y;
+      bz = at / gridDim.x / gridDim.y;
+      int place = 0;                                     // sequences before this lane's
+      for (int j = 0; j < p.batch; ++j) {
+        const int other = __builtin_amdgcn_readlane(mine, j);
+        place += other > mine || (other == mine && j < lane);
+      }
+      int& seq = p.heads_first ? by : bz;
+      seq = __ffsll((unsigned long long)__ballot(lane < p.batch && place == seq)) - 1;
+    }
+  }
+  const int g = p.heads_first ? bx : by, b = p.heads_first ? by : bz, split = p.heads_first ? bz : bx;
   const int krow = lane & 15, kg = lane >> 4;          // MFMA layout: row in tile / lane group
   const int head = lane & 15;                          // ... and the accumulator's column
   const int slot = lane / LPR, c = lane % LPR;         // V layout: row in step / 16-byte chunk
@@ -390,6 +412,13 @@ forge_status launch_dg(const AttnArgs& a, const SplitPlan& pl, hipStream_t s) {
   // 13.8 | 17.1; 16 up to 6556, 16 heads, 512 blocks 107.6 | 117.5; 21 up to 4096, 12 heads, 3 ranges 38.1 | 40.9).
   const int64_t blocks = (int64_t)p.splits * yheads * a.batch;
   p.heads_first = (p.splits == 2 || p.splits == 4) && blocks % compute_units() != 0;
+  p.batch = a.batch;
+  // By length: where some CU gets a second block and the rows are worth the look at all lengths.  us, batch order | by length, up to
+  // 1400 rows of 21 x 16 heads of 128 37.6 | 34.1, 1494 of 41 x 16 74.0 | 62.6, 2410 of 39 x 8 62.4 | 55.4, 950 of 38 x 8
+  // 29.5 | 25.9, 3152 of 24 x 12 of 64 40.6 | 34.5; not 513 of 64 x 12 of 64 15.9 | 17.5, 792 of 61 x 16 49.4 | 50.4.
+  const int cus = compute_units();
+  const int64_t row_elements = (int64_t)a.kv_len * DH;
+  p.by_length = a.kv_pos != nullptr && a.batch <= 64 && blocks > cus && row_elements >= (blocks > 3 * cus ? 131072 : 65536) ? cus : 0;
   const dim3 grid = p.heads_first ? dim3(yheads, a.batch, p.splits) : dim3(p.splits, yheads, a.batch);
   bool eight = false;
   if constexpr (DH == 64 && G == 1) {
