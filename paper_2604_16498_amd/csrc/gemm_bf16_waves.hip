@@ -29,8 +29,8 @@ struct WavesParams {
   int qkv;                                           // head split
 };
 
-// SHORT: no wave has more than DEPTH slabs; otherwise every wave has DEPTH at least
-template <int RB, int CB, bool GATED, bool SHORT>
+// SLABS: no wave has more than 1 or 2; 0: every wave has DEPTH at least
+template <int RB, int CB, bool GATED, int SLABS>
 __global__ __launch_bounds__(NW * 64, RB * CB <= 4 ? 4 : 2) void gemm_bf16_waves_kernel(WavesParams r) {
   const GemmParams& p = r.g;
   constexpr int FM = 16 * RB, WR = 16 * CB;          // rows of x, weight rows
@@ -38,9 +38,10 @@ __global__ __launch_bounds__(NW * 64, RB * CB <= 4 ? 4 : 2) void gemm_bf16_waves
   constexpr int PATCH = (FM + WR) * LDB;             // bytes
   constexpr int LDR = WR + 4;                        // floats of a row of a partial tile
   static_assert(FM * LDR * 4 <= PATCH, "the partial tiles fit where the patches lie");
+  constexpr bool BIG = RB * CB >= 16;                // its slabs take long to multiply: left to the scheduler
   extern __shared__ __attribute__((aligned(16))) char smem[];   // [NW * PATCH]
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tid = threadIdx.x, lane = tid & 63, wave = BIG ? tid >> 6 : __builtin_amdgcn_readfirstlane(tid >> 6);
   const int M = p.M, N = p.N, K = p.K;
   const int m0 = blockIdx.y * FM, n0 = blockIdx.x * OUT;
   char* const ax = smem + wave * PATCH;
@@ -75,7 +76,7 @@ __global__ __launch_bounds__(NW * 64, RB * CB <= 4 ? 4 : 2) void gemm_bf16_waves
 
   const int fr = lane & 15, fg = lane >> 4;
   auto multiply = [&](int d) {
-    __builtin_amdgcn_sched_barrier(0);               // (mixed with its neighbours' loads and stores a slab wants twice the registers)
+    if constexpr (!BIG) __builtin_amdgcn_sched_barrier(0);      // (mixed with its neighbours' loads and stores a slab wants twice the registers)
     wave_lds_sync();                                 // the previous slab has been read
 #pragma unroll
     for (int i = 0; i < FM / 8; ++i) *reinterpret_cast<u32x4*>(ax + (lrow + 8 * i) * LDB + lcol) = va[d][i];
@@ -94,7 +95,7 @@ __global__ __launch_bounds__(NW * 64, RB * CB <= 4 ? 4 : 2) void gemm_bf16_waves
 #pragma unroll
         for (int c = 0; c < CB; ++c) acc[i][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[c], xf[i], acc[i][c], 0, 0, 0);
     }
-    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (!BIG) __builtin_amdgcn_sched_barrier(0);
   };
   // bias and residual of the outputs that this thread finishes: requested behind the first slabs, long before they are
   // needed.  Unconditional (a load under a branch would make every wait behind it a full one): what is not there is read
@@ -121,11 +122,20 @@ __global__ __launch_bounds__(NW * 64, RB * CB <= 4 ? 4 : 2) void gemm_bf16_waves
   // instead of 16, and a loop that may be skipped makes the compiler copy the slabs in flight, a wait for each: 128 rows against
   // 2304 x 768 6.8 -> 5.95 us, 3072 x 768 7.1 -> 6.4, 768 x 3072 8.0 -> 7.8, 256 x 2048 x 2048 10.6 -> 9.9.)
   load(0, 0);
-  load(1, 1);
+  if constexpr (SLABS != 1) load(1, 1);
+  if constexpr (!BIG) __builtin_amdgcn_sched_barrier(0);       // (among the slabs' requests: 128 rows against 768 x 768 4.0 instead of 3.8 us)
   fetch_ends();
-  if constexpr (SHORT) {
+  if constexpr (SLABS > 0) {
     if (0 < n_slabs) multiply(0);                    // (wave-uniform)
-    if (1 < n_slabs) multiply(1);
+    if (SLABS > 1 && 1 < n_slabs) multiply(1);
+  } else if constexpr (BIG) {                        // (always refilling: 109 rows against 5968 x 1088 10.5 us, 12.0 as below)
+    for (int i = 0; i < n_slabs; i += DEPTH) {
+#pragma unroll
+      for (int d = 0; d < DEPTH; ++d) {
+        if (i + d < n_slabs) multiply(d);
+        load(i + d + DEPTH, d);
+      }
+    }
   } else {                                           // (n_slabs >= DEPTH)
     int i = DEPTH;
 #pragma unroll 1
@@ -191,10 +201,10 @@ __global__ __launch_bounds__(NW * 64, RB * CB <= 4 ? 4 : 2) void gemm_bf16_waves
   }
 }
 
-template <int RB, int CB, bool GATED, bool SHORT>
+template <int RB, int CB, bool GATED, int SLABS>
 forge_status launch_slabs(const WavesParams& r, hipStream_t s) {
   constexpr int smem = NW * 16 * (RB + CB) * LDB;
-  auto kern = gemm_bf16_waves_kernel<RB, CB, GATED, SHORT>;
+  auto kern = gemm_bf16_waves_kernel<RB, CB, GATED, SLABS>;
   static std::atomic<uint64_t> lds_raised{0};        // per kernel instantiation
   if (raise_lds_limit(reinterpret_cast<const void*>(kern), smem, lds_raised) != FORGE_OK) return FORGE_ERR_HIP;
   kern<<<dim3(ceil_div(r.g.N, GATED ? 8 * CB : 16 * CB), ceil_div(r.g.M, 16 * RB)), NW * 64, smem, s>>>(r);
@@ -203,29 +213,44 @@ forge_status launch_slabs(const WavesParams& r, hipStream_t s) {
 
 template <int RB, int CB, bool GATED>
 forge_status launch_tile(const WavesParams& r, hipStream_t s) {
-  if (r.g.K / BK <= DEPTH * NW) return launch_slabs<RB, CB, GATED, true>(r, s);
-  return launch_slabs<RB, CB, GATED, false>(r, s);
+  const int slabs = r.g.K / BK;
+  if (slabs <= NW) return launch_slabs<RB, CB, GATED, 1>(r, s);
+  if (slabs <= DEPTH * NW) return launch_slabs<RB, CB, GATED, 2>(r, s);
+  return launch_slabs<RB, CB, GATED, 0>(r, s);
 }
 
 }  // namespace
 
-// Tiles (row blocks, column blocks) and their times in us: a start, a round of tiles over the CUs, and what 1024 elements of
-// K add to a round; fitted to 3400 drawn problems with the weight in HBM (within 4 % for half of them, 11 % for nine of ten).
+// Tiles (row blocks, column blocks) and their times in us: a start, a round of tiles over the CUs, what 1024 elements of K add
+// to a round, and what they add per tile and CU (blocks that run into each other's loads); fitted to 1100 drawn problems
+// with the weight in HBM (within 5 to 8 % for half of them, 11 to 20 % for nine of ten; the tile picked is 0.6 % off the
+// fastest of them in the geometric mean, K below 512 3 %).  48 rows or columns come to one round where 32 and 64 do not (us, 128 rows against 2304 x 768 64 x 32 5.7 | 48 x 32 5.0, 3072 x 768 5.6 | 32 x 48 5.3, 68 rows against
+// 6144 x 2048 14.0 | 48 x 48 12.0); where they do not, and with very short rows, the others.
+// At most 64 rows are weighed against x in registers (rows_us), and both estimates come from the kernels before their last
+// changes (each about 5 % faster now), so these keep their own constants: 28 rows against 3000 x 1024 5.1 | 4.6 there, 21 against
+// 8192 x 2048 10.1 | 10.5.
 namespace {
-struct WavesTile { int rb, cb; double start, round, per_k; };
-constexpr WavesTile kTiles[] = {{1, 1, 3.5, 0.23, 0.8}, {1, 2, 3.6, 0.36, 1.3}, {2, 2, 3.5, 0.62, 1.64}, {4, 2, 2.2, 2.46, 2.4}, {4, 4, 2.1, 3.8, 3.56}};
+struct WavesTile { int rb, cb; double start, round, per_k, full; };
+constexpr WavesTile kTiles[] = {{1, 1, 2.5, 0.36, 0.51, 0.14}, {1, 2, 2.5, 0.65, 0.81, 0.22}, {2, 2, 2.97, 0.4, 1.19, 0.34}, {4, 2, 1.35, 2.34, 2.05, 0.33},
+                                {4, 4, 1.3, 3.1, 3.05, 0.73}, {2, 3, 1.4, 1.99, 1.68, 0.73}, {3, 2, 1.43, 2.09, 1.57, 0.38}, {3, 3, 1.7, 2.3, 2.12, 0.77}};
+constexpr WavesTile kFewRows[] = {{1, 1, 3.5, 0.23, 0.8, 0}, {1, 2, 3.6, 0.36, 1.3, 0}, {2, 2, 3.5, 0.62, 1.64, 0}, {4, 2, 2.2, 2.46, 2.4, 0},
+                                  {4, 4, 2.1, 3.8, 3.56, 0}, {2, 3, 2.3, 2.1, 2.2, 0}, {3, 2, 2.2, 2.3, 1.95, 0}, {3, 3, 2.9, 2.1, 2.7, 0}};
+constexpr int kTileCount = sizeof(kTiles) / sizeof(kTiles[0]);
+static_assert(sizeof(kFewRows) == sizeof(kTiles), "the same tiles in the same order");
 }  // namespace
 
 WavesPlan plan_waves(int M, int N, int K, bool gated) {
   const int rows = gated ? 2 * N : N;
   WavesPlan best = {-1, 0.0};
-  for (int i = gated ? 1 : 0; i < (int)(sizeof(kTiles) / sizeof(kTiles[0])); ++i) {
-    const WavesTile& t = kTiles[i];
-    const int64_t rounds = ceil_div64((int64_t)ceil_div(M, 16 * t.rb) * ceil_div(rows, 16 * t.cb), compute_units());
-    const double us = t.start + rounds * (t.round + t.per_k * K / 1024);
+  for (int i = gated ? 1 : 0; i < kTileCount; ++i) {
+    const WavesTile& t = M > 64 ? kTiles[i] : kFewRows[i];
+    const int64_t tiles = (int64_t)ceil_div(M, 16 * t.rb) * ceil_div(rows, 16 * t.cb), rounds = ceil_div64(tiles, compute_units());
+    if ((t.rb == 3 || t.cb == 3) && (K < 256 || rounds > 1)) continue;
+    const double k = K / 1024.0, late = t.full > 0 && rounds > 1 ? 1.09 : 1.0;      // (the fit is too good for some of several rounds)
+    const double us = late * (t.start + rounds * (t.round + t.per_k * k) + t.full * k * tiles / compute_units());
     if (best.tile < 0 || us < best.us) best = WavesPlan{i, us};
   }
-  best.us += (double)rows * K * 2 * 0.62 / 6e6;      // the weight from HBM
+  best.us += (double)rows * K * 2 * (M > 64 ? 0.73 : 0.62) / 6e6;      // the weight from HBM
   return best;
 }
 
@@ -238,13 +263,16 @@ forge_status launch_waves(const GemmParams& p, int tile, int act, bool qkv, hipS
     case 2: return gated ? launch_tile<2, 2, true>(r, s) : launch_tile<2, 2, false>(r, s);
     case 3: return gated ? launch_tile<4, 2, true>(r, s) : launch_tile<4, 2, false>(r, s);
     case 4: return gated ? launch_tile<4, 4, true>(r, s) : launch_tile<4, 4, false>(r, s);
+    case 5: return gated ? launch_tile<2, 3, true>(r, s) : launch_tile<2, 3, false>(r, s);
+    case 6: return gated ? launch_tile<3, 2, true>(r, s) : launch_tile<3, 2, false>(r, s);
+    case 7: return gated ? launch_tile<3, 3, true>(r, s) : launch_tile<3, 3, false>(r, s);
     default: return FORGE_ERR_UNSUPPORTED;
   }
 }
 
 const char* waves_variant(int tile) {
   constexpr const char* names[] = {"gemm_bf16_waves<1,1>", "gemm_bf16_waves<1,2>", "gemm_bf16_waves<2,2>", "gemm_bf16_waves<4,2>",
-                                   "gemm_bf16_waves<4,4>"};
+                                   "gemm_bf16_waves<4,4>", "gemm_bf16_waves<2,3>", "gemm_bf16_waves<3,2>", "gemm_bf16_waves<3,3>"};
   return names[tile];
 }
 
