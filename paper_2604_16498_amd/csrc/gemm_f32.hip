@@ -15,6 +15,7 @@
 // Long reductions with few tiles are split along K over grid.z: raw fp32 partial sums go to the workspace
 // and a second kernel adds them in split order (fixed order, no atomics: bitwise reproducible) and
 // carries the epilogue.
+#include <stdint.h>
 #include "common.hpp"
 
 namespace forge {
@@ -210,11 +211,11 @@ __global__ __launch_bounds__(256) void gemm_f32_reduce_kernel(
 constexpr int FW = 8;                                // waves per block
 constexpr int FM = 32, RB = FM / 16;                 // rows of x per block
 
-constexpr int slabs_in_flight(int cb) { return cb == 1 ? 3 : 2; }   // per wave (128 registers: two blocks per CU)
+constexpr int slabs_in_flight(int cb) { return cb == 1 ? 3 : 2; }   // per wave (up to CB 2 in 128 registers: two blocks per CU)
 
 // SHORT: no wave has more than DEPTH slabs; otherwise every wave has DEPTH at least
 template <int CB, int ACT, bool SPLIT, bool SHORT>
-__global__ __launch_bounds__(FW * 64, 4) void gemm_f32_waves_kernel(
+__global__ __launch_bounds__(FW * 64, CB > 2 ? 2 : 4) void gemm_f32_waves_kernel(
     const float* __restrict__ x, const float* __restrict__ w, const float* __restrict__ bias,
     const float* residual, float* y, int M, int N, int K, int ldy, QkvSplit sp) {
   constexpr bool SWIGLU = ACT == FORGE_ACT_SWIGLU;
@@ -222,13 +223,16 @@ __global__ __launch_bounds__(FW * 64, 4) void gemm_f32_waves_kernel(
   constexpr int WR = 16 * CB;                        // weight rows per block
   constexpr int OUT = SWIGLU ? 16 : WR;              // output columns per block
   constexpr int DEPTH = slabs_in_flight(CB);
+  // the 32 x 32 tiles run two to a CU in several rounds: left to the scheduler, in a loop that always refills (us, 255 rows against
+  // 2304 x 768 18.2 as the others | 16.3, 742 against 3072 x 768 46.7 | 40.7)
+  constexpr bool REFILL = CB == 2;
   constexpr int CHAINS = CB == 1 ? 4 : 2;            // sums per output of a wave: shorter chains, smaller rounding error
   constexpr int PATCH = (FM + WR) * LDK;             // floats of one wave's patch; rows padded as above
   constexpr int LDR = WR + 4;                        // row of a partial tile
   static_assert(FM * LDR <= PATCH, "the partial tiles fit where the patches lie");
   extern __shared__ __attribute__((aligned(16))) float lds[];   // [FW * PATCH]
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tid = threadIdx.x, lane = tid & 63, wave = REFILL ? tid >> 6 : __builtin_amdgcn_readfirstlane(tid >> 6);
   const int m0 = blockIdx.y * FM, n0 = blockIdx.x * OUT;
   float* const ax = lds + wave * PATCH;
   float* const bx = ax + FM * LDK;
@@ -262,7 +266,7 @@ __global__ __launch_bounds__(FW * 64, 4) void gemm_f32_waves_kernel(
       for (int j = 0; j < CB; ++j) acc[h][i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
 
   auto multiply = [&](int i, int d) {                // slab i of this wave, from slot d
-    __builtin_amdgcn_sched_barrier(0);               // (mixed with its neighbours' loads and stores a slab wants more registers)
+    if constexpr (!REFILL) __builtin_amdgcn_sched_barrier(0);               // (mixed with its neighbours' loads and stores a slab wants more registers)
     const bool k_ok = (wave + i * FW) * BK + lcol < K;
     const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
     wave_lds_sync();                                 // the previous slab has been read
@@ -287,7 +291,7 @@ __global__ __launch_bounds__(FW * 64, 4) void gemm_f32_waves_kernel(
           for (int c = 0; c < CB; ++c)
             acc[(j + 2 * e) % CHAINS][i][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][e], b[c][e], acc[(j + 2 * e) % CHAINS][i][c], 0, 0, 0);
     }
-    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (!REFILL) __builtin_amdgcn_sched_barrier(0);
   };
   // bias and residual of the outputs that this thread finishes, behind the first slabs: unconditional (a load under a branch would
   // make every wait behind it a full one), what is not there is read from the weight and dropped
@@ -316,6 +320,13 @@ __global__ __launch_bounds__(FW * 64, 4) void gemm_f32_waves_kernel(
 #pragma unroll
     for (int d = 0; d < DEPTH; ++d)
       if (d < n_slabs) multiply(d, d);               // (wave-uniform)
+  } else if constexpr (REFILL) {
+    for (int i = 0; i < n_slabs; i += DEPTH)
+#pragma unroll
+      for (int d = 0; d < DEPTH; ++d) {
+        if (i + d < n_slabs) multiply(i + d, d);
+        gload((wave + (i + d + DEPTH) * FW) * BK, d);
+      }
   } else {                                           // (n_slabs >= DEPTH)
     int i = DEPTH;
 #pragma unroll 1
@@ -405,11 +416,12 @@ template <int ACT, bool SPLIT>
 forge_status launch_waves(int cb, const float* x, const float* w, const float* bias, const float* res, float* y, int M, int N,
                           int K, int ldy, const QkvSplit& sp, hipStream_t s) {
   if constexpr (ACT != FORGE_ACT_SWIGLU) {
+    if (cb == 3) return launch_tile<3, ACT, SPLIT>(x, w, bias, res, y, M, N, K, ldy, sp, s);
     if (cb == 1) return launch_tile<1, ACT, SPLIT>(x, w, bias, res, y, M, N, K, ldy, sp, s);
   }
   return launch_tile<2, ACT, SPLIT>(x, w, bias, res, y, M, N, K, ldy, sp, s);
 }
-// Column blocks (1 or 2) of the wave-shared tiles, or 0 for the 64 x 64 tiles.  Times are rounds of tiles over the
+// Column blocks (1, 2 or 3) of the wave-shared tiles, or 0 for the 64 x 64 tiles.  Times are rounds of tiles over the
 // CUs times slabs plus a start, in units of 0.1 us as measured (7 per round of 64 x 64 tiles and slab, 1.9 and 1.2 per round
 // of 32 x 32 and 32 x 16; us, 64 x 64 with its reduce | wave-shared: 128 rows against 2304 x 768 15.1 | 10.6, 768 x 768 9.8 | 5.2,
 // 3072 x 768 18.1 | 10.9, 768 x 3072 17.4 | 12.9; 512 rows against 3072 x 768 34.3 | 29.4, 2048 rows 99 | 108, 256 rows
@@ -427,7 +439,11 @@ int plan_waves(int M, int N, int K, bool gated) {
   const int64_t slab64 = slabs * (gated ? 14 : 7), c64 = (t64 > 4 * cus ? t64 * slab64 / cus : ceil_div64(t64, cus) * slab64) + 45;
   const int64_t c2 = ceil_div64(mt * ceil_div64(rows, 32), cus) * slabs8 * 19 / 10 + 22;
   const int64_t c1 = gated ? c2 : ceil_div64(mt * ceil_div64(N, 16), cus) * slabs8 * 12 / 10 + 21;
-  if (c64 < c2 && c64 < c1) return 0;
+  // 32 x 48 where these are one round: 128 rows against 2304 x 768 32 x 16 11.9 | 11.0, 3072 x 768 12.3 | 11.1, 512 against
+  // 768 x 3072 30.6 | 28.2; not in several rounds (512 against 2304 x 768 32 x 32 26.5 | 27.0)
+  const int64_t c3 = !gated && mt * ceil_div64(N, 48) <= cus ? slabs8 * 2 + 44 : INT64_MAX;
+  if (c64 < c2 && c64 < c1 && c64 < c3) return 0;
+  if (c3 < c1 && c3 < c2) return 3;
   return c1 < c2 ? 1 : 2;
 }
 }  // namespace
@@ -450,7 +466,7 @@ size_t gemm_f32_workspace_bytes(int M, int N, int K, forge_act act) {
 
 const char* gemm_f32_variant(int M, int N, int K, forge_act act) {
   const int cb = plan_waves(M, N, K, act == FORGE_ACT_SWIGLU);
-  if (cb > 0) return cb == 1 ? "gemm_f32_waves<1>" : "gemm_f32_waves<2>";
+  if (cb > 0) return cb == 1 ? "gemm_f32_waves<1>" : cb == 2 ? "gemm_f32_waves<2>" : "gemm_f32_waves<3>";
   return plan_split(M, N, K).splits > 1 ? "gemm_f32<64,64,2,2>+splitk" : "gemm_f32<64,64,2,2>";
 }
 
