@@ -64,7 +64,7 @@ struct AttnParams {
   bf16* out;
   int batch, q_heads, kv_heads, q_len, kv_len;
   int64_t kv_bs, kv_hs;
-  float scale_log2e;
+  float scale, scale_log2e;
   int causal;
   int n_qblocks;
   const float* mask;        // additive, fp32 [*, *, q_len, kv_len]; only read by the MASKED kernel
@@ -90,8 +90,10 @@ __device__ inline float xchg32_sum(float x) {
 // SPLIT: block z of a query block walks only its share of the key tiles and writes unnormalised fp32
 // rows with their (maximum, sum); attn_prefill_merge adds the shares.  For calls with fewer query blocks
 // than CUs (a turn of 777 tokens has 4 per head).
-template <int DH, bool MASKED, bool SPLIT, int WAVES>
-__global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : DH == 128 || MASKED ? 2 : 3) void attn_prefill_kernel(AttnParams p) {
+// THREE: a masked kernel that fits three blocks on a CU: K and V of the tile after next are requested behind the softmax, where
+// the scores and mask values no longer take their registers.
+template <int DH, bool MASKED, bool SPLIT, int WAVES, bool THREE>
+__global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : !THREE && (DH == 128 || MASKED) ? 2 : 3) void attn_prefill_kernel(AttnParams p) {
   constexpr int BQ = WAVES * 32, BKV = 64;
   constexpr int CPR = DH / 8;                 // 16-byte chunks per row
   constexpr int KS = DH * 2 + 16;             // K row stride in LDS (bytes)
@@ -195,9 +197,9 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : DH == 128 || MASKED ? 
 #pragma unroll
     for (int e = 0; e < 16; ++e) o_acc[i][e] = 0.f;
   float m_run = -1e30f, l_run = 0.f;   // finite start: no inf - inf anywhere
-  // MASKED works on pre-scaled scores (s * scale * log2e + mask * log2e), so the factor inside
-  // the softmax is 1 there
-  const float c = MASKED ? 1.0f : p.scale_log2e;
+  // MASKED works on scaled scores with the mask added (s * scale + mask, one instruction), so the factor inside the softmax
+  // is log2e there
+  const float c = MASKED ? 1.4426950408889634f : p.scale_log2e;
   const float* mask_row = nullptr;
   if (MASKED)
     mask_row = p.mask + b * p.mask_bs + h * p.mask_hs + (int64_t)min(my_q, p.q_len - 1) * p.kv_len;
@@ -261,11 +263,10 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : DH == 128 || MASKED ? 
   auto softmax = [&](int t) {
     const int kv0 = t * BKV;
     if (MASKED) {
-      constexpr float LOG2E = 1.4426950408889634f;
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) sc[kb][v] = sc[kb][v] * p.scale_log2e + mk[kb * 4 + (v >> 2)][v & 3] * LOG2E;
+        for (int v = 0; v < 16; ++v) sc[kb][v] = sc[kb][v] * p.scale + mk[kb * 4 + (v >> 2)][v & 3];
     }
     if (kv0 + BKV - 1 > wave_min_limit) {       // diagonal / tail tiles only
 #pragma unroll
@@ -356,14 +357,20 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : DH == 128 || MASKED ? 
         store_k((t + 1) & 1);
         store_v((t + 1) & 1);
       }
-      load_rows(kbase, t + 2, rk);
-      load_rows(vbase, t + 2, rv);
+      if (!THREE) {
+        load_rows(kbase, t + 2, rk);
+        load_rows(vbase, t + 2, rv);
+      }
       if (wave_needs(t)) {
         scores(t);
         softmax(t);
         if (wave_needs(t + 1)) mask_prefetch(t + 1);
-        pv_mm(t);
       }
+      if (THREE) {
+        load_rows(kbase, t + 2, rk);
+        load_rows(vbase, t + 2, rv);
+      }
+      if (wave_needs(t)) pv_mm(t);
       lds_barrier();
     }
   } else {
@@ -472,7 +479,7 @@ __global__ __launch_bounds__(256) void attn_prefill_merge(const float* __restric
   Vec8<bf16>::store(out + ((b * q_len + q) * q_heads + h) * DH + c * 8, o);
 }
 
-template <int DH, bool MASKED, bool SPLIT, int WAVES>
+template <int DH, bool MASKED, bool SPLIT, int WAVES, bool THREE = false>
 forge_status launch_split(const AttnArgs& a, int splits, hipStream_t s) {
   AttnParams p;
   p.q = (const bf16*)a.q;
@@ -486,6 +493,7 @@ forge_status launch_split(const AttnArgs& a, int splits, hipStream_t s) {
   p.kv_len = a.kv_len;
   p.kv_bs = a.kv_batch_stride;
   p.kv_hs = a.kv_head_stride;
+  p.scale = a.scale;
   p.scale_log2e = a.scale * 1.4426950408889634f;
   p.causal = a.causal;
   p.n_qblocks = ceil_div(a.q_len, WAVES * 32);
@@ -495,7 +503,7 @@ forge_status launch_split(const AttnArgs& a, int splits, hipStream_t s) {
   p.mask_bs = a.mask_batch_stride;
   p.mask_hs = a.mask_head_stride;
   constexpr int smem = 2 * 64 * ((DH * 2 + 16) + (DH * 2 + (DH == 64 ? 32 : 64)));
-  auto kern = attn_prefill_kernel<DH, MASKED, SPLIT, WAVES>;
+  auto kern = attn_prefill_kernel<DH, MASKED, SPLIT, WAVES, THREE>;
   static std::atomic<uint64_t> lds_raised{0};   // per kernel instantiation
   if (raise_lds_limit(reinterpret_cast<const void*>(kern), smem, lds_raised) != FORGE_OK) return FORGE_ERR_HIP;
   dim3 grid((unsigned)a.q_heads * a.batch * p.n_qblocks, 1, splits), block(WAVES * 64);
@@ -585,6 +593,11 @@ forge_status launch_dh(const AttnArgs& a, hipStream_t s) {
     const int64_t blocks4 = query_blocks(a.batch, a.q_heads, a.q_len, 4), blocks8 = query_blocks(a.batch, a.q_heads, a.q_len, 8);
     if (MASKED ? blocks4 > cus : eight_waves(a.batch, a.q_heads, a.q_len) || (even && blocks4 > cus && blocks8 <= cus))
       return launch_split<DH, MASKED, false, 8>(a, 1, s);
+  }
+  // a third block per CU where two leave blocks over (us, two | three: 8 x 12 heads of 64 x 1000, 768 blocks, 69 | 63, 7 x 12 x 800,
+  // 588 blocks, 51 | 48.5; but 5 x 12 x 511, 240 blocks, 18.3 | 20.4)
+  if constexpr (MASKED && DH == 64) {
+    if (query_blocks(a.batch, a.q_heads, a.q_len, 4) > 2 * cus) return launch_split<DH, MASKED, false, 4, true>(a, 1, s);
   }
   return launch_split<DH, MASKED, false, 4>(a, 1, s);
 }
