@@ -71,6 +71,7 @@ struct AttnParams {
   int64_t mask_bs, mask_hs;
   float* part;              // SPLIT: fp32 partial rows [splits][batch * q_heads * q_len][dh], then (max, sum) pairs
   int splits;
+  int round;                // > 0: every other round of this many blocks runs backwards
 };
 
 __device__ inline float xchg32_max(float x) {
@@ -113,7 +114,14 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : !THREE && (DH == 128 |
   const int fr = lane & 31, fh = lane >> 5;
   // late (long) query blocks first, over all heads: they carry the most key tiles under the
   // causal mask, and blocks are handed out in launch order
-  const int at = blockIdx.x, pairs = p.batch * p.q_heads;
+  // (and the blocks that are resident from the start are dealt there and back over the CUs: a CU's later blocks come a round of
+  // the chip after its first, and forwards some would hold the longest of every round)
+  int at = blockIdx.x;
+  const int pairs = p.batch * p.q_heads;
+  if (p.round > 0) {
+    const int from = at - at % p.round;
+    if ((at / p.round) & 1) at = 2 * from + min((int)gridDim.x - from, p.round) - 1 - at;
+  }
   int qb = p.n_qblocks - 1 - at / pairs;
   int h = at % pairs % p.q_heads, b = at % pairs / p.q_heads;
   if (MASKED && p.mask_hs == 0) {
@@ -497,16 +505,20 @@ forge_status launch_split(const AttnArgs& a, int splits, hipStream_t s) {
   p.scale_log2e = a.scale * 1.4426950408889634f;
   p.causal = a.causal;
   p.n_qblocks = ceil_div(a.q_len, WAVES * 32);
+  const int64_t grid_x = (int64_t)a.q_heads * a.batch * p.n_qblocks;
   p.part = (float*)a.workspace;
   p.splits = splits;
   p.mask = a.mask;
   p.mask_bs = a.mask_batch_stride;
   p.mask_hs = a.mask_head_stride;
+  // three blocks per CU of unequal length (us, forwards | there and back, 8 x 12 heads of 64 x 1024 31.0 | 29.2; with two, heads of
+  // 128, within the spread of the runs)
+  p.round = DH == 64 && WAVES == 4 && !SPLIT && a.causal && grid_x > compute_units() ? compute_units() : 0;
   constexpr int smem = 2 * 64 * ((DH * 2 + 16) + (DH * 2 + (DH == 64 ? 32 : 64)));
   auto kern = attn_prefill_kernel<DH, MASKED, SPLIT, WAVES, THREE>;
   static std::atomic<uint64_t> lds_raised{0};   // per kernel instantiation
   if (raise_lds_limit(reinterpret_cast<const void*>(kern), smem, lds_raised) != FORGE_OK) return FORGE_ERR_HIP;
-  dim3 grid((unsigned)a.q_heads * a.batch * p.n_qblocks, 1, splits), block(WAVES * 64);
+  dim3 grid((unsigned)grid_x, 1, splits), block(WAVES * 64);
   kern<<<grid, block, smem, s>>>(p);
   if (!SPLIT) return launch_status();
   if (hipGetLastError() != hipSuccess) return FORGE_ERR_HIP;
