@@ -314,10 +314,10 @@ __global__ __launch_bounds__(DH) void attn_decode_combine(const float* __restric
     o *= a;
     m = mn;
 #pragma unroll
-    for (int z = 0; z < 8; ++z) {
-      const float w = z0 + z < splits ? __builtin_amdgcn_exp2f(mz[z] - mn) : 0.f;
-      l += lz[z] * w;
-      o += oz[z] * w;
+    for (int z = 0; z < 8; ++z) {                         // (selects: a weight of 0 would turn an infinite output into NaN)
+      const float w = __builtin_amdgcn_exp2f(mz[z] - mn);
+      l += z0 + z < splits ? lz[z] * w : 0.f;
+      o += z0 + z < splits ? oz[z] * w : 0.f;
     }
   }
   out[((int64_t)b * q_heads + h) * DH + d] = (bf16)(o / l);

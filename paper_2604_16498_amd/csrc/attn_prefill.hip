@@ -458,6 +458,8 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : !THREE && (DH == 128 |
   }
 }
 
+constexpr int MAX_SHARES = 8;
+
 // Merge of the key shares: DH / 8 lanes per row, 8 columns each; shares in order.
 template <int DH>
 __global__ __launch_bounds__(256) void attn_prefill_merge(const float* __restrict__ part, bf16* __restrict__ out,
@@ -466,25 +468,41 @@ __global__ __launch_bounds__(256) void attn_prefill_merge(const float* __restric
   const int64_t row = (int64_t)blockIdx.x * (256 / LPR) + threadIdx.x / LPR;
   const int c = threadIdx.x % LPR;
   if (row >= rows) return;
+  // all maxima and sums and the rows of the first P shares in one round trip, from clamped addresses
   const floatx2* ml = reinterpret_cast<const floatx2*>(part + (int64_t)splits * rows * DH);
-  float mx = -INFINITY;
-  for (int z = 0; z < splits; ++z) mx = fmaxf(mx, ml[z * rows + row][0]);
-  float o[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, l = 0.f;
-#pragma unroll 2
-  for (int z = 0; z < splits; ++z) {
-    const floatx2 t = ml[z * rows + row];
-    const float w = __builtin_amdgcn_exp2f(t[0] - mx);
-    l += t[1] * w;
-    float v[8];
-    Vec8<float>::load(part + (z * rows + row) * DH + c * 8, v);
+  constexpr int P = 4;
+  floatx2 t[MAX_SHARES];
+  float v[P][8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) o[e] += v[e] * w;
+  for (int z = 0; z < MAX_SHARES; ++z) t[z] = ml[min(z, splits - 1) * rows + row];
+#pragma unroll
+  for (int z = 0; z < P; ++z) Vec8<float>::load(part + (min(z, splits - 1) * rows + row) * DH + c * 8, v[z]);
+  float mx = t[0][0];
+#pragma unroll
+  for (int z = 1; z < MAX_SHARES; ++z) mx = fmaxf(mx, t[z][0]);
+  float o[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, l = 0.f;
+#pragma unroll
+  for (int z0 = 0; z0 < MAX_SHARES; z0 += P) {
+    if (z0 >= splits) break;
+    if (z0 > 0) {
+#pragma unroll
+      for (int z = 0; z < P; ++z) Vec8<float>::load(part + (min(z0 + z, splits - 1) * rows + row) * DH + c * 8, v[z]);
+    }
+#pragma unroll
+    for (int z = 0; z < P; ++z) {                           // (selects: a weight of 0 would turn an infinite output into NaN)
+      const bool in = z0 + z < splits;
+      const float w = __builtin_amdgcn_exp2f(t[z0 + z][0] - mx);
+      l += in ? t[z0 + z][1] * w : 0.f;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) o[e] += in ? v[z][e] * w : 0.f;
+    }
   }
   const float inv = 1.0f / l;
 #pragma unroll
   for (int e = 0; e < 8; ++e) o[e] *= inv;
-  const int64_t bh = row / q_len, q = row % q_len, b = bh / q_heads, h = bh % q_heads;
-  Vec8<bf16>::store(out + ((b * q_len + q) * q_heads + h) * DH + c * 8, o);
+  const uint32_t bh = (uint32_t)row / (uint32_t)q_len, b = bh / (uint32_t)q_heads, h = bh - b * q_heads;   // (shares: few rows)
+  const int64_t q = (uint32_t)row - bh * (uint32_t)q_len;
+  Vec8<bf16>::store(out + (((int64_t)b * q_len + q) * q_heads + h) * DH + c * 8, o);
 }
 
 template <int DH, bool MASKED, bool SPLIT, int WAVES, bool THREE = false>
@@ -539,7 +557,7 @@ inline int64_t query_blocks(int batch, int q_heads, int q_len, int w) { return (
 inline int plan_shares(int batch, int q_heads, int q_len, int kv_len, int head_dim, int w) {
   const int64_t cus = compute_units(), blocks = query_blocks(batch, q_heads, q_len, w);
   const int per_cu = w == 8 ? 1 : head_dim == 128 ? 2 : 3;
-  const int most = (int)min(min(per_cu * cus / blocks, (int64_t)kv_len / 256), (int64_t)8);
+  const int most = (int)min(min(per_cu * cus / blocks, (int64_t)kv_len / 256), (int64_t)MAX_SHARES);
   const double tiles = kv_len / 64.0, share_us = (double)((int64_t)batch * q_heads * q_len) * head_dim * 8 / 5e6;
   auto tile_us = [&](int n) {
     const int64_t r = ceil_div64(blocks * n, cus);       // blocks on the fullest CU
