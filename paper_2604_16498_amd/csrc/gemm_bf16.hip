@@ -1106,7 +1106,8 @@ __global__ __launch_bounds__(256) void splitk_reduce_qkv_rope_kernel(GemmParams 
 // before the partial planes, and the block has no more waves than columns need (the barriers of
 // the two reductions cost by the wave): 21 rows of 2048 6.3 -> 4.4 us, 8 rows of 768 5.9 -> 5.0.
 // P planes are requested at once, from clamped addresses (a loop unrolled by 8 fetched 3, 4 or 6 planes one by one, 0.2 us each),
-// and each wave takes the mean and the squared deviations of its own columns first: one barrier instead of two.
+// and each wave takes the mean and the squared deviations of its own columns first: one barrier instead of two (8 rows of 768 in
+// the kernel trace, one and six planes, 3.4 on average -> 2.6 and 3.0).
 constexpr int NORM_TAIL_MAX_G = 4;
 constexpr int NORM_TAIL_THREADS = 1024;
 template <int G, int P>

@@ -10,9 +10,10 @@
 // The weight is the A operand, so that a lane holds 4 consecutive output columns of one row.
 //
 // us, cold weights, the kernel that took the problem before (x in registers, 128 x 128 tiles, slab-wise, with a reduce launch
-// where it needed one) | this one: 128 rows against 768 x 768 7.0 | 3.9, 2304 x 768 7.4 | 6.2, 3072 x 768 8.0 | 6.4, 768 x 3072
-// 10.3 | 6.3, 256 x 2048 x 2048 11.6 | 9.5, 128 x 2048 x 8192 23.1 | 19.7, 24 x 2048 x 2048 6.6 | 4.9, 64 x 4096 x 4096
-// 17.4 | 13.6.  plan_waves says where.
+// where it needed one) | this one: 128 rows against 768 x 768 7.0 | 3.8, 2304 x 768 7.4 | 5.4, 3072 x 768 8.0 | 6.0, 768 x 3072
+// 10.3 | 7.8, 256 x 2048 x 2048 11.6 | 9.9, 128 x 2048 x 8192 23.1 | 19.7, 24 x 2048 x 2048 6.6 | 4.9, 64 x 4096 x 4096
+// 17.4 | 13.6.  What is left at 128 rows: a start of 2.5 us, the block's operands at about 50 KB per us and CU, the exchange
+// of the partial tiles.  plan_waves says where.
 #include <math.h>
 #include "gemm_bf16.hpp"
 

@@ -207,7 +207,8 @@ __global__ __launch_bounds__(256) void gemm_f32_reduce_kernel(
 // each slab.  Counted at 128 rows against 2304 x 768 and 3072 x 768: matrix units 14 and 18 % busy, LDS 2.5 and 3.4 us of
 // the 14.3 and 13.9 us under a profiler (a quarter of that bank conflicts).  Tiles of 64 x 32 and 64 x 64 halve the LDS
 // traffic and are slower (2304 x 768 at 128 rows 11.9 and 22 us against 10.6); two blocks per CU need the 128 registers.
-// The four products of a 128-row layer of 768 (MLP 3072): 60.4 us with their reduce launches before, 39.6 now; the layer 76.8 -> 57.6.
+// The four products of a 128-row layer of 768 (MLP 3072): 60.4 us with their reduce launches before, 39.6 on tiles of one
+// and two column blocks with requests past the end, 37 now; the layer 76.8 -> 57.6 and 55.3 -> 51.9 by these.
 constexpr int FW = 8;                                // waves per block
 constexpr int FM = 32, RB = FM / 16;                 // rows of x per block
 
