@@ -206,7 +206,8 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : !THREE && (DH == 128 |
     for (int e = 0; e < 16; ++e) o_acc[i][e] = 0.f;
   float m_run = -1e30f, l_run = 0.f;   // finite start: no inf - inf anywhere
   // MASKED works on scaled scores with the mask added (s * scale + mask, one instruction), so the factor inside the softmax
-  // is log2e there
+  // is log2e there; the difference to the maximum is taken first and exactly: a mask may hold any finite value, and maximum * log2e
+  // rounded by itself is off by 440 at -1e10
   const float c = MASKED ? 1.4426950408889634f : p.scale_log2e;
   const float* mask_row = nullptr;
   if (MASKED)
@@ -309,7 +310,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : !THREE && (DH == 128 |
     for (int kb = 0; kb < 2; ++kb) {
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        const float pv = __builtin_amdgcn_exp2f(sc[kb][v] * c - mc);
+        const float pv = __builtin_amdgcn_exp2f(MASKED ? (sc[kb][v] - m_run) * c : sc[kb][v] * c - mc);
         sc[kb][v] = pv;
         psum += pv;
       }
