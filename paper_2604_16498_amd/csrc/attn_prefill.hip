@@ -91,10 +91,11 @@ __device__ inline float xchg32_sum(float x) {
 // SPLIT: block z of a query block walks only its share of the key tiles and writes unnormalised fp32
 // rows with their (maximum, sum); attn_prefill_merge adds the shares.  For calls with fewer query blocks
 // than CUs (a turn of 777 tokens has 4 per head).
-// THREE: a masked kernel that fits three blocks on a CU: K and V of the tile after next are requested behind the softmax, where
-// the scores and mask values no longer take their registers.
-template <int DH, bool MASKED, bool SPLIT, int WAVES, bool THREE>
-__global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : !THREE && (DH == 128 || MASKED) ? 2 : 3) void attn_prefill_kernel(AttnParams p) {
+// head_dim 64, 4 waves: three blocks on a CU, with a mask by one register (168, left to itself 169; us, two blocks | three:
+// 8 x 12 heads of 64 x 1000 masked 68.6 | 62.7, 7 x 12 x 800 53.7 | 48.7, 11 x 12 x 500 36.0 | 31.4, with at most two to
+// place, 6 x 12 x 700 and fewer, alike).
+template <int DH, bool MASKED, bool SPLIT, int WAVES>
+__global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : DH == 128 || (MASKED && WAVES == 2) ? 2 : 3) void attn_prefill_kernel(AttnParams p) {
   constexpr int BQ = WAVES * 32, BKV = 64;
   constexpr int CPR = DH / 8;                 // 16-byte chunks per row
   constexpr int KS = DH * 2 + 16;             // K row stride in LDS (bytes)
@@ -366,20 +367,14 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : !THREE && (DH == 128 |
         store_k((t + 1) & 1);
         store_v((t + 1) & 1);
       }
-      if (!THREE) {
-        load_rows(kbase, t + 2, rk);
-        load_rows(vbase, t + 2, rv);
-      }
+      load_rows(kbase, t + 2, rk);
+      load_rows(vbase, t + 2, rv);
       if (wave_needs(t)) {
         scores(t);
         softmax(t);
         if (wave_needs(t + 1)) mask_prefetch(t + 1);
       }
-      if (THREE) {
-        load_rows(kbase, t + 2, rk);
-        load_rows(vbase, t + 2, rv);
-      }
-      if (wave_needs(t)) pv_mm(t);
+      if (wave_needs(t)) pv_mm(t);            // (a branch of its own: in the one above, masked 8 x 12 x 1000 takes 65.5 us, not 62.7)
       lds_barrier();
     }
   } else {
@@ -506,7 +501,7 @@ __global__ __launch_bounds__(256) void attn_prefill_merge(const float* __restric
   Vec8<bf16>::store(out + (((int64_t)b * q_len + q) * q_heads + h) * DH + c * 8, o);
 }
 
-template <int DH, bool MASKED, bool SPLIT, int WAVES, bool THREE = false>
+template <int DH, bool MASKED, bool SPLIT, int WAVES>
 forge_status launch_split(const AttnArgs& a, int splits, hipStream_t s) {
   AttnParams p;
   p.q = (const bf16*)a.q;
@@ -534,7 +529,7 @@ forge_status launch_split(const AttnArgs& a, int splits, hipStream_t s) {
   // 128, within the spread of the runs)
   p.round = DH == 64 && WAVES == 4 && !SPLIT && a.causal && grid_x > compute_units() ? compute_units() : 0;
   constexpr int smem = 2 * 64 * ((DH * 2 + 16) + (DH * 2 + (DH == 64 ? 32 : 64)));
-  auto kern = attn_prefill_kernel<DH, MASKED, SPLIT, WAVES, THREE>;
+  auto kern = attn_prefill_kernel<DH, MASKED, SPLIT, WAVES>;
   static std::atomic<uint64_t> lds_raised{0};   // per kernel instantiation
   if (raise_lds_limit(reinterpret_cast<const void*>(kern), smem, lds_raised) != FORGE_OK) return FORGE_ERR_HIP;
   dim3 grid((unsigned)grid_x, 1, splits), block(WAVES * 64);
@@ -624,11 +619,6 @@ forge_status launch_dh(const AttnArgs& a, hipStream_t s) {
     const int64_t blocks4 = query_blocks(a.batch, a.q_heads, a.q_len, 4), blocks8 = query_blocks(a.batch, a.q_heads, a.q_len, 8);
     if (MASKED ? blocks4 > cus : eight_waves(a.batch, a.q_heads, a.q_len) || (even && blocks4 > cus && blocks8 <= cus))
       return launch_split<DH, MASKED, false, 8>(a, 1, s);
-  }
-  // a third block per CU where two leave blocks over (us, two | three: 8 x 12 heads of 64 x 1000, 768 blocks, 69 | 63, 7 x 12 x 800,
-  // 588 blocks, 51 | 48.5; but 5 x 12 x 511, 240 blocks, 18.3 | 20.4)
-  if constexpr (MASKED && DH == 64) {
-    if (query_blocks(a.batch, a.q_heads, a.q_len, 4) > 2 * cus) return launch_split<DH, MASKED, false, 4, true>(a, 1, s);
   }
   return launch_split<DH, MASKED, false, 4>(a, 1, s);
 }
