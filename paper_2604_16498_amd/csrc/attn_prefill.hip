@@ -373,8 +373,11 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : DH == 128 || (MASKED &
         scores(t);
         softmax(t);
         if (wave_needs(t + 1)) mask_prefetch(t + 1);
+        if (!MASKED) pv_mm(t);
       }
-      if (wave_needs(t)) pv_mm(t);            // (a branch of its own: in the one above, masked 8 x 12 x 1000 takes 65.5 us, not 62.7)
+      // (with a mask in a branch of its own: masked 8 x 12 heads of 64 x 1000 65.5 us in the one above, 62.7; without a mask the
+      // second branch costs: 2 x 12 x 267 8.0 | 7.75, 1 x 12 x 578 12.3 | 11.9)
+      if (MASKED && wave_needs(t)) pv_mm(t);
       lds_barrier();
     }
   } else {
