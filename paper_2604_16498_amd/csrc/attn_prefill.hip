@@ -119,7 +119,8 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : DH == 128 || (MASKED &
   // the chip after its first, and forwards some would hold the longest of every round)
   int at = blockIdx.x;
   const int pairs = p.batch * p.q_heads;
-  if (p.round > 0) {
+  constexpr bool ROUNDS = DH == 64 && WAVES == 4 && !SPLIT;
+  if (ROUNDS && p.round > 0) {
     const int from = at - at % p.round;
     if ((at / p.round) & 1) at = 2 * from + min((int)gridDim.x - from, p.round) - 1 - at;
   }
@@ -130,7 +131,9 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : DH == 128 || (MASKED &
     // round-robin over the 8), whose L2 then fetches their mask rows once; dealt over all of them, every L2 fetched
     // the whole mask (8 x 12 heads x 1000: 83 -> 70 us by this alone).  Every XCD gets its share of each row, so that a last
     // row that is mostly padding does not leave some of them idle (3 x 64 heads of 128 x 541 90 us with whole rows per XCD, 81).
-    // Blocks r of this row with (r + o) % 8 == x are XCD x's; the k-th of them is pair (those of the XCDs before) + k.
+    // Blocks r of this row with (r + o) % 8 == x are XCD x's; the k-th of them is pair (those of the XCDs before) + k.  (Where
+    // every other round runs backwards x stands for XCD 7 - x in it, and a row that two rounds share has its masks in two L2s
+    // there; causal 8 x 12 x 1024, rounds forwards | there and back, 46.9 | 43.1 all the same.)
     const int o = (at - at % pairs) & 7, x = at & 7, r = at % pairs;
     int item = r >> 3;
     for (int y = 0; y < x; ++y) item += (pairs - ((y - o) & 7) + 7) >> 3;
@@ -528,9 +531,13 @@ forge_status launch_split(const AttnArgs& a, int splits, hipStream_t s) {
   p.mask = a.mask;
   p.mask_bs = a.mask_batch_stride;
   p.mask_hs = a.mask_head_stride;
-  // three blocks per CU of unequal length (us, forwards | there and back, 8 x 12 heads of 64 x 1024 31.0 | 29.2; with two, heads of
-  // 128, within the spread of the runs)
-  p.round = DH == 64 && WAVES == 4 && !SPLIT && a.causal && grid_x > compute_units() ? compute_units() : 0;
+  // There and back where up to three blocks per CU, all resident from the start, differ in many steps of length: 2 to 3 rounds of the
+  // chip and 7 query blocks per head or more (17 drawn calls 1 to 7 % faster, us 8 x 12 heads of 64 x 1024 31.0 | 28.9, 6 x 12
+  // x 902 22.7 | 21.4).  Fewer query blocks: 28 x 12 x 210 12.9 | 14.4, 13 x 12 x 418 16.8 | 17.7; more than three blocks, which
+  // are handed out as others end: 16 x 12 x 1024 52.4 | 56, 4 x 32 x 1500 63.8 | 66; up to two rounds, and with two blocks per CU
+  // (heads of 128) within the spread of the runs.
+  p.round = DH == 64 && WAVES == 4 && !SPLIT && a.causal && p.n_qblocks >= 7 && grid_x > 2 * compute_units() && grid_x <= 3 * compute_units()
+                ? compute_units() : 0;
   constexpr int smem = 2 * 64 * ((DH * 2 + 16) + (DH * 2 + (DH == 64 ? 32 : 64)));
   auto kern = attn_prefill_kernel<DH, MASKED, SPLIT, WAVES>;
   static std::atomic<uint64_t> lds_raised{0};   // per kernel instantiation

@@ -23,6 +23,8 @@ def _qkv(B, Hq, Hkv, Sq, Skv, dh):
     (1, 4, 2, 2, 2, 64), (1, 4, 4, 63, 63, 128), (1, 2, 2, 64, 191, 64), (2, 3, 1, 65, 65, 128),
     # 4 waves (more than 256 blocks of 64 queries)
     (3, 48, 48, 127, 127, 64), (4, 40, 8, 129, 129, 64), (4, 34, 34, 128, 200, 128), (2, 50, 10, 193, 193, 128),
+    # ... in rounds there and back, a broken third one
+    (3, 29, 29, 800, 850, 64), (1, 74, 37, 801, 801, 64),
     # 4 waves with shares: the last share short, heads of both sizes
     (1, 4, 4, 33, 1100, 64), (1, 6, 2, 130, 1500, 128),
     # 8 waves: shares, of nine tenths of the chip and of less (the edge in keys too), then whole query blocks well past one round
