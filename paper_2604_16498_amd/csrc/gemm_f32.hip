@@ -227,7 +227,7 @@ __global__ __launch_bounds__(FW * 64, CB > 2 ? 2 : 4) void gemm_f32_waves_kernel
   // the 32 x 32 tiles run two to a CU in several rounds: left to the scheduler, in a loop that always refills (us, 255 rows against
   // 2304 x 768 18.2 as the others | 16.3, 742 against 3072 x 768 46.7 | 40.7)
   constexpr bool REFILL = CB == 2;
-  constexpr int CHAINS = CB == 1 ? 4 : 2;            // sums per output of a wave: shorter chains, smaller rounding error
+  constexpr int CHAINS = CB == 2 ? 2 : 4;            // sums per output of a wave: shorter chains, smaller rounding error
   constexpr int PATCH = (FM + WR) * LDK;             // floats of one wave's patch; rows padded as above
   constexpr int LDR = WR + 4;                        // row of a partial tile
   static_assert(FM * LDR <= PATCH, "the partial tiles fit where the patches lie");
