@@ -214,7 +214,7 @@ constexpr int FM = 32, RB = FM / 16;                 // rows of x per block
 
 constexpr int slabs_in_flight(int cb) { return cb == 1 ? 3 : 2; }   // per wave (up to CB 2 in 128 registers: two blocks per CU)
 
-// SHORT: no wave has more than DEPTH slabs; otherwise every wave has DEPTH at least
+// SHORT: no wave has more than DEPTH slabs; otherwise every wave has DEPTH at least (CB 2: any number)
 template <int CB, int ACT, bool SPLIT, bool SHORT>
 __global__ __launch_bounds__(FW * 64, CB > 2 ? 2 : 4) void gemm_f32_waves_kernel(
     const float* __restrict__ x, const float* __restrict__ w, const float* __restrict__ bias,
@@ -225,7 +225,8 @@ __global__ __launch_bounds__(FW * 64, CB > 2 ? 2 : 4) void gemm_f32_waves_kernel
   constexpr int OUT = SWIGLU ? 16 : WR;              // output columns per block
   constexpr int DEPTH = slabs_in_flight(CB);
   // the 32 x 32 tiles run two to a CU in several rounds: left to the scheduler, in a loop that always refills (us, 255 rows against
-  // 2304 x 768 18.2 as the others | 16.3, 742 against 3072 x 768 46.7 | 40.7)
+  // 2304 x 768 18.2 as the others | 16.3, 742 against 3072 x 768 46.7 | 40.7; short rows too: 190 against 4096 x 512 16.7 | 15.1,
+  // 73 against 2048 gated pairs x 512 9.7 | 8.9, 300 against 768 x 256 4.6 | 4.4)
   constexpr bool REFILL = CB == 2;
   constexpr int CHAINS = CB == 2 ? 2 : 4;            // sums per output of a wave: shorter chains, smaller rounding error
   constexpr int PATCH = (FM + WR) * LDK;             // floats of one wave's patch; rows padded as above
@@ -310,9 +311,10 @@ __global__ __launch_bounds__(FW * 64, CB > 2 ? 2 : 4) void gemm_f32_waves_kernel
       rv[it] = rsrc[(int64_t)(m & has_res) * ldy + (n & has_res)];
     }
   };
-  // At most DEPTH - 1 slabs past the end are loaded, none of short rows (one loop that always refills made 768 of K 48 slabs of
-  // requests instead of 24; one that may be skipped makes the compiler copy the slabs in flight, a wait for each: 128 rows
-  // against 3072 x 768 14.6 -> 12.4 us, 2304 x 768 12.4 -> 11.8, 768 x 3072 13.2 -> 12.9).
+  // Past the end of K a wave of short rows loads what DEPTH exceeds its slabs by, one of long rows at most DEPTH - 1, or DEPTH where
+  // it has just DEPTH (one loop that always refills made 768 of K 48 slabs of requests instead of 24; one that may be skipped
+  // makes the compiler copy the slabs in flight, a wait for each: 128 rows against 3072 x 768 14.6 -> 12.4 us, 2304 x 768
+  // 12.4 -> 11.8, 768 x 3072 13.2 -> 12.9).
   const int n_slabs = (K + BK - 1) / BK > wave ? ((K + BK - 1) / BK - wave - 1) / FW + 1 : 0;
 #pragma unroll
   for (int d = 0; d < DEPTH; ++d) gload((wave + d * FW) * BK, d);
@@ -410,7 +412,9 @@ forge_status launch_slabs(const float* x, const float* w, const float* bias, con
 template <int CB, int ACT, bool SPLIT>
 forge_status launch_tile(const float* x, const float* w, const float* bias, const float* res, float* y, int M, int N,
                          int K, int ldy, const QkvSplit& sp, hipStream_t s) {
-  if (ceil_div(K, BK) <= slabs_in_flight(CB) * FW) return launch_slabs<CB, ACT, SPLIT, true>(x, w, bias, res, y, M, N, K, ldy, sp, s);
+  if constexpr (CB != 2) {
+    if (ceil_div(K, BK) <= slabs_in_flight(CB) * FW) return launch_slabs<CB, ACT, SPLIT, true>(x, w, bias, res, y, M, N, K, ldy, sp, s);
+  }
   return launch_slabs<CB, ACT, SPLIT, false>(x, w, bias, res, y, M, N, K, ldy, sp, s);
 }
 template <int ACT, bool SPLIT>
