@@ -88,14 +88,16 @@ __global__ __launch_bounds__(NWAVES * 64, G > 4 || NWAVES == 8 ? 2 : 3) void att
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   // Lengths are known here only.  All blocks of a round are resident, one per CU, and a CU's next block comes a round later: the
-  // sequences from the longest to the shortest, every other round backwards, give each CU about the same number of rows.
+  // sequences from the longest to the shortest, every other round backwards, give each CU about the same number of rows.  The
+  // last round runs forwards: where it is broken, its blocks come to the first CUs, which a backward round before it left the
+  // shorter ones.
   int bx = blockIdx.x, by = blockIdx.y, bz = blockIdx.z;
   if (p.by_length > 0) {
     const int mine = lane < p.batch ? min(max(p.kv_pos[lane], 0), p.kv_len - 1) : -1;    // a lane per sequence
     if (!__all(mine == __builtin_amdgcn_readfirstlane(mine) || mine < 0)) {
       const int l = bx + gridDim.x * (by + gridDim.y * bz), first = l - l % p.by_length;
       const int all = gridDim.x * gridDim.y * gridDim.z;
-      const int at = (l / p.by_length) & 1 ? 2 * first + min(all - first, p.by_length) - 1 - l : l;
+      const int at = ((all - 1) / p.by_length - l / p.by_length) & 1 ? 2 * first + min(all - first, p.by_length) - 1 - l : l;
       bx = at % gridDim.x;
       by = at / gridDim.x % gridDim.y;
       bz = at / gridDim.x / gridDim.y;
@@ -413,12 +415,15 @@ forge_status launch_dg(const AttnArgs& a, const SplitPlan& pl, hipStream_t s) {
   const int64_t blocks = (int64_t)p.splits * yheads * a.batch;
   p.heads_first = (p.splits == 2 || p.splits == 4) && blocks % compute_units() != 0;
   p.batch = a.batch;
-  // By length: where some CU gets a second block and the rows are worth the look at all lengths.  us, batch order | by length, up to
-  // 1400 rows of 21 x 16 heads of 128 37.6 | 34.1, 1494 of 41 x 16 74.0 | 62.6, 2410 of 39 x 8 62.4 | 55.4, 950 of 38 x 8
-  // 29.5 | 25.9, 3152 of 24 x 12 of 64 40.6 | 34.5; not 513 of 64 x 12 of 64 15.9 | 17.5, 792 of 61 x 16 49.4 | 50.4.
+  // By length: where some CU gets a second block and the rows are worth the look at all lengths.  us, batch order | by length:
+  // 25 x 12 heads of 128 up to 899 rows 26.0 | 21.2, 31 x 12 of 64 up to 1897 29.5 | 25.1, 51 x 16 of 128 up to 1392 86 | 74, 39 x 8
+  // of 128 up to 2410 62.4 | 55.4; of 170 drawn caches in one and two ranges 7 % less in the geometric mean, seven of them 2 to 6 %
+  // more.  Of more ranges the last ones of a short sequence are empty, and its length says little about the first: 12 drawn
+  // ones with heads of 128 2.3 % less, 33 with heads of 64 2.8 % more, up to 19 % (15 x 12 up to 4200).  Not, times batch order, up
+  // to 552 rows of 60 x 8 heads of 128 1.04, 584 of 44 x 16 1.05, 699 of 61 x 8 1.05, 792 of 61 x 16 1.02, 513 of 64 x 12 of 64 1.10.
   const int cus = compute_units();
-  const int64_t row_elements = (int64_t)a.kv_len * DH;
-  p.by_length = a.kv_pos != nullptr && a.batch <= 64 && blocks > cus && row_elements >= (blocks > 3 * cus ? 131072 : 65536) ? cus : 0;
+  const int64_t least = blocks > 3 * cus ? 131072 / DH : blocks * 5 > cus * 8 ? max(65536 / DH, 768) : 65536 / DH;    // rows
+  p.by_length = a.kv_pos != nullptr && a.batch <= 64 && blocks > cus && (p.splits <= 2 || DH == 128) && a.kv_len >= least ? cus : 0;
   const dim3 grid = p.heads_first ? dim3(yheads, a.batch, p.splits) : dim3(p.splits, yheads, a.batch);
   bool eight = false;
   if constexpr (DH == 64 && G == 1) {
