@@ -75,7 +75,8 @@ __device__ inline float sum_to_rows(const float* x) {
 
 // G: query heads per KV head, 1 ... 8 (the MFMA's 16 head columns hold them zero-padded; the
 // P . V accumulators grow with G, so the larger groups run at two blocks per SIMD instead of three)
-template <int DH, int G, int NWAVES>
+// FREE: the loads of a tile are left to the scheduler.
+template <int DH, int G, int NWAVES, bool FREE = false>
 __global__ __launch_bounds__(NWAVES * 64, G > 4 || NWAVES == 8 ? 2 : 3) void attn_decode_kernel(DecParams p) {
   constexpr int NJ = DH / 32;          // MFMAs (and K loads) per tile
   constexpr int LPR = DH / 8;          // lanes per V row
@@ -146,7 +147,7 @@ __global__ __launch_bounds__(NWAVES * 64, G > 4 || NWAVES == 8 ? 2 : 3) void att
   // the reductions on the vector ALU, us: 8 sequences up to 641 rows of 12 heads of 64 7.6 -> 7.0, 25 of 950 rows of 8 of 128
   // 21.6 -> 20.7, 64 of 2049 98.0 -> 97.0)
   auto load_tile = [&](int t, u32x4 (&kk)[NJ], u32x4 (&vv)[VSTEPS]) {
-    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (!FREE) __builtin_amdgcn_sched_barrier(0);
     const int base = tile_base(t);
 #pragma unroll
     for (int j = 0; j < NJ; ++j)   // rows past the end re-read the last row (masked below)
@@ -154,7 +155,7 @@ __global__ __launch_bounds__(NWAVES * 64, G > 4 || NWAVES == 8 ? 2 : 3) void att
 #pragma unroll
     for (int s = 0; s < VSTEPS; ++s)
       vv[s] = *reinterpret_cast<const u32x4*>(vb + (int64_t)min(base + s * KPS + slot, last) * DH + c * 8);
-    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (!FREE) __builtin_amdgcn_sched_barrier(0);
   };
   load_tile(0, kr[0], vr[0]);
   load_tile(1, kr[1], vr[1]);
@@ -430,7 +431,16 @@ forge_status launch_dg(const AttnArgs& a, const SplitPlan& pl, hipStream_t s) {
     eight = p.splits == 1 && eight_waves(a.batch, yheads, a.kv_len, DH, G);
     if (eight) attn_decode_kernel<DH, G, 8><<<grid, 8 * 64, 0, s>>>(p);
   }
-  if (!eight) attn_decode_kernel<DH, G, 4><<<grid, 4 * 64, 0, s>>>(p);
+  // Loads left to the scheduler: short caches of heads of 128, one query head each, in more blocks than CUs; waves without a tile
+  // then request nothing (us, in place | free: 64 x 32 up to 64 rows 18.7 | 16.9, 51 x 32 up to 119 17.3 | 15.9; 66 drawn calls up to
+  // 128 rows 5.4 % less, 48 up to 300 1.3 %, longer ones alike; with a block per CU at most 15 x 16 up to 73 4.5 | 4.9).  A branch
+  // around the loads in place does the same for those and makes every wait of the loop a full one: 33 x 8 up to 358 11.1 | 12.5.
+  bool free_loads = false;
+  if constexpr (DH == 128 && G == 1) {
+    free_loads = p.splits == 1 && blocks > cus && a.kv_len <= 256;
+    if (free_loads) attn_decode_kernel<DH, G, 4, true><<<grid, 4 * 64, 0, s>>>(p);
+  }
+  if (!eight && !free_loads) attn_decode_kernel<DH, G, 4><<<grid, 4 * 64, 0, s>>>(p);
   if (p.splits == 1) return launch_status();
   if (hipGetLastError() != hipSuccess) return FORGE_ERR_HIP;
   attn_decode_combine<DH><<<dim3(a.q_heads, a.batch), DH, 0, s>>>(p.part, (bf16*)a.out, a.q_heads,

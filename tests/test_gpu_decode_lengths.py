@@ -1,5 +1,5 @@
 """Decode attention that takes the sequences by length: more blocks than compute units, whole and broken rounds, equal and repeated
-lengths, clamped positions, one range and several in both block orders, up to 64 sequences and more."""
+lengths, clamped positions, short caches, one range and several in both block orders, up to 64 sequences and more."""
 import numpy as np
 import pytest
 import torch
@@ -14,6 +14,7 @@ pytestmark = pytest.mark.gpu
     (17, 16, 16, 128, 600), (64, 8, 8, 128, 520),          # a broken second round; two whole ones
     (22, 12, 12, 64, 1030), (65, 8, 8, 64, 1030),          # narrow heads; one sequence too many for a lane each
     (33, 16, 8, 128, 1100), (49, 64, 16, 128, 1030),       # shared heads; more rounds than are resident
+    (20, 16, 16, 128, 17), (40, 32, 32, 128, 95), (33, 8, 8, 128, 256), (33, 8, 8, 128, 257),   # short caches in many blocks
 ])
 @pytest.mark.parametrize("lengths", ["spread", "equal", "repeated", "clamped"])
 def test_sequences_by_length(B, Hq, Hkv, dh, cap, lengths):
