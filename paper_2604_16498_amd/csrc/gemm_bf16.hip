@@ -1398,7 +1398,9 @@ Route plan_route(int M, int N, int K, int ldy, forge_act act, bool qkv, bool nor
     double rows_prompt_us = 0.0;
     if (wp.tile >= 0) r.rows = plan_rows_prompt(M, ncols, K, &rows_prompt_us);
     if (r.rows.ranges > 0) {
-      if (rows_prompt_us < 0.97 * wp.us) return r;
+      // (us, rows | waves where the two estimates are 3 to 5 % apart: 122 rows against 6144 gated pairs x 1536 21.1 | 22.5, 126 against
+      // 6144 x 2048 24.7 | 25.5, 118 against 6144 x 1024 14.7 | 15.0, 98 against 5784 x 1024 15.5 | 16.7; 107 x 6144 x 1728 23.6 | 22.8)
+      if (rows_prompt_us < 1.05 * wp.us) return r;
       r.rows = RowsPlan{0, 0, 0};
     }
     if (wp.tile >= 0 && few_outputs(M, ncols, K, 0)) {

@@ -118,8 +118,8 @@ __global__ __launch_bounds__(NW * 64, RB * CB <= 4 ? 4 : 2) void gemm_bf16_waves
       rv[it] = *reinterpret_cast<const u32x2*>(rsrc + (int64_t)(m & ldr) * p.ldy + (n & ldr));
     }
   };
-  // No slab past the end is loaded but one where the count is odd: at most DEPTH slabs per wave are straight code, and the loop
-  // runs at least once and is followed by the last slabs.  (As one loop that always refills, 768 of K were 32 slabs of requests
+  // Past the end a wave loads one slab where its count is odd, in the loop two where it has just DEPTH (K = 1088: 15 of 32): at most
+  // DEPTH slabs per wave are straight code, and the loop runs at least once and is followed by the last slabs.  (As one loop that always refills, 768 of K were 32 slabs of requests
   // instead of 16, and a loop that may be skipped makes the compiler copy the slabs in flight, a wait for each: 128 rows against
   // 2304 x 768 6.8 -> 5.95 us, 3072 x 768 7.1 -> 6.4, 768 x 3072 8.0 -> 7.8, 256 x 2048 x 2048 10.6 -> 9.9.)
   load(0, 0);
@@ -227,9 +227,10 @@ forge_status launch_tile(const WavesParams& r, hipStream_t s) {
 // with the weight in HBM (within 5 to 8 % for half of them, 11 to 20 % for nine of ten; the tile picked is 0.6 % off the
 // fastest of them in the geometric mean, K below 512 3 %).  48 rows or columns come to one round where 32 and 64 do not (us, 128 rows against 2304 x 768 64 x 32 5.7 | 48 x 32 5.0, 3072 x 768 5.6 | 32 x 48 5.3, 68 rows against
 // 6144 x 2048 14.0 | 48 x 48 12.0); where they do not, and with very short rows, the others.
-// At most 64 rows are weighed against x in registers (rows_us), and both estimates come from the kernels before their last
-// changes (each about 5 % faster now), so these keep their own constants: 28 rows against 3000 x 1024 5.1 | 4.6 there, 21 against
-// 8192 x 2048 10.1 | 10.5.
+// At most 64 rows are weighed against x in registers (rows_us), whose estimate is of the same age as those of the tiles of 16, 32 and
+// 64 here; both kernels are about 5 % faster now, so these keep their own constants: 28 rows against 3000 x 1024 5.1 | 4.6 there, 21
+// against 8192 x 2048 10.1 | 10.5.  Those of 48 only order the tiles: 50 drawn problems of 33 to 64 rows that take one are 2 to 14 %
+// faster on it than without them, 6.3 % in the geometric mean (50 x 6144 x 2048 11.4 | 10.0, 47 x 8192 x 4096 20.4 | 20.0).
 namespace {
 struct WavesTile { int rb, cb; double start, round, per_k, full; };
 constexpr WavesTile kTiles[] = {{1, 1, 2.5, 0.36, 0.51, 0.14}, {1, 2, 2.5, 0.65, 0.81, 0.22}, {2, 2, 2.97, 0.4, 1.19, 0.34}, {4, 2, 1.35, 2.34, 2.05, 0.33},
@@ -247,8 +248,11 @@ WavesPlan plan_waves(int M, int N, int K, bool gated) {
     const WavesTile& t = M > 64 ? kTiles[i] : kFewRows[i];
     const int64_t tiles = (int64_t)ceil_div(M, 16 * t.rb) * ceil_div(rows, 16 * t.cb), rounds = ceil_div64(tiles, compute_units());
     if ((t.rb == 3 || t.cb == 3) && (K < 256 || rounds > 1)) continue;
-    const double k = K / 1024.0, late = t.full > 0 && rounds > 1 ? 1.09 : 1.0;      // (the fit is too good for some of several rounds)
-    const double us = late * (t.start + rounds * (t.round + t.per_k * k) + t.full * k * tiles / compute_units());
+    const double k = K / 1024.0, fit = t.start + rounds * (t.round + t.per_k * k) + t.full * k * tiles / compute_units();
+    // (the fit is a little hard on 48 x 48 where K is long or the output gated: us, 32 x 32 | 48 x 48 where it has them equal, 73 rows
+    // against 2304 gated pairs x 768 6.4 | 6.05, 84 against 2304 x 512 5.2 | 5.0, 150 rows against 2880 x 1984 12.0 | 10.8; plain and
+    // short, 214 against 2304 x 512, 4.4 | 4.85)
+    const double us = fit * (t.rb * t.cb == 9 && t.full > 0 && (gated || K > 1024) ? 0.98 : 1.0);
     if (best.tile < 0 || us < best.us) best = WavesPlan{i, us};
   }
   best.us += (double)rows * K * 2 * (M > 64 ? 0.73 : 0.62) / 6e6;      // the weight from HBM

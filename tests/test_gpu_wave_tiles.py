@@ -1,13 +1,14 @@
-"""bf16 linears on shared slabs with tiles of 48 rows or columns: edges of the tiles, one, two, three and more slabs per wave, all
-epilogues, padded and odd row strides, the head split of a short prompt."""
+"""bf16 linears on shared slabs with tiles of 48 rows or columns: edges of the tiles, one to five slabs per wave,
+all epilogues, padded and odd row strides, the head split of a short prompt."""
 import math
 
+import numpy as np
 import pytest
 import torch
 
 from oracle import forge_oracle as O
 from paper_2604_16498_amd import inputs as I
-from util import check, dev
+from util import check, dev, dev_dict
 
 pytestmark = pytest.mark.gpu
 
@@ -17,6 +18,9 @@ pytestmark = pytest.mark.gpu
     ("2,3", 128, 3072, 768, 0), ("2,3", 97, 3000, 512, 0), ("2,3", 127, 2875, 576, 2880),          # 32 x 48
     ("3,2", 128, 2304, 768, 0), ("3,2", 143, 2272, 1088, 0), ("3,2", 97, 2299, 1472, 2304),        # 48 x 32
     ("3,3", 186, 3072, 768, 0), ("3,3", 145, 3017, 1088, 3024), ("3,3", 190, 2976, 448, 0),        # 48 x 48
+    # the back edge of the slab loop: four slabs per wave, four and five
+    ("2,3", 97, 3000, 2048, 0), ("2,3", 128, 3056, 2304, 0), ("3,2", 143, 2272, 2048, 0), ("3,2", 128, 2304, 2304, 2312),
+    ("3,3", 68, 6144, 2048, 0), ("3,3", 145, 3024, 2304, 3032),
 ])
 def test_tiles_of_48(tile, M, N, K, ld, act, use_b, use_r):
     from paper_2604_16498_amd import binding as F
@@ -34,3 +38,37 @@ def test_tiles_of_48(tile, M, N, K, ld, act, use_b, use_r):
     torch.cuda.synchronize()
     check(ty[:, :N], ref, True, "%dx%dx%d %s" % (M, N, K, act))
     assert torch.all(ty[:, N:] == 7.0)
+
+
+@pytest.mark.parametrize("act,use_b,use_r", [("none", True, True), ("gelu_tanh", True, False), ("silu", False, True)])
+@pytest.mark.parametrize("tile,M,N,K,ld", [
+    ("2,3", 64, 6144, 1024, 0), ("2,3", 57, 4493, 2304, 4497), ("2,3", 50, 4301, 3072, 4301),
+    ("3,2", 33, 7079, 1088, 7081), ("3,2", 48, 8192, 2048, 0), ("3,2", 47, 5075, 1024, 5076),
+])
+def test_tiles_of_48_few_rows(tile, M, N, K, ld, act, use_b, use_r):
+    """At most 64 rows, where x in registers is the alternative: outputs element by element where the stride is odd."""
+    test_tiles_of_48(tile, M, N, K, ld, act, use_b, use_r)
+
+
+@pytest.mark.parametrize("tile,B,S,pos0,heads", [("3,2", 1, 128, 0, 12), ("2,3", 2, 64, 37, 16), ("3,3", 2, 93, 5, 16)])
+def test_head_split_on_tiles_of_48(tile, B, S, pos0, heads):
+    from paper_2604_16498_amd import binding as F
+    sh = I.BlockShape(768, heads, heads, 64, 256)
+    assert F.forge_gemm_variant(B * S, sh.qkv_out, 768, "none", torch.bfloat16) == "gemm_bf16_waves<%s>" % tile
+    cap = pos0 + S + 3
+    w = I.block_weights(sh, 68, 0, bf16=True, bias_std=0.05, random_affine=True, weight_std=0.04)
+    x = I.normal(68, 0, "x", (B, S, 768), 1.0, bf16=True)
+    kc, vc = (np.zeros((B, heads, cap, 64), np.float32) for _ in range(2))
+    for c, name in ((kc, "k_cache"), (vc, "v_cache")):
+        c[:, :, :pos0] = I.normal(68, 0, name, (B, heads, pos0, 64), 1.0, bf16=True)
+    tk, tv = dev(kc, True), dev(vc, True)
+    kc, vc = kc.astype(np.float64), vc.astype(np.float64)
+    ref = O.decoder_block(sh, w, x, kc, vc, pos0=pos0)
+    tw = dev_dict(w, True)                     # (the descriptor holds raw pointers)
+    desc = F.make_block_desc(sh, tw)
+    out = torch.empty(B, S, 768, dtype=torch.bfloat16, device="cuda")
+    F.forge_decoder_block(desc, dev(x, True), out, tk, tv, pos0, F.workspace(F.forge_decoder_block_workspace_bytes(desc, B, S, cap)))
+    torch.cuda.synchronize()
+    check(tk, kc, True, "k cache")
+    check(tv, vc, True, "v cache")
+    check(out, ref, True, "layer", chain=True)
