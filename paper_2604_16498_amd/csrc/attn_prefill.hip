@@ -208,7 +208,8 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 8 ? 1 : DH == 128 || (MASKED &
   for (int i = 0; i < NDT; ++i)
 #pragma unroll
     for (int e = 0; e < 16; ++e) o_acc[i][e] = 0.f;
-  float m_run = -1e30f, l_run = 0.f;   // finite start: no inf - inf anywhere
+  // finite start: no inf - inf anywhere; with a mask no value of it lies below (a row cut throughout by -1e30 or less has a maximum)
+  float m_run = MASKED ? -__FLT_MAX__ : -1e30f, l_run = 0.f;
   // MASKED works on scaled scores with the mask added (s * scale + mask, one instruction), so the factor inside the softmax
   // is log2e there; the difference to the maximum is taken first and exactly: a mask may hold any finite value, and maximum * log2e
   // rounded by itself is off by 440 at -1e10

@@ -37,7 +37,8 @@ __global__ __launch_bounds__(256) void attn_simple_kernel(
   if (kv_pos != nullptr) kv_len = min(max(kv_pos[b], 0) + q_len, kv_len);
   const int limit = causal ? i + (kv_len - q_len) + 1 : kv_len;   // keys [0, limit)
   const float* mrow = mask == nullptr ? nullptr : mask + b * mask_bs + h * mask_hs + (int64_t)i * kv_len;
-  float m = -1e30f, l = 0.f, acc[NO];      // finite start: a chunk that is masked out entirely stays 0
+  // finite start: a chunk that is cut by -inf entirely stays 0; no finite mask value lies below it
+  float m = -__FLT_MAX__, l = 0.f, acc[NO];
 #pragma unroll
   for (int t = 0; t < NO; ++t) acc[t] = 0.f;
 
@@ -59,7 +60,7 @@ __global__ __launch_bounds__(256) void attn_simple_kernel(
     }
     const float m_new = fmaxf(m, wave_max(s));
     const float p = __expf(s - m_new);        // exp(-inf) = 0 for lanes past the limit
-    const float corr = __expf(m - m_new);     // first chunk: exp(-1e30 - m_new) = 0
+    const float corr = __expf(m - m_new);     // first chunk: 0, or 1 with nothing summed
     l = l * corr + wave_sum(p);
 #pragma unroll
     for (int t = 0; t < NO; ++t) acc[t] *= corr;
