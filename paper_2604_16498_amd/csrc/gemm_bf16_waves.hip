@@ -30,7 +30,7 @@ struct WavesParams {
   int qkv;                                           // head split
 };
 
-// SLABS: no wave has more than 1 or 2; 0: every wave has DEPTH at least
+// SLABS: no wave has more than 1, 2 or 3; 0: every wave has 3 at least
 template <int RB, int CB, bool GATED, int SLABS>
 __global__ __launch_bounds__(NW * 64, RB * CB <= 4 ? 4 : 2) void gemm_bf16_waves_kernel(WavesParams r) {
   const GemmParams& p = r.g;
@@ -118,17 +118,20 @@ __global__ __launch_bounds__(NW * 64, RB * CB <= 4 ? 4 : 2) void gemm_bf16_waves
       rv[it] = *reinterpret_cast<const u32x2*>(rsrc + (int64_t)(m & ldr) * p.ldy + (n & ldr));
     }
   };
-  // Past the end a wave loads one slab where its count is odd, in the loop two where it has just DEPTH (K = 1088: 15 of 32): at most
-  // DEPTH slabs per wave are straight code, and the loop runs at least once and is followed by the last slabs.  (As one loop that always refills, 768 of K were 32 slabs of requests
-  // instead of 16, and a loop that may be skipped makes the compiler copy the slabs in flight, a wait for each: 128 rows against
-  // 2304 x 768 6.8 -> 5.95 us, 3072 x 768 7.1 -> 6.4, 768 x 3072 8.0 -> 7.8, 256 x 2048 x 2048 10.6 -> 9.9.)
+  // Past the end of K a wave loads one slab at most (in the loop of the 64 x 64 tiles three): up to three slabs per wave are straight
+  // code, and the loop runs at least once and is followed by the last slabs.  (As one loop that always refills, 768 of K were 32 slabs of requests instead of 16, and a loop
+  // that may be skipped makes the compiler copy the slabs in flight, a wait for each: 128 rows against 2304 x 768 6.8 -> 5.95 us,
+  // 3072 x 768 7.1 -> 6.4, 768 x 3072 8.0 -> 7.8, 256 x 2048 x 2048 10.6 -> 9.9.  Three slabs in the loop load a fourth and lose to
+  // refilling: 400 rows against 2560 x 1280 14.8 refilling, 15.6 in the loop, 14.0 straight, 150 against 3072 x 1088 8.2, 8.8, 8.0.)
   load(0, 0);
   if constexpr (SLABS != 1) load(1, 1);
   if constexpr (!BIG) __builtin_amdgcn_sched_barrier(0);       // (among the slabs' requests: 128 rows against 768 x 768 4.0 instead of 3.8 us)
   fetch_ends();
   if constexpr (SLABS > 0) {
     if (0 < n_slabs) multiply(0);                    // (wave-uniform)
+    if (SLABS > 2) load(2, 0);
     if (SLABS > 1 && 1 < n_slabs) multiply(1);
+    if (SLABS > 2 && 2 < n_slabs) multiply(0);
   } else if constexpr (BIG) {                        // (always refilling: 109 rows against 5968 x 1088 10.5 us, 12.0 as below)
     for (int i = 0; i < n_slabs; i += DEPTH) {
 #pragma unroll
@@ -137,7 +140,7 @@ __global__ __launch_bounds__(NW * 64, RB * CB <= 4 ? 4 : 2) void gemm_bf16_waves
         load(i + d + DEPTH, d);
       }
     }
-  } else {                                           // (n_slabs >= DEPTH)
+  } else {                                           // (n_slabs > DEPTH)
     int i = DEPTH;
 #pragma unroll 1
     do {
@@ -217,6 +220,7 @@ forge_status launch_tile(const WavesParams& r, hipStream_t s) {
   const int slabs = r.g.K / BK;
   if (slabs <= NW) return launch_slabs<RB, CB, GATED, 1>(r, s);
   if (slabs <= DEPTH * NW) return launch_slabs<RB, CB, GATED, 2>(r, s);
+  if (slabs <= 3 * NW) return launch_slabs<RB, CB, GATED, 3>(r, s);
   return launch_slabs<RB, CB, GATED, 0>(r, s);
 }
 
