@@ -34,7 +34,7 @@ namespace {
 
 constexpr int TILE = 16;                  // cache rows per MFMA tile
 constexpr int GRAIN = 128;                // a split is a multiple of this many rows (two tiles per wave of four)
-constexpr int MAX_SPLITS = 64;            // the combine holds one split per lane
+constexpr int MAX_SPLITS = 64;            // what plan_splits was fitted over, and a bound of the workspace
 
 struct DecParams {
   const bf16* q;

@@ -47,7 +47,7 @@
 // Blocks of 4 and 2 waves: all waves copy, one barrier per tile, and S, the softmax and P.V of a tile follow each other in a
 // wave.  At head_dim 64 the vector work is twice the matrix work, the 8-wave kernel left two waves per SIMD
 // with it (154 registers) and its blocks filled the chip in 1.5 rounds at 8 x 12 heads x 1024; three blocks of 4 waves fit a
-// CU (131 registers, 39 KB).  us, 8 waves | 4 waves: 8 x 12 heads of 64 x 1024 causal 31.8 | 27.7, x 600 20.4 | 16.0, the
+// CU (133 registers, 39 KB).  us, 8 waves | 4 waves: 8 x 12 heads of 64 x 1024 causal 31.8 | 27.7, x 600 20.4 | 16.0, the
 // same dense 54 | 41.5, masked 82.6 | 60; head_dim 128 (two blocks per CU): 32 heads x 300 15.1 | 11.2, x 1500 49.6 | 42.4.
 #include "common.hpp"
 

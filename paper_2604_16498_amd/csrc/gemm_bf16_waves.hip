@@ -229,8 +229,9 @@ forge_status launch_tile(const WavesParams& r, hipStream_t s) {
 // Tiles (row blocks, column blocks) and their times in us: a start, a round of tiles over the CUs, what 1024 elements of K add
 // to a round, and what they add per tile and CU (blocks that run into each other's loads); fitted to 1100 drawn problems
 // with the weight in HBM (within 5 to 8 % for half of them, 11 to 20 % for nine of ten; the tile picked is 0.6 % off the
-// fastest of them in the geometric mean, K below 512 3 %).  48 rows or columns come to one round where 32 and 64 do not (us, 128 rows against 2304 x 768 64 x 32 5.7 | 48 x 32 5.0, 3072 x 768 5.6 | 32 x 48 5.3, 68 rows against
-// 6144 x 2048 14.0 | 48 x 48 12.0); where they do not, and with very short rows, the others.
+// fastest of them in the geometric mean, K below 512 3 %).  48 rows or columns come to one round where 32 and 64 do not (us,
+// 128 rows against 2304 x 768 64 x 32 5.7 | 48 x 32 5.0, 3072 x 768 5.6 | 32 x 48 5.3, 68 rows against 6144 x 2048 14.0 | 48 x 48
+// 12.0); where they do not, and with very short rows, the others.
 // At most 64 rows are weighed against x in registers (rows_us), whose estimate is of the same age as those of the tiles of 16, 32 and
 // 64 here; both kernels are about 5 % faster now, so these keep their own constants: 28 rows against 3000 x 1024 5.1 | 4.6 there, 21
 // against 8192 x 2048 10.1 | 10.5.  Those of 48 only order the tiles: 50 drawn problems of 33 to 64 rows that take one are 2 to 14 %

@@ -1,5 +1,5 @@
 """Masked attention on three blocks per CU (head_dim 64, more than two blocks of 128 queries per CU): ragged ends of queries and keys,
-additive values, keys cut by -inf, by the type's lowest value and by large finite ones, a mask for all heads and one each."""
+additive values, the last keys cut by -inf, by the type's lowest value and by -1e4, a mask for all heads and one each; causal calls."""
 import math
 
 import numpy as np
