@@ -249,6 +249,7 @@ static_assert(sizeof(kFewRows) == sizeof(kTiles), "the same tiles in the same or
 WavesPlan plan_waves(int M, int N, int K, bool gated) {
   const int rows = gated ? 2 * N : N;
   WavesPlan best = {-1, 0.0};
+  double empty = 0.0;                                // share of the last of several rounds
   for (int i = gated ? 1 : 0; i < kTileCount; ++i) {
     const WavesTile& t = M > 64 ? kTiles[i] : kFewRows[i];
     const int64_t tiles = (int64_t)ceil_div(M, 16 * t.rb) * ceil_div(rows, 16 * t.cb), rounds = ceil_div64(tiles, compute_units());
@@ -258,8 +259,13 @@ WavesPlan plan_waves(int M, int N, int K, bool gated) {
     // against 2304 gated pairs x 768 6.4 | 6.05, 84 against 2304 x 512 5.2 | 5.0, 150 rows against 2880 x 1984 12.0 | 10.8; plain and
     // short, 214 against 2304 x 512, 4.4 | 4.85)
     const double us = fit * (t.rb * t.cb == 9 && t.full > 0 && (gated || K > 1024) ? 0.98 : 1.0);
-    if (best.tile < 0 || us < best.us) best = WavesPlan{i, us};
+    if (best.tile >= 0 && us >= best.us) continue;
+    best = WavesPlan{i, us};
+    empty = t.full > 0 && rounds > 1 ? 1.0 - (double)tiles / (rounds * compute_units()) : 0.0;
   }
+  // Against other kernels: too good where the last of several rounds is mostly empty, 330 and 368 tiles over 256 CUs (690 rows against
+  // 1920 x 2560 29.0 us, fitted 26.6, 1433 against 1024 x 2560 27.7, 26.0), not where it is full (294 against 6144 x 2048 24.1, 25.5).
+  best.us *= 1.0 + 0.3 * empty;
   best.us += (double)rows * K * 2 * (M > 64 ? 0.73 : 0.62) / 6e6;      // the weight from HBM
   return best;
 }
